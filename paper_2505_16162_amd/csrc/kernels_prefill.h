@@ -9,30 +9,31 @@
 // lane = 16*kg + r holding row r of the tile and columns 8*kg..8*kg+7 of the step, i.e. the MFMA B
 // operand of v_mfma_f32_16x16x32_bf16 as stored, so staging a tile is a linear copy.
 //
-// prefill_gemm_kernel: a workgroup owns up to 16 weight tiles (G consecutive row groups of the decode
-// layout, T tile slots each) and 4*TBW token tiles; per 32-column step it stages the 16 weight units
-// and the 3 x 4*TBW token fragments through LDS (double buffered, one meeting per step); its 8
-// wavefronts form a 2 x 4 grid, each holding 8 x TBW accumulator tiles. Epilogues are the decode
-// ones (RoPE + KV write, residual + next norm's operands, SwiGLU) applied to 16 rows at a time.
+// prefill_gemm_kernel: a workgroup owns TA tiles of 16 weight rows x TB tiles of 16 tokens and walks K (or one of S parts
+// of it) in steps of 32 columns. Weights and activations go from memory straight to LDS (16-byte loads whose LDS side is
+// linear and whose memory side is free), so a tile is filled with whatever rows suit it, wherever they lie in the decode
+// layout: no dead rows from the decode layout's short tiles (20 rows per workgroup = two tiles of 10), and the two dot
+// products an epilogue combines sit in one lane's accumulators, so epilogues run in registers on four rows at a time.
 #pragma once
 #include "kernels_bf16.h"
 
 namespace ks {
 
 constexpr int PF_NT = 512;             // threads per workgroup of the prefill GEMM (8 wavefronts)
-constexpr int PF_SLOTS = 16;           // weight tiles per workgroup
-constexpr int PF_LR = PF_SLOTS * 16;   // local rows (slot, row in tile)
-constexpr int PF_VLD = PF_LR + 1;      // leading dimension of the epilogue's staging array
 
 struct PfArgs {
-    GemmOp op;              // type, W, N, K, x, gain_next, q_out, kv_block, cos_t, sin_t, H, Hkv, hd, max_seq
+    GemmOp op;              // type, W, N, K, split, x, gain_next, q_out, kv_block, cos_t, sin_t, H, Hkv, hd, max_seq, inv_dim, eps
     const bf16_t *frag_in;  // [3][K/32][TT][512] fragment order
     bf16_t *frag_out;       // same layout over the output features (OP_RESID / OP_SWIGLU)
-    const float *rstd;      // [n_tok] rsqrt(mean(x^2) + eps) of the input rows; nullptr: input is not normalised
-    float *ss_out;          // OP_RESID: [gridDim.x][TT*16] this workgroup's share of sum(x^2) per row
+    const float *ss_in;     // [n_ss][TT*16] shares of sum(x^2) per input row; nullptr: input is not normalised
+    int n_ss;
+    float *ss_out;          // OP_RESID: [row tiles][TT*16] this workgroup's share of sum(x^2) per row
+    float *part;            // split K: [tile][S][wavefront][accumulator tile][lane][4] partial sums
+    int *arrivals;          // split K: [tile] arrival counters, zero between launches
     int TT;                 // token tiles the fragment buffers are laid out for
-    int n_tok;              // live rows (a multiple of 16)
-    int G, T;               // row groups per workgroup, tile slots per row group (G*T <= PF_SLOTS)
+    int n_tok;              // live rows
+    int n_mt, n_mr;         // row tiles of the matrix; OP_QKV: those that hold rotary pairs (the others hold value rows)
+    int n_tt, S;            // token tiles (workgroup tiles) of the launch, parts K is split into
 };
 
 __device__ __forceinline__ size_t frag_off(int KS, int TT, int pl, int ks, int tt) {
@@ -52,255 +53,453 @@ __device__ __forceinline__ void store_frag(bf16_t *frag, int KS, int TT, int tt,
     frag[frag_off(KS, TT, 2, n >> 5, tt) + in_tile] = (bf16_t)(__float_as_uint(lo) >> 16);
 }
 
-// Row-group tables of one workgroup (LDS)
-struct PfTables {
-    int grp_R[PF_SLOTS], grp_nfirst[PF_SLOTS], grp_rpt[PF_SLOTS];
-    int rowidx[PF_LR];          // [G][16*T] global row of local row lr of group gi
+// ... of the four values at features n..n+3 (n a multiple of 4): one 8-byte store per plane
+__device__ __forceinline__ void store_frag4(bf16_t *frag, int KS, int TT, int tt, int m, int n, f32x4 v) {
+    unsigned int h[4], md[4], l[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        h[e] = __float_as_uint(v[e]);
+        const float r1 = v[e] - __uint_as_float(h[e] & 0xffff0000u);
+        md[e] = __float_as_uint(r1);
+        l[e] = __float_as_uint(r1 - __uint_as_float(md[e] & 0xffff0000u));
+    }
+    const size_t in_tile = (size_t)((((n & 31) >> 3) * 16 + m) * 8 + (n & 7));
+    auto put = [&](int pl, const unsigned int *u) {
+        *reinterpret_cast<u32x2 *>(frag + frag_off(KS, TT, pl, n >> 5, tt) + in_tile) =
+            u32x2{__builtin_amdgcn_perm(u[1], u[0], 0x07060302u), __builtin_amdgcn_perm(u[3], u[2], 0x07060302u)};
+    };
+    put(0, h); put(1, md); put(2, l);
+}
+
+// four values rounded to bf16 (nearest even), 8-byte store
+__device__ __forceinline__ void pf_store_bf16x4(bf16_t *p, f32x4 v) {
+    *reinterpret_cast<u32x2 *>(p) = u32x2{(unsigned int)float_to_bf16_rne(v[0]) | ((unsigned int)float_to_bf16_rne(v[1]) << 16),
+                                          (unsigned int)float_to_bf16_rne(v[2]) | ((unsigned int)float_to_bf16_rne(v[3]) << 16)};
+}
+
+// Loads that go straight to LDS: lane l's 16 bytes land at LDS byte lds_off + 16*l, whatever its source address is.
+// (s_nop: a scalar address that a vector instruction has just written, e.g. one kept in a vector lane, may be read by a
+// vector memory instruction five wait states later at the earliest, and inside asm nobody else sees to that.)
+// The compiler does not count them; every use of the data sits behind a hand-placed vmcnt wait and a workgroup meeting.
+__device__ __forceinline__ void dma_lane(const void *p, unsigned int lds_off) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(p), "s"(lds_off) : "memory");
+}
+__device__ __forceinline__ void dma_lane_nt(const void *p, unsigned int lds_off) {
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off nt" : : "v"(p), "s"(lds_off) : "memory");
+}
+__device__ __forceinline__ void dma_linear(const void *base, unsigned int voff, unsigned int lds_off) {
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 4\n\tglobal_load_lds_dwordx4 %0, %1" : : "v"(voff), "s"(base), "s"(lds_off) : "memory");
+}
+template <int KEEP> __device__ __forceinline__ void dma_wait() { asm volatile("s_waitcnt vmcnt(%0)" : : "n"(KEEP) : "memory"); }
+// a workgroup meeting that leaves loads in flight (LDS reads of this wavefront have returned)
+__device__ __forceinline__ void pf_meet() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+}
+
+// Partial sums that another workgroup of the launch reads: written through to memory and read from there, whichever die's
+// L2 the two sit behind.
+__device__ __forceinline__ void store_part(char *base, unsigned int off, f32x4 v) {
+    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2 sc1" : : "v"(off), "v"(v), "s"(base) : "memory");
+}
+// N pieces, 1 KB apart (the wait is part of the block: no register is ever seen with a load in flight)
+template <int N> __device__ __forceinline__ void load_part(const char *base, unsigned int off, f32x4 *v);
+template <> __device__ __forceinline__ void load_part<4>(const char *base, unsigned int off, f32x4 *v) {
+    asm volatile(
+        "s_nop 4\n\tglobal_load_dwordx4 %0, %4, %5 offset:-4096 sc1\n\t"
+        "global_load_dwordx4 %1, %4, %5 offset:-3072 sc1\n\t"
+        "global_load_dwordx4 %2, %4, %5 offset:-2048 sc1\n\t"
+        "global_load_dwordx4 %3, %4, %5 offset:-1024 sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
+        : "v"(off), "s"(base + 4096) : "memory");
+}
+template <> __device__ __forceinline__ void load_part<16>(const char *base, unsigned int off, f32x4 *v) {
+    asm volatile(
+        "s_nop 4\n\tglobal_load_dwordx4 %0, %16, %17 offset:-4096 sc1\n\t"
+        "global_load_dwordx4 %1, %16, %17 offset:-3072 sc1\n\t"
+        "global_load_dwordx4 %2, %16, %17 offset:-2048 sc1\n\t"
+        "global_load_dwordx4 %3, %16, %17 offset:-1024 sc1\n\t"
+        "global_load_dwordx4 %4, %16, %17 offset:0 sc1\n\t"
+        "global_load_dwordx4 %5, %16, %17 offset:1024 sc1\n\t"
+        "global_load_dwordx4 %6, %16, %17 offset:2048 sc1\n\t"
+        "global_load_dwordx4 %7, %16, %17 offset:3072 sc1\n\t"
+        "global_load_dwordx4 %8, %16, %18 offset:-4096 sc1\n\t"
+        "global_load_dwordx4 %9, %16, %18 offset:-3072 sc1\n\t"
+        "global_load_dwordx4 %10, %16, %18 offset:-2048 sc1\n\t"
+        "global_load_dwordx4 %11, %16, %18 offset:-1024 sc1\n\t"
+        "global_load_dwordx4 %12, %16, %18 offset:0 sc1\n\t"
+        "global_load_dwordx4 %13, %16, %18 offset:1024 sc1\n\t"
+        "global_load_dwordx4 %14, %16, %18 offset:2048 sc1\n\t"
+        "global_load_dwordx4 %15, %16, %18 offset:3072 sc1\n\t"
+        "s_waitcnt vmcnt(0)"
+        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]), "=&v"(v[8]), "=&v"(v[9]), "=&v"(v[10]), "=&v"(v[11]), "=&v"(v[12]), "=&v"(v[13]), "=&v"(v[14]), "=&v"(v[15])
+        : "v"(off), "s"(base + 4096), "s"(base + 12288) : "memory");
+}
+
+// Where one row of a workgroup's tile lies in the packed matrix: the 16-byte piece (8 columns 8*kg..) of step 0's unit
+struct PfRow { const bf16_t *p; int unit, gshift; };
+
+// workgroup of the decode layout that owns item n of N (inverse of wg_share)
+__device__ __forceinline__ int pf_owner(int n, int N) { return (int)((((unsigned int)n + 1u) * (unsigned int)KS_NWG - 1u) / (unsigned int)N); }
+
+// Row sr of row tile mt (TM rows). Which matrix row that is, is free to choose, since every row is fetched from wherever
+// it lies: pairs whose two dot products meet in an epilogue (rotary halves, gate / up rows) sit in neighbouring 16-row
+// tiles at the same place, so that one lane holds both. Rows past the end repeat the last one (never stored).
+template <int TM>
+__device__ __forceinline__ PfRow pf_row(const PfArgs &a, int mt, int sr, int kg) {
+    const GemmOp &op = a.op;
+    const bool pairs = op.type == OP_SWIGLU || (op.type == OP_QKV && mt < a.n_mr);
+    int wg, lr;
+    if (pairs) {
+        const int P = op.type == OP_SWIGLU ? op.N : (op.H + op.Hkv) * (op.hd >> 1);
+        const int p = min(mt * (TM / 2) + (sr >> 5) * 16 + (sr & 15), P - 1);
+        wg = pf_owner(p, P);
+        lr = p - wg_share(P, wg) + ((sr >> 4) & 1) * a.op.split[wg].n_first;
+    } else if (op.type == OP_QKV) {
+        const int VR = op.Hkv * op.hd, v = min((mt - a.n_mr) * TM + sr, VR - 1);
+        wg = pf_owner(v, VR);
+        lr = v - wg_share(VR, wg) + 2 * a.op.split[wg].n_first;
+    } else {
+        const int n = min(mt * TM + sr, op.N - 1);
+        wg = pf_owner(n, op.N);
+        lr = n - wg_share(op.N, wg);
+    }
+    const WgSplit &s = a.op.split[wg];
+    const int t = lr / s.rpt, rit = lr - t * s.rpt, rows_t = min(s.rpt, s.R - t * s.rpt);
+    PfRow r;
+    r.p = op.W + s.wg_base + (size_t)(t * s.rpt) * op.K + (size_t)(kg * rows_t + rit) * 8;
+    r.unit = rows_t * 32;
+    r.gshift = s.gshift;
+    return r;
+}
+
+// position of 32-column step st among the units of a tile (the order pack_matrix_kernel wrote them in)
+__device__ __forceinline__ int pf_unit_index(int st, int KS, int gshift) {
+    const int nfull = KS >> 4, rem = KS & 15, g = 1 << gshift, w16 = st & 15, kpart = w16 >> gshift;
+    return nfull * g * kpart + min(rem, kpart * g) + (st >> 4) * g + (w16 & (g - 1));
+}
+
+// TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS.
+// PP: the wavefronts form two groups (one wavefront of each on every SIMD) that run one phase apart: while one group
+// issues its matrix instructions the other reads its operands from LDS.
+// What bounds it: at 256 x 256 the matrix cores (96 matrix instructions of 16 cycles per wavefront and step against 20 KB
+// of LDS reads); 13B-shaped, 4096 rows: 1.50-1.55 PFLOP/s issued (three planes) on QKV and gate+up, where a large library
+// product in bf16 reaches 1.59 on this card; one meeting per step for all wavefronts together ran at 1.18. Up to 64 rows
+// it is the weight stream: 128-row tiles, two workgroups per unit, K split until every unit has work.
+// Whole prompts, 4 blocks, before (a tile per decode-layout tile, the last rows in a 16-row pass of their own) and after:
+// 7B 45 rows 4.47 -> 0.82 ms, Qwen-14B 777 rows 8.24 -> 5.28, 13B 1024 rows 9.41 -> 6.17, 13B 4096 rows 37.3 -> 27.2.
+template <int TA, int TB, int WA, int NS, bool PP>
+struct PfShape {
+    static constexpr int WB = 8 / WA, TAW = TA / WA, TBW = TB / WB;
+    static constexpr int TM = TA * 16;
+    static constexpr int A_BYTES = TA * 1024, STAGE = A_BYTES + 3 * TB * 1024;
+    static constexpr int NA = TA * 64 / PF_NT;                   // weight pieces per thread and step
+    static constexpr int NB = (3 * TB + 7) / 8;                  // token fragments per wavefront and step
+    static constexpr size_t LDS = (size_t)NS * STAGE + (size_t)TB * 16 * 4 * (1 + WA);
 };
 
-// Epilogue for the 16 rows of token tile tt: vals[m*PF_VLD + slot*16 + row_in_tile] holds the finished dot products.
-// Thread (m = tid / 32, jj = tid % 32) walks the local rows jj, jj+32, ... of every row group of the workgroup.
-__device__ __forceinline__ void pf_epilogue(const PfArgs &a, const PfTables *tb, const float *vals, int tt, int n_groups) {
+template <int TA, int TB, int WA, int NS, bool PP>
+__global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(PfArgs a) {
+    typedef PfShape<TA, TB, WA, NS, PP> Sh;
+    constexpr int TAW = Sh::TAW, TBW = Sh::TBW, TM = Sh::TM;
+    extern __shared__ __align__(16) char lds[];
+    float *rs = reinterpret_cast<float *>(lds + NS * Sh::STAGE);     // [TB*16] norm scale of the tile's tokens
+    float *sq = rs + TB * 16;                                        // [WA][TB*16]
+    __shared__ int ticket;
     const GemmOp &op = a.op;
-    const int tid = threadIdx.x, m = tid >> 5, jj = tid & 31;
-    const int tok = tt * 16 + m;
-    const float rs = a.rstd ? a.rstd[tok] : 1.0f;
-    const float *vrow = vals + (size_t)m * PF_VLD;
-    float sq = 0.f;
-    for (int gi = 0; gi < n_groups; ++gi) {
-        const int R = tb->grp_R[gi], nf = tb->grp_nfirst[gi], rpt = tb->grp_rpt[gi];
-        const int *rowidx = tb->rowidx + gi * 16 * a.T;
-        const int slot0 = gi * a.T;
-        auto col = [&](int lr) { const int t = lr / rpt; return (slot0 + t) * 16 + (lr - t * rpt); };
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wa = PP ? wave >> 2 : wave / Sh::WB, wb = PP ? wave & 3 : wave % Sh::WB, kg = lane >> 4, r16 = lane & 15;
+    const int KS = op.K >> 5;
+
+    // workgroup -> (K part, token tile, row tile). Workgroups are dealt to the 8 dies by index: each die takes a run of
+    // the order below, in which neighbours share weights (four token tiles) or activations (consecutive row tiles)
+    const int total = a.n_mt * a.n_tt * a.S;
+    const int per = (total + 7) >> 3, lin = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per || lin >= total) return;
+    const int part_tiles = a.n_mt * a.n_tt;
+    const int sp = lin / part_tiles, in_part = lin - sp * part_tiles;
+    const int tb4 = in_part / (a.n_mt * 4), in_blk = in_part - tb4 * (a.n_mt * 4), tw = min(4, a.n_tt - tb4 * 4);
+    const int mt = in_blk / tw, tk = tb4 * 4 + (in_blk - mt * tw);
+    const int tt0 = tk * TB;
+    const int st0 = (int)((long long)KS * sp / a.S), cnt = (int)((long long)KS * (sp + 1) / a.S) - st0;
+
+    // what this thread stages per step
+    PfRow ar[Sh::NA];
+#pragma unroll
+    for (int q = 0; q < Sh::NA; ++q) ar[q] = pf_row<TM>(a, mt, (wave + q * 8) * 16 + r16, kg);
+    const unsigned int l0 = (unsigned int)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    const char *bsrc[Sh::NB];
+    unsigned int bdst[Sh::NB];
+#pragma unroll
+    for (int q = 0; q < Sh::NB; ++q) {
+        const int f = min(wave + q * 8, 3 * TB - 1), pl = f / TB, t = f - pl * TB;    // a repeat writes the same bytes again
+        bsrc[q] = reinterpret_cast<const char *>(a.frag_in + frag_off(KS, a.TT, pl, st0, min(tt0 + t, a.TT - 1)));
+        bdst[q] = Sh::A_BYTES + f * 1024;
+    }
+    const size_t bstep = (size_t)a.TT * 1024;
+    const unsigned int voff = lane * 16;
+    const bool once = a.n_tt == 1;                 // every weight byte is used by one workgroup only: nothing to keep in a cache
+    auto issue = [&](int t, int buf) {             // step st0 + t into LDS buffer buf
+        const unsigned int d = l0 + buf * Sh::STAGE;
+#pragma unroll
+        for (int q = 0; q < Sh::NA; ++q) {
+            const bf16_t *p = ar[q].p + (size_t)pf_unit_index(st0 + t, KS, ar[q].gshift) * ar[q].unit;
+            if (once) dma_lane_nt(p, d + (wave + q * 8) * 1024);
+            else dma_lane(p, d + (wave + q * 8) * 1024);
+        }
+#pragma unroll
+        for (int q = 0; q < Sh::NB; ++q) dma_linear(bsrc[q] + t * bstep, voff, d + bdst[q]);
+    };
+
+    f32x4 acc[TAW][TBW];
+#pragma unroll
+    for (int i = 0; i < TAW; ++i)
+#pragma unroll
+        for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const char *la = lds + wa * TAW * 1024 + lane * 16, *lb = lds + Sh::A_BYTES + wb * TBW * 1024 + lane * 16;
+    auto read_a = [&](int buf, bf16x8 *v) {
+#pragma unroll
+        for (int i = 0; i < TAW; ++i) v[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(la + buf * Sh::STAGE + i * 1024));
+    };
+    auto read_b = [&](int buf, int j, bf16x8 *v) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p) v[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(lb + buf * Sh::STAGE + (p * TB + j) * 1024));
+    };
+
+    constexpr int NDMA = Sh::NA + Sh::NB;          // loads per wavefront and step
+    constexpr int JC = TBW < 2 ? TBW : 2, CL = TBW / JC;      // token tiles per cluster of matrix instructions, clusters per step
+    bf16x8 av[TAW], bv[JC][3];
+    auto mfma_cluster = [&](int c) {
+#pragma unroll
+        for (int p = 0; p < 3; ++p)
+#pragma unroll
+            for (int jj = 0; jj < JC; ++jj)
+#pragma unroll
+                for (int i = 0; i < TAW; ++i)
+                    acc[i][c * JC + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[jj][p], acc[i][c * JC + jj], 0, 0, 0);
+    };
+#pragma unroll
+    for (int t = 0; t < NS - 1; ++t) issue(min(t, cnt - 1), t);     // (a step past the end re-reads the last one: loads stay countable)
+    // norm scale of the tile's tokens, from the producers' shares in their order (read while the first steps arrive)
+    if (a.ss_in && tid < TB * 16) {
+        float s = 0.f;
+        const float *p = a.ss_in + tt0 * 16 + tid;
+        const int stride = a.TT * 16;
+        for (int i0 = 0; i0 < a.n_ss; i0 += 16) {      // sixteen loads at a time: one memory round trip, not sixteen
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = p[(size_t)min(i0 + i, a.n_ss - 1) * stride];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) s += i0 + i < a.n_ss ? v[i] : 0.f;
+        }
+        rs[tid] = 1.0f / sqrtf(s * op.inv_dim + op.eps);
+    }
+    dma_wait<0>();
+    pf_meet();
+    if constexpr (PP) {
+        // Phases of a group: read operands | meet | matrix instructions | meet. The second group enters one phase later.
+        // With two buffers (two clusters per step) step t+1 is requested while cluster 0 of step t is read, when the
+        // last reads of step t-1 are one phase old; with three (one cluster per step) step t+2 is.
+        if (wa == 1) pf_meet();
+        int buf = 0;
+        for (int t = 0; t < cnt; ++t) {
+            read_a(buf, av);
+#pragma unroll
+            for (int jj = 0; jj < JC; ++jj) read_b(buf, jj, bv[jj]);
+            const int nb = NS == 2 ? buf ^ 1 : (buf == 0 ? 2 : buf - 1);
+            issue(min(t + NS - 1, cnt - 1), nb);
+            if (CL == 1) dma_wait<NDMA>();         // step t+1 has arrived (t+2 stays in flight)
+            pf_meet();
+            __builtin_amdgcn_s_setprio(1);
+            mfma_cluster(0);
+            __builtin_amdgcn_s_setprio(0);
+            pf_meet();
+            if constexpr (CL == 2) {
+#pragma unroll
+                for (int jj = 0; jj < JC; ++jj) read_b(buf, JC + jj, bv[jj]);
+                if (wa == 1) dma_wait<0>();        // the first group reads step t+1 one phase from here
+                pf_meet();
+                __builtin_amdgcn_s_setprio(1);
+                mfma_cluster(1);
+                __builtin_amdgcn_s_setprio(0);
+                if (wa == 0) dma_wait<0>();
+                pf_meet();
+            }
+            buf = NS == 2 ? buf ^ 1 : (buf == 2 ? 0 : buf + 1);
+        }
+        if (wa == 0) pf_meet();
+    } else {
+        int buf = 0;
+        for (int t = 0; t < cnt; ++t) {
+            if (t > 0) { dma_wait<(NS - 2) * NDMA>(); pf_meet(); }      // step t has arrived; every wavefront is done with step t-1
+            const int nb = buf == 0 ? NS - 1 : buf - 1;
+            issue(min(t + NS - 1, cnt - 1), nb);
+            read_a(buf, av);
+#pragma unroll
+            for (int c = 0; c < CL; ++c) {
+#pragma unroll
+                for (int jj = 0; jj < JC; ++jj) read_b(buf, c * JC + jj, bv[jj]);
+                mfma_cluster(c);
+            }
+            buf = buf == NS - 1 ? 0 : buf + 1;
+        }
+    }
+    dma_wait<0>();                                 // nothing is in flight towards LDS from here on
+
+    if (a.S > 1) {
+        // partial sums of this K part, written through; the workgroup that arrives last adds the parts up in order
+        const int tile = mt * a.n_tt + tk;
+        constexpr int NACC = TAW * TBW, NBT = NACC < 16 ? NACC : 16;        // tiles fetched per round trip
+        char *pw = reinterpret_cast<char *>(a.part) + (size_t)tile * a.S * (NACC * PF_NT * 16) + wave * (NACC * 1024);
+        char *mine = pw + (size_t)sp * (NACC * PF_NT * 16);
+#pragma unroll
+        for (int i = 0; i < TAW; ++i)
+#pragma unroll
+            for (int j = 0; j < TBW; ++j) store_part(mine + (i * TBW + j) * 1024, voff, acc[i][j]);
+        if (!last_arrival(a.arrivals + tile, a.S, &ticket)) return;
+#pragma unroll
+        for (int i = 0; i < TAW; ++i)
+#pragma unroll
+            for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int k = 0; k < a.S; ++k) {
+#pragma unroll
+            for (int t0 = 0; t0 < NACC; t0 += NBT) {
+                f32x4 v[NBT];
+                load_part<NBT>(pw + (size_t)k * (NACC * PF_NT * 16) + t0 * 1024, voff, v);
+#pragma unroll
+                for (int t = 0; t < NBT; ++t) acc[(t0 + t) / TBW][(t0 + t) % TBW] += v[t];
+            }
+        }
+    }
+
+    // epilogue: lane (kg, r16) holds rows 4*kg..4*kg+3 of its TAW row tiles for token r16 of its TBW token tiles
+    const bool pairs = op.type == OP_SWIGLU || (op.type == OP_QKV && mt < a.n_mr);
+#pragma unroll
+    for (int j = 0; j < TBW; ++j) {
+        const int ttl = wb * TBW + j, tt = tt0 + ttl, tok = tt * 16 + r16;
+        const bool live = tok < a.n_tok;
+        const float scale = a.ss_in ? rs[ttl * 16 + r16] : 1.0f;
+        float s = 0.f;
         if (op.type == OP_RESID) {
-            for (int lr = jj; lr < R; lr += 32) {
-                const int n = rowidx[lr];
-                const size_t xi = (size_t)tok * op.N + n;
-                const float xn = op.x[xi] + vrow[col(lr)];
-                op.x[xi] = xn;
-                store_frag(a.frag_out, op.N >> 5, a.TT, tt, m, n, op.gain_next[n] * xn);
-                sq = fmaf(xn, xn, sq);
+#pragma unroll
+            for (int i = 0; i < TAW; ++i) {
+                const int n = mt * TM + (wa * TAW + i) * 16 + 4 * kg;
+                if (live && n < op.N) {
+                    f32x4 *xp = reinterpret_cast<f32x4 *>(op.x + (size_t)tok * op.N + n);
+                    const f32x4 xn = *xp + acc[i][j];
+                    *xp = xn;
+                    store_frag4(a.frag_out, op.N >> 5, a.TT, tt, r16, n, *reinterpret_cast<const f32x4 *>(op.gain_next + n) * xn);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) s = fmaf(xn[q], xn[q], s);
+                }
             }
-        } else if (op.type == OP_SWIGLU) {
-            for (int t = jj; t < nf; t += 32) {
-                const int n = rowidx[t];
-                const float g = vrow[col(t)] * rs, u = vrow[col(t + nf)] * rs;
-                store_frag(a.frag_out, op.N >> 5, a.TT, tt, m, n, (g / (1.0f + expf(-g))) * u);
-            }
-        } else {   // OP_QKV
-            const int half = op.hd >> 1, qd = op.H * op.hd, np = nf;
-            bf16_t *kc = op.kv_block;
-            bf16_t *vc = op.kv_block + (size_t)op.Hkv * op.max_seq * op.hd;
-            const int pos = tok;                                   // the prompt starts at position 0
-            for (int t = jj; t < R - np; t += 32) {
-                const bool is_pair = t < np;
-                const int lr = is_pair ? t : t + np;
-                const int n = rowidx[lr];
-                if (is_pair) {
-                    const int head = n / op.hd, i = n - head * op.hd;
-                    const float c = op.cos_t[(size_t)pos * half + i], s = op.sin_t[(size_t)pos * half + i];
-                    const float x0 = vrow[col(lr)] * rs, x1 = vrow[col(lr + np)] * rs;
-                    const float ra = x0 * c - x1 * s, rb = x1 * c + x0 * s;
-                    if (head < op.H) {
-                        op.q_out[(size_t)tok * qd + n] = ra;
-                        op.q_out[(size_t)tok * qd + n + half] = rb;
-                    } else {
-                        const size_t base = ((size_t)(head - op.H) * op.max_seq + pos) * op.hd + i;
-                        kc[base] = float_to_bf16_rne(ra);
-                        kc[base + half] = float_to_bf16_rne(rb);
+            s += __shfl_xor(s, 16, 64);
+            s += __shfl_xor(s, 32, 64);
+            if (kg == 0) sq[wa * TB * 16 + ttl * 16 + r16] = s;
+        } else if (pairs) {
+#pragma unroll
+            for (int i = 0; i < TAW; i += 2) {
+                const int p = mt * (TM / 2) + (wa * TAW + i) * 8 + 4 * kg;
+                if (op.type == OP_SWIGLU) {
+                    if (live && p < op.N) {
+                        f32x4 u;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float g = acc[i][j][q] * scale;
+                            u[q] = (g / (1.0f + expf(-g))) * (acc[i + 1][j][q] * scale);
+                        }
+                        store_frag4(a.frag_out, op.N >> 5, a.TT, tt, r16, p, u);
                     }
                 } else {
-                    const int vr = n - (op.H + op.Hkv) * op.hd;
-                    const int head = vr / op.hd, i = vr - head * op.hd;
-                    vc[((size_t)head * op.max_seq + pos) * op.hd + i] = float_to_bf16_rne(vrow[col(lr)] * rs);
+                    const int half = op.hd >> 1, qd = op.H * op.hd;
+                    if (live && p < (op.H + op.Hkv) * half) {
+                        const int head = p / half, d = p - head * half;            // four neighbours of one head: half is a multiple of 4
+                        const f32x4 c = *reinterpret_cast<const f32x4 *>(op.cos_t + (size_t)tok * half + d);
+                        const f32x4 sn = *reinterpret_cast<const f32x4 *>(op.sin_t + (size_t)tok * half + d);
+                        f32x4 ra, rb;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            const float x0 = acc[i][j][q] * scale, x1 = acc[i + 1][j][q] * scale;
+                            ra[q] = x0 * c[q] - x1 * sn[q];
+                            rb[q] = x1 * c[q] + x0 * sn[q];
+                        }
+                        if (head < op.H) {
+                            float *qp = op.q_out + (size_t)tok * qd + head * op.hd + d;
+                            *reinterpret_cast<f32x4 *>(qp) = ra;
+                            *reinterpret_cast<f32x4 *>(qp + half) = rb;
+                        } else {
+                            bf16_t *kp = op.kv_block + ((size_t)(head - op.H) * op.max_seq + tok) * op.hd + d;   // the prompt starts at position 0
+                            pf_store_bf16x4(kp, ra);
+                            pf_store_bf16x4(kp + half, rb);
+                        }
+                    }
+                }
+            }
+        } else {    // value rows of OP_QKV
+#pragma unroll
+            for (int i = 0; i < TAW; ++i) {
+                const int v = (mt - a.n_mr) * TM + (wa * TAW + i) * 16 + 4 * kg;
+                if (live && v < op.Hkv * op.hd) {
+                    const int head = v / op.hd, d = v - head * op.hd;
+                    pf_store_bf16x4(op.kv_block + (((size_t)op.Hkv + head) * op.max_seq + tok) * op.hd + d, acc[i][j] * scale);
                 }
             }
         }
     }
     if (op.type == OP_RESID) {
-        // this workgroup's share of sum(x^2) of row tok: the 32 threads of the row sit in one wavefront
-#pragma unroll
-        for (int off = 1; off < 32; off <<= 1) sq += __shfl_xor(sq, off, 64);
-        if (jj == 0) a.ss_out[(size_t)blockIdx.x * a.TT * 16 + tok] = sq;
-    }
-}
-
-template <int TBW>
-__global__ __launch_bounds__(PF_NT, 1) void prefill_gemm_kernel(PfArgs a) {
-    extern __shared__ __align__(16) char lds[];
-    constexpr int TB = 4 * TBW;                       // token tiles of the workgroup
-    constexpr int NB = 3 * TB * 64 / PF_NT;           // 16-byte pieces of token fragments per thread and step
-    constexpr int A_BYTES = PF_SLOTS * 1024, B_BYTES = 3 * TB * 1024;
-    char *abuf = lds;                                 // [2][A_BYTES]
-    char *bbuf = lds + 2 * A_BYTES;                   // [2][B_BYTES]
-    PfTables *tb = reinterpret_cast<PfTables *>(lds + 2 * A_BYTES + 2 * B_BYTES);
-    __shared__ size_t slot_base[PF_SLOTS];            // element offset of the slot's tile in the packed matrix
-    __shared__ int slot_rows[PF_SLOTS], slot_g[PF_SLOTS], slot_gshift[PF_SLOTS];
-
-    const GemmOp &op = a.op;
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wa = wave >> 2, wb = wave & 3, kg = lane >> 4, r16 = lane & 15;
-    const int K = op.K, KS = K >> 5, nfull = KS >> 4, rem = KS & 15;
-    const int tt0 = blockIdx.y * TB;
-    const int TTL = a.n_tok >> 4;                     // live token tiles
-
-    // row groups of this workgroup and their tile slots
-    int n_groups = 0;
-    if (tid < PF_SLOTS) { slot_rows[tid] = 0; slot_base[tid] = 0; slot_g[tid] = 1; slot_gshift[tid] = 0; }
-    __syncthreads();
-    for (int gi = 0; gi < a.G; ++gi) {
-        const int wgid = blockIdx.x * a.G + gi;
-        if (wgid >= KS_NWG) break;
-        const WgSplit s = make_split(op, wgid, KS_NWG, tb->rowidx + gi * 16 * a.T);
-        if (tid == 0) { tb->grp_R[gi] = s.R; tb->grp_nfirst[gi] = s.n_first; tb->grp_rpt[gi] = s.rpt > 0 ? s.rpt : 1; }
-        if (tid < s.T) {
-            const int slot = gi * a.T + tid;
-            slot_rows[slot] = min(s.rpt, s.R - tid * s.rpt);
-            slot_base[slot] = s.wg_base + (size_t)(tid * s.rpt) * K;
-            slot_g[slot] = s.g; slot_gshift[slot] = s.gshift;
-        }
-        n_groups = gi + 1;
-    }
-    __syncthreads();
-    // empty slots borrow slot 0's geometry and data: their products land in accumulators that are never stored
-    if (tid < PF_SLOTS && slot_rows[tid] == 0) {
-        slot_rows[tid] = max(slot_rows[0], 1); slot_base[tid] = slot_base[0]; slot_g[tid] = slot_g[0]; slot_gshift[tid] = slot_gshift[0];
-    }
-    __syncthreads();
-
-    // what this thread stages per step: two pieces of weight units, NB pieces of token fragments (kept as element
-    // offsets from the kernel's own pointers, so that the loads stay global loads)
-    size_t a_off[2]; int a_unit[2], a_g[2], a_gshift[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        const int i = tid + q * PF_NT, slot = i >> 6, piece = i & 63, rows = slot_rows[slot];
-        a_off[q] = slot_base[slot] + (size_t)min(piece, rows * 4 - 1) * 8;
-        a_unit[q] = rows * 32; a_g[q] = slot_g[slot]; a_gshift[q] = slot_gshift[slot];
-    }
-    size_t b_off[NB];
-#pragma unroll
-    for (int q = 0; q < NB; ++q) {
-        const int i = tid + q * PF_NT, pl = i / (TB * 64), ttl = (i >> 6) % TB, ln = i & 63;
-        b_off[q] = frag_off(KS, a.TT, pl, 0, min(tt0 + ttl, a.TT - 1)) + ln * 8;
-    }
-    const size_t b_step = (size_t)a.TT * 512;          // elements between consecutive steps of one plane
-    const bf16_t *__restrict__ Wg = op.W;
-    const bf16_t *__restrict__ Fg = a.frag_in;
-    u32x4 ra[2], rb[NB];
-    auto stage_load = [&](int st) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const int w16 = st & 15, kpart = w16 >> a_gshift[q], u = (st >> 4) * a_g[q] + (w16 & (a_g[q] - 1));
-            const int before = nfull * a_g[q] * kpart + min(rem, kpart * a_g[q]);
-            ra[q] = *reinterpret_cast<const u32x4 *>(Wg + a_off[q] + (size_t)(before + u) * a_unit[q]);
-        }
-#pragma unroll
-        for (int q = 0; q < NB; ++q) rb[q] = *reinterpret_cast<const u32x4 *>(Fg + b_off[q] + (size_t)st * b_step);
-        __builtin_amdgcn_sched_barrier(0);             // the loads stay at the top of the step, ahead of the MFMAs that hide them
-    };
-    auto stage_store = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) *reinterpret_cast<u32x4 *>(abuf + buf * A_BYTES + (tid + q * PF_NT) * 16) = ra[q];
-#pragma unroll
-        for (int q = 0; q < NB; ++q) *reinterpret_cast<u32x4 *>(bbuf + buf * B_BYTES + (tid + q * PF_NT) * 16) = rb[q];
-    };
-
-    // this wavefront's operand addresses inside a staged step
-    int aoff[8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        const int slot = wa * 8 + i, rows = slot_rows[slot];
-        aoff[i] = slot * 1024 + (kg * rows + min(r16, rows - 1)) * 16;
-    }
-    const int boff = (wb * TBW) * 1024 + lane * 16;
-
-    f32x4 acc[8][TBW];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-    stage_load(0);
-    stage_store(0);
-    __syncthreads();
-    for (int st = 0; st < KS; ++st) {
-        const int buf = st & 1;
-        stage_load(min(st + 1, KS - 1));               // the last step re-reads itself: harmless, keeps the loads unconditional
-        bf16x8 av[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) av[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(abuf + buf * A_BYTES + aoff[i]));
-#pragma unroll
-        for (int j = 0; j < TBW; ++j) {
-            bf16x8 bv[3];
-#pragma unroll
-            for (int p = 0; p < 3; ++p)
-                bv[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(bbuf + buf * B_BYTES + p * TB * 1024 + boff + j * 1024));
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int p = 0; p < 3; ++p) acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[p], acc[i][j], 0, 0, 0);
-        }
-        stage_store(buf ^ 1);
         __syncthreads();
-    }
-
-    // epilogue, one token tile at a time through a staging array that reuses the operand buffers
-    float *vals = reinterpret_cast<float *>(lds);      // [16][PF_VLD]
+        if (tid < TB * 16) {
+            float s = 0.f;
 #pragma unroll
-    for (int j = 0; j < TBW; ++j) {
-        for (int wq = 0; wq < 4; ++wq) {
-            const int tt = tt0 + wq * TBW + j;
-            if (tt >= TTL) continue;                   // uniform over the workgroup
-            __syncthreads();
-            if (wb == wq) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) vals[r16 * PF_VLD + (wa * 8 + i) * 16 + 4 * kg + q] = acc[i][j][q];
-            }
-            __syncthreads();
-            pf_epilogue(a, tb, vals, tt, n_groups);
+            for (int w = 0; w < WA; ++w) s += sq[w * TB * 16 + tid];
+            a.ss_out[(size_t)mt * a.TT * 16 + tt0 * 16 + tid] = s;
         }
     }
-}
-
-__host__ __device__ inline size_t pf_gemm_lds_bytes(int tbw) {
-    return (size_t)2 * PF_SLOTS * 1024 + (size_t)2 * 3 * 4 * tbw * 1024 + sizeof(PfTables);
 }
 
 // ------------------------------------------------------------------------------------------
 // Embedding of the prompt rows: x = E[tok], the first norm's operands gain (.) x in fragment order
-// and the row's rsqrt(mean(x^2) + eps). One workgroup per row.
+// and the row's sum(x^2) as its only share. One workgroup per row; d is a multiple of 32.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(PF_NT) void prefill_embed_kernel(const int32_t *toks, const bf16_t *embed, const float *gain, int d,
-                                                              float eps, int TT, float *x, bf16_t *frag, float *rstd) {
-    __shared__ float part[PF_NT / 64];
+__global__ __launch_bounds__(256) void prefill_embed_kernel(const int32_t *toks, const bf16_t *embed, const float *gain, int d,
+                                                            int TT, float *x, bf16_t *frag, float *ss) {
+    __shared__ float part[4];
     const int tok = blockIdx.x, tt = tok >> 4, m = tok & 15;
     const bf16_t *row = embed + (size_t)toks[tok] * d;
     float sq = 0.f;
-    for (int n = threadIdx.x; n < d; n += PF_NT) {
-        const float v = bf16_to_float(row[n]);
-        x[(size_t)tok * d + n] = v;
-        store_frag(frag, d >> 5, TT, tt, m, n, gain[n] * v);
-        sq = fmaf(v, v, sq);
+    for (int n = threadIdx.x * 4; n < d; n += 256 * 4) {
+        const u32x2 w = *reinterpret_cast<const u32x2 *>(row + n);
+        const f32x4 v = f32x4{bf_lo(w.x), bf_hi(w.x), bf_lo(w.y), bf_hi(w.y)};
+        *reinterpret_cast<f32x4 *>(x + (size_t)tok * d + n) = v;
+        store_frag4(frag, d >> 5, TT, tt, m, n, *reinterpret_cast<const f32x4 *>(gain + n) * v);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) sq = fmaf(v[q], v[q], sq);
     }
     sq = wave_sum(sq);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sq;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        float s = 0.f;
-        for (int w = 0; w < PF_NT / 64; ++w) s += part[w];
-        rstd[tok] = 1.0f / sqrtf(s / (float)d + eps);
-    }
+    if (threadIdx.x == 0) ss[tok] = (part[0] + part[1]) + (part[2] + part[3]);
 }
 
-// rsqrt(mean(x^2) + eps) per row from the producers' shares, summed in share order
-__global__ void prefill_rstd_kernel(const float *ss, int n_shares, int stride, int n_tok, float inv_dim, float eps, float *rstd) {
-    const int tok = blockIdx.x * blockDim.x + threadIdx.x;
-    if (tok >= n_tok) return;
+// The prompt's last row after the last block: the final norm's operands and shares as a one-row pass of the decode
+// kernels reads them (the LM head follows), and the final-norm hidden state.
+__global__ __launch_bounds__(NT) void prefill_last_row_kernel(const float *x_row, const float *gain, int d, float eps, float *act,
+                                                              float *ss, float *out0, float *out1) {
+    __shared__ float scratch[NWV];
     float s = 0.f;
-    for (int i = 0; i < n_shares; ++i) s += ss[(size_t)i * stride + tok];
-    rstd[tok] = 1.0f / sqrtf(s * inv_dim + eps);
+    for (int n = threadIdx.x; n < d; n += NT) s = fmaf(x_row[n], x_row[n], s);
+    const float sum = block_sum(s, scratch), rs = 1.0f / sqrtf(sum / (float)d + eps);
+    if (threadIdx.x < KS_NWG) ss[threadIdx.x] = threadIdx.x == 0 ? sum : 0.f;
+    for (int n = threadIdx.x; n < d; n += NT) {
+        const float v = gain[n] * x_row[n];
+        act[n] = v;
+        out0[n] = v * rs;
+        if (out1) out1[n] = v * rs;
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -349,7 +548,7 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(PfAttn a) {
     __shared__ __align__(16) float pb[4][16 * PSTR];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = lane >> 4, r16 = lane & 15;
-    const int n_rt = a.n_tok >> 4, n_b = (n_rt + 3) >> 2;
+    const int n_rt = (a.n_tok + 15) >> 4, n_b = (n_rt + 3) >> 2;
     const int b = n_b - 1 - (int)(blockIdx.x / a.H);          // long blocks first
     const int h = blockIdx.x % a.H, kvh = h / (a.H / a.Hkv);
     const int rt = min(b * 4 + wave, n_rt - 1);               // a wavefront past the last tile repeats it and stores nothing
@@ -363,7 +562,7 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(PfAttn a) {
     // the wavefront's 16 query rows as operand fragments: lane (kg, i) holds row i, dims 32*ks + 8*kg .. +7
     bf16x8 qa[QS][3];
     {
-        const float *qp = a.q + (size_t)(rt * 16 + r16) * qd + h * HD + kg * 8;
+        const float *qp = a.q + (size_t)min(rt * 16 + r16, last_pos) * qd + h * HD + kg * 8;     // rows past the prompt repeat its last one
 #pragma unroll
         for (int ks = 0; ks < QS; ++ks) {
             float v[8];

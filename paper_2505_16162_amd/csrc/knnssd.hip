@@ -46,7 +46,8 @@ struct WsLayout {
     // tuned bf16 path
     size_t act_d, qrot, ss, head_part, attn_part, attn_arrivals, split_tab;
     // tuned prompt prefill (stream-order weights only): all prompt rows at once
-    size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_ss, pf_rstd;
+    size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_ss, pf_part, pf_arrivals;
+    int pf_n_arrivals;
     int pf_tt;          // token tiles the fragment buffers are laid out for
     size_t total;
 };
@@ -71,6 +72,52 @@ static bool cfg_supported(const knnssd_model_cfg *c) {
     if (c->d_model % 8 || c->d_ffn % 8) return false;
     if (c->max_seq > 15360) return false;  // attention scores of one row are kept in LDS (60 KB)
     return true;
+}
+
+// How the prefill GEMM covers one matrix for a prompt of tt token tiles (16 rows each)
+struct PfPlan {
+    int tb;                  // token tiles per workgroup: 16, 8 (256 weight rows) or 4 (128 weight rows)
+    int n_mt, n_mr, n_tt;    // row tiles, those of them with rotary pairs (OP_QKV), workgroup tiles along the tokens
+    int S;                   // parts K is split into
+    int tiles() const { return n_mt * n_tt; }
+    size_t part_bytes() const { return S > 1 ? (size_t)tiles() * S * (tb == 4 ? 128 : 256) * tb * 16 * 4 : 0; }
+};
+
+enum { PF_QKV = 0, PF_O, PF_GU, PF_DOWN, PF_OPS };
+
+// The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x cycles of a step + what a
+// workgroup pays once + the exchange of partial sums when K is split). Estimates in cycles, from timings of whole prompts
+// with one matrix's plan varied (13B, 1024 rows: O projection 256 x 128 unsplit 155 us, 256 x 256 in three parts 170, two
+// parts 192; gate+up 256 x 256 unsplit 610, 256 x 128 630; 7B, 45 rows: QKV in 2 to 5 parts within 2 us, in one +9).
+static PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
+    const int half = g.head_dim / 2, P = (g.n_heads + g.n_kv_heads) * half, VR = g.n_kv_heads * g.head_dim;
+    const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
+    PfPlan best{};
+    double best_cost = 0;
+    for (int tb = 4; tb <= 16; tb *= 2) {
+        const int tm = tb == 4 ? 128 : 256;
+        PfPlan p{};
+        p.tb = tb;
+        p.n_mr = which == PF_QKV ? (P + tm / 2 - 1) / (tm / 2) : 0;
+        p.n_mt = which == PF_QKV ? p.n_mr + (VR + tm - 1) / tm
+                                 : (which == PF_GU ? (g.d_ffn + tm / 2 - 1) / (tm / 2) : (g.d_model + tm - 1) / tm);
+        p.n_tt = (tt + tb - 1) / tb;
+        const int slots = tb == 4 ? 2 * KS_NWG : KS_NWG;
+        const double step = tb == 16 ? 3500 : 2000, fixed = 6000, exchange = tb == 16 ? 6000 : (tb == 8 ? 3000 : 900);
+        for (int S = 1; S <= 16 && S * 4 <= KS; ++S) {
+            const int rounds = (p.tiles() * S + slots - 1) / slots;
+            if (S > 1 && rounds > 2) break;
+            const double cost = rounds * (((KS + S - 1) / S) * step + fixed + (S > 1 ? (S + 1) * exchange : 0));
+            p.S = S;
+            if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
+        }
+        if (p.S == 0) {     // K too short to split at all
+            p.S = 1;
+            const double cost = ((p.tiles() + slots - 1) / slots) * (KS * step + fixed);
+            if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
+        }
+    }
+    return best;
 }
 
 static WsLayout ws_layout(const knnssd_model_cfg *c) {
@@ -119,8 +166,18 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
             L.pf_frag_d = take(3 * rows * (size_t)c->d_model * 2);
             L.pf_frag_att = take(3 * rows * qd * 2);
             L.pf_frag_u = take(3 * rows * (size_t)c->d_ffn * 2);
-            L.pf_ss = take((size_t)KS_NWG * rows * 4);
-            L.pf_rstd = take(rows * 4);
+            L.pf_ss = take(((size_t)c->d_model + 127) / 128 * rows * 4);
+            size_t part = 0;
+            int tiles = 0;
+            for (int w = 0; w < PF_OPS; ++w)
+                for (int t = 1; t <= (int)tt; ++t) {
+                    const PfPlan p = pf_plan(*c, w, t);
+                    if (p.part_bytes() > part) part = p.part_bytes();
+                    if (p.S > 1 && p.tiles() > tiles) tiles = p.tiles();
+                }
+            L.pf_part = take(part);
+            L.pf_n_arrivals = tiles;
+            L.pf_arrivals = take((size_t)tiles * 4);
         }
     }
     L.total = off;
@@ -260,9 +317,11 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         if (ea == hipSuccess)
             ea = hipFuncSetAttribute((const void *)attn_partial_mfma_kernel<64, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)vattn_lds_bytes<64>());
         if (ea == hipSuccess)
-            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<4>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pf_gemm_lds_bytes(4));
+            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<16, 16, 2, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PfShape<16, 16, 2, 2, true>::LDS);
         if (ea == hipSuccess)
-            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<2>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)pf_gemm_lds_bytes(2));
+            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<16, 8, 2, 3, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PfShape<16, 8, 2, 3, true>::LDS);
+        if (ea == hipSuccess)
+            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<8, 4, 4, 3, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PfShape<8, 4, 4, 3, false>::LDS);
         if (ea != hipSuccess) {
             snprintf(g_hip_err, sizeof(g_hip_err), "%s (hipFuncSetAttribute)", hipGetErrorString(ea));
             delete c;
@@ -288,6 +347,8 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         c->split_head = tabulate(4, OP_HEAD, cfg->vocab, d);
         // arrival counters of the attention kernel that merges its own chunks: zero between launches
         hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, c->stream, c->wsp<int>(c->L.attn_arrivals), KS_MAX_ROWS * cfg->n_heads);
+        if (c->L.pf_n_arrivals > 0)
+            hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, c->stream, c->wsp<int>(c->L.pf_arrivals), c->L.pf_n_arrivals);
         hipError_t et = hipGetLastError();
         if (et != hipSuccess) {
             snprintf(g_hip_err, sizeof(g_hip_err), "%s (split_table_kernel)", hipGetErrorString(et));
@@ -660,94 +721,106 @@ static int32_t read_back(knnssd_ctx *c, const void *dev, size_t bytes) {
     return KNNSSD_OK;
 }
 
-// Tile slots a row group of each matrix needs in the prefill GEMM (<= 0: the shape does not fit its 16 slots)
-static int pf_slots(const knnssd_model_cfg &g, int type) {
-    auto per = [&](long long n) { return (int)((n + KS_NWG - 1) / KS_NWG); };
-    int rows;
-    if (type == OP_QKV) rows = 2 * per((long long)(g.n_heads + g.n_kv_heads) * g.head_dim / 2) + per((long long)g.n_kv_heads * g.head_dim);
-    else if (type == OP_SWIGLU) rows = 2 * per(g.d_ffn);
-    else rows = per(g.d_model);
-    const int t = (rows + 15) / 16;
-    return t <= PF_SLOTS ? t : 0;
-}
+// The prefill GEMM reads rows in runs of four neighbours of one kind: every count is a multiple of that here (tuned_ok).
+static bool prefill_tuned_ok(const knnssd_model_cfg &g) { return g.d_model % 4 == 0 && g.d_ffn % 4 == 0; }
 
-static bool prefill_tuned_ok(const knnssd_model_cfg &g) {
-    return pf_slots(g, OP_QKV) > 0 && pf_slots(g, OP_SWIGLU) > 0 && pf_slots(g, OP_RESID) > 0;
-}
-
-// The full model over the first n_tok prompt rows (a multiple of 16) with the matrix-core prefill kernels: fills the
-// KV cache at positions 0..n_tok-1. The last rows of the prompt go through an ordinary 16-row pass afterwards,
-// which also produces the first token and the routing query.
+// The full model over the n_tok prompt rows with the matrix-core prefill kernels: fills the KV cache at positions
+// 0..n_tok-1 and leaves the last row's residual stream in pf_x.
 static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_tok) {
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn;
-    const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd, TT = c->L.pf_tt, TTL = n_tok / 16;
+    const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd, TT = c->L.pf_tt, TTL = (n_tok + 15) / 16;
     hipStream_t s = c->stream;
     int32_t *toks = c->wsp<int32_t>(c->L.pf_tokens);
     float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *ss = c->wsp<float>(c->L.pf_ss);
-    float *rstd = c->wsp<float>(c->L.pf_rstd);
     bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att);
     bf16_t *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
     HIP_TRY(hipMemcpyAsync(toks, tokens_host, (size_t)n_tok * 4, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(prefill_embed_kernel, dim3(n_tok), dim3(PF_NT), 0, s, toks, (const bf16_t *)c->embed,
-                       next_gain(c, nullptr, -1), d, g.rms_eps, TT, x, frag_d, rstd);
+    hipLaunchKernelGGL(prefill_embed_kernel, dim3(n_tok), dim3(256), 0, s, toks, (const bf16_t *)c->embed,
+                       next_gain(c, nullptr, -1), d, TT, x, frag_d, ss);
+    int n_ss = 1;               // shares of sum(x^2) the producer of the residual rows left in ss
 
     GemmOp base{};
-    base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq;
+    base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq; base.inv_dim = 1.0f / (float)d; base.eps = g.rms_eps;
     base.cos_t = c->wsp<float>(c->L.rope_cos); base.sin_t = c->wsp<float>(c->L.rope_sin);
-    auto gemm = [&](const GemmOp &op, const bf16_t *fin, bf16_t *fout, const float *rs, float *ss_out, int *n_shares) {
+    PfPlan plan[PF_OPS];
+    for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_plan(g, w, TTL);
+    auto gemm = [&](int which, const GemmOp &op, const bf16_t *fin, bf16_t *fout) {
+        const PfPlan &p = plan[which];
         PfArgs a{};
-        a.op = op; a.frag_in = fin; a.frag_out = fout; a.rstd = rs; a.ss_out = ss_out; a.TT = TT; a.n_tok = n_tok;
-        a.T = pf_slots(g, op.type); a.G = PF_SLOTS / a.T;
-        const int gx = (KS_NWG + a.G - 1) / a.G;
-        // enough workgroups to fill the chip with 16 token tiles each? otherwise 8 per workgroup
-        const bool wide = (long long)gx * ((TTL + 15) / 16) >= 200;
-        if (n_shares) *n_shares = gx;
-        if (wide) hipLaunchKernelGGL(prefill_gemm_kernel<4>, dim3(gx, (TTL + 15) / 16), dim3(PF_NT), pf_gemm_lds_bytes(4), s, a);
-        else hipLaunchKernelGGL(prefill_gemm_kernel<2>, dim3(gx, (TTL + 7) / 8), dim3(PF_NT), pf_gemm_lds_bytes(2), s, a);
-    };
-    auto norm = [&](int n_shares) {
-        hipLaunchKernelGGL(prefill_rstd_kernel, dim3((n_tok + 255) / 256), dim3(256), 0, s, ss, n_shares, TT * 16, n_tok,
-                           1.0f / (float)d, g.rms_eps, rstd);
+        a.op = op; a.frag_in = fin; a.frag_out = fout; a.TT = TT; a.n_tok = n_tok;
+        const bool normed = which == PF_QKV || which == PF_GU;
+        a.ss_in = normed ? ss : nullptr; a.n_ss = n_ss; a.ss_out = ss;
+        a.part = c->wsp<float>(c->L.pf_part); a.arrivals = c->wsp<int>(c->L.pf_arrivals);
+        a.n_mt = p.n_mt; a.n_mr = p.n_mr; a.n_tt = p.n_tt; a.S = p.S;
+        const dim3 grid((p.tiles() * p.S + 7) / 8 * 8), wg(PF_NT);
+        if (p.tb == 16) hipLaunchKernelGGL((prefill_gemm_kernel<16, 16, 2, 2, true>), grid, wg, (PfShape<16, 16, 2, 2, true>::LDS), s, a);
+        else if (p.tb == 8) hipLaunchKernelGGL((prefill_gemm_kernel<16, 8, 2, 3, true>), grid, wg, (PfShape<16, 8, 2, 3, true>::LDS), s, a);
+        else hipLaunchKernelGGL((prefill_gemm_kernel<8, 4, 4, 3, false>), grid, wg, (PfShape<8, 4, 4, 3, false>::LDS), s, a);
+        if (!normed) n_ss = p.n_mt;
     };
     for (int b = 0; b < g.n_blocks; ++b) {
         bf16_t *kvb = (bf16_t *)(c->kv + (size_t)b * c->kv_block_bytes);
-        int shares = 0;
         GemmOp o = base;
-        o.type = OP_QKV; o.W = (const bf16_t *)c->wqkv[b]; o.N = qkvd; o.K = d; o.q_out = q; o.kv_block = kvb;
-        gemm(o, frag_d, nullptr, rstd, nullptr, nullptr);
+        o.type = OP_QKV; o.W = (const bf16_t *)c->wqkv[b]; o.N = qkvd; o.K = d; o.q_out = q; o.kv_block = kvb; o.split = c->split_qkv;
+        gemm(PF_QKV, o, frag_d, nullptr);
         PfAttn at{};
         at.q = q; at.kv_block = kvb; at.frag_out = frag_att; at.H = H; at.Hkv = Hkv; at.max_seq = g.max_seq; at.TT = TT; at.n_tok = n_tok;
         if (hd == 128) hipLaunchKernelGGL(prefill_attn_kernel<128>, dim3(((TTL + 3) / 4) * H), dim3(256), 0, s, at);
         else hipLaunchKernelGGL(prefill_attn_kernel<64>, dim3(((TTL + 3) / 4) * H), dim3(256), 0, s, at);
         GemmOp r = base;
-        r.type = OP_RESID; r.W = (const bf16_t *)c->wo[b]; r.N = d; r.K = qd; r.x = x; r.gain_next = next_gain(c, nullptr, 2 * b);
-        gemm(r, frag_att, frag_d, nullptr, ss, &shares);
-        norm(shares);
+        r.type = OP_RESID; r.W = (const bf16_t *)c->wo[b]; r.N = d; r.K = qd; r.x = x; r.gain_next = next_gain(c, nullptr, 2 * b); r.split = c->split_o;
+        gemm(PF_O, r, frag_att, frag_d);
         GemmOp u = base;
-        u.type = OP_SWIGLU; u.W = (const bf16_t *)c->wgu[b]; u.N = F; u.K = d;
-        gemm(u, frag_d, frag_u, rstd, nullptr, nullptr);
+        u.type = OP_SWIGLU; u.W = (const bf16_t *)c->wgu[b]; u.N = F; u.K = d; u.split = c->split_gu;
+        gemm(PF_GU, u, frag_d, frag_u);
         GemmOp dn = base;
-        dn.type = OP_RESID; dn.W = (const bf16_t *)c->wdown[b]; dn.N = d; dn.K = F; dn.x = x; dn.gain_next = next_gain(c, nullptr, 2 * b + 1);
-        gemm(dn, frag_u, frag_d, nullptr, ss, &shares);
-        norm(shares);
+        dn.type = OP_RESID; dn.W = (const bf16_t *)c->wdown[b]; dn.N = d; dn.K = F; dn.x = x; dn.gain_next = next_gain(c, nullptr, 2 * b + 1); dn.split = c->split_down;
+        gemm(PF_DOWN, dn, frag_u, frag_d);
     }
+    HIP_TRY(hipGetLastError());
+    return KNNSSD_OK;
+}
+
+// Prompts of at least this many rows take the prefill kernels in one go, shorter ones one pass of the verification kernels
+// (7B widths, 4 blocks: a 16-row pass 0.65 ms, 17 to 45 rows 0.82 ms here, two 16-row passes 1.2 ms)
+static const int PF_MIN_ROWS = 17;
+
+// The LM head over the prompt's last row (a one-row pass of the decode kernel) behind prefill_tuned. `row`: the logits row
+// it is kept in (the row the prompt's last chunk would have it at when it is cut into chunks of 16).
+static int32_t prefill_head(knnssd_ctx *c, int n_tok, int row, float *last_hidden_dev) {
+    const knnssd_model_cfg &g = c->cfg;
+    const int d = g.d_model;
+    PassCtl *ver = c->wsp<PassCtl>(c->L.ver_ctl);
+    const int32_t none = 0;
+    KS_TRY(set_pass(c, ver, 1, 1, n_tok - 1, 0, &none));
+    hipLaunchKernelGGL(prefill_last_row_kernel, dim3(1), dim3(NT), 0, c->stream, c->wsp<float>(c->L.pf_x) + (size_t)(n_tok - 1) * d,
+                       c->final_norm, d, g.rms_eps, c->wsp<float>(c->L.act_d), c->wsp<float>(c->L.ss), c->wsp<float>(c->L.hidden_last), last_hidden_dev);
+    GemmOp h{};
+    h.n_ss = KS_NWG; h.inv_dim = 1.0f / (float)d; h.eps = g.rms_eps;
+    h.type = OP_HEAD; h.W = (const bf16_t *)c->lm_head; h.N = g.vocab; h.K = d; h.act_in = c->wsp<float>(c->L.act_d);
+    h.ss_in = c->wsp<float>(c->L.ss); h.logits = c->wsp<float>(c->L.logits) + (size_t)row * g.vocab;
+    h.head_part = c->wsp<HeadPartial>(c->L.head_part); h.split = c->split_head; h.n_rows = 1;
+    hipLaunchKernelGGL(gemv_kernel, dim3(KS_NWG), dim3(NT), gemv_lds_bytes(d), c->stream, h, ver);
+    hipLaunchKernelGGL(head_final_kernel, dim3(KS_MAX_ROWS), dim3(NT), 0, c->stream, c->wsp<HeadPartial>(c->L.head_part), KS_NWG, ver,
+                       c->wsp<HeadResult>(c->L.head));
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }
 
 static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, float *last_hidden_dev, int32_t *first_token) {
     PassCtl *ver = c->wsp<PassCtl>(c->L.ver_ctl);
-    int s0 = 0;
-    if (c->tuned_prefill) {
-        // every complete 16-row tile before the prompt's last rows goes through the matrix-core prefill
-        const int n_main = (n - 1) / KS_MAX_ROWS * KS_MAX_ROWS;
-        if (n_main >= 2 * KS_MAX_ROWS) {
-            KS_TRY(prefill_tuned(c, tokens, n_main));
-            s0 = n_main;
-        }
+    if (c->tuned_prefill && n >= PF_MIN_ROWS) {
+        KS_TRY(prefill_tuned(c, tokens, n));
+        KS_TRY(prefill_head(c, n, (n - 1) % KS_MAX_ROWS, last_hidden_dev));
+        KS_TRY(read_back(c, &c->wsp<HeadResult>(c->L.head)->tok[0], 4));
+        *first_token = c->h_stage[0];
+        c->prefilled = true;
+        c->cache_len = n;
+        c->draft_len = n;
+        return KNNSSD_OK;
     }
-    for (int s = s0; s < n; s += KS_MAX_ROWS) {
+    for (int s = 0; s < n; s += KS_MAX_ROWS) {
         int rows = n - s < KS_MAX_ROWS ? n - s : KS_MAX_ROWS;
         bool last = s + rows >= n;
         KS_TRY(set_pass(c, ver, 1, rows, s, last ? rows - 1 : rows, tokens + s));
