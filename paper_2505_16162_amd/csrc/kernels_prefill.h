@@ -1,74 +1,88 @@
 // Prompt prefill for the tuned bf16 path (gfx950): the full model over hundreds to thousands of rows.
 //
 // Unlike a decode pass this is bound by the matrix cores, so it has kernels of its own. They read the
-// SAME stream-order weights as the decode kernels (a unit = <= 16 rows x 32 columns is one MFMA A
-// operand) and keep the same arithmetic: activations stay fp32-exact as three bf16 planes, so an
-// output takes three MFMAs per 32 columns and the products are exact in the fp32 accumulator.
+// SAME stream-order weights as the decode kernels (a unit = <= 16 rows x 32 columns is one MFMA A operand).
+//
+// Arithmetic. Activations are fp32. A row of them (one token) is scaled by a power of two so that its largest value lies
+// just below 2^15 and split into two fp16 planes, hi = fp16(v), lo = fp16(v - hi): 22 bits and a sign, |v - hi - lo| <=
+// 2^-24 |v| down to 2^-16 of the row's largest value and 2^-40 of that largest value below. Weights are bf16; times 2^11
+// they are fp16 numbers without rounding while 2^-28 <= |w| < 32. So a product takes two matrix instructions, exact in the
+// fp32 accumulator. (Three bf16 planes hold all 24 bits and take three; measured against 64 bits the two are the same: what
+// is left is the accumulator's rounding.) The kernels look at every weight they convert: one that fp16 cannot hold
+// (|w| >= 32, infinities, NaN) or eight neighbours whose largest is below 2^-15 raise a flag, and the host runs the prompt
+// again with three bf16 planes, which hold any weight and any activation as they are.
 //
 // Activations of all rows live in "fragment order": [plane][32-column step][16-row tile][lane][8],
 // lane = 16*kg + r holding row r of the tile and columns 8*kg..8*kg+7 of the step, i.e. the MFMA B
-// operand of v_mfma_f32_16x16x32_bf16 as stored, so staging a tile is a linear copy.
+// operand of v_mfma_f32_16x16x32 as stored, so staging a tile is a linear copy. Beside them one factor per row: the power of
+// two the planes were scaled by (and the weights' 2^-11), times the RMSNorm's rsqrt where the rows were normalised.
 //
 // prefill_gemm_kernel: a workgroup owns TA tiles of 16 weight rows x TB tiles of 16 tokens and walks K (or one of S parts
-// of it) in steps of 32 columns. Weights and activations go from memory straight to LDS (16-byte loads whose LDS side is
-// linear and whose memory side is free), so a tile is filled with whatever rows suit it, wherever they lie in the decode
-// layout: no dead rows from the decode layout's short tiles (20 rows per workgroup = two tiles of 10), and the two dot
-// products an epilogue combines sit in one lane's accumulators, so epilogues run in registers on four rows at a time.
+// of it) in steps of 32 columns. Activations, and weights where they are not converted on the way, go from memory straight
+// to LDS (16-byte loads whose LDS side is linear and whose memory side is free). A tile is filled with whatever rows suit
+// it, wherever they lie in the decode layout: no dead rows from the decode layout's short tiles (20 rows per workgroup = two
+// tiles of 10), and the two dot products an epilogue combines sit in one lane's accumulators.
 #pragma once
 #include "kernels_bf16.h"
 
 namespace ks {
 
 constexpr int PF_NT = 512;             // threads per workgroup of the prefill GEMM (8 wavefronts)
+constexpr int PF_RT = 1024;            // ... and of the row kernels between the products
+constexpr int PF_WSHIFT = 11;          // fp16 weights hold w * 2^11
+constexpr unsigned int PF_W_TOO_LARGE = 0x4200, PF_W_SMALL = 0x3800;      // bf16 bits of 32 and of 2^-15
+
+typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 struct PfArgs {
-    GemmOp op;              // type, W, N, K, split, x, gain_next, q_out, kv_block, cos_t, sin_t, H, Hkv, hd, max_seq, inv_dim, eps
-    const bf16_t *frag_in;  // [3][K/32][TT][512] fragment order
-    bf16_t *frag_out;       // same layout over the output features (OP_RESID / OP_SWIGLU)
-    const float *ss_in;     // [n_ss][TT*16] shares of sum(x^2) per input row; nullptr: input is not normalised
-    int n_ss;
-    float *ss_out;          // OP_RESID: [row tiles][TT*16] this workgroup's share of sum(x^2) per row
-    float *part;            // split K: [tile][S][wavefront][accumulator tile][lane][4] partial sums
-    int *arrivals;          // split K: [tile] arrival counters, zero between launches
+    GemmOp op;              // type, W, N, K, split, x, gain_next, q_out, kv_block, cos_t, sin_t, H, Hkv, hd, max_seq
+    const bf16_t *frag_in;  // [planes][K/32][TT][512] fragment order
+    const float *scale;     // [TT*16] factor of the input rows
+    float *out;             // PF_PARTS: [K part][out_rows][n_mt * rows of a tile], tile order along the columns; PF_SWIGLU: [n_tok][N]
+    const u32x2 *rows;      // (PfRow) [n_mt * rows of a tile] where each row of the tiles lies
+    int *flag;              // raised when a weight does not fit the two-plane arithmetic
     int TT;                 // token tiles the fragment buffers are laid out for
-    int n_tok;              // live rows
+    int n_tok, out_rows;    // live rows; row stride of a K part in out
     int n_mt, n_mr;         // row tiles of the matrix; OP_QKV: those that hold rotary pairs (the others hold value rows)
-    int n_tt, S;            // token tiles (workgroup tiles) of the launch, parts K is split into
+    int n_tt;               // token tiles (workgroup tiles) of the launch
+    int S, steps, longer;   // K parts, 32-column steps of a part, and how many parts take one more
+    float inv_tiles;        // 1 / (n_mt * n_tt)
 };
 
 __device__ __forceinline__ size_t frag_off(int KS, int TT, int pl, int ks, int tt) {
     return (((size_t)pl * KS + ks) * TT + tt) * 512;
 }
 
-// the three bf16 planes of v at feature n of row (tt, m), fragment order
-__device__ __forceinline__ void store_frag(bf16_t *frag, int KS, int TT, int tt, int m, int n, float v) {
-    const unsigned int u = __float_as_uint(v);
-    const float hi = __uint_as_float(u & 0xffff0000u);
-    const float r1 = v - hi;
-    const float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-    const float lo = r1 - mid;
-    const size_t in_tile = (size_t)((((n & 31) >> 3) * 16 + m) * 8 + (n & 7));
-    frag[frag_off(KS, TT, 0, n >> 5, tt) + in_tile] = (bf16_t)(u >> 16);
-    frag[frag_off(KS, TT, 1, n >> 5, tt) + in_tile] = (bf16_t)(__float_as_uint(mid) >> 16);
-    frag[frag_off(KS, TT, 2, n >> 5, tt) + in_tile] = (bf16_t)(__float_as_uint(lo) >> 16);
-}
-
-// ... of the four values at features n..n+3 (n a multiple of 4): one 8-byte store per plane
-__device__ __forceinline__ void store_frag4(bf16_t *frag, int KS, int TT, int tt, int m, int n, f32x4 v) {
-    unsigned int h[4], md[4], l[4];
+// The planes of the eight values at features n..n+7 (n a multiple of 8) of row (tt, m), fragment order: one 16-byte store
+// per plane. NP = 2: fp16 (v is scaled already); NP = 3: bf16 by truncation, hi + mid + lo = v.
+template <int NP>
+__device__ __forceinline__ void store_frag8(bf16_t *frag, int KS, int TT, int tt, int m, int n, const float *v) {
+    const size_t in_tile = (size_t)(((n & 31) >> 3) * 16 + m) * 8;
+    unsigned int w[NP][4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-        h[e] = __float_as_uint(v[e]);
-        const float r1 = v[e] - __uint_as_float(h[e] & 0xffff0000u);
-        md[e] = __float_as_uint(r1);
-        l[e] = __float_as_uint(r1 - __uint_as_float(md[e] & 0xffff0000u));
+        const float a = v[2 * e], b = v[2 * e + 1];
+        if constexpr (NP == 2) {
+            const f16x2 h = f16x2{(_Float16)a, (_Float16)b};
+            const f16x2 l = f16x2{(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1])};
+            w[0][e] = __builtin_bit_cast(unsigned int, h);
+            w[1][e] = __builtin_bit_cast(unsigned int, l);
+        } else {
+            // the upper halves of two neighbouring values make one register of a plane
+            const unsigned int a0 = __float_as_uint(a), b0 = __float_as_uint(b);
+            const float ra = a - __uint_as_float(a0 & 0xffff0000u), rb = b - __uint_as_float(b0 & 0xffff0000u);
+            const unsigned int a1 = __float_as_uint(ra), b1 = __float_as_uint(rb);
+            const unsigned int a2 = __float_as_uint(ra - __uint_as_float(a1 & 0xffff0000u)), b2 = __float_as_uint(rb - __uint_as_float(b1 & 0xffff0000u));
+            w[0][e] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+            w[1][e] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+            w[2][e] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);
+        }
     }
-    const size_t in_tile = (size_t)((((n & 31) >> 3) * 16 + m) * 8 + (n & 7));
-    auto put = [&](int pl, const unsigned int *u) {
-        *reinterpret_cast<u32x2 *>(frag + frag_off(KS, TT, pl, n >> 5, tt) + in_tile) =
-            u32x2{__builtin_amdgcn_perm(u[1], u[0], 0x07060302u), __builtin_amdgcn_perm(u[3], u[2], 0x07060302u)};
-    };
-    put(0, h); put(1, md); put(2, l);
+#pragma unroll
+    for (int pl = 0; pl < NP; ++pl)
+        *reinterpret_cast<u32x4 *>(frag + frag_off(KS, TT, pl, n >> 5, tt) + in_tile) = u32x4{w[pl][0], w[pl][1], w[pl][2], w[pl][3]};
 }
 
 // four values rounded to bf16 (nearest even), 8-byte store
@@ -100,81 +114,61 @@ __device__ __forceinline__ void pf_meet() {
     asm volatile("" ::: "memory");
 }
 
-// Partial sums that another workgroup of the launch reads: written through to memory and read from there, whichever die's
-// L2 the two sit behind.
-__device__ __forceinline__ void store_part(char *base, unsigned int off, f32x4 v) {
-    asm volatile("s_nop 4\n\tglobal_store_dwordx4 %0, %1, %2 sc1" : : "v"(off), "v"(v), "s"(base) : "memory");
+// Eight bf16 weights as fp16 times 2^11, and what the running check of them needs: the largest magnitude seen (bf16 bits,
+// both halves of the word) and the smallest nonzero maximum of eight, minus one.
+struct PfCheck { u16x2 top; unsigned int low; };
+__device__ __forceinline__ u32x4 weights_to_f16(u32x4 w, PfCheck &c) {
+    u32x4 r;
+    u16x2 m = u16x2{0, 0};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        constexpr float k = (float)(1 << PF_WSHIFT);
+        r[e] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_pkrtz(bf_lo(w[e]) * k, bf_hi(w[e]) * k));
+        m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[e] & 0x7fff7fffu));
+    }
+    c.top = __builtin_elementwise_max(c.top, m);
+    c.low = min(c.low, max((unsigned int)m[0], (unsigned int)m[1]) - 1u);        // eight zeros wrap round and do not count
+    return r;
 }
-// N pieces, 1 KB apart (the wait is part of the block: no register is ever seen with a load in flight)
-template <int N> __device__ __forceinline__ void load_part(const char *base, unsigned int off, f32x4 *v);
-template <> __device__ __forceinline__ void load_part<4>(const char *base, unsigned int off, f32x4 *v) {
-    asm volatile(
-        "s_nop 4\n\tglobal_load_dwordx4 %0, %4, %5 offset:-4096 sc1\n\t"
-        "global_load_dwordx4 %1, %4, %5 offset:-3072 sc1\n\t"
-        "global_load_dwordx4 %2, %4, %5 offset:-2048 sc1\n\t"
-        "global_load_dwordx4 %3, %4, %5 offset:-1024 sc1\n\t"
-        "s_waitcnt vmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3])
-        : "v"(off), "s"(base + 4096) : "memory");
-}
-template <> __device__ __forceinline__ void load_part<16>(const char *base, unsigned int off, f32x4 *v) {
-    asm volatile(
-        "s_nop 4\n\tglobal_load_dwordx4 %0, %16, %17 offset:-4096 sc1\n\t"
-        "global_load_dwordx4 %1, %16, %17 offset:-3072 sc1\n\t"
-        "global_load_dwordx4 %2, %16, %17 offset:-2048 sc1\n\t"
-        "global_load_dwordx4 %3, %16, %17 offset:-1024 sc1\n\t"
-        "global_load_dwordx4 %4, %16, %17 offset:0 sc1\n\t"
-        "global_load_dwordx4 %5, %16, %17 offset:1024 sc1\n\t"
-        "global_load_dwordx4 %6, %16, %17 offset:2048 sc1\n\t"
-        "global_load_dwordx4 %7, %16, %17 offset:3072 sc1\n\t"
-        "global_load_dwordx4 %8, %16, %18 offset:-4096 sc1\n\t"
-        "global_load_dwordx4 %9, %16, %18 offset:-3072 sc1\n\t"
-        "global_load_dwordx4 %10, %16, %18 offset:-2048 sc1\n\t"
-        "global_load_dwordx4 %11, %16, %18 offset:-1024 sc1\n\t"
-        "global_load_dwordx4 %12, %16, %18 offset:0 sc1\n\t"
-        "global_load_dwordx4 %13, %16, %18 offset:1024 sc1\n\t"
-        "global_load_dwordx4 %14, %16, %18 offset:2048 sc1\n\t"
-        "global_load_dwordx4 %15, %16, %18 offset:3072 sc1\n\t"
-        "s_waitcnt vmcnt(0)"
-        : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]), "=&v"(v[7]), "=&v"(v[8]), "=&v"(v[9]), "=&v"(v[10]), "=&v"(v[11]), "=&v"(v[12]), "=&v"(v[13]), "=&v"(v[14]), "=&v"(v[15])
-        : "v"(off), "s"(base + 4096), "s"(base + 12288) : "memory");
+__device__ __forceinline__ bool weights_fit(const PfCheck &c) {
+    return max((unsigned int)c.top[0], (unsigned int)c.top[1]) < PF_W_TOO_LARGE && c.low >= PF_W_SMALL - 1u;
 }
 
-// Where one row of a workgroup's tile lies in the packed matrix: the 16-byte piece (8 columns 8*kg..) of step 0's unit
-struct PfRow { const bf16_t *p; int unit, gshift; };
+// Where one row of a tile lies in the packed matrix. Tabulated when the context is created (prefill_row_table_kernel), one
+// entry per row of each tile: x = the row's first 16-byte piece (8 columns) of step 0, in pieces from the matrix's start;
+// y = rows of the decode layout's tile it belongs to (pieces between column groups, a quarter of a unit) | gshift << 16.
+typedef u32x2 PfRow;
 
 // workgroup of the decode layout that owns item n of N (inverse of wg_share)
 __device__ __forceinline__ int pf_owner(int n, int N) { return (int)((((unsigned int)n + 1u) * (unsigned int)KS_NWG - 1u) / (unsigned int)N); }
 
 // Row sr of row tile mt (TM rows). Which matrix row that is, is free to choose, since every row is fetched from wherever
 // it lies: pairs whose two dot products meet in an epilogue (rotary halves, gate / up rows) sit in neighbouring 16-row
-// tiles at the same place, so that one lane holds both. Rows past the end repeat the last one (never stored).
-template <int TM>
-__device__ __forceinline__ PfRow pf_row(const PfArgs &a, int mt, int sr, int kg) {
-    const GemmOp &op = a.op;
-    const bool pairs = op.type == OP_SWIGLU || (op.type == OP_QKV && mt < a.n_mr);
+// tiles at the same place, so that one lane holds both. Rows past the end repeat the last one (never used).
+// op: type, N, K, head counts and split table of the matrix; n_mr: its row tiles of rotary pairs (OP_QKV).
+__global__ void prefill_row_table_kernel(GemmOp op, int TM, int n_mr, int n_entries, PfRow *table) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= n_entries) return;
+    const int mt = i / TM, sr = i - mt * TM;
+    const bool pairs = op.type == OP_SWIGLU || (op.type == OP_QKV && mt < n_mr);
     int wg, lr;
     if (pairs) {
         const int P = op.type == OP_SWIGLU ? op.N : (op.H + op.Hkv) * (op.hd >> 1);
         const int p = min(mt * (TM / 2) + (sr >> 5) * 16 + (sr & 15), P - 1);
         wg = pf_owner(p, P);
-        lr = p - wg_share(P, wg) + ((sr >> 4) & 1) * a.op.split[wg].n_first;
+        lr = p - wg_share(P, wg) + ((sr >> 4) & 1) * op.split[wg].n_first;
     } else if (op.type == OP_QKV) {
-        const int VR = op.Hkv * op.hd, v = min((mt - a.n_mr) * TM + sr, VR - 1);
+        const int VR = op.Hkv * op.hd, v = min((mt - n_mr) * TM + sr, VR - 1);
         wg = pf_owner(v, VR);
-        lr = v - wg_share(VR, wg) + 2 * a.op.split[wg].n_first;
+        lr = v - wg_share(VR, wg) + 2 * op.split[wg].n_first;
     } else {
         const int n = min(mt * TM + sr, op.N - 1);
         wg = pf_owner(n, op.N);
         lr = n - wg_share(op.N, wg);
     }
-    const WgSplit &s = a.op.split[wg];
+    const WgSplit &s = op.split[wg];
     const int t = lr / s.rpt, rit = lr - t * s.rpt, rows_t = min(s.rpt, s.R - t * s.rpt);
-    PfRow r;
-    r.p = op.W + s.wg_base + (size_t)(t * s.rpt) * op.K + (size_t)(kg * rows_t + rit) * 8;
-    r.unit = rows_t * 32;
-    r.gshift = s.gshift;
-    return r;
+    table[i] = u32x2{(unsigned int)((s.wg_base + (size_t)(t * s.rpt) * op.K) / 8 + rit), (unsigned int)(rows_t | (s.gshift << 16))};
 }
 
 // position of 32-column step st among the units of a tile (the order pack_matrix_kernel wrote them in)
@@ -183,76 +177,140 @@ __device__ __forceinline__ int pf_unit_index(int st, int KS, int gshift) {
     return nfull * g * kpart + min(rem, kpart * g) + (st >> 4) * g + (w16 & (g - 1));
 }
 
-// TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS.
+// Epilogue arithmetic on four neighbours (a head's half and every row count are multiples of 4)
+__device__ __forceinline__ f32x4 pf_swiglu(f32x4 g, f32x4 u) {
+    f32x4 r;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) r[q] = (g[q] / (1.0f + expf(-g[q]))) * u[q];
+    return r;
+}
+// rotary pairs p..p+3 (first and second members x0, x1) of row tok (the prompt starts at position 0)
+__device__ __forceinline__ void pf_rope_store(const GemmOp &op, int tok, int p, f32x4 x0, f32x4 x1) {
+    const int half = op.hd >> 1, head = p >> (op.hd == 128 ? 6 : 5), d = p & (half - 1);      // head_dim is 64 or 128
+    const f32x4 c = *reinterpret_cast<const f32x4 *>(op.cos_t + (size_t)tok * half + d);
+    const f32x4 sn = *reinterpret_cast<const f32x4 *>(op.sin_t + (size_t)tok * half + d);
+    f32x4 ra, rb;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        ra[q] = x0[q] * c[q] - x1[q] * sn[q];
+        rb[q] = x1[q] * c[q] + x0[q] * sn[q];
+    }
+    if (head < op.H) {
+        float *qp = op.q_out + ((size_t)tok * op.H + head) * op.hd + d;
+        *reinterpret_cast<f32x4 *>(qp) = ra;
+        *reinterpret_cast<f32x4 *>(qp + half) = rb;
+    } else {
+        bf16_t *kp = op.kv_block + ((size_t)(head - op.H) * op.max_seq + tok) * op.hd + d;
+        pf_store_bf16x4(kp, ra);
+        pf_store_bf16x4(kp + half, rb);
+    }
+}
+__device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v, f32x4 val) {
+    const int head = v >> (op.hd == 128 ? 7 : 6), d = v & (op.hd - 1);
+    pf_store_bf16x4(op.kv_block + (((size_t)op.Hkv + head) * op.max_seq + tok) * op.hd + d, val);
+}
+
+// TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS, NP planes.
+// What bounds it. 256 x 256 (long prompts): the matrix cores. One meeting per step for all wavefronts together kept the
+// matrix pipe 55 % busy; two groups one phase apart 82 % at three bf16 planes, and 1.50-1.55 PFLOP/s issued, where a large
+// library product in bf16 reaches 1.59 on this card (the clock falls to 1.8 GHz). So the way on was fewer instructions, two
+// fp16 planes: 13B-shaped, 4096 rows, QKV 1.30 -> 0.94-1.05 ms, gate+up 2.23 -> 1.64-1.75 ms. 256 x 128 (65 to about 250
+// rows): operand reads and the conversion of the weights weigh more, 0.72 of that rate. 128 x 64 (up to 64 rows): the weight
+// stream; three workgroups per unit and K parts so that every unit streams; 8 us of a launch are its fixed cost.
 // PP: the wavefronts form two groups (one wavefront of each on every SIMD) that run one phase apart: while one group
-// issues its matrix instructions the other reads its operands from LDS.
-// What bounds it: at 256 x 256 the matrix cores (96 matrix instructions of 16 cycles per wavefront and step against 20 KB
-// of LDS reads); 13B-shaped, 4096 rows: 1.50-1.55 PFLOP/s issued (three planes) on QKV and gate+up, where a large library
-// product in bf16 reaches 1.59 on this card; one meeting per step for all wavefronts together ran at 1.18. Up to 64 rows
-// it is the weight stream: 128-row tiles, two workgroups per unit, K split until every unit has work.
-// Whole prompts, 4 blocks, before (a tile per decode-layout tile, the last rows in a 16-row pass of their own) and after:
-// 7B 45 rows 4.47 -> 0.82 ms, Qwen-14B 777 rows 8.24 -> 5.28, 13B 1024 rows 9.41 -> 6.17, 13B 4096 rows 37.3 -> 27.2.
-template <int TA, int TB, int WA, int NS, bool PP>
+// issues its matrix instructions the other reads its operands from LDS and converts the weights of a later step.
+template <int NP, int TA, int TB, int WA, int NS, bool PP>
 struct PfShape {
     static constexpr int WB = 8 / WA, TAW = TA / WA, TBW = TB / WB;
     static constexpr int TM = TA * 16;
-    static constexpr int A_BYTES = TA * 1024, STAGE = A_BYTES + 3 * TB * 1024;
+    static constexpr int A_BYTES = TA * 1024, STAGE = A_BYTES + NP * TB * 1024;
     static constexpr int NA = TA * 64 / PF_NT;                   // weight pieces per thread and step
-    static constexpr int NB = (3 * TB + 7) / 8;                  // token fragments per wavefront and step
-    static constexpr size_t LDS = (size_t)NS * STAGE + (size_t)TB * 16 * 4 * (1 + WA);
+    static constexpr int NB = (NP * TB + 7) / 8;                 // token fragments per wavefront and step
+    static constexpr size_t LDS = (size_t)NS * STAGE;
 };
 
-template <int TA, int TB, int WA, int NS, bool PP>
-__global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(PfArgs a) {
-    typedef PfShape<TA, TB, WA, NS, PP> Sh;
+// What becomes of the sums: stored as they are (a K part, or a row kernel finishes them anyway), SwiGLU, or RoPE + cache.
+// (A build per kind: a workgroup's fixed cost is largely its instructions in front of the first load and the fetch of those
+// behind the loop, 4-5 us with everything in one build.)
+enum { PF_PARTS = 0, PF_SWIGLU, PF_ROPE };
+
+template <int NP, int TA, int TB, int WA, int NS, bool PP, int EPI>
+__global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(PfArgs a) {
+    typedef PfShape<NP, TA, TB, WA, NS, PP> Sh;
     constexpr int TAW = Sh::TAW, TBW = Sh::TBW, TM = Sh::TM;
+    constexpr bool CONV_STAGE = NP == 2 && PP, CONV_READ = NP == 2 && !PP;     // where weights become fp16: on the way to LDS, or
+                                                                               // (few tokens, nothing to save) when they are read
     extern __shared__ __align__(16) char lds[];
-    float *rs = reinterpret_cast<float *>(lds + NS * Sh::STAGE);     // [TB*16] norm scale of the tile's tokens
-    float *sq = rs + TB * 16;                                        // [WA][TB*16]
-    __shared__ int ticket;
     const GemmOp &op = a.op;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wa = PP ? wave >> 2 : wave / Sh::WB, wb = PP ? wave & 3 : wave % Sh::WB, kg = lane >> 4, r16 = lane & 15;
     const int KS = op.K >> 5;
 
-    // workgroup -> (K part, token tile, row tile). Workgroups are dealt to the 8 dies by index: each die takes a run of
-    // the order below, in which neighbours share weights (four token tiles) or activations (consecutive row tiles)
-    const int total = a.n_mt * a.n_tt * a.S;
-    const int per = (total + 7) >> 3, lin = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per || lin >= total) return;
-    const int part_tiles = a.n_mt * a.n_tt;
-    const int sp = lin / part_tiles, in_part = lin - sp * part_tiles;
-    const int tb4 = in_part / (a.n_mt * 4), in_blk = in_part - tb4 * (a.n_mt * 4), tw = min(4, a.n_tt - tb4 * 4);
-    const int mt = in_blk / tw, tk = tb4 * 4 + (in_blk - mt * tw);
+    // workgroup -> (K part, token tile, row tile). Workgroups are dealt to the 8 dies by index: each die takes a run of the
+    // order below, in which neighbours share weights (four token tiles) or activations. At most seven workgroups of a launch
+    // are left over: ones that return at once still take their turn on the units, and 48 of them among 240 cost the
+    // others a second round.
+    const int tiles = a.n_mt * a.n_tt, total = tiles * a.S, run = blockIdx.x & 7;
+    int lin = (total * run >> 3) + (int)(blockIdx.x >> 3), sp = 0;
+    if (lin >= total * (run + 1) >> 3) return;
+    if (a.S > 1) { sp = div_small(lin, tiles, a.inv_tiles); lin -= sp * tiles; }
+    int mt = lin, tk = 0;
+    if (a.n_tt > 1) {
+        const int tb4 = lin / (a.n_mt * 4), in_blk = lin - tb4 * (a.n_mt * 4), tw = min(4, a.n_tt - tb4 * 4);
+        mt = in_blk / tw;
+        tk = tb4 * 4 + (in_blk - mt * tw);
+    }
     const int tt0 = tk * TB;
-    const int st0 = (int)((long long)KS * sp / a.S), cnt = (int)((long long)KS * (sp + 1) / a.S) - st0;
+    const int st0 = sp * a.steps + min(sp, a.longer), cnt = a.steps + (sp < a.longer);
 
     // what this thread stages per step
-    PfRow ar[Sh::NA];
+    const bf16_t *ap[Sh::NA];
+    unsigned int ar[Sh::NA];
 #pragma unroll
-    for (int q = 0; q < Sh::NA; ++q) ar[q] = pf_row<TM>(a, mt, (wave + q * 8) * 16 + r16, kg);
+    for (int q = 0; q < Sh::NA; ++q) {
+        const PfRow r = a.rows[mt * TM + (wave + q * 8) * 16 + r16];
+        ar[q] = r.y;
+        ap[q] = op.W + ((size_t)r.x + kg * (r.y & 0xffffu)) * 8;
+    }
     const unsigned int l0 = (unsigned int)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
     const char *bsrc[Sh::NB];
     unsigned int bdst[Sh::NB];
 #pragma unroll
     for (int q = 0; q < Sh::NB; ++q) {
-        const int f = min(wave + q * 8, 3 * TB - 1), pl = f / TB, t = f - pl * TB;    // a repeat writes the same bytes again
+        const int f = min(wave + q * 8, NP * TB - 1), pl = f / TB, t = f - pl * TB;    // a repeat writes the same bytes again
         bsrc[q] = reinterpret_cast<const char *>(a.frag_in + frag_off(KS, a.TT, pl, st0, min(tt0 + t, a.TT - 1)));
         bdst[q] = Sh::A_BYTES + f * 1024;
     }
     const size_t bstep = (size_t)a.TT * 1024;
     const unsigned int voff = lane * 16;
     const bool once = a.n_tt == 1;                 // every weight byte is used by one workgroup only: nothing to keep in a cache
-    auto issue = [&](int t, int buf) {             // step st0 + t into LDS buffer buf
-        const unsigned int d = l0 + buf * Sh::STAGE;
+    auto weight_piece = [&](int t, int q) {        // (the three possible deals of the columns in scalar arithmetic, then a choice)
+        const int u0 = pf_unit_index(st0 + t, KS, 0), u1 = pf_unit_index(st0 + t, KS, 1), u2 = pf_unit_index(st0 + t, KS, 2);
+        const unsigned int u = ar[q] >= 0x20000u ? u2 : (ar[q] >= 0x10000u ? u1 : u0);
+        return ap[q] + (unsigned long long)u * ((ar[q] & 0xffffu) * 32u);
+    };
+    auto issue_b = [&](int t, int buf) {           // activations of step st0 + t into LDS buffer buf
+#pragma unroll
+        for (int q = 0; q < Sh::NB; ++q) dma_linear(bsrc[q] + t * bstep, voff, l0 + buf * Sh::STAGE + bdst[q]);
+    };
+    auto issue_a = [&](int t, int buf) {           // ... and its weights as they are
 #pragma unroll
         for (int q = 0; q < Sh::NA; ++q) {
-            const bf16_t *p = ar[q].p + (size_t)pf_unit_index(st0 + t, KS, ar[q].gshift) * ar[q].unit;
-            if (once) dma_lane_nt(p, d + (wave + q * 8) * 1024);
-            else dma_lane(p, d + (wave + q * 8) * 1024);
+            const unsigned int d = l0 + buf * Sh::STAGE + (wave + q * 8) * 1024;
+            if (once) dma_lane_nt(weight_piece(t, q), d);
+            else dma_lane(weight_piece(t, q), d);
         }
+    };
+    PfCheck chk{u16x2{0, 0}, 0xffffffffu};
+    u32x4 wreg[Sh::NA];
+    auto load_w = [&](int t) {                     // CONV_STAGE: weights of step st0 + t to registers
 #pragma unroll
-        for (int q = 0; q < Sh::NB; ++q) dma_linear(bsrc[q] + t * bstep, voff, d + bdst[q]);
+        for (int q = 0; q < Sh::NA; ++q) wreg[q] = *reinterpret_cast<const u32x4 *>(weight_piece(t, q));
+    };
+    auto store_w = [&](int buf) {                  // ... and as fp16 to LDS buffer buf
+#pragma unroll
+        for (int q = 0; q < Sh::NA; ++q)
+            *reinterpret_cast<u32x4 *>(lds + buf * Sh::STAGE + (wave + q * 8) * 1024 + voff) = weights_to_f16(wreg[q], chk);
     };
 
     f32x4 acc[TAW][TBW];
@@ -260,71 +318,86 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
     for (int i = 0; i < TAW; ++i)
 #pragma unroll
         for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const char *la = lds + wa * TAW * 1024 + lane * 16, *lb = lds + Sh::A_BYTES + wb * TBW * 1024 + lane * 16;
-    auto read_a = [&](int buf, bf16x8 *v) {
+    // few tokens: registers to spare, so even and odd steps have accumulators of their own (half the roundings in a chain)
+    constexpr bool ODD = NP == 2 && !PP;
+    f32x4 odd[ODD ? TAW : 1][ODD ? TBW : 1];
+    if constexpr (ODD) {
 #pragma unroll
-        for (int i = 0; i < TAW; ++i) v[i] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(la + buf * Sh::STAGE + i * 1024));
+        for (int i = 0; i < TAW; ++i)
+#pragma unroll
+            for (int j = 0; j < TBW; ++j) odd[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    const char *la = lds + wa * TAW * 1024 + voff, *lb = lds + Sh::A_BYTES + wb * TBW * 1024 + voff;
+    constexpr int JC = NP == 2 ? TBW : (TBW < 2 ? TBW : 2), CL = TBW / JC;    // token tiles per cluster of matrix instructions, clusters per step
+    u32x4 av[TAW], bv[JC][NP];
+    auto read_a = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < TAW; ++i) av[i] = *reinterpret_cast<const u32x4 *>(la + buf * Sh::STAGE + i * 1024);
     };
-    auto read_b = [&](int buf, int j, bf16x8 *v) {
+    auto read_b = [&](int buf, int c) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p) v[p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(lb + buf * Sh::STAGE + (p * TB + j) * 1024));
+        for (int jj = 0; jj < JC; ++jj)
+#pragma unroll
+            for (int p = 0; p < NP; ++p) bv[jj][p] = *reinterpret_cast<const u32x4 *>(lb + buf * Sh::STAGE + (p * TB + c * JC + jj) * 1024);
     };
-
-    constexpr int NDMA = Sh::NA + Sh::NB;          // loads per wavefront and step
-    constexpr int JC = TBW < 2 ? TBW : 2, CL = TBW / JC;      // token tiles per cluster of matrix instructions, clusters per step
-    bf16x8 av[TAW], bv[JC][3];
-    auto mfma_cluster = [&](int c) {
+    auto mfma_cluster = [&](int c, auto odd_step) {
 #pragma unroll
-        for (int p = 0; p < 3; ++p)
+        for (int p = 0; p < NP; ++p)
 #pragma unroll
             for (int jj = 0; jj < JC; ++jj)
 #pragma unroll
-                for (int i = 0; i < TAW; ++i)
-                    acc[i][c * JC + jj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av[i], bv[jj][p], acc[i][c * JC + jj], 0, 0, 0);
+                for (int i = 0; i < TAW; ++i) {
+                    constexpr bool o = ODD && decltype(odd_step)::value;
+                    f32x4 &d = o ? odd[o ? i : 0][o ? c * JC + jj : 0] : acc[i][c * JC + jj];
+                    if constexpr (NP == 2)
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, av[i]), __builtin_bit_cast(f16x8, bv[jj][p]), d, 0, 0, 0);
+                    else
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[i]), __builtin_bit_cast(bf16x8, bv[jj][p]), d, 0, 0, 0);
+                }
     };
+
+    // the first NS - 1 steps (a step past the end repeats the last one, here and below: the loads stay countable)
 #pragma unroll
-    for (int t = 0; t < NS - 1; ++t) issue(min(t, cnt - 1), t);     // (a step past the end re-reads the last one: loads stay countable)
-    // norm scale of the tile's tokens, from the producers' shares in their order (read while the first steps arrive)
-    if (a.ss_in && tid < TB * 16) {
-        float s = 0.f;
-        const float *p = a.ss_in + tt0 * 16 + tid;
-        const int stride = a.TT * 16;
-        for (int i0 = 0; i0 < a.n_ss; i0 += 16) {      // sixteen loads at a time: one memory round trip, not sixteen
-            float v[16];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = p[(size_t)min(i0 + i, a.n_ss - 1) * stride];
-#pragma unroll
-            for (int i = 0; i < 16; ++i) s += i0 + i < a.n_ss ? v[i] : 0.f;
-        }
-        rs[tid] = 1.0f / sqrtf(s * op.inv_dim + op.eps);
+    for (int t = 0; t < NS - 1; ++t) {
+        if constexpr (CONV_STAGE) load_w(min(t, cnt - 1));
+        else issue_a(min(t, cnt - 1), t);
+        issue_b(min(t, cnt - 1), t);
+        if constexpr (CONV_STAGE) store_w(t);
     }
+    if constexpr (CONV_STAGE) load_w(min(NS - 1, cnt - 1));
     dma_wait<0>();
     pf_meet();
     if constexpr (PP) {
         // Phases of a group: read operands | meet | matrix instructions | meet. The second group enters one phase later.
-        // With two buffers (two clusters per step) step t+1 is requested while cluster 0 of step t is read, when the
-        // last reads of step t-1 are one phase old; with three (one cluster per step) step t+2 is.
+        // With three buffers (one cluster per step) step t+2 is staged while step t is read, when the last reads of step
+        // t-1 are one phase old; with two (two clusters per step) step t+1 is requested while cluster 0 of step t is read.
+        constexpr int YOUNG = Sh::NB + Sh::NA;     // loads issued in one reading phase
         if (wa == 1) pf_meet();
         int buf = 0;
         for (int t = 0; t < cnt; ++t) {
-            read_a(buf, av);
-#pragma unroll
-            for (int jj = 0; jj < JC; ++jj) read_b(buf, jj, bv[jj]);
-            const int nb = NS == 2 ? buf ^ 1 : (buf == 0 ? 2 : buf - 1);
-            issue(min(t + NS - 1, cnt - 1), nb);
-            if (CL == 1) dma_wait<NDMA>();         // step t+1 has arrived (t+2 stays in flight)
+            const int nb = NS == 2 ? buf ^ 1 : (buf == 0 ? 2 : buf - 1), tn = min(t + NS - 1, cnt - 1);
+            read_a(buf);
+            read_b(buf, 0);
+            if constexpr (CONV_STAGE) {
+                store_w(nb);                       // step t+2, loaded one step ago
+                issue_b(tn, nb);
+                load_w(min(t + NS, cnt - 1));
+            } else {
+                issue_a(tn, nb);
+                issue_b(tn, nb);
+            }
+            if constexpr (CL == 1) dma_wait<YOUNG>();       // step t+1 has arrived (what was issued just now stays in flight)
             pf_meet();
             __builtin_amdgcn_s_setprio(1);
-            mfma_cluster(0);
+            mfma_cluster(0, std::false_type{});
             __builtin_amdgcn_s_setprio(0);
             pf_meet();
             if constexpr (CL == 2) {
-#pragma unroll
-                for (int jj = 0; jj < JC; ++jj) read_b(buf, JC + jj, bv[jj]);
+                read_b(buf, 1);
                 if (wa == 1) dma_wait<0>();        // the first group reads step t+1 one phase from here
                 pf_meet();
                 __builtin_amdgcn_s_setprio(1);
-                mfma_cluster(1);
+                mfma_cluster(1, std::false_type{});
                 __builtin_amdgcn_s_setprio(0);
                 if (wa == 0) dma_wait<0>();
                 pf_meet();
@@ -334,155 +407,213 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
         if (wa == 0) pf_meet();
     } else {
         int buf = 0;
-        for (int t = 0; t < cnt; ++t) {
-            if (t > 0) { dma_wait<(NS - 2) * NDMA>(); pf_meet(); }      // step t has arrived; every wavefront is done with step t-1
+        auto step = [&](int t, auto odd_step) {
+            if (t > 0) { dma_wait<(NS - 2) * (Sh::NA + Sh::NB)>(); pf_meet(); }      // step t has arrived; every wavefront is done with step t-1
             const int nb = buf == 0 ? NS - 1 : buf - 1;
-            issue(min(t + NS - 1, cnt - 1), nb);
-            read_a(buf, av);
+            issue_a(min(t + NS - 1, cnt - 1), nb);
+            issue_b(min(t + NS - 1, cnt - 1), nb);
+            read_a(buf);
+            if constexpr (CONV_READ) {
+#pragma unroll
+                for (int i = 0; i < TAW; ++i) av[i] = weights_to_f16(av[i], chk);
+            }
 #pragma unroll
             for (int c = 0; c < CL; ++c) {
-#pragma unroll
-                for (int jj = 0; jj < JC; ++jj) read_b(buf, c * JC + jj, bv[jj]);
-                mfma_cluster(c);
+                read_b(buf, c);
+                mfma_cluster(c, odd_step);
             }
             buf = buf == NS - 1 ? 0 : buf + 1;
+        };
+        for (int t = 0; t < cnt; t += 2) {
+            step(t, std::false_type{});
+            if (t + 1 < cnt) step(t + 1, std::true_type{});
         }
     }
-    dma_wait<0>();                                 // nothing is in flight towards LDS from here on
-
-    if (a.S > 1) {
-        // partial sums of this K part, written through; the workgroup that arrives last adds the parts up in order
-        const int tile = mt * a.n_tt + tk;
-        constexpr int NACC = TAW * TBW, NBT = NACC < 16 ? NACC : 16;        // tiles fetched per round trip
-        char *pw = reinterpret_cast<char *>(a.part) + (size_t)tile * a.S * (NACC * PF_NT * 16) + wave * (NACC * 1024);
-        char *mine = pw + (size_t)sp * (NACC * PF_NT * 16);
+    dma_wait<0>();                                 // nothing is in flight towards LDS when the workgroup ends
+    if (NP == 2 && !weights_fit(chk)) *a.flag = 1;
+    if constexpr (ODD) {
 #pragma unroll
         for (int i = 0; i < TAW; ++i)
 #pragma unroll
-            for (int j = 0; j < TBW; ++j) store_part(mine + (i * TBW + j) * 1024, voff, acc[i][j]);
-        if (!last_arrival(a.arrivals + tile, a.S, &ticket)) return;
-#pragma unroll
-        for (int i = 0; i < TAW; ++i)
-#pragma unroll
-            for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int k = 0; k < a.S; ++k) {
-#pragma unroll
-            for (int t0 = 0; t0 < NACC; t0 += NBT) {
-                f32x4 v[NBT];
-                load_part<NBT>(pw + (size_t)k * (NACC * PF_NT * 16) + t0 * 1024, voff, v);
-#pragma unroll
-                for (int t = 0; t < NBT; ++t) acc[(t0 + t) / TBW][(t0 + t) % TBW] += v[t];
-            }
-        }
+            for (int j = 0; j < TBW; ++j) acc[i][j] += odd[i][j];
     }
 
-    // epilogue: lane (kg, r16) holds rows 4*kg..4*kg+3 of its TAW row tiles for token r16 of its TBW token tiles
-    const bool pairs = op.type == OP_SWIGLU || (op.type == OP_QKV && mt < a.n_mr);
+    // lane (kg, r16) holds rows 4*kg..4*kg+3 of its TAW row tiles for token r16 of its TBW token tiles
 #pragma unroll
     for (int j = 0; j < TBW; ++j) {
-        const int ttl = wb * TBW + j, tt = tt0 + ttl, tok = tt * 16 + r16;
-        const bool live = tok < a.n_tok;
-        const float scale = a.ss_in ? rs[ttl * 16 + r16] : 1.0f;
-        float s = 0.f;
-        if (op.type == OP_RESID) {
+        const int tok = (tt0 + wb * TBW + j) * 16 + r16;
+        if (tok >= a.n_tok) continue;
+        const float scale = a.scale[tok];
+        if constexpr (EPI == PF_PARTS) {
+            float *o = a.out + ((size_t)sp * a.out_rows + tok) * ((size_t)a.n_mt * TM) + mt * TM + wa * TAW * 16 + 4 * kg;
 #pragma unroll
-            for (int i = 0; i < TAW; ++i) {
-                const int n = mt * TM + (wa * TAW + i) * 16 + 4 * kg;
-                if (live && n < op.N) {
-                    f32x4 *xp = reinterpret_cast<f32x4 *>(op.x + (size_t)tok * op.N + n);
-                    const f32x4 xn = *xp + acc[i][j];
-                    *xp = xn;
-                    store_frag4(a.frag_out, op.N >> 5, a.TT, tt, r16, n, *reinterpret_cast<const f32x4 *>(op.gain_next + n) * xn);
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) s = fmaf(xn[q], xn[q], s);
-                }
-            }
-            s += __shfl_xor(s, 16, 64);
-            s += __shfl_xor(s, 32, 64);
-            if (kg == 0) sq[wa * TB * 16 + ttl * 16 + r16] = s;
-        } else if (pairs) {
+            for (int i = 0; i < TAW; ++i) *reinterpret_cast<f32x4 *>(o + i * 16) = acc[i][j] * scale;
+        } else if (EPI == PF_SWIGLU || mt < a.n_mr) {
 #pragma unroll
             for (int i = 0; i < TAW; i += 2) {
                 const int p = mt * (TM / 2) + (wa * TAW + i) * 8 + 4 * kg;
-                if (op.type == OP_SWIGLU) {
-                    if (live && p < op.N) {
-                        f32x4 u;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float g = acc[i][j][q] * scale;
-                            u[q] = (g / (1.0f + expf(-g))) * (acc[i + 1][j][q] * scale);
-                        }
-                        store_frag4(a.frag_out, op.N >> 5, a.TT, tt, r16, p, u);
-                    }
-                } else {
-                    const int half = op.hd >> 1, qd = op.H * op.hd;
-                    if (live && p < (op.H + op.Hkv) * half) {
-                        const int head = p / half, d = p - head * half;            // four neighbours of one head: half is a multiple of 4
-                        const f32x4 c = *reinterpret_cast<const f32x4 *>(op.cos_t + (size_t)tok * half + d);
-                        const f32x4 sn = *reinterpret_cast<const f32x4 *>(op.sin_t + (size_t)tok * half + d);
-                        f32x4 ra, rb;
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) {
-                            const float x0 = acc[i][j][q] * scale, x1 = acc[i + 1][j][q] * scale;
-                            ra[q] = x0 * c[q] - x1 * sn[q];
-                            rb[q] = x1 * c[q] + x0 * sn[q];
-                        }
-                        if (head < op.H) {
-                            float *qp = op.q_out + (size_t)tok * qd + head * op.hd + d;
-                            *reinterpret_cast<f32x4 *>(qp) = ra;
-                            *reinterpret_cast<f32x4 *>(qp + half) = rb;
-                        } else {
-                            bf16_t *kp = op.kv_block + ((size_t)(head - op.H) * op.max_seq + tok) * op.hd + d;   // the prompt starts at position 0
-                            pf_store_bf16x4(kp, ra);
-                            pf_store_bf16x4(kp + half, rb);
-                        }
-                    }
+                if constexpr (EPI == PF_SWIGLU) {
+                    if (p < op.N) *reinterpret_cast<f32x4 *>(a.out + (size_t)tok * op.N + p) = pf_swiglu(acc[i][j] * scale, acc[i + 1][j] * scale);
+                } else if (p < (op.H + op.Hkv) * (op.hd >> 1)) {
+                    pf_rope_store(op, tok, p, acc[i][j] * scale, acc[i + 1][j] * scale);
                 }
             }
-        } else {    // value rows of OP_QKV
+        } else {    // value rows
 #pragma unroll
             for (int i = 0; i < TAW; ++i) {
                 const int v = (mt - a.n_mr) * TM + (wa * TAW + i) * 16 + 4 * kg;
-                if (live && v < op.Hkv * op.hd) {
-                    const int head = v / op.hd, d = v - head * op.hd;
-                    pf_store_bf16x4(op.kv_block + (((size_t)op.Hkv + head) * op.max_seq + tok) * op.hd + d, acc[i][j] * scale);
-                }
+                if (v < op.Hkv * op.hd) pf_value_store(op, tok, v, acc[i][j] * scale);
             }
-        }
-    }
-    if (op.type == OP_RESID) {
-        __syncthreads();
-        if (tid < TB * 16) {
-            float s = 0.f;
-#pragma unroll
-            for (int w = 0; w < WA; ++w) s += sq[w * TB * 16 + tid];
-            a.ss_out[(size_t)mt * a.TT * 16 + tt0 * 16 + tid] = s;
         }
     }
 }
 
 // ------------------------------------------------------------------------------------------
-// Embedding of the prompt rows: x = E[tok], the first norm's operands gain (.) x in fragment order
-// and the row's sum(x^2) as its only share. One workgroup per row; d is a multiple of 32.
+// Row kernels: one workgroup per token, between the products. They add up the K parts, finish the row and write the next
+// product's operands. Bound by memory (the row is read once and kept in LDS). A row's share of a fragment is 16 bytes of
+// each 256: the workgroups of the 16 rows that share the fragments are neighbours on one die, so that its L2 puts whole
+// lines together.
 // ------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void prefill_embed_kernel(const int32_t *toks, const bf16_t *embed, const float *gain, int d,
-                                                            int TT, float *x, bf16_t *frag, float *ss) {
-    __shared__ float part[4];
-    const int tok = blockIdx.x, tt = tok >> 4, m = tok & 15;
-    const bf16_t *row = embed + (size_t)toks[tok] * d;
-    float sq = 0.f;
-    for (int n = threadIdx.x * 4; n < d; n += 256 * 4) {
-        const u32x2 w = *reinterpret_cast<const u32x2 *>(row + n);
-        const f32x4 v = f32x4{bf_lo(w.x), bf_hi(w.x), bf_lo(w.y), bf_hi(w.y)};
-        *reinterpret_cast<f32x4 *>(x + (size_t)tok * d + n) = v;
-        store_frag4(frag, d >> 5, TT, tt, m, n, *reinterpret_cast<const f32x4 *>(gain + n) * v);
+struct PfRowArgs {
+    GemmOp op;                  // as in PfArgs
+    const int32_t *toks;        // embedding: token ids
+    const float *in;            // [S][out_rows][ld] K parts, or [n_tok][d] finished rows
+    int n_tok, S, out_rows, ld, TM;     // TM: rows per tile of the product's column order
+    int d;                      // features of the row
+    float inv_dim, eps;
+    float *x;                   // [n_tok][d] residual stream
+    const float *gain;
+    bf16_t *frag;
+    float *scale;
+    int *flag;                  // embedding: cleared for the prompt
+    int TT;
+};
+
+// the workgroup's token: tiles of 16 tokens are dealt to the dies, a die's consecutive workgroups take a tile's rows
+__device__ __forceinline__ int pf_row_token() {
+    const int die = blockIdx.x & 7, i = blockIdx.x >> 3;
+    return ((i >> 4) * 8 + die) * 16 + (i & 15);
+}
+
+// sum and maximum over the workgroup's PF_RT threads
+__device__ __forceinline__ void pf_row_reduce(float &s, float &mx) {
+    __shared__ float rs[PF_RT / 64], rm[PF_RT / 64];
+    s = wave_sum(s);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) sq = fmaf(v[q], v[q], sq);
-    }
-    sq = wave_sum(sq);
-    if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = sq;
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+    if ((threadIdx.x & 63) == 0) { rs[threadIdx.x >> 6] = s; rm[threadIdx.x >> 6] = mx; }
     __syncthreads();
-    if (threadIdx.x == 0) ss[tok] = (part[0] + part[1]) + (part[2] + part[3]);
+    s = 0.f; mx = 0.f;
+#pragma unroll
+    for (int w = 0; w < PF_RT / 64; ++w) { s += rs[w]; mx = fmaxf(mx, rm[w]); }
+}
+
+// the row in LDS (largest magnitude mx) -> planes and factor; norm: what the row's products are multiplied by besides
+template <int NP>
+__device__ __forceinline__ void pf_row_split(const PfRowArgs &a, int tok, const float *row, float mx, float norm) {
+    int e = 0;
+    if (NP == 2 && mx > 0.f) e = min(max((int)(__float_as_uint(mx) >> 23) - 127 - 14, -110), 110);     // mx * 2^-e in [2^14, 2^15)
+    const float k = ldexpf(1.0f, -e);
+    if (threadIdx.x == 0) a.scale[tok] = NP == 2 ? ldexpf(norm, e - PF_WSHIFT) : norm;
+    for (int n = threadIdx.x * 8; n < a.d; n += PF_RT * 8) {
+        float v[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) v[q] = row[n + q] * k;
+        store_frag8<NP>(a.frag, a.d >> 5, a.TT, tok >> 4, tok & 15, n, v);
+    }
+}
+
+// columns c..c+3 of the K parts, added up in order
+__device__ __forceinline__ f32x4 pf_sum_parts(const PfRowArgs &a, int tok, int c) {
+    const float *p = a.in + (size_t)tok * a.ld + c;
+    const size_t st = (size_t)a.out_rows * a.ld;
+    f32x4 v = *reinterpret_cast<const f32x4 *>(p);
+    int s = 1;
+    auto take = [&](auto n) {              // that many loads in flight
+        f32x4 t[decltype(n)::value];
+#pragma unroll
+        for (int i = 0; i < decltype(n)::value; ++i) t[i] = *reinterpret_cast<const f32x4 *>(p + (s + i) * st);
+#pragma unroll
+        for (int i = 0; i < decltype(n)::value; ++i) v += t[i];
+        s += decltype(n)::value;
+    };
+    while (s + 8 <= a.S) take(std::integral_constant<int, 8>{});
+    if (s + 4 <= a.S) take(std::integral_constant<int, 4>{});
+    if (s + 2 <= a.S) take(std::integral_constant<int, 2>{});
+    if (s < a.S) take(std::integral_constant<int, 1>{});
+    return v;
+}
+// column of the first member of pair p (the second sits 16 columns on): the row order of the product's tiles
+__device__ __forceinline__ int pf_pair_col(int p, int TM) {
+    const int mt = p / (TM / 2), r = p - mt * (TM / 2);
+    return mt * TM + (r >> 4) * 32 + (r & 15);
+}
+
+// x = E[tok] or x += the product's row; the next norm's operands gain (.) x and their factor
+template <int NP, bool EMBED>
+__global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
+    extern __shared__ __align__(16) float row[];
+    const int tok = pf_row_token();
+    if (tok >= a.n_tok) return;
+    if (EMBED && tok == 0 && threadIdx.x == 0) *a.flag = 0;
+    float sq = 0.f, mx = 0.f;
+    for (int n = threadIdx.x * 4; n < a.d; n += PF_RT * 4) {
+        f32x4 v;
+        f32x4 *xp = reinterpret_cast<f32x4 *>(a.x + (size_t)tok * a.d + n);
+        if constexpr (EMBED) {
+            const u32x2 w = *reinterpret_cast<const u32x2 *>(a.op.embed + (size_t)a.toks[tok] * a.d + n);
+            v = f32x4{bf_lo(w.x), bf_hi(w.x), bf_lo(w.y), bf_hi(w.y)};
+        } else {
+            const f32x4 x0 = *xp;
+            v = x0 + pf_sum_parts(a, tok, n);
+        }
+        *xp = v;
+        const f32x4 g = *reinterpret_cast<const f32x4 *>(a.gain + n) * v;
+        *reinterpret_cast<f32x4 *>(row + n) = g;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) { sq = fmaf(v[q], v[q], sq); mx = fmaxf(mx, fabsf(g[q])); }
+    }
+    pf_row_reduce(sq, mx);
+    pf_row_split<NP>(a, tok, row, mx, 1.0f / sqrtf(sq * a.inv_dim + a.eps));
+}
+
+// PARTS: SwiGLU of the gate+up product's K parts; otherwise a finished row (attention output, SwiGLU of an unsplit product)
+template <int NP, bool PARTS>
+__global__ __launch_bounds__(PF_RT) void prefill_u_row_kernel(PfRowArgs a) {
+    extern __shared__ __align__(16) float row[];
+    const int tok = pf_row_token();
+    if (tok >= a.n_tok) return;
+    float none = 0.f, mx = 0.f;
+    for (int n = threadIdx.x * 4; n < a.d; n += PF_RT * 4) {
+        f32x4 v;
+        if constexpr (PARTS) {
+            const int c = pf_pair_col(n, a.TM);
+            v = pf_swiglu(pf_sum_parts(a, tok, c), pf_sum_parts(a, tok, c + 16));
+        } else {
+            v = *reinterpret_cast<const f32x4 *>(a.in + (size_t)tok * a.d + n);
+        }
+        *reinterpret_cast<f32x4 *>(row + n) = v;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(v[q]));
+    }
+    pf_row_reduce(none, mx);
+    pf_row_split<NP>(a, tok, row, mx, 1.0f);
+}
+
+// rotary embedding, queries and cache entries from the K parts of a split QKV product (n_mr: its row tiles of rotary pairs)
+__global__ __launch_bounds__(PF_RT) void prefill_qkv_row_kernel(PfRowArgs a, int n_mr) {
+    const int tok = pf_row_token();
+    if (tok >= a.n_tok) return;
+    const int P = (a.op.H + a.op.Hkv) * (a.op.hd >> 1), VR = a.op.Hkv * a.op.hd;
+    for (int i = (blockIdx.y * PF_RT + threadIdx.x) * 4; i < P + VR; i += gridDim.y * PF_RT * 4) {     // gridDim.y workgroups per row
+        if (i < P) {
+            const int c = pf_pair_col(i, a.TM);
+            const f32x4 x0 = pf_sum_parts(a, tok, c), x1 = pf_sum_parts(a, tok, c + 16);
+            pf_rope_store(a.op, tok, i, x0, x1);
+        } else {
+            pf_value_store(a.op, tok, i - P, pf_sum_parts(a, tok, n_mr * a.TM + i - P));
+        }
+    }
 }
 
 // The prompt's last row after the last block: the final norm's operands and shares as a one-row pass of the decode
@@ -503,49 +634,51 @@ __global__ __launch_bounds__(NT) void prefill_last_row_kernel(const float *x_row
 }
 
 // ------------------------------------------------------------------------------------------
-// Causal attention of the prompt rows over the bf16 cache, on the matrix cores. A workgroup = one query
-// head x four consecutive 16-row tiles (one wavefront each); keys and values go through LDS in chunks
-// of 64 positions shared by the four wavefronts (values transposed on the way in, so that both are
-// MFMA B operands as stored). Per chunk a wavefront computes S = Q K^T (Q exact as three bf16 planes),
-// the running softmax in fp32 on the vector ALUs, and O += P V with P exact as three bf16 planes;
-// P changes from accumulator layout to operand layout through a wavefront-private LDS tile.
+// Causal attention of the prompt rows over the bf16 cache, on the matrix cores. A workgroup = one query head x four
+// consecutive 16-row tiles (one wavefront each); keys and values go to LDS in chunks of 64 positions shared by the four
+// wavefronts, one chunk ahead. Q and P stay exact as three bf16 planes.
+// Everything is computed transposed, S^T = K Q^T and O^T = V^T P^T, so that a lane keeps one query from end to end: the
+// accumulators of two 16-position tiles of S^T (4 positions each) are the eight positions that lane needs as the operand of
+// the second product, with V's rows taken in the same order; no exchange through LDS, two shuffles per row maximum. V is
+// read as it lies: a lane takes HD/16 neighbouring dimensions of its eight positions and regroups them with byte permutes,
+// so that matrix instruction t produces the dimensions {HD/16 * n + t}, which end up next to each other in one lane.
+// LDS rows are not padded (the loads to LDS are linear); the 16-byte pieces of a row are stored rotated by an exclusive or
+// with the row number instead, which spreads the 16 rows of an operand read over the banks.
+// Bound by the vector ALUs and the matrix cores about equally. 13B-shaped, 40 heads, before (values transposed on their way
+// into LDS by 2-byte stores, P through LDS, expf) and after: 1024 rows 97 -> 45 us, 4096 rows 1.20 -> 0.49 ms.
 // ------------------------------------------------------------------------------------------
 struct PfAttn {
     const float *q;          // [n_tok][H*hd] rotated queries
     const bf16_t *kv_block;  // [2][Hkv][max_seq][hd]
-    bf16_t *frag_out;        // attention output in fragment order over H*hd features
-    int H, Hkv, max_seq, TT, n_tok;
+    float *out;              // [n_tok][H*hd] attention output
+    int H, Hkv, max_seq, n_tok;
 };
 
 // eight fp32 values -> the three bf16 planes of an MFMA operand fragment (exact: hi + mid + lo = value)
 __device__ __forceinline__ void split_planes8(const float *v, bf16x8 *out3) {
-    unsigned int w[3][4];
+    u32x4 w[3];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-        const unsigned int u = __float_as_uint(v[e]);
-        const float hi = __uint_as_float(u & 0xffff0000u);
-        const float r1 = v[e] - hi;
-        const unsigned int um = __float_as_uint(r1);
-        const float mid = __uint_as_float(um & 0xffff0000u);
-        const unsigned int ul = __float_as_uint(r1 - mid);
-        const unsigned int h16 = u >> 16, m16 = um >> 16, l16 = ul >> 16;
-        if (e & 1) { w[0][e >> 1] |= h16 << 16; w[1][e >> 1] |= m16 << 16; w[2][e >> 1] |= l16 << 16; }
-        else { w[0][e >> 1] = h16; w[1][e >> 1] = m16; w[2][e >> 1] = l16; }
+    for (int e = 0; e < 4; ++e) {
+        const unsigned int a0 = __float_as_uint(v[2 * e]), b0 = __float_as_uint(v[2 * e + 1]);
+        const float ra = v[2 * e] - __uint_as_float(a0 & 0xffff0000u), rb = v[2 * e + 1] - __uint_as_float(b0 & 0xffff0000u);
+        const unsigned int a1 = __float_as_uint(ra), b1 = __float_as_uint(rb);
+        const unsigned int a2 = __float_as_uint(ra - __uint_as_float(a1 & 0xffff0000u)), b2 = __float_as_uint(rb - __uint_as_float(b1 & 0xffff0000u));
+        w[0][e] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+        w[1][e] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+        w[2][e] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);
     }
 #pragma unroll
-    for (int p = 0; p < 3; ++p) out3[p] = __builtin_bit_cast(bf16x8, u32x4{w[p][0], w[p][1], w[p][2], w[p][3]});
+    for (int p = 0; p < 3; ++p) out3[p] = __builtin_bit_cast(bf16x8, w[p]);
 }
 
+template <int HD> constexpr size_t pf_attn_lds_bytes() { return (size_t)2 * 2 * 64 * HD * 2; }
+
 template <int HD>
-__global__ __launch_bounds__(256) void prefill_attn_kernel(PfAttn a) {
-    constexpr int CH = 64, LPP = HD / 8, QS = HD / 32, DT = HD / 16;
-    constexpr int KSTR = HD * 2 + 16;      // bytes per staged key row (+16: the 16 rows of an operand read spread over the banks)
-    constexpr int VSTR = CH * 2 + 16;      // bytes per staged (transposed) value row
-    constexpr int PSTR = CH + 4;           // floats per row of the P tile
-    constexpr int PIECES = CH * LPP, PQ = PIECES / 256;
-    __shared__ __align__(16) char kl[CH * KSTR];
-    __shared__ __align__(16) char vl[HD * VSTR];
-    __shared__ __align__(16) float pb[4][16 * PSTR];
+__global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
+    constexpr int CH = 64, QS = HD / 32, DT = HD / 16, SL = HD / 8, RB = HD * 2;
+    constexpr int KV = CH * RB;                               // bytes of a chunk's keys (or values)
+    constexpr int ROWS = 1024 / RB, NI = KV / 1024 / 4;       // rows one wavefront load covers, loads per wavefront for the keys
+    extern __shared__ __align__(16) char lds[];               // [2][keys | values]
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int kg = lane >> 4, r16 = lane & 15;
     const int n_rt = (a.n_tok + 15) >> 4, n_b = (n_rt + 3) >> 2;
@@ -555,129 +688,142 @@ __global__ __launch_bounds__(256) void prefill_attn_kernel(PfAttn a) {
     const bool live = b * 4 + wave < n_rt;
     const int n_chunks = b + 1;                               // positions 0 .. 64b+63 cover every row of the block
     const int last_pos = a.n_tok - 1, qd = a.H * HD;
-    const float scale = 1.0f / sqrtf((float)HD);
+    const float c2 = 1.4426950408889634f / sqrtf((float)HD);  // softmax in powers of two: log2(e) / sqrt(hd)
     const bf16_t *kg_ = a.kv_block + (size_t)kvh * a.max_seq * HD;
     const bf16_t *vg_ = a.kv_block + ((size_t)a.Hkv + kvh) * a.max_seq * HD;
+    const unsigned int l0 = (unsigned int)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
+    auto swz = [](int row) { return HD == 128 ? row & 15 : (row >> 1) & 7; };
 
-    // the wavefront's 16 query rows as operand fragments: lane (kg, i) holds row i, dims 32*ks + 8*kg .. +7
+    auto issue = [&](int c, int buf) {                        // chunk c of keys and values into buffer buf
+#pragma unroll
+        for (int i = 0; i < NI; ++i) {
+            const int row = (i * 4 + wave) * ROWS + lane / SL, piece = (lane % SL) ^ swz(row);
+            const size_t off = (size_t)min(c * CH + row, last_pos) * HD + piece * 8;
+            const unsigned int d = l0 + buf * 2 * KV + (i * 4 + wave) * 1024;
+            dma_lane(kg_ + off, d);
+            dma_lane(vg_ + off, d + KV);
+        }
+    };
+    issue(0, 0);
+    // the wavefront's 16 query rows as operand fragments: lane (kg, n) holds query n, dims 32*ks + 8*kg .. +7
     bf16x8 qa[QS][3];
     {
         const float *qp = a.q + (size_t)min(rt * 16 + r16, last_pos) * qd + h * HD + kg * 8;     // rows past the prompt repeat its last one
 #pragma unroll
         for (int ks = 0; ks < QS; ++ks) {
             float v[8];
-            const float4 v0 = *reinterpret_cast<const float4 *>(qp + ks * 32), v1 = *reinterpret_cast<const float4 *>(qp + ks * 32 + 4);
-            v[0] = v0.x; v[1] = v0.y; v[2] = v0.z; v[3] = v0.w; v[4] = v1.x; v[5] = v1.y; v[6] = v1.z; v[7] = v1.w;
+            const f32x4 v0 = *reinterpret_cast<const f32x4 *>(qp + ks * 32), v1 = *reinterpret_cast<const f32x4 *>(qp + ks * 32 + 4);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { v[e] = v0[e]; v[4 + e] = v1[e]; }
             split_planes8(v, qa[ks]);
         }
     }
 
-    u32x4 kr[PQ], vr[PQ];
-    auto chunk_load = [&](int c) {
-#pragma unroll
-        for (int q = 0; q < PQ; ++q) {
-            const int i = tid + q * 256;
-            const int pos = min(c * CH + i / LPP, last_pos);
-            kr[q] = *reinterpret_cast<const u32x4 *>(kg_ + (size_t)pos * HD + (i % LPP) * 8);
-            vr[q] = *reinterpret_cast<const u32x4 *>(vg_ + (size_t)pos * HD + (i % LPP) * 8);
-        }
-    };
-    auto chunk_store = [&]() {
-#pragma unroll
-        for (int q = 0; q < PQ; ++q) {
-            const int i = tid + q * 256, pos = i / LPP, d0 = (i % LPP) * 8;
-            *reinterpret_cast<u32x4 *>(kl + pos * KSTR + d0 * 2) = kr[q];
-            const unsigned int w[4] = {vr[q].x, vr[q].y, vr[q].z, vr[q].w};
-#pragma unroll
-            for (int e = 0; e < 8; ++e)        // transpose: value of dim d0+e at position pos
-                *reinterpret_cast<bf16_t *>(vl + (d0 + e) * VSTR + pos * 2) = (bf16_t)((e & 1) ? (w[e >> 1] >> 16) : (w[e >> 1] & 0xffffu));
-        }
-    };
-
-    float mrun[4], lsum[4];
+    const int qpos = rt * 16 + r16;                           // the lane's query
+    float mrun = -INFINITY, lsum = 0.f;
     f32x4 o[DT];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) { mrun[q] = -INFINITY; lsum[q] = 0.f; }
-#pragma unroll
-    for (int dt = 0; dt < DT; ++dt) o[dt] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float *pw = pb[wave];
-    const int row_tok = rt * 16 + 4 * kg;                     // position of accumulator row q of this lane: row_tok + q
+    for (int t = 0; t < DT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    chunk_load(0);
     for (int c = 0; c < n_chunks; ++c) {
-        __syncthreads();                                      // the previous chunk has been consumed by every wavefront
-        chunk_store();
-        __syncthreads();
-        chunk_load(min(c + 1, n_chunks - 1));
-        // S = Q K^T for the chunk's four position tiles: lane (kg, j) holds rows 4*kg..4*kg+3 at position 16*pt + j
-        float sc[4][4];
+        const int buf = c & 1;
+        dma_wait<0>();
+        pf_meet();                                            // chunk c is here and every wavefront is done with chunk c-1
+        if (c + 1 < n_chunks) issue(c + 1, buf ^ 1);
+        const char *kl = lds + buf * 2 * KV, *vl = kl + KV;
+        // S^T = K Q^T: lane (kg, n) holds positions 16*pt + 4*kg .. +3 of query n
+        const int n_pt = c * CH + CH - 1 <= rt * 16 ? 4 : min(4, (rt * 16 + 15 - c * CH) / 16 + 1);     // tiles that hold a visible position
+        f32x4 s[4];
 #pragma unroll
         for (int pt = 0; pt < 4; ++pt) {
-            f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+            if (pt < n_pt) {
+                f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int ks = 0; ks < QS; ++ks) {
-                const bf16x8 kb = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kl + (pt * 16 + r16) * KSTR + (ks * 32 + kg * 8) * 2));
+                for (int ks = 0; ks < QS; ++ks) {
+                    const int row = pt * 16 + r16;
+                    const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kl + row * RB + ((ks * 4 + kg) ^ swz(row)) * 16));
 #pragma unroll
-                for (int p = 0; p < 3; ++p) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa[ks][p], kb, acc, 0, 0, 0);
+                    for (int p = 0; p < 3; ++p) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qa[ks][p], acc, 0, 0, 0);
+                }
+                s[pt] = acc;
+            } else {
+                s[pt] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
             }
-            const int pos = c * CH + pt * 16 + r16;
-#pragma unroll
-            for (int q = 0; q < 4; ++q) sc[pt][q] = (pos <= row_tok + q) ? acc[q] * scale : -INFINITY;
         }
-        // running softmax per row (rows are replicated over the 16 lanes of a kg group)
-        float f[4];
+        if (c * CH + CH - 1 > rt * 16) {                      // the diagonal runs through this chunk
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            float cm = fmaxf(fmaxf(sc[0][q], sc[1][q]), fmaxf(sc[2][q], sc[3][q]));
+            for (int pt = 0; pt < 4; ++pt)
 #pragma unroll
-            for (int off = 1; off < 16; off <<= 1) cm = fmaxf(cm, __shfl_xor(cm, off, 64));
-            const float mnew = fmaxf(mrun[q], cm);            // finite: position 0 is visible to every row
-            f[q] = (mrun[q] > -INFINITY) ? expf(mrun[q] - mnew) : 0.f;
-            mrun[q] = mnew;
-            float ps = 0.f;
+                for (int q = 0; q < 4; ++q)
+                    if (c * CH + pt * 16 + 4 * kg + q > qpos) s[pt][q] = -INFINITY;
+        }
+        // running softmax of the lane's query (its positions are spread over the four kg lanes)
+        float cm = s[0][0];
 #pragma unroll
-            for (int pt = 0; pt < 4; ++pt) {
-                const float e = (sc[pt][q] > -INFINITY) ? expf(sc[pt][q] - mnew) : 0.f;
-                pw[(4 * kg + q) * PSTR + pt * 16 + r16] = e;
-                ps += e;
+        for (int pt = 0; pt < 4; ++pt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) cm = fmaxf(cm, s[pt][q]);
+        cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
+        cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
+        const float mnew = fmaxf(mrun, cm);                   // finite: position 0 is visible to every row
+        const float f = __builtin_amdgcn_exp2f((mrun - mnew) * c2), off = mnew * c2;
+        mrun = mnew;
+        float ps = 0.f;
+#pragma unroll
+        for (int pt = 0; pt < 4; ++pt)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                s[pt][q] = __builtin_amdgcn_exp2f(fmaf(s[pt][q], c2, -off));
+                ps += s[pt][q];
             }
-            lsum[q] = lsum[q] * f[q] + ps;
+        lsum = lsum * f + ps;
+        if (__any(f != 1.0f)) {
+#pragma unroll
+            for (int t = 0; t < DT; ++t) o[t] *= f;
         }
+        // O^T += V^T P^T, 32 positions at a time: the lane's positions 4*kg..+3 of two tiles, V's rows in the same order
 #pragma unroll
-        for (int dt = 0; dt < DT; ++dt)
+        for (int hf = 0; hf < 2; ++hf) {
+            if (hf * 2 >= n_pt) continue;
+            const float pv[8] = {s[2 * hf][0], s[2 * hf][1], s[2 * hf][2], s[2 * hf][3], s[2 * hf + 1][0], s[2 * hf + 1][1], s[2 * hf + 1][2], s[2 * hf + 1][3]};
+            bf16x8 pb[3];
+            split_planes8(pv, pb);
+            unsigned int vr[8][DT / 2];                       // [position][pairs of dims DT*n + 2w, +1]
 #pragma unroll
-            for (int q = 0; q < 4; ++q) o[dt][q] *= f[q];
-        // O += P V: P back from LDS in operand layout (lane (kg, i): row i, positions 32*ks2 + 8*kg .. +7)
+            for (int i = 0; i < 8; ++i) {
+                const int row = hf * 32 + (i >> 2) * 16 + 4 * kg + (i & 3);
+                if constexpr (HD == 128) {
+                    const u32x4 v = *reinterpret_cast<const u32x4 *>(vl + row * RB + (r16 ^ swz(row)) * 16);
 #pragma unroll
-        for (int ks2 = 0; ks2 < 2; ++ks2) {
-            float pv[8];
-            const float4 p0 = *reinterpret_cast<const float4 *>(pw + r16 * PSTR + ks2 * 32 + kg * 8);
-            const float4 p1 = *reinterpret_cast<const float4 *>(pw + r16 * PSTR + ks2 * 32 + kg * 8 + 4);
-            pv[0] = p0.x; pv[1] = p0.y; pv[2] = p0.z; pv[3] = p0.w; pv[4] = p1.x; pv[5] = p1.y; pv[6] = p1.z; pv[7] = p1.w;
-            bf16x8 pa[3];
-            split_planes8(pv, pa);
+                    for (int w = 0; w < 4; ++w) vr[i][w] = v[w];
+                } else {
+                    const u32x2 v = *reinterpret_cast<const u32x2 *>(vl + row * RB + ((r16 >> 1) ^ swz(row)) * 16 + (r16 & 1) * 8);
+                    vr[i][0] = v.x; vr[i][1] = v.y;
+                }
+            }
 #pragma unroll
-            for (int dt = 0; dt < DT; ++dt) {
-                const bf16x8 vb = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(vl + (dt * 16 + r16) * VSTR + (ks2 * 32 + kg * 8) * 2));
+            for (int t = 0; t < DT; ++t) {
+                u32x4 vf;
 #pragma unroll
-                for (int p = 0; p < 3; ++p) o[dt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(pa[p], vb, o[dt], 0, 0, 0);
+                for (int j = 0; j < 4; ++j)
+                    vf[j] = __builtin_amdgcn_perm(vr[2 * j + 1][t >> 1], vr[2 * j][t >> 1], (t & 1) ? 0x07060302u : 0x05040100u);
+#pragma unroll
+                for (int p = 0; p < 3; ++p)
+                    o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), pb[p], o[t], 0, 0, 0);
             }
         }
     }
-    // row sums over the 16 lanes of a kg group, then the rows' outputs in fragment order
+    lsum += __shfl_xor(lsum, 16, 64);
+    lsum += __shfl_xor(lsum, 32, 64);
+    if (live && qpos <= last_pos) {
+        const float inv = 1.0f / lsum;
+        // accumulator row 4*kg + q of instruction t is dimension DT * (4*kg + q) + t
+        float *op = a.out + (size_t)qpos * qd + h * HD + DT * 4 * kg;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int off = 1; off < 16; off <<= 1) lsum[q] += __shfl_xor(lsum[q], off, 64);
-    }
-    if (live) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float inv = 1.0f / lsum[q];
-#pragma unroll
-            for (int dt = 0; dt < DT; ++dt)
-                store_frag(a.frag_out, qd >> 5, a.TT, rt, 4 * kg + q, h * HD + dt * 16 + r16, o[dt][q] * inv);
-        }
+            for (int t = 0; t < DT; t += 4)
+                *reinterpret_cast<f32x4 *>(op + q * DT + t) = f32x4{o[t][q], o[t + 1][q], o[t + 2][q], o[t + 3][q]} * inv;
     }
 }
 

@@ -39,6 +39,8 @@ static const size_t KS_MAX_DYN_LDS = 160 * 1024;  // dynamic LDS the tuned kerne
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+enum { PF_QKV = 0, PF_O, PF_GU, PF_DOWN, PF_OPS };     // the four matrices of a block
+
 // Workspace layout (byte offsets, all 256-byte aligned).
 struct WsLayout {
     size_t draft_ctl, ver_ctl, gen, head, knn, out3;
@@ -46,8 +48,7 @@ struct WsLayout {
     // tuned bf16 path
     size_t act_d, qrot, ss, head_part, attn_part, attn_arrivals, split_tab;
     // tuned prompt prefill (stream-order weights only): all prompt rows at once
-    size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_ss, pf_part, pf_arrivals;
-    int pf_n_arrivals;
+    size_t pf_tokens, pf_x, pf_q, pf_att, pf_u, pf_frag_d, pf_frag_att, pf_frag_u, pf_scale_d, pf_scale_att, pf_scale_u, pf_part, pf_rows[PF_OPS][2];
     int pf_tt;          // token tiles the fragment buffers are laid out for
     size_t total;
 };
@@ -80,40 +81,44 @@ struct PfPlan {
     int n_mt, n_mr, n_tt;    // row tiles, those of them with rotary pairs (OP_QKV), workgroup tiles along the tokens
     int S;                   // parts K is split into
     int tiles() const { return n_mt * n_tt; }
-    size_t part_bytes() const { return S > 1 ? (size_t)tiles() * S * (tb == 4 ? 128 : 256) * tb * 16 * 4 : 0; }
+    // sums through memory to a row kernel? (residual rows always; the others unless one large workgroup finishes them)
+    bool parts(int which) const { return S > 1 || tb != 16 || which == PF_O || which == PF_DOWN; }
+    int tm() const { return tb == 4 ? 128 : 256; }
+    int out_rows() const { return n_tt * tb * 16; }
+    size_t part_bytes() const { return (size_t)S * out_rows() * n_mt * tm() * 4; }       // K parts of the product
 };
 
-enum { PF_QKV = 0, PF_O, PF_GU, PF_DOWN, PF_OPS };
+// row tiles of tm rows that cover a matrix (n_mr: those of rotary pairs)
+static int pf_row_tiles(const knnssd_model_cfg &g, int which, int tm, int *n_mr = nullptr) {
+    const int P = (g.n_heads + g.n_kv_heads) * (g.head_dim / 2), VR = g.n_kv_heads * g.head_dim;
+    const int mr = which == PF_QKV ? (P + tm / 2 - 1) / (tm / 2) : 0;
+    if (n_mr) *n_mr = mr;
+    if (which == PF_QKV) return mr + (VR + tm - 1) / tm;
+    return which == PF_GU ? (g.d_ffn + tm / 2 - 1) / (tm / 2) : (g.d_model + tm - 1) / tm;
+}
 
-// The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x cycles of a step + what a
-// workgroup pays once + the exchange of partial sums when K is split). Estimates in cycles, from timings of whole prompts
-// with one matrix's plan varied (13B, 1024 rows: O projection 256 x 128 unsplit 155 us, 256 x 256 in three parts 170, two
-// parts 192; gate+up 256 x 256 unsplit 610, 256 x 128 630; 7B, 45 rows: QKV in 2 to 5 parts within 2 us, in one +9).
+// The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x ns of a step + what a workgroup
+// pays once), plus the K parts' way through memory.
 static PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
-    const int half = g.head_dim / 2, P = (g.n_heads + g.n_kv_heads) * half, VR = g.n_kv_heads * g.head_dim;
     const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
     PfPlan best{};
     double best_cost = 0;
     for (int tb = 4; tb <= 16; tb *= 2) {
-        const int tm = tb == 4 ? 128 : 256;
         PfPlan p{};
         p.tb = tb;
-        p.n_mr = which == PF_QKV ? (P + tm / 2 - 1) / (tm / 2) : 0;
-        p.n_mt = which == PF_QKV ? p.n_mr + (VR + tm - 1) / tm
-                                 : (which == PF_GU ? (g.d_ffn + tm / 2 - 1) / (tm / 2) : (g.d_model + tm - 1) / tm);
+        const int tm = p.tm();
+        p.n_mt = pf_row_tiles(g, which, tm, &p.n_mr);
         p.n_tt = (tt + tb - 1) / tb;
-        const int slots = tb == 4 ? 2 * KS_NWG : KS_NWG;
-        const double step = tb == 16 ? 3500 : 2000, fixed = 6000, exchange = tb == 16 ? 6000 : (tb == 8 ? 3000 : 900);
-        for (int S = 1; S <= 16 && S * 4 <= KS; ++S) {
-            const int rounds = (p.tiles() * S + slots - 1) / slots;
-            if (S > 1 && rounds > 2) break;
-            const double cost = rounds * (((KS + S - 1) / S) * step + fixed + (S > 1 ? (S + 1) * exchange : 0));
+        // 256 x 256 and 256 x 128: one workgroup per unit, bound by the matrix cores. 128 x 64: bound by the weight stream, so
+        // the three workgroups a unit holds take turns, but pay their fixed cost together
+        const double step = tb == 16 ? 1460 : (tb == 8 ? 1050 : 370), fixed = tb == 16 ? 14000 : (tb == 8 ? 10000 : 8000);
+        for (int S = 1; S <= 16; ++S) {
+            if (S > 1 && S * 4 > KS) break;
             p.S = S;
-            if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
-        }
-        if (p.S == 0) {     // K too short to split at all
-            p.S = 1;
-            const double cost = ((p.tiles() + slots - 1) / slots) * (KS * step + fixed);
+            const int rounds = (p.tiles() * S + KS_NWG - 1) / KS_NWG;
+            if (S > 1 && rounds > 8) break;
+            const double moved = p.parts(which) ? 2.0 * p.part_bytes() : 0;
+            const double cost = rounds * ((KS + S - 1) / S * step) + (tb == 4 ? (rounds + 2) / 3 : rounds) * fixed + moved / 3000;
             if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
         }
     }
@@ -129,7 +134,7 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
     L.draft_ctl = take(sizeof(PassCtl));
     L.ver_ctl = take(sizeof(PassCtl));
     L.gen = take(sizeof(GenState));
-    L.head = take(sizeof(HeadResult));
+    L.head = take(sizeof(HeadResult) + 4);      // and the prefill's flag behind it: both come back in one copy
     L.knn = take(sizeof(KnnResult));
     L.out3 = take(4 * sizeof(int32_t));
     L.x = take(R * c->d_model * 4);
@@ -166,18 +171,20 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
             L.pf_frag_d = take(3 * rows * (size_t)c->d_model * 2);
             L.pf_frag_att = take(3 * rows * qd * 2);
             L.pf_frag_u = take(3 * rows * (size_t)c->d_ffn * 2);
-            L.pf_ss = take(((size_t)c->d_model + 127) / 128 * rows * 4);
+            L.pf_att = take(rows * qd * 4);
+            L.pf_u = take(rows * (size_t)c->d_ffn * 4);
+            L.pf_scale_d = take(rows * 4);
+            L.pf_scale_att = take(rows * 4);
+            L.pf_scale_u = take(rows * 4);
             size_t part = 0;
-            int tiles = 0;
             for (int w = 0; w < PF_OPS; ++w)
                 for (int t = 1; t <= (int)tt; ++t) {
                     const PfPlan p = pf_plan(*c, w, t);
-                    if (p.part_bytes() > part) part = p.part_bytes();
-                    if (p.S > 1 && p.tiles() > tiles) tiles = p.tiles();
+                    if (p.parts(w) && p.part_bytes() > part) part = p.part_bytes();
                 }
             L.pf_part = take(part);
-            L.pf_n_arrivals = tiles;
-            L.pf_arrivals = take((size_t)tiles * 4);
+            for (int w = 0; w < PF_OPS; ++w)
+                for (int i = 0; i < 2; ++i) L.pf_rows[w][i] = take((size_t)pf_row_tiles(*c, w, i ? 256 : 128) * (i ? 256 : 128) * sizeof(PfRow));
         }
     }
     L.total = off;
@@ -209,6 +216,7 @@ struct knnssd_ctx {
     bool tuned;         // shape fits the tuned bf16 draft kernels
     bool tuned_verify;  // ... and the matrix-core verification kernels (every K a multiple of 32)
     bool tuned_prefill; // ... and the many-row prefill kernels (a row group fits 16 tile slots)
+    bool wide_weights = false;   // a prompt has met weights that the prefill's two fp16 planes do not hold
     bool verify_attn_mfma;  // verification passes run their split-KV attention on the matrix cores
     // tabulated workgroup splits of the five matrix shapes (tuned kernels)
     const WgSplit *split_qkv = nullptr, *split_o = nullptr, *split_gu = nullptr, *split_down = nullptr, *split_head = nullptr;
@@ -226,6 +234,36 @@ struct knnssd_ctx {
 
     template <typename T> T *wsp(size_t off) { return reinterpret_cast<T *>(ws + off); }
 };
+
+// The prefill GEMM's builds: f(planes, token tiles, epilogue, kernel, dynamic LDS) for each
+template <int NP, int TA, int TB, int WA, int NS, bool PP, int EPI, typename F> static void pf_build(F f) {
+    f(NP, TB, EPI, prefill_gemm_kernel<NP, TA, TB, WA, NS, PP, EPI>, PfShape<NP, TA, TB, WA, NS, PP>::LDS);
+}
+template <typename F> static void pf_each_build(F f) {
+    pf_build<2, 16, 16, 2, 3, true, PF_PARTS>(f);
+    pf_build<2, 16, 16, 2, 3, true, PF_SWIGLU>(f);
+    pf_build<2, 16, 16, 2, 3, true, PF_ROPE>(f);
+    pf_build<2, 16, 8, 2, 3, true, PF_PARTS>(f);
+    pf_build<2, 8, 4, 8, 3, false, PF_PARTS>(f);
+    pf_build<3, 16, 16, 2, 2, true, PF_PARTS>(f);
+    pf_build<3, 16, 16, 2, 2, true, PF_SWIGLU>(f);
+    pf_build<3, 16, 16, 2, 2, true, PF_ROPE>(f);
+    pf_build<3, 16, 8, 2, 3, true, PF_PARTS>(f);
+    pf_build<3, 8, 4, 8, 3, false, PF_PARTS>(f);
+}
+static hipError_t pf_set_lds_limits() {
+    hipError_t e = hipSuccess;
+    auto set = [&](const void *k, size_t bytes) {
+        if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    };
+    pf_each_build([&](int, int, int, void (*k)(PfArgs), size_t lds) { set((const void *)k, lds); });
+    void (*rows[])(PfRowArgs) = {prefill_x_row_kernel<2, false>, prefill_x_row_kernel<2, true>, prefill_x_row_kernel<3, false>, prefill_x_row_kernel<3, true>,
+                                 prefill_u_row_kernel<2, false>, prefill_u_row_kernel<2, true>, prefill_u_row_kernel<3, false>, prefill_u_row_kernel<3, true>};
+    for (auto k : rows) set((const void *)k, KS_MAX_DYN_LDS - 4096);
+    set((const void *)prefill_attn_kernel<128>, pf_attn_lds_bytes<128>());
+    set((const void *)prefill_attn_kernel<64>, pf_attn_lds_bytes<64>());
+    return e;
+}
 
 extern "C" size_t knnssd_workspace_bytes(const knnssd_model_cfg *cfg) {
     if (!cfg_valid(cfg) || !cfg_supported(cfg)) return 0;
@@ -317,11 +355,7 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         if (ea == hipSuccess)
             ea = hipFuncSetAttribute((const void *)attn_partial_mfma_kernel<64, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)vattn_lds_bytes<64>());
         if (ea == hipSuccess)
-            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<16, 16, 2, 2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PfShape<16, 16, 2, 2, true>::LDS);
-        if (ea == hipSuccess)
-            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<16, 8, 2, 3, true>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PfShape<16, 8, 2, 3, true>::LDS);
-        if (ea == hipSuccess)
-            ea = hipFuncSetAttribute((const void *)prefill_gemm_kernel<8, 4, 4, 3, false>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)PfShape<8, 4, 4, 3, false>::LDS);
+            ea = pf_set_lds_limits();
         if (ea != hipSuccess) {
             snprintf(g_hip_err, sizeof(g_hip_err), "%s (hipFuncSetAttribute)", hipGetErrorString(ea));
             delete c;
@@ -345,10 +379,20 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         c->split_gu = tabulate(2, OP_SWIGLU, cfg->d_ffn, d);
         c->split_down = tabulate(3, OP_RESID, d, cfg->d_ffn);
         c->split_head = tabulate(4, OP_HEAD, cfg->vocab, d);
+        for (int w = 0; c->tuned_prefill && w < PF_OPS; ++w) {
+            GemmOp o = shape;
+            o.type = w == PF_QKV ? OP_QKV : (w == PF_GU ? OP_SWIGLU : OP_RESID);
+            o.N = w == PF_QKV ? (H + 2 * Hkv) * hd : (w == PF_GU ? cfg->d_ffn : d);
+            o.K = w == PF_O ? H * hd : (w == PF_DOWN ? cfg->d_ffn : d);
+            o.split = w == PF_QKV ? c->split_qkv : (w == PF_O ? c->split_o : (w == PF_GU ? c->split_gu : c->split_down));
+            for (int i = 0; i < 2; ++i) {
+                int n_mr = 0;
+                const int tm = i ? 256 : 128, n = pf_row_tiles(*cfg, w, tm, &n_mr) * tm;
+                hipLaunchKernelGGL(prefill_row_table_kernel, dim3((n + 255) / 256), dim3(256), 0, c->stream, o, tm, n_mr, n, c->wsp<PfRow>(c->L.pf_rows[w][i]));
+            }
+        }
         // arrival counters of the attention kernel that merges its own chunks: zero between launches
         hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, c->stream, c->wsp<int>(c->L.attn_arrivals), KS_MAX_ROWS * cfg->n_heads);
-        if (c->L.pf_n_arrivals > 0)
-            hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(256), 0, c->stream, c->wsp<int>(c->L.pf_arrivals), c->L.pf_n_arrivals);
         hipError_t et = hipGetLastError();
         if (et != hipSuccess) {
             snprintf(g_hip_err, sizeof(g_hip_err), "%s (split_table_kernel)", hipGetErrorString(et));
@@ -721,62 +765,101 @@ static int32_t read_back(knnssd_ctx *c, const void *dev, size_t bytes) {
     return KNNSSD_OK;
 }
 
-// The prefill GEMM reads rows in runs of four neighbours of one kind: every count is a multiple of that here (tuned_ok).
-static bool prefill_tuned_ok(const knnssd_model_cfg &g) { return g.d_model % 4 == 0 && g.d_ffn % 4 == 0; }
+// The prefill kernels work on four neighbouring features at a time and keep a row in LDS.
+static bool prefill_tuned_ok(const knnssd_model_cfg &g) {
+    const size_t lds = KS_MAX_DYN_LDS - 4096;
+    return g.d_model % 32 == 0 && g.d_ffn % 32 == 0 && (size_t)g.d_model * 4 <= lds && (size_t)g.d_ffn * 4 <= lds &&
+           (size_t)g.n_heads * g.head_dim * 4 <= lds;
+}
 
 // The full model over the n_tok prompt rows with the matrix-core prefill kernels: fills the KV cache at positions
-// 0..n_tok-1 and leaves the last row's residual stream in pf_x.
+// 0..n_tok-1 and leaves the last row's residual stream in pf_x. NP: planes of the activations (see kernels_prefill.h).
+template <int NP>
 static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_tok) {
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn;
     const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd, TT = c->L.pf_tt, TTL = (n_tok + 15) / 16;
+    const dim3 rows((TTL + 7) / 8 * 128);        // row kernels: see pf_row_token
     hipStream_t s = c->stream;
-    int32_t *toks = c->wsp<int32_t>(c->L.pf_tokens);
-    float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *ss = c->wsp<float>(c->L.pf_ss);
-    bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att);
-    bf16_t *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
-    HIP_TRY(hipMemcpyAsync(toks, tokens_host, (size_t)n_tok * 4, hipMemcpyHostToDevice, s));
-    hipLaunchKernelGGL(prefill_embed_kernel, dim3(n_tok), dim3(256), 0, s, toks, (const bf16_t *)c->embed,
-                       next_gain(c, nullptr, -1), d, TT, x, frag_d, ss);
-    int n_ss = 1;               // shares of sum(x^2) the producer of the residual rows left in ss
-
-    GemmOp base{};
-    base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq; base.inv_dim = 1.0f / (float)d; base.eps = g.rms_eps;
-    base.cos_t = c->wsp<float>(c->L.rope_cos); base.sin_t = c->wsp<float>(c->L.rope_sin);
+    float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *att = c->wsp<float>(c->L.pf_att), *u = c->wsp<float>(c->L.pf_u);
+    float *part = c->wsp<float>(c->L.pf_part);
+    bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att), *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
+    float *scale_d = c->wsp<float>(c->L.pf_scale_d), *scale_att = c->wsp<float>(c->L.pf_scale_att), *scale_u = c->wsp<float>(c->L.pf_scale_u);
+    int *flag = reinterpret_cast<int *>(c->ws + c->L.head + sizeof(HeadResult));
     PfPlan plan[PF_OPS];
     for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_plan(g, w, TTL);
-    auto gemm = [&](int which, const GemmOp &op, const bf16_t *fin, bf16_t *fout) {
+
+    GemmOp base{};
+    base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq;
+    base.cos_t = c->wsp<float>(c->L.rope_cos); base.sin_t = c->wsp<float>(c->L.rope_sin);
+    auto gemm = [&](int which, const GemmOp &op, const bf16_t *fin, const float *scale, float *out) {
         const PfPlan &p = plan[which];
         PfArgs a{};
-        a.op = op; a.frag_in = fin; a.frag_out = fout; a.TT = TT; a.n_tok = n_tok;
-        const bool normed = which == PF_QKV || which == PF_GU;
-        a.ss_in = normed ? ss : nullptr; a.n_ss = n_ss; a.ss_out = ss;
-        a.part = c->wsp<float>(c->L.pf_part); a.arrivals = c->wsp<int>(c->L.pf_arrivals);
-        a.n_mt = p.n_mt; a.n_mr = p.n_mr; a.n_tt = p.n_tt; a.S = p.S;
-        const dim3 grid((p.tiles() * p.S + 7) / 8 * 8), wg(PF_NT);
-        if (p.tb == 16) hipLaunchKernelGGL((prefill_gemm_kernel<16, 16, 2, 2, true>), grid, wg, (PfShape<16, 16, 2, 2, true>::LDS), s, a);
-        else if (p.tb == 8) hipLaunchKernelGGL((prefill_gemm_kernel<16, 8, 2, 3, true>), grid, wg, (PfShape<16, 8, 2, 3, true>::LDS), s, a);
-        else hipLaunchKernelGGL((prefill_gemm_kernel<8, 4, 4, 3, false>), grid, wg, (PfShape<8, 4, 4, 3, false>::LDS), s, a);
-        if (!normed) n_ss = p.n_mt;
+        const int epi = p.parts(which) ? PF_PARTS : (which == PF_GU ? PF_SWIGLU : PF_ROPE);
+        a.op = op; a.frag_in = fin; a.scale = scale; a.out = epi == PF_PARTS ? part : out; a.flag = flag; a.TT = TT; a.n_tok = n_tok;
+        a.rows = c->wsp<PfRow>(c->L.pf_rows[which][p.tm() == 256]); a.out_rows = p.out_rows();
+        a.n_mt = p.n_mt; a.n_mr = p.n_mr; a.n_tt = p.n_tt; a.S = p.S; a.inv_tiles = 1.0f / (float)p.tiles();
+        a.steps = op.K / 32 / p.S; a.longer = op.K / 32 % p.S;
+        pf_each_build([&](int np, int tb, int e, void (*k)(PfArgs), size_t lds) {
+            if (np == NP && tb == p.tb && e == epi) hipLaunchKernelGGL(k, dim3((p.tiles() * p.S + 7) / 8 * 8), dim3(PF_NT), lds, s, a);
+        });
     };
+    auto row_args = [&](int which, int width) {     // the row kernel behind a product (width: features it finishes)
+        const PfPlan &p = plan[which];
+        PfRowArgs r{};
+        r.op = base; r.n_tok = n_tok; r.in = part; r.S = p.S; r.out_rows = p.out_rows(); r.ld = p.n_mt * p.tm(); r.TM = p.tm(); r.d = width; r.TT = TT;
+        r.inv_dim = 1.0f / (float)d; r.eps = g.rms_eps;
+        return r;
+    };
+    auto x_row = [&](int which, int after) {
+        PfRowArgs r = row_args(which, d);
+        r.x = x; r.gain = next_gain(c, nullptr, after); r.frag = frag_d; r.scale = scale_d;
+        hipLaunchKernelGGL((prefill_x_row_kernel<NP, false>), rows, dim3(PF_RT), (size_t)d * 4, s, r);
+    };
+    {
+        int32_t *toks = c->wsp<int32_t>(c->L.pf_tokens);
+        HIP_TRY(hipMemcpyAsync(toks, tokens_host, (size_t)n_tok * 4, hipMemcpyHostToDevice, s));
+        PfRowArgs r = row_args(PF_O, d);
+        r.op.embed = (const bf16_t *)c->embed; r.toks = toks; r.flag = flag;
+        r.x = x; r.gain = next_gain(c, nullptr, -1); r.frag = frag_d; r.scale = scale_d;
+        hipLaunchKernelGGL((prefill_x_row_kernel<NP, true>), rows, dim3(PF_RT), (size_t)d * 4, s, r);
+    }
     for (int b = 0; b < g.n_blocks; ++b) {
         bf16_t *kvb = (bf16_t *)(c->kv + (size_t)b * c->kv_block_bytes);
         GemmOp o = base;
         o.type = OP_QKV; o.W = (const bf16_t *)c->wqkv[b]; o.N = qkvd; o.K = d; o.q_out = q; o.kv_block = kvb; o.split = c->split_qkv;
-        gemm(PF_QKV, o, frag_d, nullptr);
+        gemm(PF_QKV, o, frag_d, scale_d, nullptr);
+        if (plan[PF_QKV].parts(PF_QKV)) {
+            PfRowArgs r = row_args(PF_QKV, 0);
+            r.op = o;
+            hipLaunchKernelGGL(prefill_qkv_row_kernel, dim3(rows.x, ((H + Hkv) * hd / 2 + Hkv * hd + 4 * PF_RT - 1) / (4 * PF_RT)), dim3(PF_RT), 0, s, r, plan[PF_QKV].n_mr);
+        }
         PfAttn at{};
-        at.q = q; at.kv_block = kvb; at.frag_out = frag_att; at.H = H; at.Hkv = Hkv; at.max_seq = g.max_seq; at.TT = TT; at.n_tok = n_tok;
-        if (hd == 128) hipLaunchKernelGGL(prefill_attn_kernel<128>, dim3(((TTL + 3) / 4) * H), dim3(256), 0, s, at);
-        else hipLaunchKernelGGL(prefill_attn_kernel<64>, dim3(((TTL + 3) / 4) * H), dim3(256), 0, s, at);
+        at.q = q; at.kv_block = kvb; at.out = att; at.H = H; at.Hkv = Hkv; at.max_seq = g.max_seq; at.n_tok = n_tok;
+        if (hd == 128) hipLaunchKernelGGL(prefill_attn_kernel<128>, dim3(((TTL + 3) / 4) * H), dim3(256), pf_attn_lds_bytes<128>(), s, at);
+        else hipLaunchKernelGGL(prefill_attn_kernel<64>, dim3(((TTL + 3) / 4) * H), dim3(256), pf_attn_lds_bytes<64>(), s, at);
+        PfRowArgs ra = row_args(PF_O, qd);
+        ra.in = att; ra.frag = frag_att; ra.scale = scale_att;
+        hipLaunchKernelGGL((prefill_u_row_kernel<NP, false>), rows, dim3(PF_RT), (size_t)qd * 4, s, ra);
         GemmOp r = base;
-        r.type = OP_RESID; r.W = (const bf16_t *)c->wo[b]; r.N = d; r.K = qd; r.x = x; r.gain_next = next_gain(c, nullptr, 2 * b); r.split = c->split_o;
-        gemm(PF_O, r, frag_att, frag_d);
-        GemmOp u = base;
-        u.type = OP_SWIGLU; u.W = (const bf16_t *)c->wgu[b]; u.N = F; u.K = d; u.split = c->split_gu;
-        gemm(PF_GU, u, frag_d, frag_u);
+        r.type = OP_RESID; r.W = (const bf16_t *)c->wo[b]; r.N = d; r.K = qd; r.split = c->split_o;
+        gemm(PF_O, r, frag_att, scale_att, part);
+        x_row(PF_O, 2 * b);
+        GemmOp gu = base;
+        gu.type = OP_SWIGLU; gu.W = (const bf16_t *)c->wgu[b]; gu.N = F; gu.K = d; gu.split = c->split_gu;
+        gemm(PF_GU, gu, frag_d, scale_d, u);
+        PfRowArgs ru = row_args(PF_GU, F);
+        ru.frag = frag_u; ru.scale = scale_u;
+        if (plan[PF_GU].parts(PF_GU)) {
+            hipLaunchKernelGGL((prefill_u_row_kernel<NP, true>), rows, dim3(PF_RT), (size_t)F * 4, s, ru);
+        } else {
+            ru.in = u;
+            hipLaunchKernelGGL((prefill_u_row_kernel<NP, false>), rows, dim3(PF_RT), (size_t)F * 4, s, ru);
+        }
         GemmOp dn = base;
-        dn.type = OP_RESID; dn.W = (const bf16_t *)c->wdown[b]; dn.N = d; dn.K = F; dn.x = x; dn.gain_next = next_gain(c, nullptr, 2 * b + 1); dn.split = c->split_down;
-        gemm(PF_DOWN, dn, frag_u, frag_d);
+        dn.type = OP_RESID; dn.W = (const bf16_t *)c->wdown[b]; dn.N = d; dn.K = F; dn.split = c->split_down;
+        gemm(PF_DOWN, dn, frag_u, scale_u, part);
+        x_row(PF_DOWN, 2 * b + 1);
     }
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
@@ -811,9 +894,16 @@ static int32_t prefill_head(knnssd_ctx *c, int n_tok, int row, float *last_hidde
 static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, float *last_hidden_dev, int32_t *first_token) {
     PassCtl *ver = c->wsp<PassCtl>(c->L.ver_ctl);
     if (c->tuned_prefill && n >= PF_MIN_ROWS) {
-        KS_TRY(prefill_tuned(c, tokens, n));
-        KS_TRY(prefill_head(c, n, (n - 1) % KS_MAX_ROWS, last_hidden_dev));
-        KS_TRY(read_back(c, &c->wsp<HeadResult>(c->L.head)->tok[0], 4));
+        // two fp16 planes; a model whose weights they do not hold (the kernels tell) is run with three bf16 planes, and so
+        // are its later prompts (a hint only: either way the result is right)
+        for (int again = 0; again < 2; ++again) {
+            if (c->wide_weights) KS_TRY(prefill_tuned<3>(c, tokens, n));
+            else KS_TRY(prefill_tuned<2>(c, tokens, n));
+            KS_TRY(prefill_head(c, n, (n - 1) % KS_MAX_ROWS, last_hidden_dev));
+            KS_TRY(read_back(c, c->wsp<HeadResult>(c->L.head), sizeof(HeadResult) + 4));
+            if (c->wide_weights || !c->h_stage[sizeof(HeadResult) / 4]) break;
+            c->wide_weights = true;
+        }
         *first_token = c->h_stage[0];
         c->prefilled = true;
         c->cache_len = n;
