@@ -1031,27 +1031,30 @@ __global__ __launch_bounds__(NT) void hidden_from_image_kernel(const float *imag
 // ------------------------------------------------------------------------------------------
 // Embedding as the first producer: x = E[tok], gain (.) x and the shares of sum(x^2)
 // ------------------------------------------------------------------------------------------
+// A wavefront per token row: a workgroup owns few columns (N / 256), so the rows side by side are one round trip where one
+// after the other they were one each (16 rows of the 7B shape: 17.6 -> 5 us, 9 rows 12 us before).
 template <bool PLANES>
 __global__ __launch_bounds__(NT) void embed_producer_kernel(GemmOp op, const PassCtl *ctl) {
-    __shared__ float scratch[NWV];
     if (!ctl->active) return;
     // the image layout is the one the host computed for op.n_rows rows: never more rows than that
     const int n_rows = min(min(ctl->n_rows, KS_MAX_ROWS), PLANES ? op.n_rows : KS_MAX_ROWS);
     const float inv_kc = PLANES ? __builtin_amdgcn_rcpf((float)op.out_kc) : 0.f;
     const int wg = blockIdx.x;         // launched with KS_NWG workgroups (wg_share)
     const int r0 = wg_share(op.N, wg), r1 = wg_share(op.N, wg + 1);
-    for (int m = 0; m < n_rows; ++m) {
-        const bf16_t *row = op.embed + (size_t)ctl->tok[m] * op.N;
-        float ssq = 0.f;
-        for (int n = r0 + threadIdx.x; n < r1; n += NT) {
-            float v = bf16_to_float(row[n]);
-            op.x[(size_t)m * op.N + n] = v;
-            store_act<PLANES>(op, m, n, op.N, op.gain_next[n] * v, inv_kc);
-            ssq = fmaf(v, v, ssq);
-        }
-        float s = block_sum(ssq, scratch);
-        if (threadIdx.x == 0) op.ss_out[(size_t)m * KS_NWG + wg] = s;
+    const int lane = threadIdx.x & 63;
+    static_assert(NWV >= KS_MAX_ROWS, "a wavefront for every token row");
+    const int m = threadIdx.x >> 6;
+    if (m >= n_rows) return;
+    const bf16_t *row = op.embed + (size_t)ctl->tok[m] * op.N;
+    float ssq = 0.f;
+    for (int n = r0 + lane; n < r1; n += 64) {
+        const float v = bf16_to_float(row[n]);
+        op.x[(size_t)m * op.N + n] = v;
+        store_act<PLANES>(op, m, n, op.N, op.gain_next[n] * v, inv_kc);
+        ssq = fmaf(v, v, ssq);
     }
+    ssq = wave_sum(ssq);
+    if (lane == 0) op.ss_out[(size_t)m * KS_NWG + wg] = ssq;
 }
 
 // ------------------------------------------------------------------------------------------
