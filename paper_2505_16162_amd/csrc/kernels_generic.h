@@ -117,150 +117,206 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const PassCtl *ctl, const 
 }
 
 // ------------------------------------------------------------------------------------------
-// Y = X W^T for up to MR rows of X, one output feature per wavefront (lanes stride over K in
-// 16-byte chunks of the weight row), with the epilogues the decoder needs.
+// Y = X W^T for up to MR rows of X, one output feature (or pair of them) per wavefront (lanes stride over K in
+// 16-byte chunks of the weight row), with what surrounds a product in the decoder folded in: the RMSNorm in front of it
+// (gain into the weights, every wavefront sums x^2 beside its dot products) and the epilogues.
+// Small models are bound by the length of this chain of dependent launches (a launch is at least 1.5-2 us, most of them a
+// few round trips to the L2), so there are five per block, not eight, every operand load of a step goes out before the
+// first is used (rows past the last live one repeat it: no load sits under a condition), and the MR sums are reduced over
+// the wavefront together: with every exchange a lane hands over half of its rows, 17 exchanges for 16 rows instead of 96,
+// the same tree for every row whatever MR is. fp32 configuration (4 blocks of d = 256), prompt 32 + 32 tokens in rounds of
+// four drafts, before (norms and RoPE in launches of their own, 16-row builds for every verification, one position at a time
+// per wavefront in the attention) and after: 15.3-16.1 -> 8.9-10.2 ms; attention 9.7 -> 4.2 us, 5-row products 8.9 -> 3.9 us.
+// MR is the pass's row count rounded up (gemm_rows_mr), so a short pass carries no dead rows.
 // ------------------------------------------------------------------------------------------
-enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2 };
+enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 
-template <typename WT, int MR, int EPI>
-__global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, const WT *__restrict__ W,
-                                                        const WT *__restrict__ W2, const float *__restrict__ X,
-                                                        int ldx, float *Y, int ldy, int N, int K, int use_head_from) {
+// sums of v[0..MR-1] over the wavefront: lane l returns that of row l & (MR' - 1), MR' = MR rounded up to a power of two
+template <int MR>
+__device__ __forceinline__ float wave_sum_rows(float *v) {
+    constexpr int P = MR > 8 ? 16 : (MR > 4 ? 8 : (MR > 2 ? 4 : MR));
+    float t[P];
+#pragma unroll
+    for (int i = 0; i < P; ++i) t[i] = i < MR ? v[i] : 0.f;
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int off = 1; off < P; off <<= 1) {
+        // lanes that differ in this bit swap: the one without it keeps the even rows, the other the odd ones
+        const bool hi = (lane & off) != 0;
+#pragma unroll
+        for (int i = 0; i < P / (2 * off); ++i) {
+            const float keep = hi ? t[2 * i + 1] : t[2 * i], give = hi ? t[2 * i] : t[2 * i + 1];
+            t[i] = keep + __shfl_xor(give, off, 64);
+        }
+    }
+#pragma unroll
+    for (int off = P; off < 64; off <<= 1) t[0] += __shfl_xor(t[0], off, 64);
+    return t[0];
+}
+
+struct RowsOp {
+    const float *X;             // [rows][ldx]
+    int ldx;
+    float *Y;                   // [rows][ldy]
+    int ldy, N, K;              // N: output features (EPI_SWIGLU: per half; EPI_QKV: (H + 2 Hkv) * hd)
+    const float *gain;          // RMSNorm in front of the product; nullptr: none
+    float eps;
+    int from_head;              // only rows from ctl->head_from on (LM head)
+    // EPI_QKV: rotated queries to Y, keys and values (rounded to the cache type) to the cache [2][Hkv][max_seq][hd]
+    void *kv_block;
+    const float *cos_t, *sin_t;
+    int H, Hkv, hd, max_seq;
+};
+
+template <typename WT, typename KT, int MR, int EPI>
+__global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, const WT *__restrict__ W, RowsOp op) {
     if (!ctl->active) return;
-    const int n_rows = min(ctl->n_rows, MR);
-    const int row_lo = use_head_from ? ctl->head_from : 0;
-    if (row_lo >= n_rows) return;
+    const int row_lo = op.from_head ? ctl->head_from : 0;
+    const int n_rows = min(ctl->n_rows - row_lo, MR);
+    if (n_rows <= 0) return;
     const int lane = threadIdx.x & 63;
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int n_waves = (gridDim.x * blockDim.x) >> 6;
     constexpr int VEC = WChunk<WT>::N;
+    constexpr bool DUAL = EPI == EPI_SWIGLU || EPI == EPI_QKV;      // two weight rows per item
+    const int K = op.K, half = op.hd >> 1;
+    const int P = EPI == EPI_QKV ? (op.H + op.Hkv) * half : 0;      // rotary pairs; behind them pairs of value rows
+    const int items = EPI == EPI_QKV ? P + op.Hkv * half : op.N;
+    const float *X = op.X + (size_t)row_lo * op.ldx;
 
-    for (int o = wave; o < N; o += n_waves) {
-        float acc[MR], acc2[MR];
+    for (int o = wave; o < items; o += n_waves) {
+        int r0 = o, r1 = o + op.N;
+        if (EPI == EPI_QKV) {
+            if (o < P) { const int head = o / half; r0 = head * op.hd + (o - head * half); r1 = r0 + half; }
+            else { r0 = (op.H + op.Hkv) * op.hd + (o - P) * 2; r1 = r0 + 1; }
+        }
+        float acc[MR], acc2[MR], ss[MR];
 #pragma unroll
-        for (int r = 0; r < MR; ++r) { acc[r] = 0.f; acc2[r] = 0.f; }
-        const WT *wrow = W + (size_t)o * K;
-        const WT *wrow2 = (EPI == EPI_SWIGLU) ? (W2 + (size_t)o * K) : nullptr;
+        for (int r = 0; r < MR; ++r) { acc[r] = 0.f; acc2[r] = 0.f; ss[r] = 0.f; }
+        const WT *wrow = W + (size_t)r0 * K, *wrow2 = W + (size_t)r1 * K;
         for (int k = lane * VEC; k < K; k += 64 * VEC) {
             WChunk<WT> w, w2;
             w.load(wrow + k);
-            if (EPI == EPI_SWIGLU) w2.load(wrow2 + k);
+            if (DUAL) w2.load(wrow2 + k);
+            if (op.gain) {
+#pragma unroll
+                for (int j = 0; j < VEC; ++j) {
+                    const float g = op.gain[k + j];
+                    w.v[j] *= g;
+                    if (DUAL) w2.v[j] *= g;
+                }
+            }
 #pragma unroll
             for (int r = 0; r < MR; ++r) {
-                if (r >= row_lo && r < n_rows) {
-                    const float *xp = X + (size_t)r * ldx + k;
+                const float *xp = X + (size_t)min(r, n_rows - 1) * op.ldx + k;
 #pragma unroll
-                    for (int j = 0; j < VEC; j += 4) {
-                        float4 xv = *reinterpret_cast<const float4 *>(xp + j);
-                        acc[r] = fmaf(w.v[j + 0], xv.x, acc[r]);
-                        acc[r] = fmaf(w.v[j + 1], xv.y, acc[r]);
-                        acc[r] = fmaf(w.v[j + 2], xv.z, acc[r]);
-                        acc[r] = fmaf(w.v[j + 3], xv.w, acc[r]);
-                        if (EPI == EPI_SWIGLU) {
-                            acc2[r] = fmaf(w2.v[j + 0], xv.x, acc2[r]);
-                            acc2[r] = fmaf(w2.v[j + 1], xv.y, acc2[r]);
-                            acc2[r] = fmaf(w2.v[j + 2], xv.z, acc2[r]);
-                            acc2[r] = fmaf(w2.v[j + 3], xv.w, acc2[r]);
-                        }
+                for (int j = 0; j < VEC; j += 4) {
+                    const float4 xv = *reinterpret_cast<const float4 *>(xp + j);
+                    const float x[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        acc[r] = fmaf(w.v[j + e], x[e], acc[r]);
+                        if (DUAL) acc2[r] = fmaf(w2.v[j + e], x[e], acc2[r]);
+                        if (EPI == EPI_QKV || EPI == EPI_SWIGLU) ss[r] = fmaf(x[e], x[e], ss[r]);
                     }
                 }
             }
         }
-#pragma unroll
-        for (int r = 0; r < MR; ++r) {
-            if (r >= row_lo && r < n_rows) {
-                float a = wave_sum(acc[r]);
-                float b = (EPI == EPI_SWIGLU) ? wave_sum(acc2[r]) : 0.f;
-                if (lane == 0) {
-                    float *yp = Y + (size_t)r * ldy + o;
-                    if (EPI == EPI_STORE) *yp = a;
-                    if (EPI == EPI_RESID) *yp = *yp + a;
-                    if (EPI == EPI_SWIGLU) *yp = (a / (1.0f + expf(-a))) * b;
+        float a = wave_sum_rows<MR>(acc), b = DUAL ? wave_sum_rows<MR>(acc2) : 0.f;
+        if (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
+            const float sum = wave_sum_rows<MR>(ss);
+            if (op.gain) {
+                const float rs = 1.0f / sqrtf(sum / (float)K + op.eps);
+                a *= rs;
+                b *= rs;
+            }
+        }
+        if (lane < n_rows) {           // lane r holds row r
+            const int row = row_lo + lane;
+            float *yp = op.Y + (size_t)row * op.ldy;
+            if (EPI == EPI_STORE) yp[o] = a;
+            if (EPI == EPI_RESID) yp[o] += a;
+            if (EPI == EPI_SWIGLU) yp[o] = (a / (1.0f + expf(-a))) * b;
+            if constexpr (EPI == EPI_QKV) {
+                const int pos = ctl->start + row;
+                KT *kc = reinterpret_cast<KT *>(op.kv_block), *vc = kc + (size_t)op.Hkv * op.max_seq * op.hd;
+                if (o < P) {
+                    const int head = o / half, i = o - head * half;
+                    const float c = op.cos_t[(size_t)pos * half + i], s = op.sin_t[(size_t)pos * half + i];
+                    const float ra = a * c - b * s, rb = b * c + a * s;
+                    if (head < op.H) {
+                        yp[r0] = ra; yp[r1] = rb;
+                    } else {
+                        const size_t base = ((size_t)(head - op.H) * op.max_seq + pos) * op.hd;
+                        store_rounded(kc, base + i, ra);
+                        store_rounded(kc, base + i + half, rb);
+                    }
+                } else {
+                    const int v = (o - P) * 2, head = v / op.hd, i = v - head * op.hd;
+                    const size_t base = ((size_t)head * op.max_seq + pos) * op.hd + i;
+                    store_rounded(vc, base, a);
+                    store_rounded(vc, base + 1, b);
                 }
             }
         }
-    }
-}
-
-// ------------------------------------------------------------------------------------------
-// RoPE on q (in place) and k, then k and v into the cache (rounded to the cache type).
-// qkv: [rows][(H + 2 Hkv) * hd] fp32.  cache layout: [2 (k,v)][Hkv][max_seq][hd]
-// ------------------------------------------------------------------------------------------
-template <typename KT>
-__global__ __launch_bounds__(256) void rope_kv_kernel(const PassCtl *ctl, float *qkv, KT *kv_block,
-                                                      const float *cos_t, const float *sin_t, int H, int Hkv,
-                                                      int hd, int max_seq) {
-    if (!ctl->active) return;
-    const int r = blockIdx.x;
-    if (r >= ctl->n_rows) return;
-    const int pos = ctl->start + r;
-    const int half = hd >> 1;
-    const int ld = (H + 2 * Hkv) * hd;
-    float *row = qkv + (size_t)r * ld;
-    const float *cs = cos_t + (size_t)pos * half, *sn = sin_t + (size_t)pos * half;
-    KT *kc = kv_block;
-    KT *vc = kv_block + (size_t)Hkv * max_seq * hd;
-    for (int idx = threadIdx.x; idx < (H + Hkv) * half; idx += blockDim.x) {
-        int h = idx / half, i = idx % half;
-        float c = cs[i], s = sn[i];
-        float a = row[h * hd + i], b = row[h * hd + i + half];
-        float ra = a * c - b * s, rb = b * c + a * s;
-        if (h < H) {
-            row[h * hd + i] = ra; row[h * hd + i + half] = rb;
-        } else {
-            size_t base = ((size_t)(h - H) * max_seq + pos) * hd;
-            store_rounded(kc, base + i, ra);
-            store_rounded(kc, base + i + half, rb);
-        }
-    }
-    const float *vrow = row + (size_t)(H + Hkv) * hd;
-    for (int idx = threadIdx.x; idx < Hkv * hd; idx += blockDim.x) {
-        int h = idx / hd, i = idx % hd;
-        store_rounded(vc, ((size_t)h * max_seq + pos) * hd + i, vrow[idx]);
     }
 }
 
 // ------------------------------------------------------------------------------------------
 // Attention of one (row, head): softmax(q K^T / sqrt(hd)) V over positions 0..start+r.
-// One workgroup per (head, row); scores are kept in LDS (max_seq floats of dynamic LDS).
+// One workgroup per (head, row); scores are kept in LDS (max_seq floats of dynamic LDS). A group of HD/4 lanes takes a
+// position (four dimensions per lane), 16 or 8 positions side by side, four rounds of them in flight.
 // ------------------------------------------------------------------------------------------
-template <typename KT>
+__device__ __forceinline__ float4 load4_as_float(const float *p) { return *reinterpret_cast<const float4 *>(p); }
+__device__ __forceinline__ float4 load4_as_float(const bf16_t *p) {
+    const uint2 t = *reinterpret_cast<const uint2 *>(p);
+    return float4{__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u), __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u)};
+}
+
+template <typename KT, int HD>
 __global__ __launch_bounds__(256) void attention_kernel(const PassCtl *ctl, const float *qkv, const KT *kv_block,
-                                                        float *att, int H, int Hkv, int hd, int max_seq) {
+                                                        float *att, int H, int Hkv, int max_seq) {
     if (!ctl->active) return;
     const int h = blockIdx.x, r = blockIdx.y;
     if (r >= ctl->n_rows) return;
-    extern __shared__ float score_lds[];
-    float *scores = score_lds;           // [len]
+    constexpr int LPP = HD / 4, NP = 256 / LPP, U = 4;       // lanes per position, positions side by side, rounds in flight
+    extern __shared__ float scores[];                        // [len]
     __shared__ float red[8];
-    __shared__ float outp[4][128];
+    __shared__ __align__(16) float outp[4][HD];
     const int len = ctl->start + r + 1;
     const int kvh = h / (H / Hkv);
-    const int ld = (H + 2 * Hkv) * hd;
-    const float *q = qkv + (size_t)r * ld + h * hd;
-    const KT *kc = kv_block + (size_t)kvh * max_seq * hd;
-    const KT *vc = kv_block + ((size_t)Hkv + kvh) * max_seq * hd;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const float scale = 1.0f / sqrtf((float)hd);
+    const int ld = (H + 2 * Hkv) * HD;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = tid / LPP, d0 = (tid % LPP) * 4;
+    const float4 q = *reinterpret_cast<const float4 *>(qkv + (size_t)r * ld + h * HD + d0);
+    const KT *kc = kv_block + (size_t)kvh * max_seq * HD + d0;
+    const KT *vc = kv_block + ((size_t)Hkv + kvh) * max_seq * HD + d0;
+    const float scale = 1.0f / sqrtf((float)HD);
 
-    float q0 = (lane < hd) ? q[lane] : 0.f;
-    float q1 = (lane + 64 < hd) ? q[lane + 64] : 0.f;
     float lmax = -INFINITY;
-    for (int t = wave; t < len; t += 4) {
-        const KT *kt = kc + (size_t)t * hd;
-        float p = 0.f;
-        if (lane < hd) p = q0 * load_as_float(kt, lane);
-        if (lane + 64 < hd) p = fmaf(q1, load_as_float(kt, lane + 64), p);
-        p = wave_sum(p) * scale;
-        if (lane == 0) scores[t] = p;
-        lmax = fmaxf(lmax, p);
+    for (int t0 = grp; t0 < len; t0 += NP * U) {
+        float4 k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = load4_as_float(kc + (size_t)min(t0 + u * NP, len - 1) * HD);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            float p = q.x * k[u].x;
+            p = fmaf(q.y, k[u].y, p); p = fmaf(q.z, k[u].z, p); p = fmaf(q.w, k[u].w, p);
+#pragma unroll
+            for (int off = 1; off < LPP; off <<= 1) p += __shfl_xor(p, off, 64);
+            p *= scale;
+            if (t0 + u * NP < len) {
+                if (d0 == 0) scores[t0 + u * NP] = p;
+                lmax = fmaxf(lmax, p);
+            }
+        }
     }
+    lmax = wave_max(lmax);
     if (lane == 0) red[wave] = lmax;
     __syncthreads();
     const float mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
     float lsum = 0.f;
-    for (int t = threadIdx.x; t < len; t += 256) {
-        float e = expf(scores[t] - mx);
+    for (int t = tid; t < len; t += 256) {
+        const float e = expf(scores[t] - mx);
         scores[t] = e;
         lsum += e;
     }
@@ -268,18 +324,27 @@ __global__ __launch_bounds__(256) void attention_kernel(const PassCtl *ctl, cons
     if (lane == 0) red[4 + wave] = lsum;
     __syncthreads();
     const float den = (red[4] + red[5]) + (red[6] + red[7]);
-    // output: thread (part, i) sums its share of positions for dimension i
-    const int nparts = 256 / hd;   // hd 64 -> 4 parts, hd 128 -> 2 parts
-    const int i = threadIdx.x % hd, part = threadIdx.x / hd;
-    float acc = 0.f;
-    if (part < nparts)
-        for (int t = part; t < len; t += nparts) acc = fmaf(scores[t], load_as_float(vc, (size_t)t * hd + i), acc);
-    if (part < 4) outp[part][i] = acc;
+    float4 o = float4{0.f, 0.f, 0.f, 0.f};
+    for (int t0 = grp; t0 < len; t0 += NP * U) {
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = load4_as_float(vc + (size_t)min(t0 + u * NP, len - 1) * HD);
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const float e = t0 + u * NP < len ? scores[t0 + u * NP] : 0.f;
+            if (t0 + u * NP < len) { o.x = fmaf(e, v[u].x, o.x); o.y = fmaf(e, v[u].y, o.y); o.z = fmaf(e, v[u].z, o.z); o.w = fmaf(e, v[u].w, o.w); }
+        }
+    }
+#pragma unroll
+    for (int off = LPP; off < 64; off <<= 1) {               // the wavefront's positions side by side
+        o.x += __shfl_xor(o.x, off, 64); o.y += __shfl_xor(o.y, off, 64);
+        o.z += __shfl_xor(o.z, off, 64); o.w += __shfl_xor(o.w, off, 64);
+    }
+    if (lane < LPP) *reinterpret_cast<float4 *>(&outp[wave][d0]) = o;
     __syncthreads();
-    if ((int)threadIdx.x < hd) {
-        float s = 0.f;
-        for (int p = 0; p < nparts; ++p) s += outp[p][threadIdx.x];
-        att[(size_t)r * (H * hd) + h * hd + threadIdx.x] = s / den;
+    if (tid < HD) {
+        const float s = (outp[0][tid] + outp[1][tid]) + (outp[2][tid] + outp[3][tid]);
+        att[(size_t)r * (H * HD) + h * HD + tid] = s / den;
     }
 }
 

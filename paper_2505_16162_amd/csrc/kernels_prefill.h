@@ -568,7 +568,7 @@ __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
             v = x0 + pf_sum_parts(a, tok, n);
         }
         *xp = v;
-        const f32x4 g = *reinterpret_cast<const f32x4 *>(a.gain + n) * v;
+        const f32x4 g = f32x4{a.gain[n], a.gain[n + 1], a.gain[n + 2], a.gain[n + 3]} * v;      // (gains may lie at any multiple of 4 bytes)
         *reinterpret_cast<f32x4 *>(row + n) = g;
 #pragma unroll
         for (int q = 0; q < 4; ++q) { sq = fmaf(v[q], v[q], sq); mx = fmaxf(mx, fabsf(g[q])); }
@@ -618,9 +618,11 @@ __global__ __launch_bounds__(PF_RT) void prefill_qkv_row_kernel(PfRowArgs a, int
 
 // The prompt's last row after the last block: the final norm's operands and shares as a one-row pass of the decode
 // kernels reads them (the LM head follows), and the final-norm hidden state.
-__global__ __launch_bounds__(NT) void prefill_last_row_kernel(const float *x_row, const float *gain, int d, float eps, float *act,
-                                                              float *ss, float *out0, float *out1) {
+// (It also sets the control block of that pass: one row at position pos.)
+__global__ __launch_bounds__(NT) void prefill_last_row_kernel(PassCtl *ctl, int pos, const float *x_row, const float *gain, int d, float eps,
+                                                              float *act, float *ss, float *out0, float *out1) {
     __shared__ float scratch[NWV];
+    if (threadIdx.x == 0) { ctl->active = 1; ctl->n_rows = 1; ctl->start = pos; ctl->head_from = 0; }
     float s = 0.f;
     for (int n = threadIdx.x; n < d; n += NT) s = fmaf(x_row[n], x_row[n], s);
     const float sum = block_sum(s, scratch), rs = 1.0f / sqrtf(sum / (float)d + eps);

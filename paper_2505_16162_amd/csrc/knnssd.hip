@@ -499,51 +499,64 @@ extern "C" int32_t knnssd_set_skipset(knnssd_ctx *ctx, const uint8_t *mask_host)
 // ------------------------------------------------------------------------------------------
 // one forward pass: every retained sublayer in order, then the head
 // ------------------------------------------------------------------------------------------
-template <typename WT, int MR>
-static void launch_gemm(knnssd_ctx *c, const PassCtl *ctl, int epi, const void *W, const void *W2, const float *X, int ldx,
-                        float *Y, int ldy, int N, int K, int use_head_from) {
-    int wgs = (N + 3) / 4;
+// rows a build of gemm_rows_kernel carries for a pass of n (drafts; short verifications; eight drafts; any)
+static int gemm_rows_mr(int n) { return n <= 3 ? n : (n <= 5 ? 5 : (n <= 9 ? 9 : KS_MAX_ROWS)); }
+
+template <typename WT, typename KT, int EPI>
+static void launch_rows(knnssd_ctx *c, const PassCtl *ctl, int n_rows, const void *W, const RowsOp &op) {
+    const int items = EPI == EPI_QKV ? (op.H + 2 * op.Hkv) * op.hd / 2 : op.N;
+    int wgs = (items + 3) / 4;
     if (wgs > 2048) wgs = 2048;
-    const WT *w = (const WT *)W, *w2 = (const WT *)W2;
-    if (epi == EPI_STORE)
-        hipLaunchKernelGGL((gemm_rows_kernel<WT, MR, EPI_STORE>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, w2, X, ldx, Y, ldy, N, K, use_head_from);
-    else if (epi == EPI_RESID)
-        hipLaunchKernelGGL((gemm_rows_kernel<WT, MR, EPI_RESID>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, w2, X, ldx, Y, ldy, N, K, use_head_from);
-    else
-        hipLaunchKernelGGL((gemm_rows_kernel<WT, MR, EPI_SWIGLU>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, w2, X, ldx, Y, ldy, N, K, use_head_from);
+    const WT *w = (const WT *)W;
+    switch (gemm_rows_mr(n_rows)) {
+        case 1: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 1, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
+        case 2: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 2, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
+        case 3: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 3, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
+        case 5: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 5, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
+        case 9: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 9, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
+        default: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, KS_MAX_ROWS, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
+    }
 }
 
-template <typename WT, typename KT, int MR>
-static int32_t run_pass_t(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask) {
+template <typename WT, typename KT>
+static int32_t run_pass_t(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int n_rows) {
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn;
     const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd;
     float *x = c->wsp<float>(c->L.x), *xn = c->wsp<float>(c->L.xn), *qkv = c->wsp<float>(c->L.qkv);
     float *att = c->wsp<float>(c->L.att), *u = c->wsp<float>(c->L.u), *logits = c->wsp<float>(c->L.logits);
-    const float *cos_t = c->wsp<float>(c->L.rope_cos), *sin_t = c->wsp<float>(c->L.rope_sin);
     hipStream_t s = c->stream;
-    const int rows = MR;  // grid rows; kernels drop rows >= n_rows
+    RowsOp base{};
+    base.eps = g.rms_eps; base.cos_t = c->wsp<float>(c->L.rope_cos); base.sin_t = c->wsp<float>(c->L.rope_sin);
+    base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq;
+    auto product = [&](const float *X, int ldx, float *Y, int ldy, int N, int K, const float *gain) {
+        RowsOp o = base;
+        o.X = X; o.ldx = ldx; o.Y = Y; o.ldy = ldy; o.N = N; o.K = K; o.gain = gain;
+        return o;
+    };
 
-    hipLaunchKernelGGL((embed_kernel<WT>), dim3(rows), dim3(256), 0, s, ctl, (const WT *)c->embed, x, d);
+    hipLaunchKernelGGL((embed_kernel<WT>), dim3(n_rows), dim3(256), 0, s, ctl, (const WT *)c->embed, x, d);
     for (int b = 0; b < g.n_blocks; ++b) {
         KT *kvb = (KT *)(c->kv + (size_t)b * c->kv_block_bytes);
         if (!(mask && mask[2 * b])) {
-            hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(256), 0, s, ctl, x, c->attn_norm[b], xn, d, g.rms_eps);
-            launch_gemm<WT, MR>(c, ctl, EPI_STORE, c->wqkv[b], nullptr, xn, d, qkv, qkvd, qkvd, d, 0);
-            hipLaunchKernelGGL((rope_kv_kernel<KT>), dim3(rows), dim3(256), 0, s, ctl, qkv, kvb, cos_t, sin_t, H, Hkv, hd, g.max_seq);
-            hipLaunchKernelGGL((attention_kernel<KT>), dim3(H, rows), dim3(256), (size_t)g.max_seq * 4, s, ctl, qkv, kvb, att, H, Hkv, hd, g.max_seq);
-            launch_gemm<WT, MR>(c, ctl, EPI_RESID, c->wo[b], nullptr, att, qd, x, d, d, qd, 0);
+            RowsOp o = product(x, d, qkv, qkvd, qkvd, d, c->attn_norm[b]);
+            o.kv_block = kvb;
+            launch_rows<WT, KT, EPI_QKV>(c, ctl, n_rows, c->wqkv[b], o);
+            const size_t lds = (size_t)g.max_seq * 4;
+            if (hd == 128) hipLaunchKernelGGL((attention_kernel<KT, 128>), dim3(H, n_rows), dim3(256), lds, s, ctl, qkv, kvb, att, H, Hkv, g.max_seq);
+            else hipLaunchKernelGGL((attention_kernel<KT, 64>), dim3(H, n_rows), dim3(256), lds, s, ctl, qkv, kvb, att, H, Hkv, g.max_seq);
+            launch_rows<WT, float, EPI_RESID>(c, ctl, n_rows, c->wo[b], product(att, qd, x, d, d, qd, nullptr));
         }
         if (!(mask && mask[2 * b + 1])) {
-            hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(256), 0, s, ctl, x, c->mlp_norm[b], xn, d, g.rms_eps);
-            const WT *wg = (const WT *)c->wgu[b];
-            launch_gemm<WT, MR>(c, ctl, EPI_SWIGLU, wg, wg + (size_t)F * d, xn, d, u, F, F, d, 0);
-            launch_gemm<WT, MR>(c, ctl, EPI_RESID, c->wdown[b], nullptr, u, F, x, d, d, F, 0);
+            launch_rows<WT, float, EPI_SWIGLU>(c, ctl, n_rows, c->wgu[b], product(x, d, u, F, F, d, c->mlp_norm[b]));
+            launch_rows<WT, float, EPI_RESID>(c, ctl, n_rows, c->wdown[b], product(u, F, x, d, d, F, nullptr));
         }
     }
-    hipLaunchKernelGGL(rmsnorm_kernel, dim3(rows), dim3(256), 0, s, ctl, x, c->final_norm, xn, d, g.rms_eps);
-    launch_gemm<WT, MR>(c, ctl, EPI_STORE, c->lm_head, nullptr, xn, d, logits, g.vocab, g.vocab, d, 1);
-    hipLaunchKernelGGL(argmax_kernel, dim3(rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
+    hipLaunchKernelGGL(rmsnorm_kernel, dim3(n_rows), dim3(256), 0, s, ctl, x, c->final_norm, xn, d, g.rms_eps);
+    RowsOp h = product(xn, d, logits, g.vocab, g.vocab, d, nullptr);
+    h.from_head = 1;
+    launch_rows<WT, float, EPI_STORE>(c, ctl, c->in_prefill ? 1 : n_rows, c->lm_head, h);     // a prompt's pass: its last row, or none
+    hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }
@@ -738,16 +751,10 @@ static int32_t run_pass(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int mr
     if (n_rows < 1 || n_rows > mr) return KNNSSD_ERANGE;
     if (mr == 1 && c->tuned) return run_pass_bf16(c, ctl, mask, true, true, 1, start);
     if (mr != 1 && c->tuned_verify) return run_pass_bf16(c, ctl, mask, false, want_head, n_rows, start);
-    if (mr == 1) {
-        if (wb && kb) return run_pass_t<bf16_t, bf16_t, 1>(c, ctl, mask);
-        if (wb && !kb) return run_pass_t<bf16_t, float, 1>(c, ctl, mask);
-        if (!wb && kb) return run_pass_t<float, bf16_t, 1>(c, ctl, mask);
-        return run_pass_t<float, float, 1>(c, ctl, mask);
-    }
-    if (wb && kb) return run_pass_t<bf16_t, bf16_t, KS_MAX_ROWS>(c, ctl, mask);
-    if (wb && !kb) return run_pass_t<bf16_t, float, KS_MAX_ROWS>(c, ctl, mask);
-    if (!wb && kb) return run_pass_t<float, bf16_t, KS_MAX_ROWS>(c, ctl, mask);
-    return run_pass_t<float, float, KS_MAX_ROWS>(c, ctl, mask);
+    if (wb && kb) return run_pass_t<bf16_t, bf16_t>(c, ctl, mask, n_rows);
+    if (wb && !kb) return run_pass_t<bf16_t, float>(c, ctl, mask, n_rows);
+    if (!wb && kb) return run_pass_t<float, bf16_t>(c, ctl, mask, n_rows);
+    return run_pass_t<float, float>(c, ctl, mask, n_rows);
 }
 
 static int32_t set_pass(knnssd_ctx *c, PassCtl *ctl, int active, int n_rows, int start, int head_from, const int32_t *toks) {
@@ -875,9 +882,7 @@ static int32_t prefill_head(knnssd_ctx *c, int n_tok, int row, float *last_hidde
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model;
     PassCtl *ver = c->wsp<PassCtl>(c->L.ver_ctl);
-    const int32_t none = 0;
-    KS_TRY(set_pass(c, ver, 1, 1, n_tok - 1, 0, &none));
-    hipLaunchKernelGGL(prefill_last_row_kernel, dim3(1), dim3(NT), 0, c->stream, c->wsp<float>(c->L.pf_x) + (size_t)(n_tok - 1) * d,
+    hipLaunchKernelGGL(prefill_last_row_kernel, dim3(1), dim3(NT), 0, c->stream, ver, n_tok - 1, c->wsp<float>(c->L.pf_x) + (size_t)(n_tok - 1) * d,
                        c->final_norm, d, g.rms_eps, c->wsp<float>(c->L.act_d), c->wsp<float>(c->L.ss), c->wsp<float>(c->L.hidden_last), last_hidden_dev);
     GemmOp h{};
     h.n_ss = KS_NWG; h.inv_dim = 1.0f / (float)d; h.eps = g.rms_eps;

@@ -1,0 +1,39 @@
+"""The any-shape kernels at the row counts and context lengths where they switch: passes of 1 to 16 rows go through builds for
+1, 2, 3, 5, 9 and 16 rows (a row's logits must not depend on which), contexts around the 16 or 8 positions an attention
+workgroup takes side by side and around its four rounds, both head sizes, all four pairs of storage types, grouped-query heads,
+widths that are no multiple of a wavefront's stride. Compared with the oracle."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2505_16162_amd import synth
+from gpu_common import logits_close, make_pair
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("wdt,kdt,hd,heads,kv_heads", [("fp32", "fp32", 64, 4, 4), ("fp32", "bf16", 128, 3, 1), ("bf16", "fp32", 64, 6, 2),
+                                                        ("bf16", "bf16", 128, 2, 2)])
+def test_row_counts_and_context_lengths(wdt, kdt, hd, heads, kv_heads):
+    shape = synth.small_shape("gen_%s_%s_%d" % (wdt, kdt, hd), d_model=264, n_heads=heads, n_kv_heads=kv_heads, head_dim=hd, d_ffn=424, vocab=777,
+                              max_seq=180, weight_dtype=wdt, kv_dtype=kdt)
+    w, orc, gpu = make_pair(shape, seed=51, std=0.05)
+    assert not gpu.packed
+    tokens = synth.make_prompt(shape.vocab, 170, seed=52).tolist()
+    rows = orc.forward(tokens, 0, None)
+    for ctx in (1, 7, 8, 15, 16, 31, 33, 63, 64, 65, 127, 129, 150):
+        print("case", shape.name, ctx, flush=True)
+        gpu.knnssd_prefill(tokens[:ctx])
+        kept = {}
+        for n in (16, 1, 2, 3, 4, 5, 6, 9, 10, 15):
+            gpu.knnssd_verify(tokens[ctx:ctx + n], ctx)
+            for r in {0, n // 2, n - 1}:
+                got = gpu.knnssd_get_logits(r).clone()
+                if r in kept:
+                    assert torch.equal(got, kept[r]), (ctx, n, r)
+                kept[r] = got
+        for r, got in kept.items():
+            ok, err = logits_close(got.numpy(), rows[ctx + r], shape)
+            assert ok, (ctx, r, err)
+    gpu.close()
