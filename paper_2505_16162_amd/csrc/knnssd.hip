@@ -98,7 +98,11 @@ static int pf_row_tiles(const knnssd_model_cfg &g, int which, int tm, int *n_mr 
 }
 
 // The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x ns of a step + what a workgroup
-// pays once), plus the K parts' way through memory.
+// pays once), plus the K parts' way through memory. The constants come from kernel traces; with one matrix's plan varied at
+// a time the choice was within 10 us per block of the best one at 45 to 4096 rows. 13B, 1024 rows, against the choice: O in
+// three parts of 256 x 256 (chosen), in five +4 us, in two +16, 256 x 128 in three +34; QKV unsplit (chosen), in two +52,
+// 256 x 128 +85. 7B, 45 rows: QKV in 2 to 5 parts of 128 x 64 within 6 us, unsplit +20; gate+up in four (chosen), in two +5,
+// unsplit +9, in eight +12.
 static PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
     const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
     PfPlan best{};
@@ -873,7 +877,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
 }
 
 // Prompts of at least this many rows take the prefill kernels in one go, shorter ones one pass of the verification kernels
-// (7B widths, 4 blocks: a 16-row pass 0.65 ms, 17 to 45 rows 0.82 ms here, two 16-row passes 1.2 ms)
+// (7B widths, 4 blocks: a 16-row pass 0.67 ms, 45 rows 0.76 ms here, two 16-row passes 1.2 ms)
 static const int PF_MIN_ROWS = 17;
 
 // The LM head over the prompt's last row (a one-row pass of the decode kernel) behind prefill_tuned. `row`: the logits row
