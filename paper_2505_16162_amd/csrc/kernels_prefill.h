@@ -37,7 +37,7 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
 
 struct PfArgs {
-    GemmOp op;              // type, W, N, K, split, x, gain_next, q_out, kv_block, cos_t, sin_t, H, Hkv, hd, max_seq
+    GemmOp op;              // type, W, N, K, q_out, kv_block, cos_t, sin_t, H, Hkv, hd, max_seq
     const bf16_t *frag_in;  // [planes][K/32][TT][512] fragment order
     const float *scale;     // [TT*16] factor of the input rows
     float *out;             // PF_PARTS: [K part][out_rows][n_mt * rows of a tile], tile order along the columns; PF_SWIGLU: [n_tok][N]

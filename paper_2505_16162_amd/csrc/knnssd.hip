@@ -219,7 +219,7 @@ struct knnssd_ctx {
     bool prefilled;
     bool tuned;         // shape fits the tuned bf16 draft kernels
     bool tuned_verify;  // ... and the matrix-core verification kernels (every K a multiple of 32)
-    bool tuned_prefill; // ... and the many-row prefill kernels (a row group fits 16 tile slots)
+    bool tuned_prefill; // ... and the many-row prefill kernels (prefill_tuned_ok)
     bool wide_weights = false;   // a prompt has met weights that the prefill's two fp16 planes do not hold
     bool verify_attn_mfma;  // verification passes run their split-KV attention on the matrix cores
     // tabulated workgroup splits of the five matrix shapes (tuned kernels)
