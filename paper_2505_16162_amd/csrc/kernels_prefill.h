@@ -3,24 +3,19 @@
 // Unlike a decode pass this is bound by the matrix cores, so it has kernels of its own. They read the
 // SAME stream-order weights as the decode kernels (a unit = <= 16 rows x 32 columns is one MFMA A operand).
 //
-// Arithmetic. Activations are fp32. A row of them (one token) is scaled by a power of two so that its largest value lies
-// just below 2^15 and split into two fp16 planes, hi = fp16(v), lo = fp16(v - hi): 22 bits and a sign, |v - hi - lo| <=
-// 2^-24 |v| down to 2^-16 of the row's largest value and 2^-40 of that largest value below. Weights are bf16; times 2^11
-// they are fp16 numbers without rounding while 2^-28 <= |w| < 32. So a product takes two matrix instructions, exact in the
-// fp32 accumulator. (Three bf16 planes hold all 24 bits and take three; measured against 64 bits the two are the same: what
-// is left is the accumulator's rounding.) The kernels look at every weight they convert: one that fp16 cannot hold
-// (|w| >= 32, infinities, NaN) or eight neighbours whose largest is below 2^-15 raise a flag, and the host runs the prompt
-// again with three bf16 planes, which hold any weight and any activation as they are.
+// Arithmetic, the same as in the decode kernels: activations are fp32 and stay exact, as three bf16 planes (hi + mid + lo by
+// truncation = the value, whatever it is), weights are bf16 as they are. So a product takes three matrix instructions per 32
+// columns, exact up to the sums in fp32.
 //
 // Activations of all rows live in "fragment order": [plane][32-column step][16-row tile][lane][8],
 // lane = 16*kg + r holding row r of the tile and columns 8*kg..8*kg+7 of the step, i.e. the MFMA B
-// operand of v_mfma_f32_16x16x32 as stored, so staging a tile is a linear copy. Beside them one factor per row: the power of
-// two the planes were scaled by (and the weights' 2^-11), times the RMSNorm's rsqrt where the rows were normalised.
+// operand of v_mfma_f32_16x16x32_bf16 as stored, so staging a tile is a linear copy. RMSNorm: the planes hold gain (.) x, the
+// row's rsqrt lies beside them and multiplies the product's sums.
 //
 // prefill_gemm_kernel: a workgroup owns TA tiles of 16 weight rows x TB tiles of 16 tokens and walks K (or one of S parts
-// of it) in steps of 32 columns. Activations, and weights where they are not converted on the way, go from memory straight
-// to LDS (16-byte loads whose LDS side is linear and whose memory side is free). A tile is filled with whatever rows suit
-// it, wherever they lie in the decode layout: no dead rows from the decode layout's short tiles (20 rows per workgroup = two
+// of it) in steps of 32 columns. Activations and weights go from memory straight to LDS (16-byte loads whose LDS side is
+// linear and whose memory side is free). A tile is filled with whatever rows suit it, wherever they lie in the decode
+// layout: no dead rows from the decode layout's short tiles (20 rows per workgroup = two
 // tiles of 10), and the two dot products an epilogue combines sit in one lane's accumulators.
 #pragma once
 #include "kernels_bf16.h"
@@ -29,20 +24,15 @@ namespace ks {
 
 constexpr int PF_NT = 512;             // threads per workgroup of the prefill GEMM (8 wavefronts)
 constexpr int PF_RT = 1024;            // ... and of the row kernels between the products
-constexpr int PF_WSHIFT = 11;          // fp16 weights hold w * 2^11
-constexpr unsigned int PF_W_TOO_LARGE = 0x4200, PF_W_SMALL = 0x3800;      // bf16 bits of 32 and of 2^-15
-
-typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+constexpr int PF_NP = 3;               // bf16 planes of an activation
 
 struct PfArgs {
     GemmOp op;              // type, W, N, K, q_out, kv_block, cos_t, sin_t, H, Hkv, hd, max_seq
     const bf16_t *frag_in;  // [planes][K/32][TT][512] fragment order
-    const float *scale;     // [TT*16] factor of the input rows
-    float *out;             // PF_PARTS: [K part][out_rows][n_mt * rows of a tile], tile order along the columns; PF_SWIGLU: [n_tok][N]
+    const float *rstd;      // [n_tok] RMSNorm factor of the input rows; nullptr: none
+    float *out;             // PF_PARTS: [K part][out_rows][n_mt * rows of a tile], tile order along the columns
+    bf16_t *frag_out;       // PF_SWIGLU: the next product's operands, fragment order over the N features
     const u32x2 *rows;      // (PfRow) [n_mt * rows of a tile] where each row of the tiles lies
-    int *flag;              // raised when a weight does not fit the two-plane arithmetic
     int TT;                 // token tiles the fragment buffers are laid out for
     int n_tok, out_rows;    // live rows; row stride of a K part in out
     int n_mt, n_mr;         // row tiles of the matrix; OP_QKV: those that hold rotary pairs (the others hold value rows)
@@ -55,34 +45,39 @@ __device__ __forceinline__ size_t frag_off(int KS, int TT, int pl, int ks, int t
     return (((size_t)pl * KS + ks) * TT + tt) * 512;
 }
 
-// The planes of the eight values at features n..n+7 (n a multiple of 8) of row (tt, m), fragment order: one 16-byte store
-// per plane. NP = 2: fp16 (v is scaled already); NP = 3: bf16 by truncation, hi + mid + lo = v.
-template <int NP>
-__device__ __forceinline__ void store_frag8(bf16_t *frag, int KS, int TT, int tt, int m, int n, const float *v) {
-    const size_t in_tile = (size_t)(((n & 31) >> 3) * 16 + m) * 8;
-    unsigned int w[NP][4];
+// The bf16 planes of N neighbouring values (truncation: hi + mid + lo = v), two values per word.
+template <int N>
+__device__ __forceinline__ void split_planes(const float *v, unsigned int (*w)[N / 2]) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
+    for (int e = 0; e < N / 2; ++e) {
+        // the upper halves of two neighbouring values make one register of a plane
         const float a = v[2 * e], b = v[2 * e + 1];
-        if constexpr (NP == 2) {
-            const f16x2 h = f16x2{(_Float16)a, (_Float16)b};
-            const f16x2 l = f16x2{(_Float16)(a - (float)h[0]), (_Float16)(b - (float)h[1])};
-            w[0][e] = __builtin_bit_cast(unsigned int, h);
-            w[1][e] = __builtin_bit_cast(unsigned int, l);
-        } else {
-            // the upper halves of two neighbouring values make one register of a plane
-            const unsigned int a0 = __float_as_uint(a), b0 = __float_as_uint(b);
-            const float ra = a - __uint_as_float(a0 & 0xffff0000u), rb = b - __uint_as_float(b0 & 0xffff0000u);
-            const unsigned int a1 = __float_as_uint(ra), b1 = __float_as_uint(rb);
-            const unsigned int a2 = __float_as_uint(ra - __uint_as_float(a1 & 0xffff0000u)), b2 = __float_as_uint(rb - __uint_as_float(b1 & 0xffff0000u));
-            w[0][e] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
-            w[1][e] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
-            w[2][e] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);
-        }
+        const unsigned int a0 = __float_as_uint(a), b0 = __float_as_uint(b);
+        const float ra = a - __uint_as_float(a0 & 0xffff0000u), rb = b - __uint_as_float(b0 & 0xffff0000u);
+        const unsigned int a1 = __float_as_uint(ra), b1 = __float_as_uint(rb);
+        const unsigned int a2 = __float_as_uint(ra - __uint_as_float(a1 & 0xffff0000u)), b2 = __float_as_uint(rb - __uint_as_float(b1 & 0xffff0000u));
+        w[0][e] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
+        w[1][e] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
+        w[2][e] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);
     }
+}
+// The planes of the eight values at features n..n+7 (n a multiple of 8) of row (tt, m), fragment order: one 16-byte store
+// per plane; of the four at n..n+3 (n a multiple of 4): 8 bytes per plane.
+__device__ __forceinline__ bf16_t *frag_at(bf16_t *frag, int KS, int TT, int pl, int tt, int m, int n) {
+    return frag + frag_off(KS, TT, pl, n >> 5, tt) + (((n & 31) >> 3) * 16 + m) * 8 + (n & 7);
+}
+__device__ __forceinline__ void store_frag8(bf16_t *frag, int KS, int TT, int tt, int m, int n, const float *v) {
+    unsigned int w[PF_NP][4];
+    split_planes<8>(v, w);
 #pragma unroll
-    for (int pl = 0; pl < NP; ++pl)
-        *reinterpret_cast<u32x4 *>(frag + frag_off(KS, TT, pl, n >> 5, tt) + in_tile) = u32x4{w[pl][0], w[pl][1], w[pl][2], w[pl][3]};
+    for (int pl = 0; pl < PF_NP; ++pl) *reinterpret_cast<u32x4 *>(frag_at(frag, KS, TT, pl, tt, m, n)) = u32x4{w[pl][0], w[pl][1], w[pl][2], w[pl][3]};
+}
+__device__ __forceinline__ void store_frag4(bf16_t *frag, int KS, int TT, int tt, int m, int n, f32x4 v4) {
+    const float v[4] = {v4[0], v4[1], v4[2], v4[3]};
+    unsigned int w[PF_NP][2];
+    split_planes<4>(v, w);
+#pragma unroll
+    for (int pl = 0; pl < PF_NP; ++pl) *reinterpret_cast<u32x2 *>(frag_at(frag, KS, TT, pl, tt, m, n)) = u32x2{w[pl][0], w[pl][1]};
 }
 
 // four values rounded to bf16 (nearest even), 8-byte store
@@ -112,26 +107,6 @@ __device__ __forceinline__ void pf_meet() {
     __builtin_amdgcn_s_barrier();
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
-}
-
-// Eight bf16 weights as fp16 times 2^11, and what the running check of them needs: the largest magnitude seen (bf16 bits,
-// both halves of the word) and the smallest nonzero maximum of eight, minus one.
-struct PfCheck { u16x2 top; unsigned int low; };
-__device__ __forceinline__ u32x4 weights_to_f16(u32x4 w, PfCheck &c) {
-    u32x4 r;
-    u16x2 m = u16x2{0, 0};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        constexpr float k = (float)(1 << PF_WSHIFT);
-        r[e] = __builtin_bit_cast(unsigned int, __builtin_amdgcn_cvt_pkrtz(bf_lo(w[e]) * k, bf_hi(w[e]) * k));
-        m = __builtin_elementwise_max(m, __builtin_bit_cast(u16x2, w[e] & 0x7fff7fffu));
-    }
-    c.top = __builtin_elementwise_max(c.top, m);
-    c.low = min(c.low, max((unsigned int)m[0], (unsigned int)m[1]) - 1u);        // eight zeros wrap round and do not count
-    return r;
-}
-__device__ __forceinline__ bool weights_fit(const PfCheck &c) {
-    return max((unsigned int)c.top[0], (unsigned int)c.top[1]) < PF_W_TOO_LARGE && c.low >= PF_W_SMALL - 1u;
 }
 
 // Where one row of a tile lies in the packed matrix. Tabulated when the context is created (prefill_row_table_kernel), one
@@ -210,22 +185,22 @@ __device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v,
     pf_store_bf16x4(op.kv_block + (((size_t)op.Hkv + head) * op.max_seq + tok) * op.hd + d, val);
 }
 
-// TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS, NP planes.
-// What bounds it. 256 x 256 (long prompts): the matrix cores. One meeting per step for all wavefronts together kept the
-// matrix pipe 55 % busy; two groups one phase apart 82 % at three bf16 planes, and 1.50-1.55 PFLOP/s issued, where a large
-// library product in bf16 reaches 1.59 on this card (the clock falls to 1.8 GHz). So the way on was fewer instructions, two
-// fp16 planes: 13B-shaped, 4096 rows, QKV 1.30 -> 0.94-1.05 ms, gate+up 2.23 -> 1.64-1.75 ms. 256 x 128 (65 to about 250
-// rows): operand reads and the conversion of the weights weigh more, 0.72 of that rate. 128 x 64 (up to 64 rows): the weight
-// stream; three workgroups per unit and K parts so that every unit streams; 8 us of a launch are its fixed cost.
+// TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS.
+// What bounds it. 256 x 256 and 256 x 128: the matrix cores, at 1.53-1.6 PFLOP/s issued (three instructions per product), where a
+// large library product in bf16 reaches 1.59 on this card; one meeting per step for all wavefronts together kept the matrix
+// pipe 55 % busy, two groups one phase apart 80 %. 13B-shaped, 4096 rows: QKV 1.52 ms (with its own sums, below), gate+up
+// 2.26, O 0.44, down 1.12. 128 x 64 (few rows): operand reads out of LDS about as much as the weight stream: a 4 x 2 grid
+// of wavefronts reads 8 KB a wavefront and step, 8 x 1 reads 13 (7B, 45 rows, gate+up unsplit 79 -> 75 us); 5-6 us of a
+// launch are its fixed cost. Which tile a matrix and a length take: pf_plan.
 // PP: the wavefronts form two groups (one wavefront of each on every SIMD) that run one phase apart: while one group
-// issues its matrix instructions the other reads its operands from LDS and converts the weights of a later step.
-template <int NP, int TA, int TB, int WA, int NS, bool PP>
+// issues its matrix instructions the other reads its operands from LDS.
+template <int TA, int TB, int WA, int NS, bool PP>
 struct PfShape {
     static constexpr int WB = 8 / WA, TAW = TA / WA, TBW = TB / WB;
     static constexpr int TM = TA * 16;
-    static constexpr int A_BYTES = TA * 1024, STAGE = A_BYTES + NP * TB * 1024;
+    static constexpr int A_BYTES = TA * 1024, STAGE = A_BYTES + PF_NP * TB * 1024;
     static constexpr int NA = TA * 64 / PF_NT;                   // weight pieces per thread and step
-    static constexpr int NB = (NP * TB + 7) / 8;                 // token fragments per wavefront and step
+    static constexpr int NB = (PF_NP * TB + 7) / 8;              // token fragments per wavefront and step
     static constexpr size_t LDS = (size_t)NS * STAGE;
 };
 
@@ -234,12 +209,10 @@ struct PfShape {
 // behind the loop, 4-5 us with everything in one build.)
 enum { PF_PARTS = 0, PF_SWIGLU, PF_ROPE };
 
-template <int NP, int TA, int TB, int WA, int NS, bool PP, int EPI>
-__global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(PfArgs a) {
-    typedef PfShape<NP, TA, TB, WA, NS, PP> Sh;
+template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN>
+__global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(PfArgs a) {
+    typedef PfShape<TA, TB, WA, NS, PP> Sh;
     constexpr int TAW = Sh::TAW, TBW = Sh::TBW, TM = Sh::TM;
-    constexpr bool CONV_STAGE = NP == 2 && PP, CONV_READ = NP == 2 && !PP;     // where weights become fp16: on the way to LDS, or
-                                                                               // (few tokens, nothing to save) when they are read
     extern __shared__ __align__(16) char lds[];
     const GemmOp &op = a.op;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -277,7 +250,7 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(P
     unsigned int bdst[Sh::NB];
 #pragma unroll
     for (int q = 0; q < Sh::NB; ++q) {
-        const int f = min(wave + q * 8, NP * TB - 1), pl = f / TB, t = f - pl * TB;    // a repeat writes the same bytes again
+        const int f = min(wave + q * 8, PF_NP * TB - 1), pl = f / TB, t = f - pl * TB;    // a repeat writes the same bytes again
         bsrc[q] = reinterpret_cast<const char *>(a.frag_in + frag_off(KS, a.TT, pl, st0, min(tt0 + t, a.TT - 1)));
         bdst[q] = Sh::A_BYTES + f * 1024;
     }
@@ -301,35 +274,14 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(P
             else dma_lane(weight_piece(t, q), d);
         }
     };
-    PfCheck chk{u16x2{0, 0}, 0xffffffffu};
-    u32x4 wreg[Sh::NA];
-    auto load_w = [&](int t) {                     // CONV_STAGE: weights of step st0 + t to registers
-#pragma unroll
-        for (int q = 0; q < Sh::NA; ++q) wreg[q] = *reinterpret_cast<const u32x4 *>(weight_piece(t, q));
-    };
-    auto store_w = [&](int buf) {                  // ... and as fp16 to LDS buffer buf
-#pragma unroll
-        for (int q = 0; q < Sh::NA; ++q)
-            *reinterpret_cast<u32x4 *>(lds + buf * Sh::STAGE + (wave + q * 8) * 1024 + voff) = weights_to_f16(wreg[q], chk);
-    };
-
     f32x4 acc[TAW][TBW];
 #pragma unroll
     for (int i = 0; i < TAW; ++i)
 #pragma unroll
         for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    // few tokens: registers to spare, so even and odd steps have accumulators of their own (half the roundings in a chain)
-    constexpr bool ODD = NP == 2 && !PP;
-    f32x4 odd[ODD ? TAW : 1][ODD ? TBW : 1];
-    if constexpr (ODD) {
-#pragma unroll
-        for (int i = 0; i < TAW; ++i)
-#pragma unroll
-            for (int j = 0; j < TBW; ++j) odd[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
     const char *la = lds + wa * TAW * 1024 + voff, *lb = lds + Sh::A_BYTES + wb * TBW * 1024 + voff;
-    constexpr int JC = NP == 2 ? TBW : (TBW < 2 ? TBW : 2), CL = TBW / JC;    // token tiles per cluster of matrix instructions, clusters per step
-    u32x4 av[TAW], bv[JC][NP];
+    constexpr int JC = TBW < 2 ? TBW : 2, CL = TBW / JC;       // token tiles per cluster of matrix instructions, clusters per step
+    u32x4 av[TAW], bv[JC][PF_NP];
     auto read_a = [&](int buf) {
 #pragma unroll
         for (int i = 0; i < TAW; ++i) av[i] = *reinterpret_cast<const u32x4 *>(la + buf * Sh::STAGE + i * 1024);
@@ -338,33 +290,59 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(P
 #pragma unroll
         for (int jj = 0; jj < JC; ++jj)
 #pragma unroll
-            for (int p = 0; p < NP; ++p) bv[jj][p] = *reinterpret_cast<const u32x4 *>(lb + buf * Sh::STAGE + (p * TB + c * JC + jj) * 1024);
+            for (int p = 0; p < PF_NP; ++p) bv[jj][p] = *reinterpret_cast<const u32x4 *>(lb + buf * Sh::STAGE + (p * TB + c * JC + jj) * 1024);
     };
-    auto mfma_cluster = [&](int c, auto odd_step) {
+    // OWN: a step's three planes are summed on their own, from the lowest up, and then added to the running sums: one rounding at
+    // the size of the whole sum per 32 columns instead of three. For the QKV rows, whose keys and values the cache rounds to
+    // bf16: entries that land on another value than in 64 bits 5.8e-4 -> 2.3e-4 (13B-shaped block, 1024 rows), for 335 -> 378
+    // us (a vector addition takes 0.6 of its time from the matrix pipe, among the matrix instructions or in the reading phase).
+    // In the other products, whose rows stay fp32, it changed neither that share nor the hidden state's error (gate+up 640 ->
+    // 726 us). The 128 x 64 build has it always: the matrix pipe waits there anyway. In groups of GR tiles: a group's additions stand among the next
+    // group's matrix instructions, the last group's in the next reading phase (settle).
+    constexpr int NT_CL = TAW * JC, GR = NT_CL < 4 ? NT_CL : 4, NG = NT_CL / GR;
+    f32x4 own[2][GR];
+    auto add = [&](int c, int g) {
 #pragma unroll
-        for (int p = 0; p < NP; ++p)
+        for (int k = 0; k < GR; ++k) {
+            f32x4 &d = acc[(g * GR + k) % TAW][c * JC + (g * GR + k) / TAW];
+            d += own[g & 1][k];
+            asm volatile("" : "+v"(d));        // here, not at the step's end, where every group's sums would have to be kept
+        }
+    };
+    auto settle = [&](int c) { add(c, NG - 1); };
+    auto mfma_cluster = [&](int c) {
 #pragma unroll
-            for (int jj = 0; jj < JC; ++jj)
+        for (int g = 0; g < NG; ++g) {
 #pragma unroll
-                for (int i = 0; i < TAW; ++i) {
-                    constexpr bool o = ODD && decltype(odd_step)::value;
-                    f32x4 &d = o ? odd[o ? i : 0][o ? c * JC + jj : 0] : acc[i][c * JC + jj];
-                    if constexpr (NP == 2)
-                        d = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, av[i]), __builtin_bit_cast(f16x8, bv[jj][p]), d, 0, 0, 0);
-                    else
-                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[i]), __builtin_bit_cast(bf16x8, bv[jj][p]), d, 0, 0, 0);
+            for (int p = PF_NP - 1; p >= 0; --p)
+#pragma unroll
+                for (int k = 0; k < GR; ++k) {
+                    const int i = (g * GR + k) % TAW, jj = (g * GR + k) / TAW;
+                    const bf16x8 w = __builtin_bit_cast(bf16x8, av[i]), x = __builtin_bit_cast(bf16x8, bv[jj][p]);
+                    if constexpr (OWN) {
+                        const f32x4 from = p == PF_NP - 1 ? f32x4{0.f, 0.f, 0.f, 0.f} : own[g & 1][k];
+                        own[g & 1][k] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, from, 0, 0, 0);
+                    } else {
+                        f32x4 &d = acc[i][c * JC + jj];
+                        d = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w, x, d, 0, 0, 0);
+                    }
                 }
+            if constexpr (OWN) {
+                if (g > 0) add(c, g - 1);
+                __builtin_amdgcn_sched_barrier(0);     // (at most two groups of sums: registers)
+            }
+        }
     };
+    if constexpr (OWN)
+#pragma unroll
+        for (int k = 0; k < GR; ++k) own[(NG - 1) & 1][k] = f32x4{0.f, 0.f, 0.f, 0.f};     // nothing to settle before the first step
 
     // the first NS - 1 steps (a step past the end repeats the last one, here and below: the loads stay countable)
 #pragma unroll
     for (int t = 0; t < NS - 1; ++t) {
-        if constexpr (CONV_STAGE) load_w(min(t, cnt - 1));
-        else issue_a(min(t, cnt - 1), t);
+        issue_a(min(t, cnt - 1), t);
         issue_b(min(t, cnt - 1), t);
-        if constexpr (CONV_STAGE) store_w(t);
     }
-    if constexpr (CONV_STAGE) load_w(min(NS - 1, cnt - 1));
     dma_wait<0>();
     pf_meet();
     if constexpr (PP) {
@@ -378,26 +356,22 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(P
             const int nb = NS == 2 ? buf ^ 1 : (buf == 0 ? 2 : buf - 1), tn = min(t + NS - 1, cnt - 1);
             read_a(buf);
             read_b(buf, 0);
-            if constexpr (CONV_STAGE) {
-                store_w(nb);                       // step t+2, loaded one step ago
-                issue_b(tn, nb);
-                load_w(min(t + NS, cnt - 1));
-            } else {
-                issue_a(tn, nb);
-                issue_b(tn, nb);
-            }
+            issue_a(tn, nb);
+            issue_b(tn, nb);
+            if constexpr (OWN) settle(CL - 1);     // of the step before
             if constexpr (CL == 1) dma_wait<YOUNG>();       // step t+1 has arrived (what was issued just now stays in flight)
             pf_meet();
             __builtin_amdgcn_s_setprio(1);
-            mfma_cluster(0, std::false_type{});
+            mfma_cluster(0);
             __builtin_amdgcn_s_setprio(0);
             pf_meet();
             if constexpr (CL == 2) {
                 read_b(buf, 1);
+                if constexpr (OWN) settle(0);
                 if (wa == 1) dma_wait<0>();        // the first group reads step t+1 one phase from here
                 pf_meet();
                 __builtin_amdgcn_s_setprio(1);
-                mfma_cluster(1, std::false_type{});
+                mfma_cluster(1);
                 __builtin_amdgcn_s_setprio(0);
                 if (wa == 0) dma_wait<0>();
                 pf_meet();
@@ -407,43 +381,30 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(P
         if (wa == 0) pf_meet();
     } else {
         int buf = 0;
-        auto step = [&](int t, auto odd_step) {
+        for (int t = 0; t < cnt; ++t) {
             if (t > 0) { dma_wait<(NS - 2) * (Sh::NA + Sh::NB)>(); pf_meet(); }      // step t has arrived; every wavefront is done with step t-1
             const int nb = buf == 0 ? NS - 1 : buf - 1;
             issue_a(min(t + NS - 1, cnt - 1), nb);
             issue_b(min(t + NS - 1, cnt - 1), nb);
             read_a(buf);
-            if constexpr (CONV_READ) {
-#pragma unroll
-                for (int i = 0; i < TAW; ++i) av[i] = weights_to_f16(av[i], chk);
-            }
 #pragma unroll
             for (int c = 0; c < CL; ++c) {
                 read_b(buf, c);
-                mfma_cluster(c, odd_step);
+                if constexpr (OWN) settle(c == 0 ? CL - 1 : c - 1);
+                mfma_cluster(c);
             }
             buf = buf == NS - 1 ? 0 : buf + 1;
-        };
-        for (int t = 0; t < cnt; t += 2) {
-            step(t, std::false_type{});
-            if (t + 1 < cnt) step(t + 1, std::true_type{});
         }
     }
+    if constexpr (OWN) settle(CL - 1);
     dma_wait<0>();                                 // nothing is in flight towards LDS when the workgroup ends
-    if (NP == 2 && !weights_fit(chk)) *a.flag = 1;
-    if constexpr (ODD) {
-#pragma unroll
-        for (int i = 0; i < TAW; ++i)
-#pragma unroll
-            for (int j = 0; j < TBW; ++j) acc[i][j] += odd[i][j];
-    }
 
     // lane (kg, r16) holds rows 4*kg..4*kg+3 of its TAW row tiles for token r16 of its TBW token tiles
 #pragma unroll
     for (int j = 0; j < TBW; ++j) {
         const int tok = (tt0 + wb * TBW + j) * 16 + r16;
         if (tok >= a.n_tok) continue;
-        const float scale = a.scale[tok];
+        const float scale = a.rstd ? a.rstd[tok] : 1.0f;
         if constexpr (EPI == PF_PARTS) {
             float *o = a.out + ((size_t)sp * a.out_rows + tok) * ((size_t)a.n_mt * TM) + mt * TM + wa * TAW * 16 + 4 * kg;
 #pragma unroll
@@ -453,7 +414,7 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(P
             for (int i = 0; i < TAW; i += 2) {
                 const int p = mt * (TM / 2) + (wa * TAW + i) * 8 + 4 * kg;
                 if constexpr (EPI == PF_SWIGLU) {
-                    if (p < op.N) *reinterpret_cast<f32x4 *>(a.out + (size_t)tok * op.N + p) = pf_swiglu(acc[i][j] * scale, acc[i + 1][j] * scale);
+                    if (p < op.N) store_frag4(a.frag_out, op.N >> 5, a.TT, tt0 + wb * TBW + j, r16, p, pf_swiglu(acc[i][j] * scale, acc[i + 1][j] * scale));
                 } else if (p < (op.H + op.Hkv) * (op.hd >> 1)) {
                     pf_rope_store(op, tok, p, acc[i][j] * scale, acc[i + 1][j] * scale);
                 }
@@ -469,23 +430,22 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 6) void prefill_gemm_kernel(P
 }
 
 // ------------------------------------------------------------------------------------------
-// Row kernels: one workgroup per token, between the products. They add up the K parts, finish the row and write the next
-// product's operands. Bound by memory (the row is read once and kept in LDS). A row's share of a fragment is 16 bytes of
-// each 256: the workgroups of the 16 rows that share the fragments are neighbours on one die, so that its L2 puts whole
-// lines together.
+// Row kernels, between the products: they add up the K parts, finish a row and write the next product's operands, four
+// neighbouring features per thread (loads of neighbouring lanes adjoin; eight per thread: 32 us instead of 27 for 1024 x 5120
+// in three parts). Bound by memory. A row's share of a fragment is 16 bytes of each
+// 256: the workgroups of the 16 rows that share the fragments are neighbours on one die, so that its L2 puts whole lines together.
 // ------------------------------------------------------------------------------------------
 struct PfRowArgs {
     GemmOp op;                  // as in PfArgs
     const int32_t *toks;        // embedding: token ids
-    const float *in;            // [S][out_rows][ld] K parts, or [n_tok][d] finished rows
+    const float *in;            // [S][out_rows][ld] K parts
     int n_tok, S, out_rows, ld, TM;     // TM: rows per tile of the product's column order
     int d;                      // features of the row
     float inv_dim, eps;
     float *x;                   // [n_tok][d] residual stream
     const float *gain;
     bf16_t *frag;
-    float *scale;
-    int *flag;                  // embedding: cleared for the prompt
+    float *rstd;
     int TT;
 };
 
@@ -493,34 +453,6 @@ struct PfRowArgs {
 __device__ __forceinline__ int pf_row_token() {
     const int die = blockIdx.x & 7, i = blockIdx.x >> 3;
     return ((i >> 4) * 8 + die) * 16 + (i & 15);
-}
-
-// sum and maximum over the workgroup's PF_RT threads
-__device__ __forceinline__ void pf_row_reduce(float &s, float &mx) {
-    __shared__ float rs[PF_RT / 64], rm[PF_RT / 64];
-    s = wave_sum(s);
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
-    if ((threadIdx.x & 63) == 0) { rs[threadIdx.x >> 6] = s; rm[threadIdx.x >> 6] = mx; }
-    __syncthreads();
-    s = 0.f; mx = 0.f;
-#pragma unroll
-    for (int w = 0; w < PF_RT / 64; ++w) { s += rs[w]; mx = fmaxf(mx, rm[w]); }
-}
-
-// the row in LDS (largest magnitude mx) -> planes and factor; norm: what the row's products are multiplied by besides
-template <int NP>
-__device__ __forceinline__ void pf_row_split(const PfRowArgs &a, int tok, const float *row, float mx, float norm) {
-    int e = 0;
-    if (NP == 2 && mx > 0.f) e = min(max((int)(__float_as_uint(mx) >> 23) - 127 - 14, -110), 110);     // mx * 2^-e in [2^14, 2^15)
-    const float k = ldexpf(1.0f, -e);
-    if (threadIdx.x == 0) a.scale[tok] = NP == 2 ? ldexpf(norm, e - PF_WSHIFT) : norm;
-    for (int n = threadIdx.x * 8; n < a.d; n += PF_RT * 8) {
-        float v[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) v[q] = row[n + q] * k;
-        store_frag8<NP>(a.frag, a.d >> 5, a.TT, tok >> 4, tok & 15, n, v);
-    }
 }
 
 // columns c..c+3 of the K parts, added up in order
@@ -549,17 +481,16 @@ __device__ __forceinline__ int pf_pair_col(int p, int TM) {
     return mt * TM + (r >> 4) * 32 + (r & 15);
 }
 
-// x = E[tok] or x += the product's row; the next norm's operands gain (.) x and their factor
-template <int NP, bool EMBED>
+// x = E[tok] or x += the product's row; the next norm's operands gain (.) x and the row's factor. One workgroup per token.
+template <bool EMBED>
 __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
-    extern __shared__ __align__(16) float row[];
+    __shared__ float shares[PF_RT / 64];
     const int tok = pf_row_token();
     if (tok >= a.n_tok) return;
-    if (EMBED && tok == 0 && threadIdx.x == 0) *a.flag = 0;
-    float sq = 0.f, mx = 0.f;
+    float sq = 0.f;
     for (int n = threadIdx.x * 4; n < a.d; n += PF_RT * 4) {
-        f32x4 v;
         f32x4 *xp = reinterpret_cast<f32x4 *>(a.x + (size_t)tok * a.d + n);
+        f32x4 v, g;
         if constexpr (EMBED) {
             const u32x2 w = *reinterpret_cast<const u32x2 *>(a.op.embed + (size_t)a.toks[tok] * a.d + n);
             v = f32x4{bf_lo(w.x), bf_hi(w.x), bf_lo(w.y), bf_hi(w.y)};
@@ -568,36 +499,32 @@ __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
             v = x0 + pf_sum_parts(a, tok, n);
         }
         *xp = v;
-        const f32x4 g = f32x4{a.gain[n], a.gain[n + 1], a.gain[n + 2], a.gain[n + 3]} * v;      // (gains may lie at any multiple of 4 bytes)
-        *reinterpret_cast<f32x4 *>(row + n) = g;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) { sq = fmaf(v[q], v[q], sq); mx = fmaxf(mx, fabsf(g[q])); }
+        for (int q = 0; q < 4; ++q) {
+            g[q] = a.gain[n + q] * v[q];          // (gains may lie at any multiple of 4 bytes)
+            sq = fmaf(v[q], v[q], sq);
+        }
+        store_frag4(a.frag, a.d >> 5, a.TT, tok >> 4, tok & 15, n, g);
     }
-    pf_row_reduce(sq, mx);
-    pf_row_split<NP>(a, tok, row, mx, 1.0f / sqrtf(sq * a.inv_dim + a.eps));
+    sq = wave_sum(sq);
+    if ((threadIdx.x & 63) == 0) shares[threadIdx.x >> 6] = sq;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float s = 0.f;
+#pragma unroll
+        for (int w = 0; w < PF_RT / 64; ++w) s += shares[w];
+        a.rstd[tok] = 1.0f / sqrtf(s * a.inv_dim + a.eps);
+    }
 }
 
-// PARTS: SwiGLU of the gate+up product's K parts; otherwise a finished row (attention output, SwiGLU of an unsplit product)
-template <int NP, bool PARTS>
+// SwiGLU of a gate+up product's K parts; gridDim.y workgroups per row
 __global__ __launch_bounds__(PF_RT) void prefill_u_row_kernel(PfRowArgs a) {
-    extern __shared__ __align__(16) float row[];
     const int tok = pf_row_token();
     if (tok >= a.n_tok) return;
-    float none = 0.f, mx = 0.f;
-    for (int n = threadIdx.x * 4; n < a.d; n += PF_RT * 4) {
-        f32x4 v;
-        if constexpr (PARTS) {
-            const int c = pf_pair_col(n, a.TM);
-            v = pf_swiglu(pf_sum_parts(a, tok, c), pf_sum_parts(a, tok, c + 16));
-        } else {
-            v = *reinterpret_cast<const f32x4 *>(a.in + (size_t)tok * a.d + n);
-        }
-        *reinterpret_cast<f32x4 *>(row + n) = v;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) mx = fmaxf(mx, fabsf(v[q]));
+    for (int n = (blockIdx.y * PF_RT + threadIdx.x) * 4; n < a.d; n += gridDim.y * PF_RT * 4) {
+        const int c = pf_pair_col(n, a.TM);
+        store_frag4(a.frag, a.d >> 5, a.TT, tok >> 4, tok & 15, n, pf_swiglu(pf_sum_parts(a, tok, c), pf_sum_parts(a, tok, c + 16)));
     }
-    pf_row_reduce(none, mx);
-    pf_row_split<NP>(a, tok, row, mx, 1.0f);
 }
 
 // rotary embedding, queries and cache entries from the K parts of a split QKV product (n_mr: its row tiles of rotary pairs)
@@ -652,25 +579,16 @@ __global__ __launch_bounds__(NT) void prefill_last_row_kernel(PassCtl *ctl, int 
 struct PfAttn {
     const float *q;          // [n_tok][H*hd] rotated queries
     const bf16_t *kv_block;  // [2][Hkv][max_seq][hd]
-    float *out;              // [n_tok][H*hd] attention output
-    int H, Hkv, max_seq, n_tok;
+    bf16_t *frag_out;        // attention output over H*hd features, fragment order
+    int H, Hkv, max_seq, n_tok, TT;
 };
 
-// eight fp32 values -> the three bf16 planes of an MFMA operand fragment (exact: hi + mid + lo = value)
+// eight fp32 values -> the three bf16 planes of an MFMA operand fragment
 __device__ __forceinline__ void split_planes8(const float *v, bf16x8 *out3) {
-    u32x4 w[3];
+    unsigned int w[PF_NP][4];
+    split_planes<8>(v, w);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        const unsigned int a0 = __float_as_uint(v[2 * e]), b0 = __float_as_uint(v[2 * e + 1]);
-        const float ra = v[2 * e] - __uint_as_float(a0 & 0xffff0000u), rb = v[2 * e + 1] - __uint_as_float(b0 & 0xffff0000u);
-        const unsigned int a1 = __float_as_uint(ra), b1 = __float_as_uint(rb);
-        const unsigned int a2 = __float_as_uint(ra - __uint_as_float(a1 & 0xffff0000u)), b2 = __float_as_uint(rb - __uint_as_float(b1 & 0xffff0000u));
-        w[0][e] = __builtin_amdgcn_perm(b0, a0, 0x07060302u);
-        w[1][e] = __builtin_amdgcn_perm(b1, a1, 0x07060302u);
-        w[2][e] = __builtin_amdgcn_perm(b2, a2, 0x07060302u);
-    }
-#pragma unroll
-    for (int p = 0; p < 3; ++p) out3[p] = __builtin_bit_cast(bf16x8, w[p]);
+    for (int p = 0; p < PF_NP; ++p) out3[p] = __builtin_bit_cast(bf16x8, u32x4{w[p][0], w[p][1], w[p][2], w[p][3]});
 }
 
 template <int HD> constexpr size_t pf_attn_lds_bytes() { return (size_t)2 * 2 * 64 * HD * 2; }
@@ -819,13 +737,14 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
     lsum += __shfl_xor(lsum, 32, 64);
     if (live && qpos <= last_pos) {
         const float inv = 1.0f / lsum;
-        // accumulator row 4*kg + q of instruction t is dimension DT * (4*kg + q) + t
-        float *op = a.out + (size_t)qpos * qd + h * HD + DT * 4 * kg;
+        // accumulator row 4*kg + q of instruction t is dimension DT * (4*kg + q) + t: eight neighbours at a time
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < 4; q += 8 / DT) {
+            float v[8];
 #pragma unroll
-            for (int t = 0; t < DT; t += 4)
-                *reinterpret_cast<f32x4 *>(op + q * DT + t) = f32x4{o[t][q], o[t + 1][q], o[t + 2][q], o[t + 3][q]} * inv;
+            for (int e = 0; e < 8; ++e) v[e] = o[e % DT][q + e / DT] * inv;
+            store_frag8(a.frag_out, qd >> 5, a.TT, rt, r16, h * HD + DT * (4 * kg + q), v);
+        }
     }
 }
 

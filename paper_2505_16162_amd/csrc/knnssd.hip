@@ -48,7 +48,7 @@ struct WsLayout {
     // tuned bf16 path
     size_t act_d, qrot, ss, head_part, attn_part, attn_arrivals, split_tab;
     // tuned prompt prefill (stream-order weights only): all prompt rows at once
-    size_t pf_tokens, pf_x, pf_q, pf_att, pf_u, pf_frag_d, pf_frag_att, pf_frag_u, pf_scale_d, pf_scale_att, pf_scale_u, pf_part, pf_rows[PF_OPS][2];
+    size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_rstd, pf_part, pf_rows[PF_OPS][2];
     int pf_tt;          // token tiles the fragment buffers are laid out for
     size_t total;
 };
@@ -99,10 +99,10 @@ static int pf_row_tiles(const knnssd_model_cfg &g, int which, int tm, int *n_mr 
 
 // The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x ns of a step + what a workgroup
 // pays once), plus the K parts' way through memory. The constants come from kernel traces; with one matrix's plan varied at
-// a time the choice was within 10 us per block of the best one at 45 to 4096 rows. 13B, 1024 rows, against the choice: O in
-// three parts of 256 x 256 (chosen), in five +4 us, in two +16, 256 x 128 in three +34; QKV unsplit (chosen), in two +52,
-// 256 x 128 +85. 7B, 45 rows: QKV in 2 to 5 parts of 128 x 64 within 6 us, unsplit +20; gate+up in four (chosen), in two +5,
-// unsplit +9, in eight +12.
+// a time the choice was within 16 us per block of the best one at 45 to 1500 rows. 13B, 1024 rows, against the choice: QKV
+// unsplit 256 x 256 (chosen), 256 x 128 +31 us, in two parts +60; O in three parts of 256 x 256 (chosen), of 256 x 128 -7, in two
+// +17; gate+up unsplit (chosen), 256 x 128 +86. 7B, 45 rows: QKV in five parts of 128 x 64 (chosen), in two +5, unsplit
+// +34; gate+up in four (chosen), unsplit +5, in eight +14.
 static PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
     const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
     PfPlan best{};
@@ -113,16 +113,16 @@ static PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
         const int tm = p.tm();
         p.n_mt = pf_row_tiles(g, which, tm, &p.n_mr);
         p.n_tt = (tt + tb - 1) / tb;
-        // 256 x 256 and 256 x 128: one workgroup per unit, bound by the matrix cores. 128 x 64: bound by the weight stream, so
-        // the three workgroups a unit holds take turns, but pay their fixed cost together
-        const double step = tb == 16 ? 1460 : (tb == 8 ? 1050 : 370), fixed = tb == 16 ? 14000 : (tb == 8 ? 10000 : 8000);
+        // 256 x 256 and 256 x 128: one workgroup per unit, bound by the matrix cores. 128 x 64: the two workgroups a unit holds
+        // take turns at its LDS, but pay their fixed cost together
+        const double step = tb == 16 ? (which == PF_QKV ? 2340 : 1930) : (tb == 8 ? (which == PF_QKV ? 1290 : 1040) : 540), fixed = tb == 16 ? 14000 : (tb == 8 ? 10000 : 6000);
         for (int S = 1; S <= 16; ++S) {
             if (S > 1 && S * 4 > KS) break;
             p.S = S;
             const int rounds = (p.tiles() * S + KS_NWG - 1) / KS_NWG;
             if (S > 1 && rounds > 8) break;
-            const double moved = p.parts(which) ? 2.0 * p.part_bytes() : 0;
-            const double cost = rounds * ((KS + S - 1) / S * step) + (tb == 4 ? (rounds + 2) / 3 : rounds) * fixed + moved / 3000;
+            const double moved = p.parts(which) ? 2.0 * S * tt * 16 * p.n_mt * tm * 4 : 0;
+            const double cost = rounds * ((KS + S - 1) / S * step) + (tb == 4 ? (rounds + 1) / 2 : rounds) * fixed + moved / 3000;
             if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
         }
     }
@@ -138,7 +138,7 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
     L.draft_ctl = take(sizeof(PassCtl));
     L.ver_ctl = take(sizeof(PassCtl));
     L.gen = take(sizeof(GenState));
-    L.head = take(sizeof(HeadResult) + 4);      // and the prefill's flag behind it: both come back in one copy
+    L.head = take(sizeof(HeadResult));
     L.knn = take(sizeof(KnnResult));
     L.out3 = take(4 * sizeof(int32_t));
     L.x = take(R * c->d_model * 4);
@@ -175,11 +175,7 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
             L.pf_frag_d = take(3 * rows * (size_t)c->d_model * 2);
             L.pf_frag_att = take(3 * rows * qd * 2);
             L.pf_frag_u = take(3 * rows * (size_t)c->d_ffn * 2);
-            L.pf_att = take(rows * qd * 4);
-            L.pf_u = take(rows * (size_t)c->d_ffn * 4);
-            L.pf_scale_d = take(rows * 4);
-            L.pf_scale_att = take(rows * 4);
-            L.pf_scale_u = take(rows * 4);
+            L.pf_rstd = take(rows * 4);
             size_t part = 0;
             for (int w = 0; w < PF_OPS; ++w)
                 for (int t = 1; t <= (int)tt; ++t) {
@@ -196,7 +192,6 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
 }
 
 static bool tuned_ok(const knnssd_model_cfg &g);
-static bool prefill_tuned_ok(const knnssd_model_cfg &g);
 
 struct knnssd_ctx {
     knnssd_model_cfg cfg;
@@ -219,8 +214,7 @@ struct knnssd_ctx {
     bool prefilled;
     bool tuned;         // shape fits the tuned bf16 draft kernels
     bool tuned_verify;  // ... and the matrix-core verification kernels (every K a multiple of 32)
-    bool tuned_prefill; // ... and the many-row prefill kernels (prefill_tuned_ok)
-    bool wide_weights = false;   // a prompt has met weights that the prefill's two fp16 planes do not hold
+    bool tuned_prefill; // ... and prompts go through the many-row prefill kernels
     bool verify_attn_mfma;  // verification passes run their split-KV attention on the matrix cores
     // tabulated workgroup splits of the five matrix shapes (tuned kernels)
     const WgSplit *split_qkv = nullptr, *split_o = nullptr, *split_gu = nullptr, *split_down = nullptr, *split_head = nullptr;
@@ -239,31 +233,25 @@ struct knnssd_ctx {
     template <typename T> T *wsp(size_t off) { return reinterpret_cast<T *>(ws + off); }
 };
 
-// The prefill GEMM's builds: f(planes, token tiles, epilogue, kernel, dynamic LDS) for each
-template <int NP, int TA, int TB, int WA, int NS, bool PP, int EPI, typename F> static void pf_build(F f) {
-    f(NP, TB, EPI, prefill_gemm_kernel<NP, TA, TB, WA, NS, PP, EPI>, PfShape<NP, TA, TB, WA, NS, PP>::LDS);
+// The prefill GEMM's builds: f(token tiles, epilogue, own sums, kernel, dynamic LDS) for each
+template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN, typename F> static void pf_build(F f) {
+    f(TB, EPI, OWN, prefill_gemm_kernel<TA, TB, WA, NS, PP, EPI, OWN>, PfShape<TA, TB, WA, NS, PP>::LDS);
 }
 template <typename F> static void pf_each_build(F f) {
-    pf_build<2, 16, 16, 2, 3, true, PF_PARTS>(f);
-    pf_build<2, 16, 16, 2, 3, true, PF_SWIGLU>(f);
-    pf_build<2, 16, 16, 2, 3, true, PF_ROPE>(f);
-    pf_build<2, 16, 8, 2, 3, true, PF_PARTS>(f);
-    pf_build<2, 8, 4, 8, 3, false, PF_PARTS>(f);
-    pf_build<3, 16, 16, 2, 2, true, PF_PARTS>(f);
-    pf_build<3, 16, 16, 2, 2, true, PF_SWIGLU>(f);
-    pf_build<3, 16, 16, 2, 2, true, PF_ROPE>(f);
-    pf_build<3, 16, 8, 2, 3, true, PF_PARTS>(f);
-    pf_build<3, 8, 4, 8, 3, false, PF_PARTS>(f);
+    pf_build<16, 16, 2, 2, true, PF_PARTS, false>(f);
+    pf_build<16, 16, 2, 2, true, PF_PARTS, true>(f);
+    pf_build<16, 16, 2, 2, true, PF_SWIGLU, false>(f);
+    pf_build<16, 16, 2, 2, true, PF_ROPE, true>(f);
+    pf_build<16, 8, 2, 3, true, PF_PARTS, false>(f);
+    pf_build<16, 8, 2, 3, true, PF_PARTS, true>(f);
+    pf_build<8, 4, 4, 3, false, PF_PARTS, true>(f);
 }
 static hipError_t pf_set_lds_limits() {
     hipError_t e = hipSuccess;
     auto set = [&](const void *k, size_t bytes) {
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     };
-    pf_each_build([&](int, int, int, void (*k)(PfArgs), size_t lds) { set((const void *)k, lds); });
-    void (*rows[])(PfRowArgs) = {prefill_x_row_kernel<2, false>, prefill_x_row_kernel<2, true>, prefill_x_row_kernel<3, false>, prefill_x_row_kernel<3, true>,
-                                 prefill_u_row_kernel<2, false>, prefill_u_row_kernel<2, true>, prefill_u_row_kernel<3, false>, prefill_u_row_kernel<3, true>};
-    for (auto k : rows) set((const void *)k, KS_MAX_DYN_LDS - 4096);
+    pf_each_build([&](int, int, bool, void (*k)(PfArgs), size_t lds) { set((const void *)k, lds); });
     set((const void *)prefill_attn_kernel<128>, pf_attn_lds_bytes<128>());
     set((const void *)prefill_attn_kernel<64>, pf_attn_lds_bytes<64>());
     return e;
@@ -335,7 +323,7 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
     c->prefilled = false; c->cache_len = 0; c->draft_len = 0;
     c->tuned = cfg->weights_packed != 0;     // stream-order weights <=> tuned kernels (checked above)
     c->tuned_verify = c->tuned;
-    c->tuned_prefill = c->tuned && prefill_tuned_ok(*cfg) && cfg->prefill_mode == KNNSSD_PREFILL_AUTO;
+    c->tuned_prefill = c->tuned && cfg->prefill_mode == KNNSSD_PREFILL_AUTO;
     // Attention of the verification passes: the vector-ALU kernel walks a work item's (row, head) pairs one by one,
     // the matrix-core kernel takes 16 at a time. The latter is faster from two pairs on and 10 % slower at one; the
     // choice is per context (never per pass), so a row's result does not depend on how many rows share its pass.
@@ -776,43 +764,34 @@ static int32_t read_back(knnssd_ctx *c, const void *dev, size_t bytes) {
     return KNNSSD_OK;
 }
 
-// The prefill kernels work on four neighbouring features at a time and keep a row in LDS.
-static bool prefill_tuned_ok(const knnssd_model_cfg &g) {
-    const size_t lds = KS_MAX_DYN_LDS - 4096;
-    return g.d_model % 32 == 0 && g.d_ffn % 32 == 0 && (size_t)g.d_model * 4 <= lds && (size_t)g.d_ffn * 4 <= lds &&
-           (size_t)g.n_heads * g.head_dim * 4 <= lds;
-}
-
 // The full model over the n_tok prompt rows with the matrix-core prefill kernels: fills the KV cache at positions
-// 0..n_tok-1 and leaves the last row's residual stream in pf_x. NP: planes of the activations (see kernels_prefill.h).
-template <int NP>
+// 0..n_tok-1 and leaves the last row's residual stream in pf_x.
 static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_tok) {
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn;
     const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd, TT = c->L.pf_tt, TTL = (n_tok + 15) / 16;
     const dim3 rows((TTL + 7) / 8 * 128);        // row kernels: see pf_row_token
     hipStream_t s = c->stream;
-    float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *att = c->wsp<float>(c->L.pf_att), *u = c->wsp<float>(c->L.pf_u);
+    float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *rstd = c->wsp<float>(c->L.pf_rstd);
     float *part = c->wsp<float>(c->L.pf_part);
     bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att), *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
-    float *scale_d = c->wsp<float>(c->L.pf_scale_d), *scale_att = c->wsp<float>(c->L.pf_scale_att), *scale_u = c->wsp<float>(c->L.pf_scale_u);
-    int *flag = reinterpret_cast<int *>(c->ws + c->L.head + sizeof(HeadResult));
     PfPlan plan[PF_OPS];
     for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_plan(g, w, TTL);
 
     GemmOp base{};
     base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq;
     base.cos_t = c->wsp<float>(c->L.rope_cos); base.sin_t = c->wsp<float>(c->L.rope_sin);
-    auto gemm = [&](int which, const GemmOp &op, const bf16_t *fin, const float *scale, float *out) {
+    auto gemm = [&](int which, const GemmOp &op, const bf16_t *fin, const float *rs, bf16_t *fout) {
         const PfPlan &p = plan[which];
         PfArgs a{};
         const int epi = p.parts(which) ? PF_PARTS : (which == PF_GU ? PF_SWIGLU : PF_ROPE);
-        a.op = op; a.frag_in = fin; a.scale = scale; a.out = epi == PF_PARTS ? part : out; a.flag = flag; a.TT = TT; a.n_tok = n_tok;
+        a.op = op; a.frag_in = fin; a.rstd = rs; a.out = part; a.frag_out = fout; a.TT = TT; a.n_tok = n_tok;
         a.rows = c->wsp<PfRow>(c->L.pf_rows[which][p.tm() == 256]); a.out_rows = p.out_rows();
         a.n_mt = p.n_mt; a.n_mr = p.n_mr; a.n_tt = p.n_tt; a.S = p.S; a.inv_tiles = 1.0f / (float)p.tiles();
         a.steps = op.K / 32 / p.S; a.longer = op.K / 32 % p.S;
-        pf_each_build([&](int np, int tb, int e, void (*k)(PfArgs), size_t lds) {
-            if (np == NP && tb == p.tb && e == epi) hipLaunchKernelGGL(k, dim3((p.tiles() * p.S + 7) / 8 * 8), dim3(PF_NT), lds, s, a);
+        const bool own = which == PF_QKV || p.tb == 4;       // sums of their own per step: see the kernel
+        pf_each_build([&](int tb, int e, bool ow, void (*k)(PfArgs), size_t lds) {
+            if (tb == p.tb && e == epi && ow == own) hipLaunchKernelGGL(k, dim3((p.tiles() * p.S + 7) / 8 * 8), dim3(PF_NT), lds, s, a);
         });
     };
     auto row_args = [&](int which, int width) {     // the row kernel behind a product (width: features it finishes)
@@ -824,52 +803,46 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     };
     auto x_row = [&](int which, int after) {
         PfRowArgs r = row_args(which, d);
-        r.x = x; r.gain = next_gain(c, nullptr, after); r.frag = frag_d; r.scale = scale_d;
-        hipLaunchKernelGGL((prefill_x_row_kernel<NP, false>), rows, dim3(PF_RT), (size_t)d * 4, s, r);
+        r.x = x; r.gain = next_gain(c, nullptr, after); r.frag = frag_d; r.rstd = rstd;
+        hipLaunchKernelGGL((prefill_x_row_kernel<false>), rows, dim3(PF_RT), 0, s, r);
     };
     {
         int32_t *toks = c->wsp<int32_t>(c->L.pf_tokens);
         HIP_TRY(hipMemcpyAsync(toks, tokens_host, (size_t)n_tok * 4, hipMemcpyHostToDevice, s));
         PfRowArgs r = row_args(PF_O, d);
-        r.op.embed = (const bf16_t *)c->embed; r.toks = toks; r.flag = flag;
-        r.x = x; r.gain = next_gain(c, nullptr, -1); r.frag = frag_d; r.scale = scale_d;
-        hipLaunchKernelGGL((prefill_x_row_kernel<NP, true>), rows, dim3(PF_RT), (size_t)d * 4, s, r);
+        r.op.embed = (const bf16_t *)c->embed; r.toks = toks;
+        r.x = x; r.gain = next_gain(c, nullptr, -1); r.frag = frag_d; r.rstd = rstd;
+        hipLaunchKernelGGL((prefill_x_row_kernel<true>), rows, dim3(PF_RT), 0, s, r);
     }
     for (int b = 0; b < g.n_blocks; ++b) {
         bf16_t *kvb = (bf16_t *)(c->kv + (size_t)b * c->kv_block_bytes);
         GemmOp o = base;
         o.type = OP_QKV; o.W = (const bf16_t *)c->wqkv[b]; o.N = qkvd; o.K = d; o.q_out = q; o.kv_block = kvb; o.split = c->split_qkv;
-        gemm(PF_QKV, o, frag_d, scale_d, nullptr);
+        gemm(PF_QKV, o, frag_d, rstd, nullptr);
         if (plan[PF_QKV].parts(PF_QKV)) {
             PfRowArgs r = row_args(PF_QKV, 0);
             r.op = o;
             hipLaunchKernelGGL(prefill_qkv_row_kernel, dim3(rows.x, ((H + Hkv) * hd / 2 + Hkv * hd + 4 * PF_RT - 1) / (4 * PF_RT)), dim3(PF_RT), 0, s, r, plan[PF_QKV].n_mr);
         }
         PfAttn at{};
-        at.q = q; at.kv_block = kvb; at.out = att; at.H = H; at.Hkv = Hkv; at.max_seq = g.max_seq; at.n_tok = n_tok;
+        at.q = q; at.kv_block = kvb; at.frag_out = frag_att; at.H = H; at.Hkv = Hkv; at.max_seq = g.max_seq; at.n_tok = n_tok; at.TT = TT;
         if (hd == 128) hipLaunchKernelGGL(prefill_attn_kernel<128>, dim3(((TTL + 3) / 4) * H), dim3(256), pf_attn_lds_bytes<128>(), s, at);
         else hipLaunchKernelGGL(prefill_attn_kernel<64>, dim3(((TTL + 3) / 4) * H), dim3(256), pf_attn_lds_bytes<64>(), s, at);
-        PfRowArgs ra = row_args(PF_O, qd);
-        ra.in = att; ra.frag = frag_att; ra.scale = scale_att;
-        hipLaunchKernelGGL((prefill_u_row_kernel<NP, false>), rows, dim3(PF_RT), (size_t)qd * 4, s, ra);
         GemmOp r = base;
         r.type = OP_RESID; r.W = (const bf16_t *)c->wo[b]; r.N = d; r.K = qd; r.split = c->split_o;
-        gemm(PF_O, r, frag_att, scale_att, part);
+        gemm(PF_O, r, frag_att, nullptr, nullptr);
         x_row(PF_O, 2 * b);
         GemmOp gu = base;
         gu.type = OP_SWIGLU; gu.W = (const bf16_t *)c->wgu[b]; gu.N = F; gu.K = d; gu.split = c->split_gu;
-        gemm(PF_GU, gu, frag_d, scale_d, u);
-        PfRowArgs ru = row_args(PF_GU, F);
-        ru.frag = frag_u; ru.scale = scale_u;
+        gemm(PF_GU, gu, frag_d, rstd, frag_u);
         if (plan[PF_GU].parts(PF_GU)) {
-            hipLaunchKernelGGL((prefill_u_row_kernel<NP, true>), rows, dim3(PF_RT), (size_t)F * 4, s, ru);
-        } else {
-            ru.in = u;
-            hipLaunchKernelGGL((prefill_u_row_kernel<NP, false>), rows, dim3(PF_RT), (size_t)F * 4, s, ru);
+            PfRowArgs ru = row_args(PF_GU, F);
+            ru.frag = frag_u;
+            hipLaunchKernelGGL(prefill_u_row_kernel, dim3(rows.x, (F + 4 * PF_RT - 1) / (4 * PF_RT)), dim3(PF_RT), 0, s, ru);
         }
         GemmOp dn = base;
         dn.type = OP_RESID; dn.W = (const bf16_t *)c->wdown[b]; dn.N = d; dn.K = F; dn.split = c->split_down;
-        gemm(PF_DOWN, dn, frag_u, scale_u, part);
+        gemm(PF_DOWN, dn, frag_u, nullptr, nullptr);
         x_row(PF_DOWN, 2 * b + 1);
     }
     HIP_TRY(hipGetLastError());
@@ -903,16 +876,9 @@ static int32_t prefill_head(knnssd_ctx *c, int n_tok, int row, float *last_hidde
 static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, float *last_hidden_dev, int32_t *first_token) {
     PassCtl *ver = c->wsp<PassCtl>(c->L.ver_ctl);
     if (c->tuned_prefill && n >= PF_MIN_ROWS) {
-        // two fp16 planes; a model whose weights they do not hold (the kernels tell) is run with three bf16 planes, and so
-        // are its later prompts (a hint only: either way the result is right)
-        for (int again = 0; again < 2; ++again) {
-            if (c->wide_weights) KS_TRY(prefill_tuned<3>(c, tokens, n));
-            else KS_TRY(prefill_tuned<2>(c, tokens, n));
-            KS_TRY(prefill_head(c, n, (n - 1) % KS_MAX_ROWS, last_hidden_dev));
-            KS_TRY(read_back(c, c->wsp<HeadResult>(c->L.head), sizeof(HeadResult) + 4));
-            if (c->wide_weights || !c->h_stage[sizeof(HeadResult) / 4]) break;
-            c->wide_weights = true;
-        }
+        KS_TRY(prefill_tuned(c, tokens, n));
+        KS_TRY(prefill_head(c, n, (n - 1) % KS_MAX_ROWS, last_hidden_dev));
+        KS_TRY(read_back(c, c->wsp<HeadResult>(c->L.head)->tok, 4));
         *first_token = c->h_stage[0];
         c->prefilled = true;
         c->cache_len = n;

@@ -52,10 +52,10 @@ def test_prompt_lengths_round_the_tile_edges(name):
 
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("what", ["large", "tiny", "zero", "wide_row"])
-def test_weights_that_two_fp16_planes_do_or_do_not_hold(what):
-    """Weights of 32 and more, or whole runs of weights below 2^-15, go through three bf16 planes instead of two fp16 ones
-    (the kernels find out, the prompt runs again); rows whose values span many orders of magnitude and all-zero matrices
-    stay with two. Either way the result is the oracle's. Two prompts each: the second one starts where the first ended."""
+def test_weights_and_activations_of_any_magnitude(what):
+    """Weights of 32 and more, whole matrices below 2^-24, rows whose values span many orders of magnitude, all-zero matrices:
+    the prefill's operands are three bf16 planes of the fp32 activations and the bf16 weights as they are, whatever their
+    range. The result is the oracle's. Two prompts each: the second one starts where the first ended."""
     shape = synth.small_shape("pt_wide", d_model=320, n_heads=4, n_kv_heads=2, head_dim=64, d_ffn=352, vocab=700, max_seq=400)
     w = synth.make_weights(shape, seed=31, gains="random", std=0.05)
     b0 = w["blocks"][0]
@@ -82,4 +82,66 @@ def test_weights_that_two_fp16_planes_do_or_do_not_hold(what):
             for pos in (0, n // 2, n - 1):
                 for got, want in zip(gpu.knnssd_read_kv(blk, pos), orc.read_kv(blk, pos)):
                     _kv_close(got.numpy(), want)
+    gpu.close()
+
+
+# one block whose plan takes, over these lengths, 128 x 64, 256 x 128 and 256 x 256 tiles for the QKV rows, with K split and whole
+OPERANDS = dict(d_model=4096, n_heads=32, n_kv_heads=32, head_dim=128, d_ffn=6016, vocab=64, n_blocks=1)
+OPERAND_PROMPTS = (45, 100, 520, 700, 1045)
+
+
+@pytest.mark.timeout(300)
+def test_operands_keep_every_bit():
+    """Value rows whose weights let all but the last bit of an activation cancel, take one activation past another that is 2^36
+    times as large, hold a weight of 2^-40 beside one of 1 (that meets a zero), or a single small one: every product is exact and
+    every partial sum fits 24 bits, so the cached value is the closed form below, rounded to bf16 once (2^-8) behind the fp32 norm
+    factor (2^-20)."""
+    shape = synth.small_shape("pt_operands", max_seq=1060, **OPERANDS)
+    w = synth.make_weights(shape, seed=41, gains="random", std=0.02)
+    d, b0 = shape.d_model, w["blocks"][0]
+    j, k, l, far = 8, 9, 10, 2041          # three columns of one group of eight; one far away
+    w["embed"][:, [j, k, l]] = 1.0
+    w["embed"][0::2, far] = 2.0 ** 36      # even tokens: the other activations are nothing beside it
+    b0["attn_norm"][j], b0["attn_norm"][k], b0["attn_norm"][l] = 1 + 2.0 ** -12 + 2.0 ** -23, 1 + 2.0 ** -12, 1.5
+    b0["wv"].zero_()
+    b0["wv"][0::4, j], b0["wv"][0::4, k] = 1.0, -1.0
+    b0["wv"][1::4, j] = 1.0
+    b0["wv"][2::4, l], b0["wv"][2::4, l + 1] = 1.5 * 2.0 ** -40, 1.0
+    w["embed"][:, l + 1] = 0.0
+    b0["wv"][3::4, l] = 2.0 ** -14
+    gpu = binding.KnnSsd(shape, w)
+    assert gpu.packed
+    embed = w["embed"].double()
+    rs = 1.0 / torch.sqrt((embed * embed).mean(dim=1) + shape.rms_eps)
+    row = torch.tensor([2.0 ** -23, 1 + 2.0 ** -12 + 2.0 ** -23, 1.5 * 1.5 * 2.0 ** -40, 1.5 * 2.0 ** -14], dtype=torch.float64)
+    row = row.repeat(shape.kv_dim // 4)
+    prompt = synth.make_prompt(shape.vocab, 1050, seed=42).tolist()
+    for n in OPERAND_PROMPTS:
+        print("case", n, flush=True)
+        gpu.knnssd_prefill(prompt[:n])
+        for pos in sorted({0, 1, 15, n // 2, n // 2 + 1, n - 2, n - 1}):
+            want = row * rs[prompt[pos]]
+            got = gpu.knnssd_read_kv(0, pos)[1].double()
+            rel = (got - want).abs() / want
+            assert rel.max() <= 2.0 ** -8 + 2.0 ** -20, (n, pos, prompt[pos] % 2, int(rel.argmax()) % 4, float(rel.max()))
+    gpu.close()
+
+
+@pytest.mark.timeout(300)
+def test_every_tile_against_the_oracle():
+    """The same lengths with ordinary weights: over them every build of the product runs."""
+    shape = synth.small_shape("pt_builds", max_seq=1060, **dict(OPERANDS, vocab=600))
+    w, orc, gpu = make_pair(shape, seed=43, std=0.02)
+    prompt = synth.make_prompt(shape.vocab, OPERAND_PROMPTS[-1], seed=44).tolist()
+    rows, hid = orc.forward(prompt, 0, None, want_hidden=True)
+    for n in OPERAND_PROMPTS:
+        print("case", n, flush=True)
+        _, hidden = gpu.knnssd_prefill(prompt[:n])
+        ok, err = logits_close(gpu.knnssd_get_logits((n - 1) % 16).numpy(), rows[n - 1], shape)
+        assert ok, (n, err)
+        herr = np.abs(hidden.cpu().numpy() - hid[n - 1]).max() / np.abs(hid[n - 1]).max()
+        assert herr <= 5e-3, (n, herr)
+        for pos in sorted({0, 15, 16, n // 2, n - 2, n - 1}):
+            for got, want in zip(gpu.knnssd_read_kv(0, pos), orc.read_kv(0, pos)):
+                _kv_close(got.numpy(), want)
     gpu.close()
