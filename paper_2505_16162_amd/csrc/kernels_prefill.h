@@ -591,6 +591,12 @@ __device__ __forceinline__ void split_planes8(const float *v, bf16x8 *out3) {
     for (int p = 0; p < PF_NP; ++p) out3[p] = __builtin_bit_cast(bf16x8, u32x4{w[p][0], w[p][1], w[p][2], w[p][3]});
 }
 
+// a * b rounded, also where the compiler could fold the product into a following sum
+__device__ __forceinline__ float pf_rounded_product(float a, float b) {
+#pragma clang fp contract(off)
+    return a * b;
+}
+
 template <int HD> constexpr size_t pf_attn_lds_bytes() { return (size_t)2 * 2 * 64 * HD * 2; }
 
 template <int HD>
@@ -608,7 +614,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
     const bool live = b * 4 + wave < n_rt;
     const int n_chunks = b + 1;                               // positions 0 .. 64b+63 cover every row of the block
     const int last_pos = a.n_tok - 1, qd = a.H * HD;
-    const float c2 = 1.4426950408889634f / sqrtf((float)HD);  // softmax in powers of two: log2(e) / sqrt(hd)
+    constexpr float c2 = (float)(1.4426950408889634 * (HD == 128 ? 0.08838834764831845 : 0.125));   // softmax in powers of two: log2(e) / sqrt(hd)
     const bf16_t *kg_ = a.kv_block + (size_t)kvh * a.max_seq * HD;
     const bf16_t *vg_ = a.kv_block + ((size_t)a.Hkv + kvh) * a.max_seq * HD;
     const unsigned int l0 = (unsigned int)(uintptr_t)(__attribute__((address_space(3))) char *)lds;
@@ -640,7 +646,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
     }
 
     const int qpos = rt * 16 + r16;                           // the lane's query
-    float mrun = -INFINITY, lsum = 0.f;
+    float mrun = -INFINITY, off = -INFINITY, lsum = 0.f;      // largest score so far, and its exponent
     f32x4 o[DT];
 #pragma unroll
     for (int t = 0; t < DT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -686,8 +692,12 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
         cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
         cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
         const float mnew = fmaxf(mrun, cm);                   // finite: position 0 is visible to every row
-        const float f = __builtin_amdgcn_exp2f((mrun - mnew) * c2), off = mnew * c2;
+        // Weights are 2^(score * c2 - off) with off rounded once per maximum; what earlier chunks hold moves on by the difference
+        // of the rounded values, so that all chunks are weighed against one reference. (Weights under 2^-126 of the row's
+        // largest are zero.)
+        const float off_new = pf_rounded_product(mnew, c2), f = __builtin_amdgcn_exp2f(off - off_new);
         mrun = mnew;
+        off = off_new;
         float ps = 0.f;
 #pragma unroll
         for (int pt = 0; pt < 4; ++pt)

@@ -145,3 +145,40 @@ def test_every_tile_against_the_oracle():
             for got, want in zip(gpu.knnssd_read_kv(0, pos), orc.read_kv(0, pos)):
                 _kv_close(got.numpy(), want)
     gpu.close()
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("hd", [64, 128])
+def test_chunks_of_a_prompt_are_weighed_alike(hd):
+    """Scores near 10^6 whose maximum grows by 8 (unscaled) from one 64-position chunk to the next: the weights of earlier chunks
+    have to follow to fp32 accuracy, though the exponent itself is only known to 2^-8 there. Everything in front of the
+    softmax is exact (rows of +-1 with eps = 0 have an RMS of 1, the scores are whole numbers below 2^24 and the two score
+    dimensions do not rotate), so the hidden state has a closed form; fp32 sums of 200 weights: 10^-5."""
+    d, n = 256, 200
+    shape = synth.ModelShape("pt_softmax", 1, d, 2, 2, hd, 352, 64, 240, "bf16", "bf16", rope_base=1e30, rms_eps=0.0)
+    w = synth.make_weights(shape, seed=45, gains="ones", std=0.02)
+    b0 = w["blocks"][0]
+    for name in ("wq", "wk", "wv", "wo", "wd"):
+        b0[name].zero_()
+    sign = torch.randint(0, 2, (shape.vocab, d), generator=torch.Generator().manual_seed(46)) * 2 - 1
+    sign[:, 0] = 1                                                       # column 0: one
+    sign[:, 1], sign[:, 2] = -1, -1                                      # columns 1 and 2: the token's kind, tokens 0, 1 and 2
+    sign[1:, 1], sign[2:, 2] = 1, 1
+    w["embed"].copy_(sign)
+    a, b = hd // 2 - 1, hd // 2 - 2                                      # the slowest rotations
+    b0["wq"][a, 0], b0["wk"][a, 0] = 1000.0, 1000.0
+    b0["wq"][b, 0], b0["wk"][b, 0] = 1.0, 8.0
+    b0["wk"][b, 1], b0["wk"][b, 2] = 4.0, 4.0                            # 0, 8, 16 by kind
+    b0["wv"][0, 0], b0["wv"][0, 1] = 0.5, 0.5                            # 0, 1, 1
+    b0["wo"][3, 0] = 1.0
+    gpu = binding.KnnSsd(shape, w)
+    assert gpu.packed
+    kind = np.zeros(n, dtype=np.int64)
+    kind[70:130], kind[140:] = 1, 2
+    _, hidden = gpu.knnssd_prefill(kind.tolist())
+    e = np.exp(8.0 * (kind - 2) / np.sqrt(hd))
+    x = sign[2].double().numpy()
+    x[3] += (e * (kind > 0)).sum() / e.sum()
+    want = x / np.sqrt((x * x).mean())
+    assert abs(hidden.cpu().numpy()[3] / want[3] - 1) <= 1e-5, (hidden.cpu().numpy()[3], want[3])
+    gpu.close()
