@@ -45,9 +45,11 @@ __device__ __forceinline__ size_t frag_off(int KS, int TT, int pl, int ks, int t
     return (((size_t)pl * KS + ks) * TT + tt) * 512;
 }
 
-// The bf16 planes of N neighbouring values (truncation: hi + mid + lo = v), two values per word.
+// The bf16 planes of N neighbouring values (truncation: hi + mid + lo = v), two values per word. (contract off: where v is a
+// product, the remainder has to be that of the rounded one.)
 template <int N>
 __device__ __forceinline__ void split_planes(const float *v, unsigned int (*w)[N / 2]) {
+#pragma clang fp contract(off)
 #pragma unroll
     for (int e = 0; e < N / 2; ++e) {
         // the upper halves of two neighbouring values make one register of a plane

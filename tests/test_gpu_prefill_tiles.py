@@ -109,12 +109,21 @@ def test_operands_keep_every_bit():
     b0["wv"][2::4, l], b0["wv"][2::4, l + 1] = 1.5 * 2.0 ** -40, 1.0
     w["embed"][:, l + 1] = 0.0
     b0["wv"][3::4, l] = 2.0 ** -14
+    # products gain * x that fp32 rounds up, beside columns that hold the rounded product: they cancel
+    g = torch.rand(4000, generator=torch.Generator().manual_seed(47)) + 1.0
+    g = g[(g * 1.3671875).double() > g.double() * 1.3671875][:8]
+    up = torch.arange(64, 96, 4)
+    w["embed"][:, up], w["embed"][:, up + 1] = 1.3671875, 1.0
+    b0["attn_norm"][up], b0["attn_norm"][up + 1] = g, g * 1.3671875
+    for i, c in enumerate(up.tolist()):
+        b0["wv"][4 * i + 3, l], b0["wv"][4 * i + 3, c], b0["wv"][4 * i + 3, c + 1] = 0.0, 1.0, -1.0
     gpu = binding.KnnSsd(shape, w)
     assert gpu.packed
     embed = w["embed"].double()
     rs = 1.0 / torch.sqrt((embed * embed).mean(dim=1) + shape.rms_eps)
     row = torch.tensor([2.0 ** -23, 1 + 2.0 ** -12 + 2.0 ** -23, 1.5 * 1.5 * 2.0 ** -40, 1.5 * 2.0 ** -14], dtype=torch.float64)
     row = row.repeat(shape.kv_dim // 4)
+    row[3:32:4] = 0.0
     prompt = synth.make_prompt(shape.vocab, 1050, seed=42).tolist()
     for n in OPERAND_PROMPTS:
         print("case", n, flush=True)
@@ -122,7 +131,7 @@ def test_operands_keep_every_bit():
         for pos in sorted({0, 1, 15, n // 2, n // 2 + 1, n - 2, n - 1}):
             want = row * rs[prompt[pos]]
             got = gpu.knnssd_read_kv(0, pos)[1].double()
-            rel = (got - want).abs() / want
+            rel = (got - want).abs() / want.clamp(min=1e-30)
             assert rel.max() <= 2.0 ** -8 + 2.0 ** -20, (n, pos, prompt[pos] % 2, int(rel.argmax()) % 4, float(rel.max()))
     gpu.close()
 
