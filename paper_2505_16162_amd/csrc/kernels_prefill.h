@@ -19,6 +19,7 @@
 // tiles of 10), and the two dot products an epilogue combines sit in one lane's accumulators.
 #pragma once
 #include "kernels_bf16.h"
+#include "prefill_plan.h"
 
 namespace ks {
 
@@ -205,11 +206,6 @@ struct PfShape {
     static constexpr int NB = (PF_NP * TB + 7) / 8;              // token fragments per wavefront and step
     static constexpr size_t LDS = (size_t)NS * STAGE;
 };
-
-// What becomes of the sums: stored as they are (a K part, or a row kernel finishes them anyway), SwiGLU, or RoPE + cache.
-// (A build per kind: a workgroup's fixed cost is largely its instructions in front of the first load and the fetch of those
-// behind the loop, 4-5 us with everything in one build.)
-enum { PF_PARTS = 0, PF_SWIGLU, PF_ROPE };
 
 template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN>
 __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(PfArgs a) {

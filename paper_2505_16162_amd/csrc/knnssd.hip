@@ -39,8 +39,6 @@ static const size_t KS_MAX_DYN_LDS = 160 * 1024;  // dynamic LDS the tuned kerne
 
 static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-enum { PF_QKV = 0, PF_O, PF_GU, PF_DOWN, PF_OPS };     // the four matrices of a block
-
 // Workspace layout (byte offsets, all 256-byte aligned).
 struct WsLayout {
     size_t draft_ctl, ver_ctl, gen, head, knn, out3;
@@ -73,60 +71,6 @@ static bool cfg_supported(const knnssd_model_cfg *c) {
     if (c->d_model % 8 || c->d_ffn % 8) return false;
     if (c->max_seq > 15360) return false;  // attention scores of one row are kept in LDS (60 KB)
     return true;
-}
-
-// How the prefill GEMM covers one matrix for a prompt of tt token tiles (16 rows each)
-struct PfPlan {
-    int tb;                  // token tiles per workgroup: 16, 8 (256 weight rows) or 4 (128 weight rows)
-    int n_mt, n_mr, n_tt;    // row tiles, those of them with rotary pairs (OP_QKV), workgroup tiles along the tokens
-    int S;                   // parts K is split into
-    int tiles() const { return n_mt * n_tt; }
-    // sums through memory to a row kernel? (residual rows always; the others unless one large workgroup finishes them)
-    bool parts(int which) const { return S > 1 || tb != 16 || which == PF_O || which == PF_DOWN; }
-    int tm() const { return tb == 4 ? 128 : 256; }
-    int out_rows() const { return n_tt * tb * 16; }
-    size_t part_bytes() const { return (size_t)S * out_rows() * n_mt * tm() * 4; }       // K parts of the product
-};
-
-// row tiles of tm rows that cover a matrix (n_mr: those of rotary pairs)
-static int pf_row_tiles(const knnssd_model_cfg &g, int which, int tm, int *n_mr = nullptr) {
-    const int P = (g.n_heads + g.n_kv_heads) * (g.head_dim / 2), VR = g.n_kv_heads * g.head_dim;
-    const int mr = which == PF_QKV ? (P + tm / 2 - 1) / (tm / 2) : 0;
-    if (n_mr) *n_mr = mr;
-    if (which == PF_QKV) return mr + (VR + tm - 1) / tm;
-    return which == PF_GU ? (g.d_ffn + tm / 2 - 1) / (tm / 2) : (g.d_model + tm - 1) / tm;
-}
-
-// The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x ns of a step + what a workgroup
-// pays once), plus the K parts' way through memory. The constants come from kernel traces; with one matrix's plan varied at
-// a time the choice was within 16 us per block of the best one at 45 to 1500 rows. 13B, 1024 rows, against the choice: QKV
-// unsplit 256 x 256 (chosen), 256 x 128 +31 us, in two parts +60; O in three parts of 256 x 256 (chosen), of 256 x 128 -7, in two
-// +17; gate+up unsplit (chosen), 256 x 128 +86. 7B, 45 rows: QKV in five parts of 128 x 64 (chosen), in two +5, unsplit
-// +34; gate+up in four (chosen), unsplit +5, in eight +14.
-static PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
-    const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
-    PfPlan best{};
-    double best_cost = 0;
-    for (int tb = 4; tb <= 16; tb *= 2) {
-        PfPlan p{};
-        p.tb = tb;
-        const int tm = p.tm();
-        p.n_mt = pf_row_tiles(g, which, tm, &p.n_mr);
-        p.n_tt = (tt + tb - 1) / tb;
-        // 256 x 256 and 256 x 128: one workgroup per unit, bound by the matrix cores. 128 x 64: the two workgroups a unit holds
-        // take turns at its LDS, but pay their fixed cost together
-        const double step = tb == 16 ? (which == PF_QKV ? 2340 : 1930) : (tb == 8 ? (which == PF_QKV ? 1290 : 1040) : 540), fixed = tb == 16 ? 14000 : (tb == 8 ? 10000 : 6000);
-        for (int S = 1; S <= 16; ++S) {
-            if (S > 1 && S * 4 > KS) break;
-            p.S = S;
-            const int rounds = (p.tiles() * S + KS_NWG - 1) / KS_NWG;
-            if (S > 1 && rounds > 8) break;
-            const double moved = p.parts(which) ? 2.0 * S * tt * 16 * p.n_mt * tm * 4 : 0;
-            const double cost = rounds * ((KS + S - 1) / S * step) + (tb == 4 ? (rounds + 1) / 2 : rounds) * fixed + moved / 3000;
-            if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
-        }
-    }
-    return best;
 }
 
 static WsLayout ws_layout(const knnssd_model_cfg *c) {
@@ -784,12 +728,12 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     auto gemm = [&](int which, const GemmOp &op, const bf16_t *fin, const float *rs, bf16_t *fout) {
         const PfPlan &p = plan[which];
         PfArgs a{};
-        const int epi = p.parts(which) ? PF_PARTS : (which == PF_GU ? PF_SWIGLU : PF_ROPE);
+        const int epi = p.epilogue(which);
         a.op = op; a.frag_in = fin; a.rstd = rs; a.out = part; a.frag_out = fout; a.TT = TT; a.n_tok = n_tok;
         a.rows = c->wsp<PfRow>(c->L.pf_rows[which][p.tm() == 256]); a.out_rows = p.out_rows();
         a.n_mt = p.n_mt; a.n_mr = p.n_mr; a.n_tt = p.n_tt; a.S = p.S; a.inv_tiles = 1.0f / (float)p.tiles();
         a.steps = op.K / 32 / p.S; a.longer = op.K / 32 % p.S;
-        const bool own = which == PF_QKV || p.tb == 4;       // sums of their own per step: see the kernel
+        const bool own = p.own_sums(which);
         pf_each_build([&](int tb, int e, bool ow, void (*k)(PfArgs), size_t lds) {
             if (tb == p.tb && e == epi && ow == own) hipLaunchKernelGGL(k, dim3((p.tiles() * p.S + 7) / 8 * 8), dim3(PF_NT), lds, s, a);
         });

@@ -1,0 +1,73 @@
+// How the prompt prefill cuts its products into workgroups: host code only, no HIP.
+#pragma once
+#include <stddef.h>
+
+#include "../../include/knnssd.h"
+#include "device_types.h"
+
+namespace ks {
+
+enum { PF_QKV = 0, PF_O, PF_GU, PF_DOWN, PF_OPS };     // the four matrices of a block
+
+// What becomes of the sums: stored as they are (a K part, or a row kernel finishes them anyway), SwiGLU, or RoPE + cache.
+// (A build per kind: a workgroup's fixed cost is largely its instructions in front of the first load and the fetch of those
+// behind the loop, 4-5 us with everything in one build.)
+enum { PF_PARTS = 0, PF_SWIGLU, PF_ROPE };
+
+// How the prefill GEMM covers one matrix for a prompt of tt token tiles (16 rows each)
+struct PfPlan {
+    int tb;                  // token tiles per workgroup: 16, 8 (256 weight rows) or 4 (128 weight rows)
+    int n_mt, n_mr, n_tt;    // row tiles, those of them with rotary pairs (OP_QKV), workgroup tiles along the tokens
+    int S;                   // parts K is split into
+    int tiles() const { return n_mt * n_tt; }
+    // sums through memory to a row kernel? (residual rows always; the others unless one large workgroup finishes them)
+    bool parts(int which) const { return S > 1 || tb != 16 || which == PF_O || which == PF_DOWN; }
+    int epilogue(int which) const { return parts(which) ? PF_PARTS : (which == PF_GU ? PF_SWIGLU : PF_ROPE); }
+    bool own_sums(int which) const { return which == PF_QKV || tb == 4; }       // sums of their own per step: see the kernel
+    int tm() const { return tb == 4 ? 128 : 256; }
+    int out_rows() const { return n_tt * tb * 16; }
+    size_t part_bytes() const { return (size_t)S * out_rows() * n_mt * tm() * 4; }       // K parts of the product
+};
+
+// row tiles of tm rows that cover a matrix (n_mr: those of rotary pairs)
+inline int pf_row_tiles(const knnssd_model_cfg &g, int which, int tm, int *n_mr = nullptr) {
+    const int P = (g.n_heads + g.n_kv_heads) * (g.head_dim / 2), VR = g.n_kv_heads * g.head_dim;
+    const int mr = which == PF_QKV ? (P + tm / 2 - 1) / (tm / 2) : 0;
+    if (n_mr) *n_mr = mr;
+    if (which == PF_QKV) return mr + (VR + tm - 1) / tm;
+    return which == PF_GU ? (g.d_ffn + tm / 2 - 1) / (tm / 2) : (g.d_model + tm - 1) / tm;
+}
+
+// The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x ns of a step + what a workgroup
+// pays once), plus the K parts' way through memory. The constants come from kernel traces; with one matrix's plan varied at
+// a time the choice was within 16 us per block of the best one at 45 to 1500 rows. 13B, 1024 rows, against the choice: QKV
+// unsplit 256 x 256 (chosen), 256 x 128 +31 us, in two parts +60; O in three parts of 256 x 256 (chosen), of 256 x 128 -7, in two
+// +17; gate+up unsplit (chosen), 256 x 128 +86. 7B, 45 rows: QKV in five parts of 128 x 64 (chosen), in two +5, unsplit
+// +34; gate+up in four (chosen), unsplit +5, in eight +14.
+inline PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
+    const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
+    PfPlan best{};
+    double best_cost = 0;
+    for (int tb = 4; tb <= 16; tb *= 2) {
+        PfPlan p{};
+        p.tb = tb;
+        const int tm = p.tm();
+        p.n_mt = pf_row_tiles(g, which, tm, &p.n_mr);
+        p.n_tt = (tt + tb - 1) / tb;
+        // 256 x 256 and 256 x 128: one workgroup per unit, bound by the matrix cores. 128 x 64: the two workgroups a unit holds
+        // take turns at its LDS, but pay their fixed cost together
+        const double step = tb == 16 ? (which == PF_QKV ? 2340 : 1930) : (tb == 8 ? (which == PF_QKV ? 1290 : 1040) : 540), fixed = tb == 16 ? 14000 : (tb == 8 ? 10000 : 6000);
+        for (int S = 1; S <= 16; ++S) {
+            if (S > 1 && S * 4 > KS) break;
+            p.S = S;
+            const int rounds = (p.tiles() * S + KS_NWG - 1) / KS_NWG;
+            if (S > 1 && rounds > 8) break;
+            const double moved = p.parts(which) ? 2.0 * S * tt * 16 * p.n_mt * tm * 4 : 0;
+            const double cost = rounds * ((KS + S - 1) / S * step) + (tb == 4 ? (rounds + 1) / 2 : rounds) * fixed + moved / 3000;
+            if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
+        }
+    }
+    return best;
+}
+
+}  // namespace ks
