@@ -46,7 +46,7 @@ struct WsLayout {
     // tuned bf16 path
     size_t act_d, qrot, ss, head_part, attn_part, attn_arrivals, split_tab;
     // tuned prompt prefill (stream-order weights only): all prompt rows at once
-    size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_rstd, pf_part, pf_rows[PF_OPS][2];
+    size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_rstd, pf_part[PF_OPS], pf_rows[PF_OPS][2];
     int pf_tt;          // token tiles the fragment buffers are laid out for
     size_t total;
 };
@@ -110,23 +110,26 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
         L.attn_part = take(R * c->n_heads * max_chunks * (c->head_dim + ATT_PAD) * 4);
         L.attn_arrivals = take(R * (size_t)c->n_heads * 4);
         L.split_tab = take((size_t)5 * KS_NWG * sizeof(WgSplit));
-        if (c->weights_packed) {
+        if (c->weights_packed && c->prefill_mode == KNNSSD_PREFILL_AUTO) {
             const size_t tt = (((size_t)c->max_seq + 15) / 16 + 15) / 16 * 16, rows = tt * 16;
             L.pf_tt = (int)tt;
             L.pf_tokens = take(rows * 4);
             L.pf_x = take(rows * c->d_model * 4);
-            L.pf_q = take(rows * qd * 4);
             L.pf_frag_d = take(3 * rows * (size_t)c->d_model * 2);
-            L.pf_frag_att = take(3 * rows * qd * 2);
-            L.pf_frag_u = take(3 * rows * (size_t)c->d_ffn * 2);
             L.pf_rstd = take(rows * 4);
-            size_t part = 0;
+            // A product's K parts live from its launch to the row kernel behind it, and lie in what nobody holds then: those of
+            // QKV and O where SwiGLU's operands come later, those of gate+up and down where queries and attention output were.
+            size_t part[PF_OPS] = {};
             for (int w = 0; w < PF_OPS; ++w)
                 for (int t = 1; t <= (int)tt; ++t) {
                     const PfPlan p = pf_plan(*c, w, t);
-                    if (p.parts(w) && p.part_bytes() > part) part = p.part_bytes();
+                    if (p.parts(w) && p.part_bytes() > part[w]) part[w] = p.part_bytes();
                 }
-            L.pf_part = take(part);
+            auto most = [](size_t a, size_t b, size_t d) { return a > b ? (a > d ? a : d) : (b > d ? b : d); };
+            L.pf_part[PF_QKV] = L.pf_part[PF_O] = L.pf_frag_u = take(most(3 * rows * (size_t)c->d_ffn * 2, part[PF_QKV], part[PF_O]));
+            const size_t q_bytes = align_up(rows * qd * 4, 256);
+            L.pf_part[PF_GU] = L.pf_part[PF_DOWN] = L.pf_q = take(most(q_bytes + 3 * rows * qd * 2, part[PF_GU], part[PF_DOWN]));
+            L.pf_frag_att = L.pf_q + q_bytes;
             for (int w = 0; w < PF_OPS; ++w)
                 for (int i = 0; i < 2; ++i) L.pf_rows[w][i] = take((size_t)pf_row_tiles(*c, w, i ? 256 : 128) * (i ? 256 : 128) * sizeof(PfRow));
         }
@@ -717,7 +720,6 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     const dim3 rows((TTL + 7) / 8 * 128);        // row kernels: see pf_row_token
     hipStream_t s = c->stream;
     float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *rstd = c->wsp<float>(c->L.pf_rstd);
-    float *part = c->wsp<float>(c->L.pf_part);
     bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att), *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
     PfPlan plan[PF_OPS];
     for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_plan(g, w, TTL);
@@ -729,7 +731,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         const PfPlan &p = plan[which];
         PfArgs a{};
         const int epi = p.epilogue(which);
-        a.op = op; a.frag_in = fin; a.rstd = rs; a.out = part; a.frag_out = fout; a.TT = TT; a.n_tok = n_tok;
+        a.op = op; a.frag_in = fin; a.rstd = rs; a.out = c->wsp<float>(c->L.pf_part[which]); a.frag_out = fout; a.TT = TT; a.n_tok = n_tok;
         a.rows = c->wsp<PfRow>(c->L.pf_rows[which][p.tm() == 256]); a.out_rows = p.out_rows();
         a.n_mt = p.n_mt; a.n_mr = p.n_mr; a.n_tt = p.n_tt; a.S = p.S; a.inv_tiles = 1.0f / (float)p.tiles();
         a.steps = op.K / 32 / p.S; a.longer = op.K / 32 % p.S;
@@ -741,7 +743,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     auto row_args = [&](int which, int width) {     // the row kernel behind a product (width: features it finishes)
         const PfPlan &p = plan[which];
         PfRowArgs r{};
-        r.op = base; r.n_tok = n_tok; r.in = part; r.S = p.S; r.out_rows = p.out_rows(); r.ld = p.n_mt * p.tm(); r.TM = p.tm(); r.d = width; r.TT = TT;
+        r.op = base; r.n_tok = n_tok; r.in = c->wsp<float>(c->L.pf_part[which]); r.S = p.S; r.out_rows = p.out_rows(); r.ld = p.n_mt * p.tm(); r.TM = p.tm(); r.d = width; r.TT = TT;
         r.inv_dim = 1.0f / (float)d; r.eps = g.rms_eps;
         return r;
     };

@@ -103,3 +103,21 @@ def test_stream_transition_is_a_host_call_with_argument_checks(lib):
     assert f(5, 5, 0.5, 0.1, 0.1) == -3 and f(-1, 5, 0.5, 0.1, 0.1) == -3
     assert f(0, 0, 0.5, 0.1, 0.1) == -1
     assert f(0, 5, 1.5, 0.1, 0.1) == -3 and f(0, 5, 0.5, 1.0, 0.1) == -3 and f(0, 5, 0.5, 0.1, -0.1) == -3
+
+
+@pytest.mark.parametrize("name,max_seq,more", [("llama13b", 4608, 1.05), ("llama13b", 15360, 1.05), ("llama7b", 4608, 1.05), ("qwen14b", 1600, 1.2)])
+def test_workspace_of_the_prefill(lib, name, max_seq, more):
+    """What the prompt's rows need beyond the other passes: residual stream, queries and attention output, and the three
+    products' operands in 6 bytes per value; the partial sums of split products share that memory (5 % for row tables, alignment
+    and sums that are larger; few queries' room under many gate+up rows: 20 %). A context that sends prompts through 16-row passes has none of it."""
+    s = synth.workload(name).shape
+    cfg = binding.make_cfg(s, 0)
+    cfg.max_seq, cfg.weights_packed, cfg.prefill_mode = max_seq, 1, 0
+    auto = lib.knnssd_workspace_bytes(ctypes.byref(cfg))
+    cfg.prefill_mode = 1
+    chunked = lib.knnssd_workspace_bytes(ctypes.byref(cfg))
+    cfg.weights_packed = 0
+    assert chunked == lib.knnssd_workspace_bytes(ctypes.byref(cfg))
+    rows = (max_seq + 255) // 256 * 256
+    need = rows * (4 * s.d_model + 4 * s.q_dim + 6 * (s.d_model + s.q_dim + s.d_ffn))
+    assert need <= auto - chunked <= more * need
