@@ -7,7 +7,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libknnssd.so")
 SOURCES = ["knnssd.hip"]
-NO_SPILL_KERNELS = ["gemv_kernel", "gemm_mfma_kernel"]     # mangled-name fragments of the kernels that must not spill
+NO_SPILL_KERNELS = ["gemv_kernel", "gemm_mfma_kernel", "prefill_gemm_kernel", "prefill_attn_kernel"]     # mangled-name fragments of the kernels that must not spill
 
 
 def build_library(verbose: bool = False) -> str:
@@ -45,8 +45,9 @@ def build_library(verbose: bool = False) -> str:
 
 def check_hand_placed_loads(verbose: bool = False) -> None:
     """Second compile to assembly text, then the static checks of isa_check.py: the library is deleted and the
-    build fails if the GEMV has any instruction that can touch a register with a hand-placed load in flight, or
-    if a variant of the verification GEMM copies or spills a register of its weight stream."""
+    build fails if the GEMV has any instruction that can touch a register with a hand-placed load in flight, if a
+    variant of the verification GEMM copies or spills a register of its weight stream, or if m0 or the count of the
+    loads in flight is not what the prefill kernels' loads to LDS rely on."""
     import tempfile
     from . import isa_check
     with tempfile.TemporaryDirectory() as tmp:
@@ -70,8 +71,14 @@ def check_hand_placed_loads(verbose: bool = False) -> None:
     for name, body in gemv + gemm:
         for n, t in isa_check.weight_register_copies(body)[:5]:
             problems.append(f"{name}: line {n}: {t}: reads a register of the weight stream")
+    prefill = isa_check.kernel_bodies(text, "prefill_gemm_kernel") + isa_check.kernel_bodies(text, "prefill_attn_kernel")
+    if not prefill:
+        problems.append("prefill kernels not found in the assembly text")
+    for name, body in prefill:
+        for n, t, why in isa_check.lds_load_flags(body)[:5]:
+            problems.append(f"{name}: line {n}: {t}: {why}")
     if verbose:
-        print(f"isa_check: {len(gemv)} GEMV and {len(gemm)} GEMM kernel bodies, {len(problems)} problems")
+        print(f"isa_check: {len(gemv)} GEMV, {len(gemm)} GEMM and {len(prefill)} prefill kernel bodies, {len(problems)} problems")
     if problems:
         os.remove(LIB)
         raise RuntimeError("hand-placed loads: the compiled code is not safe:\n" + "\n".join(problems))

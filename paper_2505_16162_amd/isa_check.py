@@ -16,6 +16,13 @@ remarks (build.py); this module catches the second from the assembly text:
   chunk and round conditions are correlated): every `v_mov` / `v_accvgpr` / `scratch` instruction between
   the first streaming load and the last hand-placed wait that READS a register of the weight stream.
   Those registers are read by nothing but the matrix instructions there, so any hit is a copy or a spill.
+
+The prefill kernels' hand-placed loads go straight to LDS. They have no target register, but they set m0 (which the
+compiler cannot be told), and their waits count what is in flight:
+
+* `lds_load_flags`  every such load has its m0 written in its own block of assembly; nothing else in the kernel names
+  m0; and no vector memory instruction of the compiler's (a spill, a load moved into the loop) stands between the
+  first load to LDS and the last hand-placed wait that leaves loads in flight, whose count it would upset.
 """
 import re
 
@@ -184,3 +191,45 @@ def weight_register_copies(body):
         if read & weight:
             hits.append((n, t))
     return hits
+
+
+_VMEM = ("global_", "buffer_", "scratch_", "flat_")
+
+
+def lds_load_flags(body):
+    """List of (line, instruction, reason): see the module's text. Empty for a kernel without loads to LDS."""
+    blocks, cur = [], None                     # hand-placed blocks: [(line, text)]
+    for n, raw in enumerate(body):
+        t = raw.strip()
+        if t.startswith(";;#ASMSTART"):
+            cur = []
+        elif t.startswith(";;#ASMEND"):
+            blocks.append(cur)
+            cur = None
+        elif cur is not None:
+            t = t.split(";")[0].strip()
+            if t and not t.startswith("."):
+                cur.append((n, t))
+    flags, first, last_keep = [], None, None
+    for b in blocks:
+        m0_set = False
+        for n, t in b:
+            if t.startswith("s_mov_b32 m0"):
+                m0_set = True
+            elif "_load_lds_" in t:
+                first = n if first is None else first
+                if not m0_set:
+                    flags.append((n, t, "a load to LDS without its own m0"))
+            m = re.search(r"vmcnt\((\d+)\)", t)
+            if m and int(m.group(1)) > 0:
+                last_keep = n
+    if first is None:
+        return []
+    for n, t, ia in _instructions(body):
+        if ia or t.startswith("LABEL "):
+            continue
+        if re.search(r"\bm0\b", t):
+            flags.append((n, t, "the compiler uses m0"))
+        if last_keep is not None and first < n < last_keep and t.startswith(_VMEM):
+            flags.append((n, t, "in flight with the counted loads"))
+    return flags

@@ -76,3 +76,35 @@ def test_paths_are_merged_with_the_least_count():
     t = asm_load("v[2:5]", "v[10:11]") + "\ts_cbranch_scc1 .LBB0_2\n" + asm_load("v[6:9]", "v[12:13]")
     t += ".LBB0_2:\n" + asm_wait(1) + "\tv_add_f32_e32 v20, v20, v2\n" + asm_wait(0)
     assert any(r == 2 for _, _, r, _ in C.inflight_flags(body_of(t)))
+
+
+def lds_load(addr="v[2:3]", m0=True):
+    return "\t;;#ASMSTART\n" + ("\ts_mov_b32 m0, s4\n\ts_nop 0\n" if m0 else "") + f"\tglobal_load_lds_dwordx4 {addr}, off\n\t;;#ASMEND\n"
+
+
+def lds_pipeline(extra="", m0=True, keep=1):
+    """Two steps in flight; the loop requests one, waits for the older and reads it."""
+    t = "\tglobal_load_dwordx2 v[8:9], v0, s[2:3]\n" + lds_load() + lds_load()
+    t += ".LBB0_1:\n" + lds_load(m0=m0) + extra + asm_wait(keep) + "\ts_barrier\n\tds_read_b128 v[4:7], v1\n"
+    t += "\ts_cbranch_scc1 .LBB0_1\n" + asm_wait(0) + "\tglobal_store_dwordx4 v[8:9], v[4:7], off\n"
+    return t
+
+
+def test_loads_to_lds_pass():
+    assert C.lds_load_flags(body_of(lds_pipeline())) == []
+    assert C.lds_load_flags(body_of(rolling_loop())) == []           # none in the kernel
+
+
+def test_load_to_lds_without_m0_is_flagged():
+    (_, t, why), = C.lds_load_flags(body_of(lds_pipeline(m0=False)))
+    assert "global_load_lds" in t and "m0" in why
+
+
+def test_other_use_of_m0_is_flagged():
+    assert [t for _, t, _ in C.lds_load_flags(body_of(lds_pipeline("\ts_mov_b32 m0, s7\n")))] == ["s_mov_b32 m0, s7"]
+
+
+def test_memory_instruction_among_counted_loads_is_flagged():
+    for t in ("scratch_load_dword v10, off, s32", "global_load_dword v10, v[2:3], off"):
+        assert [x for _, x, _ in C.lds_load_flags(body_of(lds_pipeline("\t" + t + "\n")))] == [t]
+        assert C.lds_load_flags(body_of(lds_pipeline("\t" + t + "\n", keep=0))) == []       # waits for everything count nothing
