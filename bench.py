@@ -34,6 +34,7 @@ TRAFFIC_FILE = os.path.join(ROOT, "profiles", "knnssd_kernels_llama13b_hbm_traff
 FAMILIES = (("gemm_mfma_kernel<false", "verification GEMM"), ("gemv_kernel", "draft GEMV"),
             ("attn_partial_mfma_kernel", "attention, matrix cores (verification)"),
             ("attn_partial_kernel", "attention, vector ALUs (draft)"), ("attn_combine_kernel", "attention merge launch"))
+TRAFFIC_SOURCES = ("device_types.h", "kernels_bf16.h", "kernels_vattn.h")       # where those kernels stand
 
 
 def traffic_parse(fetch_csv, write_csv):
@@ -75,12 +76,12 @@ def traffic_parse(fetch_csv, write_csv):
 
 
 def kernel_source_sha16():
-    """Hash of the library's sources: a counter measurement belongs to the kernels it was taken on."""
+    """Hash of the sources of the FAMILIES' kernels: a counter measurement belongs to the kernels it was taken on (and not to
+    those of the prompt or of other shapes, which change by themselves)."""
     import hashlib
     h = hashlib.sha256()
-    src = os.path.join(ROOT, "paper_2505_16162_amd", "csrc")
-    for name in sorted(os.listdir(src)):
-        h.update(open(os.path.join(src, name), "rb").read())
+    for name in TRAFFIC_SOURCES:
+        h.update(open(os.path.join(ROOT, "paper_2505_16162_amd", "csrc", name), "rb").read())
     return h.hexdigest()[:16]
 
 
