@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const PassCtl *ctl, const 
 // the same tree for every row whatever MR is. fp32 configuration (4 blocks of d = 256), prompt 32 + 32 tokens in rounds of
 // four drafts, before (norms and RoPE in launches of their own, 16-row builds for every verification, one position at a time
 // per wavefront in the attention) and after: 15.3-16.1 -> 8.9-10.2 ms; attention 9.7 -> 4.2 us, 5-row products 8.9 -> 3.9 us.
-// MR is the pass's row count rounded up (gemm_rows_mr), so a short pass carries no dead rows.
+// MR is the pass's row count (launch_rows), so no pass carries dead rows.
 // ------------------------------------------------------------------------------------------
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 

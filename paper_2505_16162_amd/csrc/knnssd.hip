@@ -438,23 +438,16 @@ extern "C" int32_t knnssd_set_skipset(knnssd_ctx *ctx, const uint8_t *mask_host)
 // ------------------------------------------------------------------------------------------
 // one forward pass: every retained sublayer in order, then the head
 // ------------------------------------------------------------------------------------------
-// rows a build of gemm_rows_kernel carries for a pass of n (drafts; short verifications; eight drafts; any)
-static int gemm_rows_mr(int n) { return n <= 3 ? n : (n <= 5 ? 5 : (n <= 9 ? 9 : KS_MAX_ROWS)); }
-
-template <typename WT, typename KT, int EPI>
+// gemm_rows_kernel in the build for n_rows rows: one per count, so that no pass carries dead rows
+template <typename WT, typename KT, int EPI, int MR = KS_MAX_ROWS>
 static void launch_rows(knnssd_ctx *c, const PassCtl *ctl, int n_rows, const void *W, const RowsOp &op) {
+    if constexpr (MR > 1) {
+        if (n_rows < MR) return launch_rows<WT, KT, EPI, MR - 1>(c, ctl, n_rows, W, op);
+    }
     const int items = EPI == EPI_QKV ? (op.H + 2 * op.Hkv) * op.hd / 2 : op.N;
     int wgs = (items + 3) / 4;
     if (wgs > 2048) wgs = 2048;
-    const WT *w = (const WT *)W;
-    switch (gemm_rows_mr(n_rows)) {
-        case 1: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 1, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
-        case 2: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 2, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
-        case 3: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 3, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
-        case 5: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 5, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
-        case 9: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, 9, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
-        default: hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, KS_MAX_ROWS, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, w, op); break;
-    }
+    hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, MR, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, (const WT *)W, op);
 }
 
 template <typename WT, typename KT>
