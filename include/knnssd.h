@@ -163,7 +163,9 @@ int32_t knnssd_set_anchors(knnssd_ctx *ctx, const void *anchors_dev, int32_t anc
 /* Prefill (Sec. 4.2: the routing query is the prompt's last hidden vector): the full model over
  * n prompt tokens at positions 0..n-1. Resets the KV cache length to n. Outputs: the first
  * generated token (host) and, if last_hidden_dev is not NULL, the final-RMSNorm hidden state of
- * the last prompt token (fp32 [d_model], device) - the vector the KNN step is queried with. */
+ * the last prompt token (fp32 [d_model], device) - the vector the KNN step is queried with. How the sums over a row
+ * are grouped follows n (the kernels are chosen by it), so the same first tokens in a longer prompt give the same
+ * hidden states and cache entries to fp32 rounding, not bit for bit; the same call gives the same bits. */
 int32_t knnssd_prefill(knnssd_ctx *ctx, const int32_t *tokens_host, int32_t n, float *last_hidden_dev,
                        int32_t *first_token_out);
 

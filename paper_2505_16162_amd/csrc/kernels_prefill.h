@@ -191,8 +191,8 @@ __device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v,
 // TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS.
 // What bounds it. 256 x 256 and 256 x 128: the matrix cores, at 1.53-1.6 PFLOP/s issued (three instructions per product), where a
 // large library product in bf16 reaches 1.59 on this card; one meeting per step for all wavefronts together kept the matrix
-// pipe 55 % busy, two groups one phase apart 80 %. 13B-shaped, 4096 rows: QKV 1.52 ms (with its own sums, below), gate+up
-// 2.26, O 0.44, down 1.12. 128 x 64 (few rows): operand reads out of LDS about as much as the weight stream: a 4 x 2 grid
+// pipe 55 % busy, two groups one phase apart 80 %. 13B-shaped, 4096 rows: QKV 1.52-1.55 ms (with its own sums, below),
+// gate+up 2.26-2.33, O 0.44, down 1.12. 128 x 64 (few rows): operand reads out of LDS about as much as the weight stream: a 4 x 2 grid
 // of wavefronts reads 8 KB a wavefront and step, 8 x 1 reads 13 (7B, 45 rows, gate+up unsplit 79 -> 75 us); 5-6 us of a
 // launch are its fixed cost. Which tile a matrix and a length take: pf_plan.
 // PP: the wavefronts form two groups (one wavefront of each on every SIMD) that run one phase apart: while one group
@@ -428,10 +428,11 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
 }
 
 // ------------------------------------------------------------------------------------------
-// Row kernels, between the products: they add up the K parts, finish a row and write the next product's operands, four
-// neighbouring features per thread (loads of neighbouring lanes adjoin; eight per thread: 32 us instead of 27 for 1024 x 5120
-// in three parts). Bound by memory. A row's share of a fragment is 16 bytes of each
-// 256: the workgroups of the 16 rows that share the fragments are neighbours on one die, so that its L2 puts whole lines together.
+// Row kernels, between the products: they add up the K parts, finish a row and write the next product's operands. Bound by
+// memory. Four neighbouring features per thread, so that the loads of neighbouring lanes adjoin (with eight, 1024 rows of
+// 5120 in three parts take 32 us instead of 30, SwiGLU of 45 x 11008 in four parts 17.6 instead of 11.2). A row's share of a
+// fragment is 16 bytes of each 256: the workgroups of the 16 rows that share the fragments are neighbours on one die, so that
+// its L2 puts whole lines together.
 // ------------------------------------------------------------------------------------------
 struct PfRowArgs {
     GemmOp op;                  // as in PfArgs

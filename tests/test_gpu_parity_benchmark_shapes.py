@@ -1,8 +1,7 @@
 """GPU parity of the prompt prefill the benchmark actually runs, against the CPU oracle.
 
-The many-row prefill kernels (prefill_gemm_kernel in its 16- and 8-token-tile variants with several tile slots per
-row group, prefill_attn_kernel) are reached only by prompts of hundreds of rows at the benchmark models' widths.
-The oracle cannot run 40 such blocks inside a test, so the widths are kept and the depth is cut: cached keys and
+The tiles and K parts that the many-row prefill kernels (prefill_gemm_kernel, prefill_attn_kernel) take for prompts of hundreds
+of rows at the benchmark models' widths. The oracle cannot run 40 such blocks inside a test, so the widths are kept and the depth is cut: cached keys and
 values at sampled positions, the last hidden vector (the routing query), the first token and its logits, and
 verification passes and a draft step on top of that context are compared with the oracle. The full-depth
 comparison is the stored oracle run under tests/golden/ (test_config3_golden_run)."""
@@ -55,7 +54,7 @@ def test_benchmark_widths_prefill_against_oracle(base, n_blocks, plen):
     first_o, hidden_o, row_o = O.prefill(orc, prompt)
     first_g, hidden_g = gpu.knnssd_prefill(prompt)
     # cached keys and values: the first and last position of the first and last tile of the many-row prefill, a
-    # position in the middle, and the rows the closing 16-row pass wrote
+    # position in the middle, and the prompt's last rows
     n_main = (plen - 1) // 16 * 16
     flips = {}
     for blk in range(n_blocks):
