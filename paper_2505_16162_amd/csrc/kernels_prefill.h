@@ -663,13 +663,15 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
         for (int pt = 0; pt < 4; ++pt) {
             if (pt < n_pt) {
                 f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+                bf16x8 kf[QS];
+                const int row = pt * 16 + r16;
 #pragma unroll
-                for (int ks = 0; ks < QS; ++ks) {
-                    const int row = pt * 16 + r16;
-                    const bf16x8 kf = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kl + row * RB + ((ks * 4 + kg) ^ swz(row)) * 16));
+                for (int ks = 0; ks < QS; ++ks) kf[ks] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(kl + row * RB + ((ks * 4 + kg) ^ swz(row)) * 16));
+                // the lowest plane first: QS roundings at the size of the whole score instead of 3 QS
 #pragma unroll
-                    for (int p = 0; p < 3; ++p) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf, qa[ks][p], acc, 0, 0, 0);
-                }
+                for (int p = 2; p >= 0; --p)
+#pragma unroll
+                    for (int ks = 0; ks < QS; ++ks) acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[ks], qa[ks][p], acc, 0, 0, 0);
                 s[pt] = acc;
             } else {
                 s[pt] = f32x4{-INFINITY, -INFINITY, -INFINITY, -INFINITY};
@@ -737,7 +739,7 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
                 for (int j = 0; j < 4; ++j)
                     vf[j] = __builtin_amdgcn_perm(vr[2 * j + 1][t >> 1], vr[2 * j][t >> 1], (t & 1) ? 0x07060302u : 0x05040100u);
 #pragma unroll
-                for (int p = 0; p < 3; ++p)
+                for (int p = 2; p >= 0; --p)
                     o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, vf), pb[p], o[t], 0, 0, 0);
             }
         }
