@@ -262,7 +262,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp &op, const PassCtl *c
         for (int m = tid >> 6; m < n_rows; m += NWV) {
             float sacc = 0.f;
             for (int t = lane; t < R; t += 64) sacc += vals[t * ld + m];
-            sacc = wave_sum(sacc);
+            sacc = wave_sum_shfl(sacc);
             if (lane == 0) op.ss_out[(size_t)m * KS_NWG + wg] = sacc;
         }
     } else if (op.type == OP_SWIGLU) {
@@ -328,7 +328,7 @@ __device__ __forceinline__ void gemm_epilogue(const GemmOp &op, const PassCtl *c
             }
             float se = 0.f;
             for (int t = lane; t < R; t += 64) se += expf(vals[t * ld + m] * rstd[m] - bv);
-            se = wave_sum(se);
+            se = wave_sum_shfl(se);
             if (lane == 0) {
                 HeadPartial hp; hp.maxv = bv; hp.idx = bi; hp.sumexp = (R > 0) ? se : 0.f; hp.pad = 0;
                 op.head_part[(size_t)m * nwg + wg] = hp;
@@ -573,7 +573,7 @@ __device__ __forceinline__ void gemv_device(const GemmOp &op, const PassCtl *ctl
         float share = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) share += sh[j];
-        const float r = op.ss_in ? 1.0f / sqrtf(wave_sum(share) * op.inv_dim + op.eps) : 1.0f;
+        const float r = op.ss_in ? 1.0f / sqrtf(wave_sum_shfl(share) * op.inv_dim + op.eps) : 1.0f;
         if (lane == 0) rstd_s[0] = r;
     }
     __syncthreads();
@@ -991,7 +991,7 @@ __device__ __forceinline__ void gemm_mfma_device(const GemmOp &op, const PassCtl
         float share = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) share += sh[j];
-        const float r = (op.ss_in && wave < n_rows) ? 1.0f / sqrtf(wave_sum(share) * op.inv_dim + op.eps) : 1.0f;
+        const float r = (op.ss_in && wave < n_rows) ? 1.0f / sqrtf(wave_sum_shfl(share) * op.inv_dim + op.eps) : 1.0f;
         if (lane == 0) rstd_s[wave] = r;
     }
     __syncthreads();
@@ -1171,13 +1171,13 @@ __device__ __forceinline__ void attn_partial_device(const AttnArgs &a, const Pas
             for (int s = 0; s < STEPS; ++s) {
                 float d = dot8(kf[s], q0, q1, 0.f);
 #pragma unroll
-                for (int off = 1; off < LPP; off <<= 1) d += __shfl_xor(d, off, 64);
+                for (int off = 1; off < LPP; off <<= 1) d += lane_xor(d, off);
                 const int pos = pos0 + s * PPS + ps;
                 sc[s] = (pos < len) ? d * scale : -INFINITY;
                 mx = fmaxf(mx, sc[s]);
             }
 #pragma unroll
-            for (int off = LPP; off < 64; off <<= 1) mx = fmaxf(mx, __shfl_xor(mx, off, 64));
+            for (int off = LPP; off < 64; off <<= 1) mx = fmaxf(mx, lane_xor(mx, off));
             float l = 0.f;
             float o[8];
 #pragma unroll
@@ -1193,9 +1193,9 @@ __device__ __forceinline__ void attn_partial_device(const AttnArgs &a, const Pas
             }
 #pragma unroll
             for (int off = LPP; off < 64; off <<= 1) {
-                l += __shfl_xor(l, off, 64);
+                l += lane_xor(l, off);
 #pragma unroll
-                for (int j = 0; j < 8; ++j) o[j] += __shfl_xor(o[j], off, 64);
+                for (int j = 0; j < 8; ++j) o[j] += lane_xor(o[j], off);
             }
             // l counted every lane of a position LPP times over? no: each lane group of LPP lanes holds the same
             // score, and the xor-sum above runs over the position groups only, so l is the sum over positions.
@@ -1396,7 +1396,7 @@ __global__ __launch_bounds__(NT) void head_final_kernel(const HeadPartial *parts
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) {
-        float ov = __shfl_xor(bv, off, 64); int oi = __shfl_xor(bi, off, 64);
+        float ov = lane_xor(bv, off); int oi = lane_xor(bi, off);
         if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; }
     }
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;

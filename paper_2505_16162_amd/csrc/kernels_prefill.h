@@ -690,8 +690,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
         for (int pt = 0; pt < 4; ++pt)
 #pragma unroll
             for (int q = 0; q < 4; ++q) cm = fmaxf(cm, s[pt][q]);
-        cm = fmaxf(cm, __shfl_xor(cm, 16, 64));
-        cm = fmaxf(cm, __shfl_xor(cm, 32, 64));
+        cm = fmaxf(cm, lane_xor(cm, 16));
+        cm = fmaxf(cm, lane_xor(cm, 32));
         const float mnew = fmaxf(mrun, cm);                   // finite: position 0 is visible to every row
         // Weights are 2^(score * c2 - off) with off rounded once per maximum; what earlier chunks hold moves on by the difference
         // of the rounded values, so that all chunks are weighed against one reference. (Weights under 2^-126 of the row's
@@ -744,8 +744,8 @@ __global__ __launch_bounds__(256, 2) void prefill_attn_kernel(PfAttn a) {
             }
         }
     }
-    lsum += __shfl_xor(lsum, 16, 64);
-    lsum += __shfl_xor(lsum, 32, 64);
+    lsum += lane_xor(lsum, 16);
+    lsum += lane_xor(lsum, 32);
     if (live && qpos <= last_pos) {
         const float inv = 1.0f / lsum;
         // accumulator row 4*kg + q of instruction t is dimension DT * (4*kg + q) + t: eight neighbours at a time

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(VA_NT, LONG ? 3 : 1) void attn_partial_mfma_kernel(
 #pragma unroll
             for (int t4 = 1; t4 < VA_TP; ++t4) cm = fmaxf(cm, sc[t4][q]);
 #pragma unroll
-            for (int off = 1; off < 16; off <<= 1) cm = fmaxf(cm, __shfl_xor(cm, off, 64));
+            for (int off = 1; off < 16; off <<= 1) cm = fmaxf(cm, lane_xor(cm, off));
             mx[q] = cm;                                       // -inf when none of the positions is visible
             float ps = 0.f;
 #pragma unroll
@@ -166,7 +166,7 @@ __global__ __launch_bounds__(VA_NT, LONG ? 3 : 1) void attn_partial_mfma_kernel(
                 ps += e;
             }
 #pragma unroll
-            for (int off = 1; off < 16; off <<= 1) ps += __shfl_xor(ps, off, 64);
+            for (int off = 1; off < 16; off <<= 1) ps += lane_xor(ps, off);
             ls[q] = ps;
         }
         // (the P tile is private to this wavefront: its stores above and its loads below are ordered by the in-order
