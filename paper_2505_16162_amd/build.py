@@ -2,6 +2,8 @@
 import os
 import re
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -23,7 +25,9 @@ def build_library(verbose: bool = False) -> str:
     cmd += ["-Rpass-analysis=kernel-resource-usage"]
     if verbose:
         print(" ".join(cmd))
-    proc = subprocess.run(cmd, check=False, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
+    with ThreadPoolExecutor(1) as pool:          # the assembly text is compiled beside the library
+        text = pool.submit(assembly_text)
+        proc = subprocess.run(cmd, check=False, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
     remarks = [ln for ln in proc.stderr.splitlines() if "remark:" in ln]
     other = [ln for ln in proc.stderr.splitlines() if "remark:" not in ln and "kernel-resource-usage" not in ln]
     if proc.returncode != 0:
@@ -39,27 +43,27 @@ def build_library(verbose: bool = False) -> str:
         if m and current and any(k in current for k in NO_SPILL_KERNELS) and int(m.group(1)) > 0:
             os.remove(LIB)
             raise RuntimeError(f"{current} spills {m.group(1)} vector registers; its hand-placed loads forbid that")
-    check_hand_placed_loads(verbose)
+    check_hand_placed_loads(text.result(), verbose)
     return LIB
 
 
-def check_hand_placed_loads(verbose: bool = False) -> None:
-    """Second compile to assembly text, then the static checks of isa_check.py: the library is deleted and the
-    build fails if the GEMV has any instruction that can touch a register with a hand-placed load in flight, if a
-    variant of the verification GEMM copies or spills a register of its weight stream, or if m0 or the count of the
-    loads in flight is not what the prefill kernels' loads to LDS rely on."""
-    import tempfile
-    from . import isa_check
+def assembly_text() -> str:
+    """The device code as assembly text (a second compile); empty if the compiler failed."""
     with tempfile.TemporaryDirectory() as tmp:
         asm = os.path.join(tmp, "knnssd.s")
         cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-S", "--cuda-device-only",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
                "-I", os.path.join(HERE, "..", "include"), "-o", asm] + [os.path.join(CSRC, s) for s in SOURCES]
         proc = subprocess.run(cmd, check=False, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
-        if proc.returncode != 0:
-            os.remove(LIB)
-            raise RuntimeError("hipcc -S failed:\n" + proc.stderr[-4000:])
-        text = open(asm).read()
+        return open(asm).read() if proc.returncode == 0 else ""
+
+
+def check_hand_placed_loads(text: str, verbose: bool = False) -> None:
+    """The static checks of isa_check.py on the assembly text: the library is deleted and the
+    build fails if the GEMV has any instruction that can touch a register with a hand-placed load in flight, if a
+    variant of the verification GEMM copies or spills a register of its weight stream, or if m0 or the count of the
+    loads in flight is not what the prefill kernels' loads to LDS rely on."""
+    from . import isa_check
     problems = []
     gemv = isa_check.kernel_bodies(text, "gemv_kernel")
     gemm = isa_check.kernel_bodies(text, "gemm_mfma_kernel")

@@ -185,6 +185,90 @@ __device__ __forceinline__ float wave_sum_rows(float *v) {
     return t[0];
 }
 
+// The lane's operands of an item's products: N 16-byte pieces of weight row w0 (and w1 for a pair), 64 pieces apart, and the
+// gain of the RMSNorm in front (nullptr: none). Past the row's end the last piece again.
+template <typename WT, bool DUAL, int N>
+struct RowsPieces {
+    WChunk<WT> w[N], w2[N];
+    float g[N][WChunk<WT>::N];
+    __device__ __forceinline__ void load(const WT *w0, const WT *w1, const float *gain, int K) {
+        constexpr int VEC = WChunk<WT>::N;
+        const int lane = threadIdx.x & 63;
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int k = min((i * 64 + lane) * VEC, K - VEC);
+            w[i].load(w0 + k);
+            if (DUAL) w2[i].load(w1 + k);
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) g[i][j] = gain ? gain[k + j] : 1.0f;
+        }
+    }
+};
+
+// Dot products of one item with MR rows of X (n_rows live ones, past them the last again): lane r returns row r's in a (and
+// b). p: the lane's first pieces, fetched by the caller.
+template <typename WT, int MR, bool DUAL, bool NORM, int N>
+__device__ __forceinline__ void rows_product(const RowsPieces<WT, DUAL, N> &p, const WT *w0, const WT *w1, const float *X, int ldx, int n_rows, int K,
+                                             const float *gain, float eps, float &a, float &b) {
+    constexpr int VEC = WChunk<WT>::N;
+    const int lane = threadIdx.x & 63;
+    float acc[MR], acc2[MR], ss[MR];
+#pragma unroll
+    for (int r = 0; r < MR; ++r) { acc[r] = 0.f; acc2[r] = 0.f; ss[r] = 0.f; }
+    auto add = [&](WChunk<WT> w, WChunk<WT> w2, const float *g, int k) {
+        if (gain) {
+#pragma unroll
+            for (int j = 0; j < VEC; ++j) {
+                w.v[j] *= g[j];
+                if (DUAL) w2.v[j] *= g[j];
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < MR; ++r) {
+            const float *xp = X + (size_t)min(r, n_rows - 1) * ldx + k;
+#pragma unroll
+            for (int j = 0; j < VEC; j += 4) {
+                const float4 xv = *reinterpret_cast<const float4 *>(xp + j);
+                const float x[4] = {xv.x, xv.y, xv.z, xv.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    acc[r] = fmaf(w.v[j + e], x[e], acc[r]);
+                    if (DUAL) acc2[r] = fmaf(w2.v[j + e], x[e], acc2[r]);
+                    if (NORM) ss[r] = fmaf(x[e], x[e], ss[r]);
+                }
+            }
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if ((i * 64 + lane) * VEC < K) add(p.w[i], p.w2[i], p.g[i], (i * 64 + lane) * VEC);
+    for (int k = (N * 64 + lane) * VEC; k < K; k += 64 * VEC) {
+        WChunk<WT> w, w2;
+        float g[VEC];
+        w.load(w0 + k);
+        if (DUAL) w2.load(w1 + k);
+#pragma unroll
+        for (int j = 0; j < VEC; ++j) g[j] = gain ? gain[k + j] : 1.0f;
+        add(w, w2, g, k);
+    }
+    a = wave_sum_rows<MR>(acc);
+    b = DUAL ? wave_sum_rows<MR>(acc2) : 0.f;
+    if (NORM) {
+        const float sum = wave_sum_rows<MR>(ss);
+        if (gain) {
+            const float rs = 1.0f / sqrtf(sum / (float)K + eps);
+            a *= rs;
+            b *= rs;
+        }
+    }
+}
+
+// a rotary pair, with the one rounding order that every kernel of these shapes has
+__device__ __forceinline__ void rotate_pair(float a, float b, float c, float s, float &ra, float &rb) {
+    ra = fmaf(a, c, -(b * s));
+    rb = fmaf(b, c, a * s);
+}
+
 struct RowsOp {
     const float *X;             // [rows][ldx]
     int ldx;
@@ -208,7 +292,6 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, cons
     const int lane = threadIdx.x & 63;
     const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
     const int n_waves = (gridDim.x * blockDim.x) >> 6;
-    constexpr int VEC = WChunk<WT>::N;
     constexpr bool DUAL = EPI == EPI_SWIGLU || EPI == EPI_QKV;      // two weight rows per item
     const int K = op.K, half = op.hd >> 1;
     const int P = EPI == EPI_QKV ? (op.H + op.Hkv) * half : 0;      // rotary pairs; behind them pairs of value rows
@@ -221,47 +304,11 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, cons
             if (o < P) { const int head = o / half; r0 = head * op.hd + (o - head * half); r1 = r0 + half; }
             else { r0 = (op.H + op.Hkv) * op.hd + (o - P) * 2; r1 = r0 + 1; }
         }
-        float acc[MR], acc2[MR], ss[MR];
-#pragma unroll
-        for (int r = 0; r < MR; ++r) { acc[r] = 0.f; acc2[r] = 0.f; ss[r] = 0.f; }
-        const WT *wrow = W + (size_t)r0 * K, *wrow2 = W + (size_t)r1 * K;
-        for (int k = lane * VEC; k < K; k += 64 * VEC) {
-            WChunk<WT> w, w2;
-            w.load(wrow + k);
-            if (DUAL) w2.load(wrow2 + k);
-            if (op.gain) {
-#pragma unroll
-                for (int j = 0; j < VEC; ++j) {
-                    const float g = op.gain[k + j];
-                    w.v[j] *= g;
-                    if (DUAL) w2.v[j] *= g;
-                }
-            }
-#pragma unroll
-            for (int r = 0; r < MR; ++r) {
-                const float *xp = X + (size_t)min(r, n_rows - 1) * op.ldx + k;
-#pragma unroll
-                for (int j = 0; j < VEC; j += 4) {
-                    const float4 xv = *reinterpret_cast<const float4 *>(xp + j);
-                    const float x[4] = {xv.x, xv.y, xv.z, xv.w};
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        acc[r] = fmaf(w.v[j + e], x[e], acc[r]);
-                        if (DUAL) acc2[r] = fmaf(w2.v[j + e], x[e], acc2[r]);
-                        if (EPI == EPI_QKV || EPI == EPI_SWIGLU) ss[r] = fmaf(x[e], x[e], ss[r]);
-                    }
-                }
-            }
-        }
-        float a = wave_sum_rows<MR>(acc), b = DUAL ? wave_sum_rows<MR>(acc2) : 0.f;
-        if (EPI == EPI_QKV || EPI == EPI_SWIGLU) {
-            const float sum = wave_sum_rows<MR>(ss);
-            if (op.gain) {
-                const float rs = 1.0f / sqrtf(sum / (float)K + op.eps);
-                a *= rs;
-                b *= rs;
-            }
-        }
+        float a, b;
+        const WT *w0 = W + (size_t)r0 * K, *w1 = W + (size_t)r1 * K;
+        RowsPieces<WT, DUAL, 1> p;
+        p.load(w0, w1, op.gain, K);
+        rows_product<WT, MR, DUAL, EPI == EPI_QKV || EPI == EPI_SWIGLU, 1>(p, w0, w1, X, op.ldx, n_rows, K, op.gain, op.eps, a, b);
         if (lane < n_rows) {           // lane r holds row r
             const int row = row_lo + lane;
             float *yp = op.Y + (size_t)row * op.ldy;
@@ -274,7 +321,8 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, cons
                 if (o < P) {
                     const int head = o / half, i = o - head * half;
                     const float c = op.cos_t[(size_t)pos * half + i], s = op.sin_t[(size_t)pos * half + i];
-                    const float ra = a * c - b * s, rb = b * c + a * s;
+                    float ra, rb;
+                    rotate_pair(a, b, c, s, ra, rb);
                     if (head < op.H) {
                         yp[r0] = ra; yp[r1] = rb;
                     } else {
@@ -295,7 +343,7 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, cons
 
 // ------------------------------------------------------------------------------------------
 // Attention of one (row, head): softmax(q K^T / sqrt(hd)) V over positions 0..start+r.
-// One workgroup per (head, row); scores are kept in LDS (max_seq floats of dynamic LDS). A group of HD/4 lanes takes a
+// 256 threads per (head, row); scores are kept in LDS (max_seq floats). A group of HD/4 lanes takes a
 // position (four dimensions per lane), 16 or 8 positions side by side, four rounds of them in flight.
 // ------------------------------------------------------------------------------------------
 __device__ __forceinline__ float4 load4_as_float(const float *p) { return *reinterpret_cast<const float4 *>(p); }
@@ -304,30 +352,26 @@ __device__ __forceinline__ float4 load4_as_float(const bf16_t *p) {
     return float4{__uint_as_float(t.x << 16), __uint_as_float(t.x & 0xffff0000u), __uint_as_float(t.y << 16), __uint_as_float(t.y & 0xffff0000u)};
 }
 
-template <typename KT, int HD>
-__global__ __launch_bounds__(256) void attention_kernel(const PassCtl *ctl, const float *qkv, const KT *kv_block,
-                                                        float *att, int H, int Hkv, int max_seq) {
-    if (!ctl->active) return;
-    const int h = blockIdx.x, r = blockIdx.y;
-    if (r >= ctl->n_rows) return;
-    constexpr int LPP = HD / 4, NP = 256 / LPP, U = 4;       // lanes per position, positions side by side, rounds in flight
-    extern __shared__ float scores[];                        // [len]
-    __shared__ float red[8];
-    __shared__ __align__(16) float outp[4][HD];
-    const int len = ctl->start + r + 1;
-    const int kvh = h / (H / Hkv);
-    const int ld = (H + 2 * Hkv) * HD;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, grp = tid / LPP, d0 = (tid % LPP) * 4;
-    const float4 q = *reinterpret_cast<const float4 *>(qkv + (size_t)r * ld + h * HD + d0);
-    const KT *kc = kv_block + (size_t)kvh * max_seq * HD + d0;
-    const KT *vc = kv_block + ((size_t)Hkv + kvh) * max_seq * HD + d0;
+struct AttnItemLds {
+    float red[8];
+    __align__(16) float outp[4][128];
+};
+
+constexpr int ATI_U = 4;                                     // rounds of positions in flight
+// the position of thread tid in round u (clamped)
+template <int HD> __device__ __forceinline__ int attention_position(int tid, int u, int len) { return min(tid / (HD / 4) + u * (256 / (HD / 4)), len - 1); }
+
+// One item by 256 threads (tid), q: the lane's four query dimensions; key(t), value(t): its four dimensions of position t;
+// k0, v0: those of the first ATI_U rounds, fetched by the caller. Every thread of the workgroup gets here (three meetings).
+// out(dim, value) is called by HD of the threads.
+template <int HD, typename FK, typename FV, typename FO>
+__device__ __forceinline__ void attention_item(float4 q, int len, int tid, float *scores, AttnItemLds &l, const float4 (&k0)[ATI_U], const float4 (&v0)[ATI_U], FK key, FV value, FO out) {
+    constexpr int LPP = HD / 4, NP = 256 / LPP, U = ATI_U;   // lanes per position, positions side by side
+    const int lane = tid & 63, wave = tid >> 6, grp = tid / LPP, d0 = (tid % LPP) * 4;
     const float scale = 1.0f / sqrtf((float)HD);
 
     float lmax = -INFINITY;
-    for (int t0 = grp; t0 < len; t0 += NP * U) {
-        float4 k[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) k[u] = load4_as_float(kc + (size_t)min(t0 + u * NP, len - 1) * HD);
+    auto score = [&](int t0, const float4 (&k)[U]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             float p = q.x * k[u].x;
@@ -340,11 +384,18 @@ __global__ __launch_bounds__(256) void attention_kernel(const PassCtl *ctl, cons
                 lmax = fmaxf(lmax, p);
             }
         }
+    };
+    score(grp, k0);
+    for (int t0 = grp + NP * U; t0 < len; t0 += NP * U) {
+        float4 k[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) k[u] = key(min(t0 + u * NP, len - 1));
+        score(t0, k);
     }
     lmax = wave_max(lmax);
-    if (lane == 0) red[wave] = lmax;
+    if (lane == 0) l.red[wave] = lmax;
     __syncthreads();
-    const float mx = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+    const float mx = fmaxf(fmaxf(l.red[0], l.red[1]), fmaxf(l.red[2], l.red[3]));
     float lsum = 0.f;
     for (int t = tid; t < len; t += 256) {
         const float e = expf(scores[t] - mx);
@@ -352,31 +403,61 @@ __global__ __launch_bounds__(256) void attention_kernel(const PassCtl *ctl, cons
         lsum += e;
     }
     lsum = wave_sum(lsum);
-    if (lane == 0) red[4 + wave] = lsum;
+    if (lane == 0) l.red[4 + wave] = lsum;
     __syncthreads();
-    const float den = (red[4] + red[5]) + (red[6] + red[7]);
+    const float den = (l.red[4] + l.red[5]) + (l.red[6] + l.red[7]);
     float4 o = float4{0.f, 0.f, 0.f, 0.f};
-    for (int t0 = grp; t0 < len; t0 += NP * U) {
-        float4 v[U];
-#pragma unroll
-        for (int u = 0; u < U; ++u) v[u] = load4_as_float(vc + (size_t)min(t0 + u * NP, len - 1) * HD);
+    auto weigh = [&](int t0, const float4 (&v)[U]) {
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const float e = t0 + u * NP < len ? scores[t0 + u * NP] : 0.f;
             if (t0 + u * NP < len) { o.x = fmaf(e, v[u].x, o.x); o.y = fmaf(e, v[u].y, o.y); o.z = fmaf(e, v[u].z, o.z); o.w = fmaf(e, v[u].w, o.w); }
         }
+    };
+    weigh(grp, v0);
+    for (int t0 = grp + NP * U; t0 < len; t0 += NP * U) {
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = value(min(t0 + u * NP, len - 1));
+        weigh(t0, v);
     }
 #pragma unroll
     for (int off = LPP; off < 64; off <<= 1) {               // the wavefront's positions side by side
         o.x += lane_xor(o.x, off); o.y += lane_xor(o.y, off);
         o.z += lane_xor(o.z, off); o.w += lane_xor(o.w, off);
     }
-    if (lane < LPP) *reinterpret_cast<float4 *>(&outp[wave][d0]) = o;
+    if (lane < LPP) *reinterpret_cast<float4 *>(&l.outp[wave][d0]) = o;
     __syncthreads();
     if (tid < HD) {
-        const float s = (outp[0][tid] + outp[1][tid]) + (outp[2][tid] + outp[3][tid]);
-        att[(size_t)r * (H * HD) + h * HD + tid] = s / den;
+        const float s = (l.outp[0][tid] + l.outp[1][tid]) + (l.outp[2][tid] + l.outp[3][tid]);
+        out(tid, s / den);
     }
+}
+
+template <typename KT, int HD>
+__global__ __launch_bounds__(256) void attention_kernel(const PassCtl *ctl, const float *qkv, const KT *kv_block,
+                                                        float *att, int H, int Hkv, int max_seq) {
+    if (!ctl->active) return;
+    const int h = blockIdx.x, r = blockIdx.y;
+    if (r >= ctl->n_rows) return;
+    extern __shared__ float scores[];                        // [len]
+    __shared__ AttnItemLds lds;
+    const int kvh = h / (H / Hkv);
+    const int ld = (H + 2 * Hkv) * HD;
+    const int d0 = (threadIdx.x % (HD / 4)) * 4;
+    const float4 q = *reinterpret_cast<const float4 *>(qkv + (size_t)r * ld + h * HD + d0);
+    const KT *kc = kv_block + (size_t)kvh * max_seq * HD + d0;
+    const KT *vc = kv_block + ((size_t)Hkv + kvh) * max_seq * HD + d0;
+    const int len = ctl->start + r + 1;
+    auto key = [&](int t) { return load4_as_float(kc + (size_t)t * HD); };
+    auto value = [&](int t) { return load4_as_float(vc + (size_t)t * HD); };
+    float4 k0[ATI_U], v0[ATI_U];
+#pragma unroll
+    for (int u = 0; u < ATI_U; ++u) k0[u] = key(attention_position<HD>(threadIdx.x, u, len));
+#pragma unroll
+    for (int u = 0; u < ATI_U; ++u) v0[u] = value(attention_position<HD>(threadIdx.x, u, len));
+    attention_item<HD>(q, len, threadIdx.x, scores, lds, k0, v0, key, value,
+                       [&](int dim, float v) { att[(size_t)r * (H * HD) + h * HD + dim] = v; });
 }
 
 // ------------------------------------------------------------------------------------------
@@ -764,7 +845,7 @@ __global__ void round_begin_kernel(GenState *st, PassCtl *draft) {
 
 // host_flag (may be null): two pinned host words: [0] receives the pass's new `active` value, so the host can decide on
 // the next draft step after a plain stream synchronisation, without a copy; [2] the drafts made so far in the round
-__global__ void draft_end_kernel(GenState *st, PassCtl *draft, const HeadResult *res, int32_t *host_flag) {
+__device__ inline void draft_end(GenState *st, PassCtl *draft, const HeadResult *res, int32_t *host_flag) {
     if (!draft->active) { if (host_flag) { host_flag[0] = 0; host_flag[2] = st->k; } return; }
     int k = st->k;
     int d = res->tok[0]; float p = res->prob[0];
@@ -776,23 +857,25 @@ __global__ void draft_end_kernel(GenState *st, PassCtl *draft, const HeadResult 
     draft->tok[0] = d;
     draft->start = st->cache_len + k;
 }
+__global__ void draft_end_kernel(GenState *st, PassCtl *draft, const HeadResult *res, int32_t *host_flag) { draft_end(st, draft, res, host_flag); }
 
 // expect_k >= 0: the pass was enqueued ahead of the host's knowledge, for a round of exactly expect_k drafts (its
 // launch arguments and activation layout are those of expect_k + 1 rows); it runs only if the draft did stop there
-__global__ void verify_begin_kernel(const GenState *st, const PassCtl *draft, PassCtl *ver, int expect_k) {
+__device__ inline void verify_begin(const GenState *st, const PassCtl *draft, PassCtl *ver, int expect_k) {
     const bool as_expected = expect_k < 0 || (draft->active == 0 && st->k == expect_k);
     ver->active = (st->done || !as_expected) ? 0 : 1;
     ver->n_rows = st->k + 1; ver->start = st->cache_len; ver->head_from = 0;
     ver->tok[0] = st->x_last;
     for (int i = 0; i < st->k; ++i) ver->tok[i + 1] = st->drafts[i];
 }
+__global__ void verify_begin_kernel(const GenState *st, const PassCtl *draft, PassCtl *ver, int expect_k) { verify_begin(st, draft, ver, expect_k); }
 
 // Greedy acceptance and rollback: keep the leading drafts that equal the full model's own
 // token, emit the model's next token after them, move the cache length behind the last kept row.
 // host_emitted (may be null): pinned host word that receives the new count of emitted tokens
 // ver: the pass whose result this is; a pass that did not run (enqueued ahead for a draft count that did not come
 // true) leaves the state alone
-__global__ void accept_kernel(GenState *st, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, int32_t *host_emitted) {
+__device__ inline void accept(GenState *st, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, int32_t *host_emitted) {
     if (st->done || !ver->active) { if (host_emitted) *host_emitted = st->emitted; return; }
     int k = st->k, j = 0;
     while (j < k && st->drafts[j] == res->tok[j]) ++j;
@@ -806,6 +889,9 @@ __global__ void accept_kernel(GenState *st, const PassCtl *ver, const HeadResult
     st->rounds += 1; st->drafted += k; st->accepted += j;
     if (st->emitted >= st->max_new) st->done = 1;
     if (host_emitted) *host_emitted = st->emitted;
+}
+__global__ void accept_kernel(GenState *st, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, int32_t *host_emitted) {
+    accept(st, ver, res, out_tokens, host_emitted);
 }
 
 // Acceptance for a stand-alone verification call: rows tok[0..n-1] = [x_last, d_1..d_k].

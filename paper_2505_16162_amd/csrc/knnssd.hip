@@ -14,6 +14,7 @@
 #include "kernels_generic.h"
 #include "kernels_bf16.h"
 #include "kernels_prefill.h"
+#include "kernels_small.h"
 #include "kernels_vattn.h"
 
 using namespace ks;
@@ -48,6 +49,8 @@ struct WsLayout {
     // tuned prompt prefill (stream-order weights only): all prompt rows at once
     size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_rstd, pf_part[PF_OPS], pf_rows[PF_OPS][2];
     int pf_tt;          // token tiles the fragment buffers are laid out for
+    // small models' one-launch passes: block table, handed-over vectors
+    size_t small_tab, small_meets, small_words, small_words_bytes;
     size_t total;
 };
 
@@ -71,6 +74,19 @@ static bool cfg_supported(const knnssd_model_cfg *c) {
     if (c->d_model % 8 || c->d_ffn % 8) return false;
     if (c->max_seq > 15360) return false;  // attention scores of one row are kept in LDS (60 KB)
     return true;
+}
+
+// Models whose passes may run in one launch (kernels_small.h). SM_G workgroups pull less than the whole chip, so what a step
+// reads has to be small: a draft step and a 5-row verification of two blocks with 2.7 MB a block take 52 / 69 us in one launch and 73
+// / 83 us as a launch per step; at 9.4 MB a block and a head of 6 MB 86 / 112 and 93 / 108, at 15 MB a block 106 / 141 and
+// 94 / 113; with a head of 33 MB 126 / 167 and 100 / 136.
+static const size_t SMALL_MAX_BYTES = 8u << 20;     // weights of a block, of the head
+static bool small_ok(const knnssd_model_cfg &g) {
+    if (g.weights_packed || g.weight_dtype != g.kv_dtype || g.n_blocks < 1 || g.n_blocks > SM_MAX_BLOCKS) return false;
+    const size_t elt = g.weight_dtype == KNNSSD_BF16 ? 2 : 4, d = (size_t)g.d_model, hd = (size_t)g.head_dim;
+    const size_t block = elt * d * ((2 * (size_t)g.n_heads + 2 * (size_t)g.n_kv_heads) * hd + 3 * (size_t)g.d_ffn);
+    if (block > SMALL_MAX_BYTES || elt * d * (size_t)g.vocab > SMALL_MAX_BYTES) return false;
+    return g.d_ffn >= SM_G && (g.n_heads + 2 * g.n_kv_heads) * g.head_dim / 2 >= SM_G;      // every workgroup contributes to these steps
 }
 
 static WsLayout ws_layout(const knnssd_model_cfg *c) {
@@ -134,6 +150,13 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
                 for (int i = 0; i < 2; ++i) L.pf_rows[w][i] = take((size_t)pf_row_tiles(*c, w, i ? 256 : 128) * (i ? 256 : 128) * sizeof(PfRow));
         }
     }
+    if (small_ok(*c)) {
+        const size_t qd = (size_t)c->n_heads * c->head_dim;
+        L.small_tab = take((size_t)c->n_blocks * sizeof(SmallBlock));
+        L.small_meets = take(SM_MEETS * sizeof(SmallMeet));
+        L.small_words_bytes = (qkv_dim + qd + 2 * (size_t)c->d_model + c->d_ffn + 3 * SM_G) * R * sizeof(u64);
+        L.small_words = take(L.small_words_bytes);
+    }
     L.total = off;
     return L;
 }
@@ -171,6 +194,8 @@ struct knnssd_ctx {
     // pinned host staging for small read-backs
     int32_t *h_stage;
     int32_t *d_flags;   // device view of h_stage + 512: words the round-control kernels write for the host
+    unsigned int small_tag = 0;    // last tag a small pass has used; 0: its words hold no tag
+    unsigned int small_launch = 0; // small passes launched
     std::vector<hipEvent_t> events;
     // knnssd_profile_pass: enqueue only the weight-streaming launches of a pass and count them
     bool gemm_only = false;
@@ -201,6 +226,24 @@ static hipError_t pf_set_lds_limits() {
     pf_each_build([&](int, int, bool, void (*k)(PfArgs), size_t lds) { set((const void *)k, lds); });
     set((const void *)prefill_attn_kernel<128>, pf_attn_lds_bytes<128>());
     set((const void *)prefill_attn_kernel<64>, pf_attn_lds_bytes<64>());
+    return e;
+}
+
+// The one-launch pass's builds: f(rows, bf16 storage, kernel) for each
+template <typename F> static void small_each_build(F f) {
+    auto both = [&](auto mr) {
+        f(decltype(mr)::value, false, small_pass_kernel<float, decltype(mr)::value>);
+        f(decltype(mr)::value, true, small_pass_kernel<bf16_t, decltype(mr)::value>);
+    };
+    both(std::integral_constant<int, 1>{}); both(std::integral_constant<int, 2>{}); both(std::integral_constant<int, 3>{});
+    both(std::integral_constant<int, 5>{}); both(std::integral_constant<int, 9>{}); both(std::integral_constant<int, 16>{});
+}
+static const size_t SMALL_MAX_LDS = 80 * 1024 - sizeof(SmallLds);     // two workgroups per unit
+static hipError_t small_set_lds_limits() {
+    hipError_t e = hipSuccess;
+    small_each_build([&](int, bool, void (*k)(SmallArgs)) {
+        if (e == hipSuccess) e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)SMALL_MAX_LDS);
+    });
     return e;
 }
 
@@ -366,6 +409,20 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         delete c;
         return KNNSSD_EHIP;
     }
+    if (small_ok(c->cfg)) {
+        std::vector<SmallBlock> tab((size_t)nb);
+        for (int b = 0; b < nb; ++b) tab[b] = SmallBlock{(uint64_t)(uintptr_t)c->attn_norm[b], (uint64_t)(uintptr_t)c->mlp_norm[b], (uint64_t)(uintptr_t)c->wqkv[b],
+                                                             (uint64_t)(uintptr_t)c->wo[b], (uint64_t)(uintptr_t)c->wgu[b], (uint64_t)(uintptr_t)c->wdown[b]};
+        e = hipMemcpyAsync(c->wsp<SmallBlock>(c->L.small_tab), tab.data(), tab.size() * sizeof(SmallBlock), hipMemcpyHostToDevice, c->stream);
+        if (e == hipSuccess) e = hipStreamSynchronize(c->stream);
+        if (e == hipSuccess) e = small_set_lds_limits();
+        if (e != hipSuccess) {
+            snprintf(g_hip_err, sizeof(g_hip_err), "%s (block table)", hipGetErrorString(e));
+            (void)hipHostFree(c->h_stage);
+            delete c;
+            return KNNSSD_EHIP;
+        }
+    }
     *out = c;
     return KNNSSD_OK;
 }
@@ -490,6 +547,47 @@ static int32_t run_pass_t(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int 
     launch_rows<WT, float, EPI_STORE>(c, ctl, c->in_prefill ? 1 : n_rows, c->lm_head, h);     // a prompt's pass: its last row, or none
     hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
     HIP_TRY(hipGetLastError());
+    return KNNSSD_OK;
+}
+
+// The same pass in one launch. *done stays false if it does not fit.
+static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int n_rows, int start, const PassEnds &ends, bool *done) {
+    const knnssd_model_cfg &g = c->cfg;
+    if (!small_ok(g)) return KNNSSD_OK;
+    const int d = g.d_model, qd = g.n_heads * g.head_dim, F = g.d_ffn, len = start + n_rows;
+    int mr = 0;
+    void (*kernel)(SmallArgs) = nullptr;
+    small_each_build([&](int rows, bool bf16, void (*k)(SmallArgs)) {
+        if (bf16 == (g.weight_dtype == KNNSSD_BF16) && rows >= n_rows && !kernel) { kernel = k; mr = rows; }
+    });
+    const size_t lds = small_lds_bytes(d, qd, F, g.head_dim, mr, (len + 3) & ~3);
+    if (!kernel || lds > SMALL_MAX_LDS) return KNNSSD_OK;
+    const unsigned int tags = small_tags(g.n_blocks);
+    u64 *w = c->wsp<u64>(c->L.small_words);
+    if (c->small_tag == 0 || c->small_tag > SM_BAD_TAG - 2 * tags) {       // the first pass, and whenever the tags run out
+        hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(1024), 0, c->stream, (int *)w, (int)(c->L.small_words_bytes / 4));
+        hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, c->stream, c->wsp<int>(c->L.small_meets), (int)(SM_MEETS * sizeof(SmallMeet) / 4));
+        c->small_tag = 0;
+    }
+    SmallArgs a{};
+    a.ctl = ctl; a.ends = ends; a.blocks = c->wsp<SmallBlock>(c->L.small_tab); a.n_blocks = g.n_blocks;
+    for (int b = 0; mask && b < g.n_blocks; ++b) {
+        a.skip_attn |= (u64)(mask[2 * b] != 0) << b;
+        a.skip_mlp |= (u64)(mask[2 * b + 1] != 0) << b;
+    }
+    a.embed = c->embed; a.lm_head = c->lm_head; a.final_norm = c->final_norm; a.kv = c->kv; a.kv_block_bytes = c->kv_block_bytes;
+    const size_t R = KS_MAX_ROWS;
+    a.w_qkv = w; a.w_att = a.w_qkv + R * (g.n_heads + 2 * g.n_kv_heads) * g.head_dim; a.w_xo = a.w_att + R * qd; a.w_xd = a.w_xo + R * d;
+    a.w_u = a.w_xd + R * d; a.w_head = a.w_u + R * F;
+    a.xn = c->wsp<float>(c->L.xn); a.logits = c->wsp<float>(c->L.logits); a.head = c->wsp<HeadResult>(c->L.head);
+    a.meets = c->wsp<SmallMeet>(c->L.small_meets); a.launch = c->small_launch++ % SM_MEETS;
+    a.cos_t = c->wsp<float>(c->L.rope_cos); a.sin_t = c->wsp<float>(c->L.rope_sin);
+    a.d = d; a.H = g.n_heads; a.Hkv = g.n_kv_heads; a.hd = g.head_dim; a.F = F; a.V = g.vocab; a.max_seq = g.max_seq; a.eps = g.rms_eps;
+    a.tag = c->small_tag + 1; a.one_head = c->in_prefill; a.score_len = (len + 3) & ~3;
+    c->small_tag += tags;
+    hipLaunchKernelGGL(kernel, dim3(SM_G), dim3(SM_NT), lds, c->stream, a);
+    HIP_TRY(hipGetLastError());
+    *done = true;
     return KNNSSD_OK;
 }
 
@@ -678,15 +776,25 @@ static int32_t run_pass_bf16(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, b
 
 // mr: 1 for a draft step, KS_MAX_ROWS for verification / prefill; n_rows: the rows the control block will hold when
 // the pass runs (the host always knows the count, the device fills in the contents)
-static int32_t run_pass(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int mr, int n_rows, int start, bool want_head = true) {
+static int32_t run_pass(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int mr, int n_rows, int start, bool want_head = true, const PassEnds &ends = PassEnds()) {
     const bool wb = c->cfg.weight_dtype == KNNSSD_BF16, kb = c->cfg.kv_dtype == KNNSSD_BF16;
     if (n_rows < 1 || n_rows > mr) return KNNSSD_ERANGE;
-    if (mr == 1 && c->tuned) return run_pass_bf16(c, ctl, mask, true, true, 1, start);
-    if (mr != 1 && c->tuned_verify) return run_pass_bf16(c, ctl, mask, false, want_head, n_rows, start);
-    if (wb && kb) return run_pass_t<bf16_t, bf16_t>(c, ctl, mask, n_rows);
-    if (wb && !kb) return run_pass_t<bf16_t, float>(c, ctl, mask, n_rows);
-    if (!wb && kb) return run_pass_t<float, bf16_t>(c, ctl, mask, n_rows);
-    return run_pass_t<float, float>(c, ctl, mask, n_rows);
+    if (!c->tuned) {
+        bool done = false;
+        KS_TRY(run_pass_small(c, ctl, mask, n_rows, start, ends, &done));
+        if (done) return KNNSSD_OK;
+    }
+    HeadResult *head = c->wsp<HeadResult>(c->L.head);
+    if (ends.kind == ENDS_VERIFY) hipLaunchKernelGGL(verify_begin_kernel, dim3(1), dim3(1), 0, c->stream, ends.st, ends.draft, ctl, ends.expect_k);
+    if (mr == 1 && c->tuned) KS_TRY(run_pass_bf16(c, ctl, mask, true, true, 1, start));
+    else if (mr != 1 && c->tuned_verify) KS_TRY(run_pass_bf16(c, ctl, mask, false, want_head, n_rows, start));
+    else if (wb && kb) KS_TRY((run_pass_t<bf16_t, bf16_t>(c, ctl, mask, n_rows)));
+    else if (wb) KS_TRY((run_pass_t<bf16_t, float>(c, ctl, mask, n_rows)));
+    else if (kb) KS_TRY((run_pass_t<float, bf16_t>(c, ctl, mask, n_rows)));
+    else KS_TRY((run_pass_t<float, float>(c, ctl, mask, n_rows)));
+    if (ends.kind == ENDS_DRAFT) hipLaunchKernelGGL(draft_end_kernel, dim3(1), dim3(1), 0, c->stream, ends.st, ctl, head, ends.flags);
+    if (ends.kind == ENDS_VERIFY) hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(1), 0, c->stream, ends.st, ctl, head, ends.out_tokens, ends.flags + 1);
+    return KNNSSD_OK;
 }
 
 static int32_t set_pass(knnssd_ctx *c, PassCtl *ctl, int active, int n_rows, int start, int head_from, const int32_t *toks) {
@@ -1107,7 +1215,6 @@ extern "C" int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, 
 
     GenState *st = ctx->wsp<GenState>(ctx->L.gen);
     PassCtl *dr = ctx->wsp<PassCtl>(ctx->L.draft_ctl), *ver = ctx->wsp<PassCtl>(ctx->L.ver_ctl);
-    HeadResult *head = ctx->wsp<HeadResult>(ctx->L.head);
     int32_t *out_dev = ctx->wsp<int32_t>(ctx->L.out_tokens);
     hipStream_t s = ctx->stream;
     hipLaunchKernelGGL(gen_init_kernel, dim3(1), dim3(1), 0, s, st, n_prompt, first, gen->max_new, gen->max_draft,
@@ -1134,15 +1241,16 @@ extern "C" int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, 
         bool verified = false;        // the round's verification pass has been enqueued for the right draft count
         bool stepwise = false;        // a prediction failed in this round: wait after every step from here on
         auto enqueue_verify = [&](int k, int expect_k) -> int32_t {
-            hipLaunchKernelGGL(verify_begin_kernel, dim3(1), dim3(1), 0, s, st, dr, ver, expect_k);
-            KS_TRY(run_pass(ctx, ver, nullptr, KS_MAX_ROWS, k + 1, cache_len_host));
-            hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(1), 0, s, st, ver, head, out_dev, ctx->d_flags + 1);
+            PassEnds ends;
+            ends.kind = ENDS_VERIFY; ends.st = st; ends.draft = dr; ends.expect_k = expect_k; ends.out_tokens = out_dev; ends.flags = ctx->d_flags;
+            KS_TRY(run_pass(ctx, ver, nullptr, KS_MAX_ROWS, k + 1, cache_len_host, true, ends));
             KS_TRY(mark(ctx, ec));
             return KNNSSD_OK;
         };
         for (int i = 0; i < kmax; ++i) {
-            KS_TRY(run_pass(ctx, dr, ctx->draft_mask.data(), 1, 1, cache_len_host + i));
-            hipLaunchKernelGGL(draft_end_kernel, dim3(1), dim3(1), 0, s, st, dr, head, ctx->d_flags);
+            PassEnds ends;
+            ends.kind = ENDS_DRAFT; ends.st = st; ends.draft = dr; ends.flags = ctx->d_flags;
+            KS_TRY(run_pass(ctx, dr, ctx->draft_mask.data(), 1, 1, cache_len_host + i, true, ends));
             ++n_draft_passes; ++k_host;
             const bool last = k_host == kmax;                  // the round ends here whatever the confidence is
             if (!(gen->conf_threshold > 0.f)) continue;        // no stop rule: kmax drafts, nothing to wait for
