@@ -576,6 +576,16 @@ struct KnnTile {
     static constexpr int L = 8 / A;
 };
 
+// The scores of A consecutive anchors from the lanes' sums (dot: [Q][A]): all of them are added up over the wavefront together
+// (wave_sum_rows: 17 exchanges for up to 16 sums instead of 96), lane q * A + t ends up with query q's score of anchor n0 + t.
+template <int Q, int A>
+__device__ __forceinline__ void knn_store_scores(float *dot, float *nn, int n0, int N, float *scores) {
+    const int lane = threadIdx.x & 63, t = lane & (A - 1), q = lane / A;
+    const float d = wave_sum_rows<Q * A>(dot), n2 = wave_sum_rows<A>(nn);
+    const bool ok = n2 > 0.f && isfinite(n2);
+    if (q < Q && n0 + t < N) scores[(size_t)q * N + n0 + t] = ok ? d * (1.0f / sqrtf(n2)) : NAN;
+}
+
 template <int Q, typename AT>
 __global__ __launch_bounds__(256) void knn_scores_multi_kernel(const float *__restrict__ queries, const AT *__restrict__ anchors,
                                                                int N, int D, float *scores /*[Q][N]*/) {
@@ -590,12 +600,12 @@ __global__ __launch_bounds__(256) void knn_scores_multi_kernel(const float *__re
         const AT *a[A];
 #pragma unroll
         for (int t = 0; t < A; ++t) a[t] = anchors + (size_t)min(n0 + t, N - 1) * D;      // past the table: the last anchor again, not stored
-        float dot[A][Q], nn[A];
+        float dot[Q][A], nn[A];
 #pragma unroll
         for (int t = 0; t < A; ++t) {
             nn[t] = 0.f;
 #pragma unroll
-            for (int q = 0; q < Q; ++q) dot[t][q] = 0.f;
+            for (int q = 0; q < Q; ++q) dot[q][t] = 0.f;
         }
         for (int k0 = 0; k0 < D; k0 += BLK) {            // blocks of A x L 16-byte loads per lane, issued together
             f4 av[A][L];
@@ -633,23 +643,102 @@ __global__ __launch_bounds__(256) void knn_scores_multi_kernel(const float *__re
                         for (int q = 0; q < Q; ++q) {
 #pragma unroll
                             for (int i4 = 0; i4 < EPL / 4; ++i4) {
-                                dot[t][q] = fmaf(e[4 * i4], qv[q][i4].x, dot[t][q]); dot[t][q] = fmaf(e[4 * i4 + 1], qv[q][i4].y, dot[t][q]);
-                                dot[t][q] = fmaf(e[4 * i4 + 2], qv[q][i4].z, dot[t][q]); dot[t][q] = fmaf(e[4 * i4 + 3], qv[q][i4].w, dot[t][q]);
+                                dot[q][t] = fmaf(e[4 * i4], qv[q][i4].x, dot[q][t]); dot[q][t] = fmaf(e[4 * i4 + 1], qv[q][i4].y, dot[q][t]);
+                                dot[q][t] = fmaf(e[4 * i4 + 2], qv[q][i4].z, dot[q][t]); dot[q][t] = fmaf(e[4 * i4 + 3], qv[q][i4].w, dot[q][t]);
                             }
                         }
                     }
                 }
             }
         }
+        knn_store_scores<Q, A>(&dot[0][0], nn, n0, N, scores);
+    }
+}
+
+// The same scan for tables far larger than the caches and several queries. The one above takes its queries from the L1, behind the
+// anchors in the queue of loads, so a wavefront drains its loads in every block: 5.0 TB/s with three queries where one query
+// reaches 6.7. Here the queries lie in LDS (zeros behind D; the two halves of eight elements apart, so that neighbouring
+// lanes read neighbouring 16 bytes), the only loads in the queue are the table's, and a wavefront has KNN_STAGES blocks of A of
+// them under way, each requested again for a later block as soon as it has been used, also across anchors.
+// One workgroup per unit stays for all its anchors. Sums are formed in the same order as above.
+constexpr int KNN_STAGES = 3, KNN_STREAM_NT = 1024;
+template <typename AT> constexpr int knn_block() { return 64 * 16 / (int)sizeof(AT); }      // elements of an anchor a wavefront's load covers
+template <typename AT> inline size_t knn_stream_lds(int Q, int D) { return (size_t)Q * ((D + knn_block<AT>() - 1) / knn_block<AT>() * knn_block<AT>()) * 4; }
+
+template <int Q, typename AT>
+__global__ __launch_bounds__(KNN_STREAM_NT) void knn_scores_stream_kernel(const float *__restrict__ queries, const AT *__restrict__ anchors,
+                                                                          int N, int D, float *scores /*[Q][N]*/) {
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    constexpr int EPL = 16 / (int)sizeof(AT), A = 4, BLK = knn_block<AT>(), H = EPL / 4;
+    extern __shared__ __align__(16) char lds_bytes[];
+    float *qs = reinterpret_cast<float *>(lds_bytes);         // [Q][blocks][H][64 lanes][4]
+    const int nb = (D + BLK - 1) / BLK, lane = threadIdx.x & 63, wave = (blockIdx.x * KNN_STREAM_NT + threadIdx.x) >> 6;
+    const int n_waves = (gridDim.x * KNN_STREAM_NT) >> 6, n_groups = (N + A - 1) / A;
+
+    int fg = min(wave, n_groups - 1), fb = 0;                 // group of A anchors and block that are requested next
+    auto fetch = [&](f4 *to) {
+        const int k = min(fb * BLK + lane * EPL, D - EPL);    // clamped, masked below
 #pragma unroll
-        for (int t = 0; t < A; ++t) {
-            const float nt = wave_sum(nn[t]);
-            const bool ok = nt > 0.f && isfinite(nt);
-            const float inv = ok ? 1.0f / sqrtf(nt) : 0.f;
+        for (int t = 0; t < A; ++t) to[t] = __builtin_nontemporal_load(reinterpret_cast<const f4 *>(anchors + (size_t)min(fg * A + t, N - 1) * D + k));
+        if (++fb == nb) { fb = 0; fg = min(fg + n_waves, n_groups - 1); }      // (behind the last group it again; not used)
+    };
+    f4 av[KNN_STAGES][A];
 #pragma unroll
-            for (int q = 0; q < Q; ++q) {
-                const float d = wave_sum(dot[t][q]);
-                if (lane == 0 && n0 + t < N) scores[(size_t)q * N + n0 + t] = ok ? d * inv : NAN;
+    for (int s = 0; s < KNN_STAGES; ++s) fetch(av[s]);
+    for (int i = threadIdx.x * 4; i < Q * nb * BLK; i += KNN_STREAM_NT * 4) {
+        const int q = i / (nb * BLK), k = i - q * (nb * BLK), b = k / BLK, in = k - b * BLK, l = in / EPL, h = (in - l * EPL) / 4;
+        const f4 v = k < D ? *reinterpret_cast<const f4 *>(queries + (size_t)q * D + k) : f4{0.f, 0.f, 0.f, 0.f};
+        *reinterpret_cast<f4 *>(qs + (((size_t)(q * nb + b) * H + h) * 64 + l) * 4) = v;
+    }
+    __syncthreads();
+    if (wave >= n_groups) return;
+    float dot[Q * A], nn[A];
+    int g = wave, b = 0;
+    auto clear = [&]() {
+#pragma unroll
+        for (int i = 0; i < Q * A; ++i) dot[i] = 0.f;
+#pragma unroll
+        for (int t = 0; t < A; ++t) nn[t] = 0.f;
+    };
+    clear();
+    for (;;) {
+#pragma unroll
+        for (int s = 0; s < KNN_STAGES; ++s) {
+            if (b * BLK + lane * EPL < D) {
+#pragma unroll
+                for (int h = 0; h < H; ++h) {
+                    float e[A][4];
+#pragma unroll
+                    for (int t = 0; t < A; ++t) {
+                        if constexpr (EPL == 4) {
+                            e[t][0] = av[s][t].x; e[t][1] = av[s][t].y; e[t][2] = av[s][t].z; e[t][3] = av[s][t].w;
+                        } else {
+#pragma unroll
+                            for (int w = 0; w < 2; ++w) {
+                                const unsigned int u = __float_as_uint(av[s][t][2 * h + w]);
+                                e[t][2 * w] = __uint_as_float(u << 16); e[t][2 * w + 1] = __uint_as_float(u & 0xffff0000u);
+                            }
+                        }
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) nn[t] = fmaf(e[t][i], e[t][i], nn[t]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < Q; ++q) {
+                        const f4 qv = *reinterpret_cast<const f4 *>(qs + (((size_t)(q * nb + b) * H + h) * 64 + lane) * 4);
+#pragma unroll
+                        for (int t = 0; t < A; ++t)
+#pragma unroll
+                            for (int i = 0; i < 4; ++i) dot[q * A + t] = fmaf(e[t][i], qv[i], dot[q * A + t]);
+                    }
+                }
+            }
+            fetch(av[s]);
+            if (++b == nb) {
+                knn_store_scores<Q, A>(dot, nn, g * A, N, scores);
+                clear();
+                b = 0;
+                g += n_waves;
+                if (g >= n_groups) return;
             }
         }
     }
@@ -665,16 +754,29 @@ __global__ __launch_bounds__(256) void knn_scores_multi_kernel(const float *__re
 #define KNN_ROUNDS_MAX_N (16 * 64 * 64)
 #define KNN_SLICES_MAX 256       // stage-1 slices per query: 256 x KNN_ROUNDS_MAX_N anchors at most
 struct KnnRoundsLds {
-    float val[16][KNN_KMAX];
-    int idx[16][KNN_KMAX];
+    unsigned long long key[16][KNN_KMAX];
 };
 
-__device__ __forceinline__ void knn_wave_best(float &bv, int &bi, int &bp) {
+// An entry as one number: its value in an order-preserving form, above the complement of its index, so that the larger key is
+// the better entry (finite values; 0: a dead entry).
+typedef unsigned long long KnnKey;
+__device__ __forceinline__ KnnKey knn_key(float v, int idx) {
+    const unsigned int u = __float_as_uint(v + 0.0f);          // (-0 counts as 0)
+    return ((KnnKey)(u ^ (u & 0x80000000u ? 0xffffffffu : 0x80000000u)) << 32) | (0xffffffffu - (unsigned int)idx);
+}
+__device__ __forceinline__ float knn_key_value(KnnKey k) {
+    const unsigned int u = (unsigned int)(k >> 32);
+    return __uint_as_float(u ^ (u & 0x80000000u ? 0x80000000u : 0xffffffffu));
+}
+__device__ __forceinline__ int knn_key_index(KnnKey k) { return (int)(0xffffffffu - (unsigned int)k); }
+// the wavefront's largest key, in every lane
+__device__ __forceinline__ KnnKey knn_wave_best(KnnKey k) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const float ov = lane_xor(bv, off); const int oi = lane_xor(bi, off), op = lane_xor(bp, off);
-        if (better(ov, oi, bv, bi)) { bv = ov; bi = oi; bp = op; }
+    for (int off = 1; off < 64; off <<= 1) {
+        const KnnKey o = ((KnnKey)(unsigned int)lane_xor((int)(k >> 32), off) << 32) | (unsigned int)lane_xor((int)k, off);
+        k = o > k ? o : k;
     }
+    return k;
 }
 
 __device__ __forceinline__ int knn_rounds(const float *val, const int32_t *map, int first, int n, int K, int *taken_idx,
@@ -684,59 +786,62 @@ __device__ __forceinline__ int knn_rounds(const float *val, const int32_t *map, 
     {
         const int w0 = (int)((long long)n * wave / 16), w1 = (int)((long long)n * (wave + 1) / 16);
         const int M = (w1 - w0 + 63) >> 6;                 // <= 64
-        unsigned long long given = 0;                       // bit m: this lane's entry w0 + 64 m + lane is among the winners
+        unsigned long long given = 0;                       // bit m: this lane's entry w0 + 64 m + lane is among the winners (m >= MR)
         // the lane's first MR entries stay in registers over the rounds (slices of a few thousand scores and the
         // candidate lists have no more); entries beyond are read again in every round
         constexpr int MR = 4;
-        float rv[MR]; int rg[MR];
+        KnnKey rk[MR];
+        auto entry = [&](int i) -> KnnKey {
+            const float v = val[i];
+            if (!isfinite(v)) { anybad = 1; return 0; }
+            const int gi = map ? map[i] : first + i;
+            return gi >= 0 ? knn_key(v, gi) : 0;
+        };
 #pragma unroll
         for (int m = 0; m < MR; ++m) {
             const int i = w0 + (m << 6) + lane;
-            rv[m] = -INFINITY; rg[m] = -1;                  // a dead entry
-            if (i < w1) {
-                const float v = val[i];
-                if (!isfinite(v)) anybad = 1;
-                else { rv[m] = v; rg[m] = map ? map[i] : first + i; }
-            }
+            rk[m] = i < w1 ? entry(i) : 0;
         }
         for (int r = 0; r < K; ++r) {
-            float bv = -INFINITY; int bi = 0x7fffffff, bp = -1;
+            KnnKey mine = rk[0];
+            int far = -1;                                   // where mine comes from, past the registers
 #pragma unroll
-            for (int m = 0; m < MR; ++m)
-                if (!((given >> m) & 1ull) && rg[m] >= 0 && better(rv[m], rg[m], bv, bi)) { bv = rv[m]; bi = rg[m]; bp = w0 + (m << 6) + lane; }
+            for (int m = 1; m < MR; ++m) mine = rk[m] > mine ? rk[m] : mine;
             for (int m = MR; m < M; ++m) {
                 const int i = w0 + (m << 6) + lane;
                 if (i >= w1 || ((given >> m) & 1ull)) continue;
-                const float v = val[i];
-                if (!isfinite(v)) { anybad = 1; continue; }
-                const int gi = map ? map[i] : first + i;
-                if (gi >= 0 && better(v, gi, bv, bi)) { bv = v; bi = gi; bp = i; }
+                const KnnKey k = entry(i);
+                if (k > mine) { mine = k; far = m; }
             }
-            knn_wave_best(bv, bi, bp);                      // every lane holds the winner
-            if (bp >= 0 && ((bp - w0) & 63) == lane) given |= 1ull << ((bp - w0) >> 6);
-            if (lane == 0) { wl->val[wave][r] = bv; wl->idx[wave][r] = bi; }
+            const KnnKey best = knn_wave_best(mine);
+            if (best == mine && best != 0) {                // indices are all different: one lane
+                if (far >= 0) given |= 1ull << far;
+#pragma unroll
+                for (int m = 0; m < MR; ++m) rk[m] = rk[m] == best ? 0 : rk[m];
+            }
+            if (lane == 0) wl->key[wave][r] = best;
         }
     }
     __syncthreads();
     if (wave == 0) {
         // 16 x KNN_KMAX slots, four per lane; slots of rounds that were not played are dead
-        float cv[4]; int ci[4];
+        KnnKey ck[4];
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
-            const int c = (m << 6) + lane, w = c / KNN_KMAX, r = c % KNN_KMAX;
-            const bool live = r < K;
-            cv[m] = live ? wl->val[w][r] : -INFINITY;
-            ci[m] = live ? wl->idx[w][r] : 0x7fffffff;
+            const int c = (m << 6) + lane;
+            ck[m] = c % KNN_KMAX < K ? wl->key[c / KNN_KMAX][c % KNN_KMAX] : 0;
         }
-        unsigned int given = 0;
         for (int r = 0; r < K; ++r) {
-            float bv = -INFINITY; int bi = 0x7fffffff, bp = -1;
+            KnnKey mine = ck[0];
 #pragma unroll
-            for (int m = 0; m < 4; ++m)
-                if (!((given >> m) & 1u) && ci[m] != 0x7fffffff && better(cv[m], ci[m], bv, bi)) { bv = cv[m]; bi = ci[m]; bp = (m << 6) + lane; }
-            knn_wave_best(bv, bi, bp);
-            if (bp >= 0 && (bp & 63) == lane) given |= 1u << (bp >> 6);
-            if (lane == 0) { taken_idx[r] = bi; taken_val[r] = bv; }
+            for (int m = 1; m < 4; ++m) mine = ck[m] > mine ? ck[m] : mine;
+            const KnnKey best = knn_wave_best(mine);
+#pragma unroll
+            for (int m = 0; m < 4; ++m) ck[m] = ck[m] == best ? 0 : ck[m];
+            if (lane == 0) {
+                taken_idx[r] = best ? knn_key_index(best) : 0x7fffffff;
+                taken_val[r] = best ? knn_key_value(best) : -INFINITY;
+            }
         }
     }
     __syncthreads();

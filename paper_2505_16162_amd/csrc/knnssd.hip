@@ -980,32 +980,42 @@ extern "C" int32_t knnssd_prefill(knnssd_ctx *ctx, const int32_t *tokens_host, i
     return prefill_impl(ctx, tokens_host, n, last_hidden_dev, first_token_out);
 }
 
-// the scan of the anchor table for nq <= KNN_QMAX queries at once, in the table's storage type
-static void launch_scan(knnssd_ctx *c, const float *queries, int nq, float *scores) {
+// The scan of the anchor table for nq <= KNN_QMAX queries at once, in the table's storage type. Which kernel, whole K-best
+// calls over 5120 elements in us, knn_scores_multi_kernel / knn_scores_stream_kernel: one query takes the first (200 000 anchors bf16 353 /
+// 355, fp32 640 / 657); two to four queries bf16 397 / 360, 456 / 378, 538 / 384, fp32 688 / 663, 701 / 679, 747 / 685. Fewer
+// anchors: 20 000 bf16 104 / 92 with four queries, 94 / 88 with two, fp32 132 / 128 and 116 / 125 (a round and a quarter of
+// wavefronts); 8192 bf16 74 / 71 and 71 / 68, fp32 88 / 84 and 79 / 82.
+template <int Q, typename AT> static int32_t launch_scan_t(knnssd_ctx *c, const float *queries, float *scores) {
     const int N = c->n_anchors, D = c->cfg.d_model;
+    const AT *a = (const AT *)c->anchors;
+    const size_t lds = knn_stream_lds<AT>(Q, D);
+    if constexpr (Q >= 2) if (N >= (sizeof(AT) == 2 ? 8192 : 32768) && lds <= KS_MAX_DYN_LDS) {
+        HIP_TRY(hipFuncSetAttribute((const void *)knn_scores_stream_kernel<Q, AT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        hipLaunchKernelGGL((knn_scores_stream_kernel<Q, AT>), dim3(KS_NWG), dim3(KNN_STREAM_NT), lds, c->stream, queries, a, N, D, scores);
+        return KNNSSD_OK;
+    }
     int wgs = (N + 3) / 4;
     if (wgs > 4096) wgs = 4096;
-    const dim3 g(wgs), b(256);
-    if (c->anchor_dtype == KNNSSD_BF16) {
-        const bf16_t *a = (const bf16_t *)c->anchors;
-        if (nq == 1) hipLaunchKernelGGL((knn_scores_multi_kernel<1, bf16_t>), g, b, 0, c->stream, queries, a, N, D, scores);
-        else if (nq == 2) hipLaunchKernelGGL((knn_scores_multi_kernel<2, bf16_t>), g, b, 0, c->stream, queries, a, N, D, scores);
-        else if (nq == 3) hipLaunchKernelGGL((knn_scores_multi_kernel<3, bf16_t>), g, b, 0, c->stream, queries, a, N, D, scores);
-        else hipLaunchKernelGGL((knn_scores_multi_kernel<4, bf16_t>), g, b, 0, c->stream, queries, a, N, D, scores);
-    } else {
-        const float *a = (const float *)c->anchors;
-        if (nq == 1) hipLaunchKernelGGL((knn_scores_multi_kernel<1, float>), g, b, 0, c->stream, queries, a, N, D, scores);
-        else if (nq == 2) hipLaunchKernelGGL((knn_scores_multi_kernel<2, float>), g, b, 0, c->stream, queries, a, N, D, scores);
-        else if (nq == 3) hipLaunchKernelGGL((knn_scores_multi_kernel<3, float>), g, b, 0, c->stream, queries, a, N, D, scores);
-        else hipLaunchKernelGGL((knn_scores_multi_kernel<4, float>), g, b, 0, c->stream, queries, a, N, D, scores);
+    hipLaunchKernelGGL((knn_scores_multi_kernel<Q, AT>), dim3(wgs), dim3(256), 0, c->stream, queries, a, N, D, scores);
+    return KNNSSD_OK;
+}
+template <typename AT> static int32_t launch_scan_q(knnssd_ctx *c, const float *queries, int nq, float *scores) {
+    switch (nq) {
+        case 1: return launch_scan_t<1, AT>(c, queries, scores);
+        case 2: return launch_scan_t<2, AT>(c, queries, scores);
+        case 3: return launch_scan_t<3, AT>(c, queries, scores);
+        default: return launch_scan_t<4, AT>(c, queries, scores);
     }
+}
+static int32_t launch_scan(knnssd_ctx *c, const float *queries, int nq, float *scores) {
+    return c->anchor_dtype == KNNSSD_BF16 ? launch_scan_q<bf16_t>(c, queries, nq, scores) : launch_scan_q<float>(c, queries, nq, scores);
 }
 
 static int32_t select_impl(knnssd_ctx *c, const float *query_dev, int32_t *idx_out, int32_t *dom_out) {
     const int N = c->n_anchors, D = c->cfg.d_model;
     float *scores = c->wsp<float>(c->L.knn_scores);
     KnnResult *res = c->wsp<KnnResult>(c->L.knn);
-    launch_scan(c, query_dev, 1, scores);
+    KS_TRY(launch_scan(c, query_dev, 1, scores));
     hipLaunchKernelGGL(knn_argmax_kernel, dim3(1), dim3(1024), 0, c->stream, scores, query_dev, c->labels, N, D, res);
     HIP_TRY(hipGetLastError());
     KS_TRY(read_back(c, res, sizeof(KnnResult)));
@@ -1033,7 +1043,7 @@ extern "C" int32_t knnssd_knn_topk(knnssd_ctx *ctx, const float *queries_dev, in
     for (int q0 = 0; q0 < n_queries; q0 += KNN_QMAX) {
         const int nq = n_queries - q0 < KNN_QMAX ? n_queries - q0 : KNN_QMAX;
         const float *qp = queries_dev + (size_t)q0 * D;
-        launch_scan(ctx, qp, nq, scores);
+        KS_TRY(launch_scan(ctx, qp, nq, scores));
         int n_slices = N / 2048;                      // stage 1 slices per query: a few thousand scores each
         if (n_slices < 1) n_slices = 1;
         if (n_slices > KNN_SLICES_MAX) n_slices = KNN_SLICES_MAX;

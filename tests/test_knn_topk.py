@@ -156,3 +156,39 @@ def test_gpu_scan_of_a_large_table_matches_oracle(dtype):
         a1, d1, m1 = gpu.knnssd_select_skipset(queries[i])
         assert (a1, d1, m1) == (n_star, d_star, mask.tolist())
     gpu.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,n,d", [("bf16", 8191, 264), ("bf16", 8192, 264), ("bf16", 8195, 1000), ("bf16", 9001, 8), ("bf16", 16385, 512), ("bf16", 33000, 520),
+                                       ("fp32", 32767, 72), ("fp32", 32768, 256), ("fp32", 32771, 264), ("fp32", 40002, 520)])
+def test_gpu_scan_kernels_agree(dtype, n, d):
+    """Around the sizes from which several queries take the streaming scan: rows in whole and broken blocks, tables that end within
+    a wavefront's four anchors, fewer and more groups of them than wavefronts. Every query gets the same bits alone (the
+    other kernel) as among two, three or four; against 64 bits; a non-finite anchor is met in both."""
+    from paper_2505_16162_amd import binding
+    shape = synth.small_shape("knn_scan", n_blocks=1, d_model=d, max_seq=64)
+    gpu = binding.KnnSsd(shape, synth.make_weights(shape, seed=4), max_anchors=n)
+    anchors, labels, centres = synth.make_anchors(d, n, 5, 1.0, seed=31)
+    if dtype == "bf16":
+        anchors = anchors.to(torch.bfloat16)
+    masks = synth.make_block_masks(1, 5, 0, seed=6)
+    gpu.knnssd_set_anchors(anchors, labels, masks)
+    queries = torch.stack([synth.make_domain_query(centres, i % 5, 1.0, seed=800 + i) for i in range(4)])
+    a64 = anchors.double()
+    want = (a64 @ queries.double().T / a64.norm(dim=1, keepdim=True)) / queries.double().norm(dim=1)
+    one = [gpu.knnssd_knn_topk(queries[i:i + 1], 9) for i in range(4)]
+    for nq in (2, 3, 4):
+        idx, cos, dom = gpu.knnssd_knn_topk(queries[:nq], 9)
+        for i in range(nq):
+            assert (idx[i], cos[i], dom[i]) == (one[i][0][0], one[i][1][0], one[i][2][0]), (nq, i)
+    for i in range(4):
+        # fp32 sums of d terms of either sign: a few units in the last place of the score
+        assert np.allclose(one[i][1][0], want[one[i][0][0], i].numpy(), atol=2e-6)
+        assert np.allclose(one[i][1][0], torch.topk(want[:, i], 9).values.numpy(), atol=2e-6)
+    bad = anchors.clone()
+    bad[n - 1, d - 1] = float("inf")
+    gpu.knnssd_set_anchors(bad, labels, masks)
+    for nq in (1, 3):
+        with pytest.raises(binding.KnnSsdError):
+            gpu.knnssd_knn_topk(queries[:nq], 2)
+    gpu.close()
