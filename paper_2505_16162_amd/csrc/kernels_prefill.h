@@ -24,7 +24,7 @@
 namespace ks {
 
 constexpr int PF_NT = 512;             // threads per workgroup of the prefill GEMM (8 wavefronts)
-constexpr int PF_RT = 1024;            // ... and of the row kernels between the products
+constexpr int PF_RT = 1024;            // ... and of the row kernels between the products (at most, where columns are on their own)
 constexpr int PF_NP = 3;               // bf16 planes of an activation
 
 struct PfArgs {
@@ -194,22 +194,31 @@ __device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v,
 // pipe 55 % busy, two groups one phase apart 80 %. 13B-shaped, 4096 rows: QKV 1.52-1.55 ms (with its own sums, below),
 // gate+up 2.26-2.33, O 0.44, down 1.12. 128 x 64 (few rows): operand reads out of LDS about as much as the weight stream: a 4 x 2 grid
 // of wavefronts reads 8 KB a wavefront and step, 8 x 1 reads 13 (7B, 45 rows, gate+up unsplit 79 -> 75 us); 5-6 us of a
-// launch are its fixed cost. Which tile a matrix and a length take: pf_plan.
+// launch are its fixed cost. Half of the wavefronts request the weights and half the activations, so that the weights run five steps
+// ahead and the activations three, and the operands of the next step are read under the matrix instructions of this one: whole prompts
+// of 45 rows 7B 777 -> 761, 13B 1056 -> 1001, Qwen 1160 -> 1099 us. (Three steps of both 1031 and four 1005 us at 13B; six and
+// two 1348; the steps in the order in which the units lie in memory: no faster.) Which tile a matrix and a length take: pf_plan.
 // PP: the wavefronts form two groups (one wavefront of each on every SIMD) that run one phase apart: while one group
 // issues its matrix instructions the other reads its operands from LDS.
-template <int TA, int TB, int WA, int NS, bool PP>
+template <int TA, int TB, int WA, int NSA, int NSB, bool PP>
 struct PfShape {
     static constexpr int WB = 8 / WA, TAW = TA / WA, TBW = TB / WB;
     static constexpr int TM = TA * 16;
-    static constexpr int A_BYTES = TA * 1024, STAGE = A_BYTES + PF_NP * TB * 1024;
-    static constexpr int NA = TA * 64 / PF_NT;                   // weight pieces per thread and step
-    static constexpr int NB = (PF_NP * TB + 7) / 8;              // token fragments per wavefront and step
-    static constexpr size_t LDS = (size_t)NS * STAGE;
+    static constexpr int A_BYTES = TA * 1024, B_BYTES = PF_NP * TB * 1024;      // a step's weights and activations in LDS
+    // PP: a step's two side by side; otherwise each kind on its own, as their buffers differ in number
+    static constexpr int A_NEXT = PP ? A_BYTES + B_BYTES : A_BYTES, B0 = PP ? A_BYTES : NSA * A_BYTES, B_NEXT = PP ? A_BYTES + B_BYTES : B_BYTES;
+    // pieces per thread (fragments per wavefront) and step. PP: every wavefront takes weights and activations; otherwise the first
+    // four take the weights, the others the activations: a wavefront's loads return in order, so this is what lets the
+    // weights be requested further ahead than the activations.
+    static constexpr int NA = PP ? TA / 8 : TA / 4, NB = PP ? (PF_NP * TB + 7) / 8 : PF_NP * TB / 4;
+    static constexpr size_t LDS = (size_t)NSA * A_BYTES + NSB * B_BYTES;
 };
 
-template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN>
+template <int TA, int TB, int WA, int NSA, int NSB, bool PP, int EPI, bool OWN>
 __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(PfArgs a) {
-    typedef PfShape<TA, TB, WA, NS, PP> Sh;
+    typedef PfShape<TA, TB, WA, NSA, NSB, PP> Sh;
+    static_assert(!PP || NSA == NSB, "one count of buffers");
+    constexpr int NS = NSA;
     constexpr int TAW = Sh::TAW, TBW = Sh::TBW, TM = Sh::TM;
     extern __shared__ __align__(16) char lds[];
     const GemmOp &op = a.op;
@@ -239,7 +248,7 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
     unsigned int ar[Sh::NA];
 #pragma unroll
     for (int q = 0; q < Sh::NA; ++q) {
-        const PfRow r = a.rows[mt * TM + (wave + q * 8) * 16 + r16];
+        const PfRow r = a.rows[mt * TM + (PP ? wave + q * 8 : (wave & 3) * Sh::NA + q) * 16 + r16];
         ar[q] = r.y;
         ap[q] = op.W + ((size_t)r.x + kg * (r.y & 0xffffu)) * 8;
     }
@@ -248,9 +257,9 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
     unsigned int bdst[Sh::NB];
 #pragma unroll
     for (int q = 0; q < Sh::NB; ++q) {
-        const int f = min(wave + q * 8, PF_NP * TB - 1), pl = f / TB, t = f - pl * TB;    // a repeat writes the same bytes again
+        const int f = PP ? min(wave + q * 8, PF_NP * TB - 1) : (wave & 3) * Sh::NB + q, pl = f / TB, t = f - pl * TB;    // a repeat writes the same bytes again
         bsrc[q] = reinterpret_cast<const char *>(a.frag_in + frag_off(KS, a.TT, pl, st0, min(tt0 + t, a.TT - 1)));
-        bdst[q] = Sh::A_BYTES + f * 1024;
+        bdst[q] = Sh::B0 + f * 1024;
     }
     const size_t bstep = (size_t)a.TT * 1024;
     const unsigned int voff = lane * 16;
@@ -262,12 +271,12 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
     };
     auto issue_b = [&](int t, int buf) {           // activations of step st0 + t into LDS buffer buf
 #pragma unroll
-        for (int q = 0; q < Sh::NB; ++q) dma_linear(bsrc[q] + t * bstep, voff, l0 + buf * Sh::STAGE + bdst[q]);
+        for (int q = 0; q < Sh::NB; ++q) dma_linear(bsrc[q] + t * bstep, voff, l0 + buf * Sh::B_NEXT + bdst[q]);
     };
     auto issue_a = [&](int t, int buf) {           // ... and its weights as they are
 #pragma unroll
         for (int q = 0; q < Sh::NA; ++q) {
-            const unsigned int d = l0 + buf * Sh::STAGE + (wave + q * 8) * 1024;
+            const unsigned int d = l0 + buf * Sh::A_NEXT + (PP ? wave + q * 8 : (wave & 3) * Sh::NA + q) * 1024;
             if (once) dma_lane_nt(weight_piece(t, q), d);
             else dma_lane(weight_piece(t, q), d);
         }
@@ -277,18 +286,19 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
     for (int i = 0; i < TAW; ++i)
 #pragma unroll
         for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-    const char *la = lds + wa * TAW * 1024 + voff, *lb = lds + Sh::A_BYTES + wb * TBW * 1024 + voff;
+    const char *la = lds + wa * TAW * 1024 + voff, *lb = lds + Sh::B0 + wb * TBW * 1024 + voff;
     constexpr int JC = TBW < 2 ? TBW : 2, CL = TBW / JC;       // token tiles per cluster of matrix instructions, clusters per step
-    u32x4 av[TAW], bv[JC][PF_NP];
-    auto read_a = [&](int buf) {
+    constexpr int SETS = PP ? 1 : 2;                           // operands of two steps in registers: the next one's are read under this one's matrix instructions
+    u32x4 avs[SETS][TAW], bvs[SETS][JC][PF_NP];
+    auto read_a = [&](int buf, int set = 0) {
 #pragma unroll
-        for (int i = 0; i < TAW; ++i) av[i] = *reinterpret_cast<const u32x4 *>(la + buf * Sh::STAGE + i * 1024);
+        for (int i = 0; i < TAW; ++i) avs[set][i] = *reinterpret_cast<const u32x4 *>(la + buf * Sh::A_NEXT + i * 1024);
     };
-    auto read_b = [&](int buf, int c) {
+    auto read_b = [&](int buf, int c, int set = 0) {
 #pragma unroll
         for (int jj = 0; jj < JC; ++jj)
 #pragma unroll
-            for (int p = 0; p < PF_NP; ++p) bv[jj][p] = *reinterpret_cast<const u32x4 *>(lb + buf * Sh::STAGE + (p * TB + c * JC + jj) * 1024);
+            for (int p = 0; p < PF_NP; ++p) bvs[set][jj][p] = *reinterpret_cast<const u32x4 *>(lb + buf * Sh::B_NEXT + (p * TB + c * JC + jj) * 1024);
     };
     // OWN: a step's three planes are summed on their own, from the lowest up, and then added to the running sums: one rounding at
     // the size of the whole sum per 32 columns instead of three. For the QKV rows, whose keys and values the cache rounds to
@@ -308,7 +318,9 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
         }
     };
     auto settle = [&](int c) { add(c, NG - 1); };
-    auto mfma_cluster = [&](int c) {
+    auto mfma_cluster = [&](int c, int set = 0) {
+        const auto &av = avs[set];
+        const auto &bv = bvs[set];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
 #pragma unroll
@@ -335,13 +347,24 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
 #pragma unroll
         for (int k = 0; k < GR; ++k) own[(NG - 1) & 1][k] = f32x4{0.f, 0.f, 0.f, 0.f};     // nothing to settle before the first step
 
-    // the first NS - 1 steps (a step past the end repeats the last one, here and below: the loads stay countable)
+    // the first steps (a step past the end repeats the last one, here and below: the loads stay countable)
+    const bool takes_a = wave < 4;
+    if constexpr (PP) {
 #pragma unroll
-    for (int t = 0; t < NS - 1; ++t) {
-        issue_a(min(t, cnt - 1), t);
-        issue_b(min(t, cnt - 1), t);
+        for (int t = 0; t < NS - 1; ++t) {
+            issue_a(min(t, cnt - 1), t);
+            issue_b(min(t, cnt - 1), t);
+        }
+        dma_wait<0>();
+    } else if (takes_a) {
+#pragma unroll
+        for (int t = 0; t < NSA; ++t) issue_a(min(t, cnt - 1), t);
+        dma_wait<(NSA - 1) * Sh::NA>();
+    } else {
+#pragma unroll
+        for (int t = 0; t < NSB; ++t) issue_b(min(t, cnt - 1), t);
+        dma_wait<(NSB - 1) * Sh::NB>();
     }
-    dma_wait<0>();
     pf_meet();
     if constexpr (PP) {
         // Phases of a group: read operands | meet | matrix instructions | meet. The second group enters one phase later.
@@ -378,20 +401,27 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
         }
         if (wa == 0) pf_meet();
     } else {
-        int buf = 0;
-        for (int t = 0; t < cnt; ++t) {
-            if (t > 0) { dma_wait<(NS - 2) * (Sh::NA + Sh::NB)>(); pf_meet(); }      // step t has arrived; every wavefront is done with step t-1
-            const int nb = buf == 0 ? NS - 1 : buf - 1;
-            issue_a(min(t + NS - 1, cnt - 1), nb);
-            issue_b(min(t + NS - 1, cnt - 1), nb);
-            read_a(buf);
-#pragma unroll
-            for (int c = 0; c < CL; ++c) {
-                read_b(buf, c);
-                if constexpr (OWN) settle(c == 0 ? CL - 1 : c - 1);
-                mfma_cluster(c);
-            }
-            buf = buf == NS - 1 ? 0 : buf + 1;
+        static_assert(CL == 1, "a step's operands are read together");
+        int ba = 0, bb = 0;                                // buffers of the step whose operands are read
+        read_a(0, 0);
+        read_b(0, 0, 0);
+        auto step = [&](int t, auto set) {                 // matrix instructions of step t, operands of step t + 1
+            constexpr int S = decltype(set)::value;
+            if (takes_a) dma_wait<(NSA - 2) * Sh::NA>();   // step t + 1 has arrived
+            else dma_wait<(NSB - 2) * Sh::NB>();
+            pf_meet();                                     // ... and every wavefront has its operands of step t
+            if (takes_a) issue_a(min(t + NSA, cnt - 1), ba);
+            else issue_b(min(t + NSB, cnt - 1), bb);
+            ba = ba == NSA - 1 ? 0 : ba + 1;
+            bb = bb == NSB - 1 ? 0 : bb + 1;
+            if constexpr (OWN) settle(0);
+            read_a(ba, S ^ 1);
+            read_b(bb, 0, S ^ 1);
+            mfma_cluster(0, S);
+        };
+        for (int t = 0; t < cnt; t += 2) {
+            step(t, std::integral_constant<int, 0>{});
+            if (t + 1 < cnt) step(t + 1, std::integral_constant<int, 1>{});
         }
     }
     if constexpr (OWN) settle(CL - 1);
@@ -448,8 +478,13 @@ struct PfRowArgs {
     int TT;
 };
 
-// the workgroup's token: tiles of 16 tokens are dealt to the dies, a die's consecutive workgroups take a tile's rows
-__device__ __forceinline__ int pf_row_token() {
+// The workgroup's token: tiles of 16 tokens are dealt to the dies, a die's consecutive workgroups take a tile's rows. The rows of up
+// to PF_SPREAD tiles are dealt to the dies singly, since most dies would be idle otherwise (7B, 20 / 45 / 64 rows 718 / 767 / 829
+// -> 682 / 743 / 784 us; 100 rows 942 -> 950, 13B 200 rows 1913 -> 1966: there the lines put together count).
+constexpr int PF_SPREAD = 4;
+inline unsigned int pf_row_grid(int n_tok, int tiles) { return tiles <= PF_SPREAD ? n_tok : (tiles + 7) / 8 * 128; }
+__device__ __forceinline__ int pf_row_token(int n_tok) {
+    if (n_tok <= PF_SPREAD * 16) return blockIdx.x;
     const int die = blockIdx.x & 7, i = blockIdx.x >> 3;
     return ((i >> 4) * 8 + die) * 16 + (i & 15);
 }
@@ -484,7 +519,7 @@ __device__ __forceinline__ int pf_pair_col(int p, int TM) {
 template <bool EMBED>
 __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
     __shared__ float shares[PF_RT / 64];
-    const int tok = pf_row_token();
+    const int tok = pf_row_token(a.n_tok);
     if (tok >= a.n_tok) return;
     float sq = 0.f;
     for (int n = threadIdx.x * 4; n < a.d; n += PF_RT * 4) {
@@ -518,9 +553,9 @@ __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
 
 // SwiGLU of a gate+up product's K parts; gridDim.y workgroups per row
 __global__ __launch_bounds__(PF_RT) void prefill_u_row_kernel(PfRowArgs a) {
-    const int tok = pf_row_token();
+    const int tok = pf_row_token(a.n_tok);
     if (tok >= a.n_tok) return;
-    for (int n = (blockIdx.y * PF_RT + threadIdx.x) * 4; n < a.d; n += gridDim.y * PF_RT * 4) {
+    for (int n = (blockIdx.y * blockDim.x + threadIdx.x) * 4; n < a.d; n += gridDim.y * blockDim.x * 4) {
         const int c = pf_pair_col(n, a.TM);
         store_frag4(a.frag, a.d >> 5, a.TT, tok >> 4, tok & 15, n, pf_swiglu(pf_sum_parts(a, tok, c), pf_sum_parts(a, tok, c + 16)));
     }
@@ -528,10 +563,10 @@ __global__ __launch_bounds__(PF_RT) void prefill_u_row_kernel(PfRowArgs a) {
 
 // rotary embedding, queries and cache entries from the K parts of a split QKV product (n_mr: its row tiles of rotary pairs)
 __global__ __launch_bounds__(PF_RT) void prefill_qkv_row_kernel(PfRowArgs a, int n_mr) {
-    const int tok = pf_row_token();
+    const int tok = pf_row_token(a.n_tok);
     if (tok >= a.n_tok) return;
     const int P = (a.op.H + a.op.Hkv) * (a.op.hd >> 1), VR = a.op.Hkv * a.op.hd;
-    for (int i = (blockIdx.y * PF_RT + threadIdx.x) * 4; i < P + VR; i += gridDim.y * PF_RT * 4) {     // gridDim.y workgroups per row
+    for (int i = (blockIdx.y * blockDim.x + threadIdx.x) * 4; i < P + VR; i += gridDim.y * blockDim.x * 4) {     // gridDim.y workgroups per row
         if (i < P) {
             const int c = pf_pair_col(i, a.TM);
             const f32x4 x0 = pf_sum_parts(a, tok, c), x1 = pf_sum_parts(a, tok, c + 16);

@@ -206,17 +206,17 @@ struct knnssd_ctx {
 };
 
 // The prefill GEMM's builds: f(token tiles, epilogue, own sums, kernel, dynamic LDS) for each
-template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN, typename F> static void pf_build(F f) {
-    f(TB, EPI, OWN, prefill_gemm_kernel<TA, TB, WA, NS, PP, EPI, OWN>, PfShape<TA, TB, WA, NS, PP>::LDS);
+template <int TA, int TB, int WA, int NSA, int NSB, bool PP, int EPI, bool OWN, typename F> static void pf_build(F f) {
+    f(TB, EPI, OWN, prefill_gemm_kernel<TA, TB, WA, NSA, NSB, PP, EPI, OWN>, PfShape<TA, TB, WA, NSA, NSB, PP>::LDS);
 }
 template <typename F> static void pf_each_build(F f) {
-    pf_build<16, 16, 2, 2, true, PF_PARTS, false>(f);
-    pf_build<16, 16, 2, 2, true, PF_PARTS, true>(f);
-    pf_build<16, 16, 2, 2, true, PF_SWIGLU, false>(f);
-    pf_build<16, 16, 2, 2, true, PF_ROPE, true>(f);
-    pf_build<16, 8, 2, 3, true, PF_PARTS, false>(f);
-    pf_build<16, 8, 2, 3, true, PF_PARTS, true>(f);
-    pf_build<8, 4, 4, 3, false, PF_PARTS, true>(f);
+    pf_build<16, 16, 2, 2, 2, true, PF_PARTS, false>(f);
+    pf_build<16, 16, 2, 2, 2, true, PF_PARTS, true>(f);
+    pf_build<16, 16, 2, 2, 2, true, PF_SWIGLU, false>(f);
+    pf_build<16, 16, 2, 2, 2, true, PF_ROPE, true>(f);
+    pf_build<16, 8, 2, 3, 3, true, PF_PARTS, false>(f);
+    pf_build<16, 8, 2, 3, 3, true, PF_PARTS, true>(f);
+    pf_build<8, 4, 4, 5, 3, false, PF_PARTS, true>(f);
 }
 static hipError_t pf_set_lds_limits() {
     hipError_t e = hipSuccess;
@@ -818,7 +818,9 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn;
     const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd, TT = c->L.pf_tt, TTL = (n_tok + 15) / 16;
-    const dim3 rows((TTL + 7) / 8 * 128);        // row kernels: see pf_row_token
+    const dim3 rows(pf_row_grid(n_tok, TTL));
+    // few rows: smaller workgroups reach more units (7B, 45 rows: SwiGLU 11.6 -> 7.2 us, QKV 7.2 -> 5.2; Qwen, 777 rows: 37 -> 40, 16.0 -> 13.4)
+    const int u_nt = TTL <= PF_SPREAD ? 256 : PF_RT;
     hipStream_t s = c->stream;
     float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *rstd = c->wsp<float>(c->L.pf_rstd);
     bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att), *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
@@ -869,7 +871,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         if (plan[PF_QKV].parts(PF_QKV)) {
             PfRowArgs r = row_args(PF_QKV, 0);
             r.op = o;
-            hipLaunchKernelGGL(prefill_qkv_row_kernel, dim3(rows.x, ((H + Hkv) * hd / 2 + Hkv * hd + 4 * PF_RT - 1) / (4 * PF_RT)), dim3(PF_RT), 0, s, r, plan[PF_QKV].n_mr);
+            hipLaunchKernelGGL(prefill_qkv_row_kernel, dim3(rows.x, ((H + Hkv) * hd / 2 + Hkv * hd + 1023) / 1024), dim3(256), 0, s, r, plan[PF_QKV].n_mr);
         }
         PfAttn at{};
         at.q = q; at.kv_block = kvb; at.frag_out = frag_att; at.H = H; at.Hkv = Hkv; at.max_seq = g.max_seq; at.n_tok = n_tok; at.TT = TT;
@@ -885,7 +887,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         if (plan[PF_GU].parts(PF_GU)) {
             PfRowArgs ru = row_args(PF_GU, F);
             ru.frag = frag_u;
-            hipLaunchKernelGGL(prefill_u_row_kernel, dim3(rows.x, (F + 4 * PF_RT - 1) / (4 * PF_RT)), dim3(PF_RT), 0, s, ru);
+            hipLaunchKernelGGL(prefill_u_row_kernel, dim3(rows.x, (F + 4 * u_nt - 1) / (4 * u_nt)), dim3(u_nt), 0, s, ru);
         }
         GemmOp dn = base;
         dn.type = OP_RESID; dn.W = (const bf16_t *)c->wdown[b]; dn.N = d; dn.K = F; dn.split = c->split_down;
