@@ -94,13 +94,9 @@ __device__ __forceinline__ float wave_max(float v) {
 // ------------------------------------------------------------------------------------------
 // pass control
 // ------------------------------------------------------------------------------------------
-struct TokArgs { int32_t t[KS_MAX_ROWS]; };
-
-__global__ void set_pass_kernel(PassCtl *ctl, int active, int n_rows, int start, int head_from, TokArgs toks) {
-    if (threadIdx.x == 0) {
-        ctl->active = active; ctl->n_rows = n_rows; ctl->start = start; ctl->head_from = head_from;
-    }
-    if (threadIdx.x < KS_MAX_ROWS) ctl->tok[threadIdx.x] = toks.t[threadIdx.x];
+__global__ void set_pass_kernel(PassCtl *ctl, PassCtl value) {
+    static_assert(sizeof(PassCtl) % 4 == 0 && sizeof(PassCtl) <= 256, "a word per thread");
+    if (threadIdx.x < sizeof(PassCtl) / 4) reinterpret_cast<int *>(ctl)[threadIdx.x] = reinterpret_cast<const int *>(&value)[threadIdx.x];
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1000,10 +996,43 @@ __global__ void accept_kernel(GenState *st, const PassCtl *ver, const HeadResult
 }
 
 // Acceptance for a stand-alone verification call: rows tok[0..n-1] = [x_last, d_1..d_k].
-__global__ void verify_accept_kernel(const PassCtl *ver, const HeadResult *res, int32_t *out3) {
+__device__ inline void verify_accept(const PassCtl *ver, const HeadResult *res, int32_t *out3) {
     int k = ver->n_rows - 1, j = 0;
     while (j < k && ver->tok[j + 1] == res->tok[j]) ++j;
     out3[0] = j; out3[1] = res->tok[j]; out3[2] = ver->start + j + 1;
+}
+__global__ void verify_accept_kernel(const PassCtl *ver, const HeadResult *res, int32_t *out3) { verify_accept(ver, res, out3); }
+
+// What surrounds a pass. Its control block is there already, or comes from the host (set), or a verification of a generation works it
+// out (verify_begin); at its end a draft step makes draft_end, a verification accept, a verification by itself verify_accept.
+enum { ENDS_NONE = 0, ENDS_DRAFT, ENDS_VERIFY, ENDS_CHECK };
+struct PassEnds {
+    int kind = ENDS_NONE;
+    GenState *st = nullptr;
+    PassCtl *draft = nullptr;
+    int expect_k = -1;               // verify_begin
+    int32_t *out_tokens = nullptr, *flags = nullptr;     // flags: host words, [0] and [2] of draft_end, [1] of accept
+    int32_t *out3 = nullptr;         // verify_accept
+    int set = 0;                     // the control block is `ctl`
+    PassCtl ctl = {};
+};
+// The pass's control block for every workgroup of its first kernel (own: LDS); the first one leaves it for the other kernels.
+__device__ __forceinline__ const PassCtl *pass_begin(const PassEnds &e, PassCtl *ctl, PassCtl *own) {
+    if (e.kind != ENDS_VERIFY && !e.set) return ctl;
+    if (threadIdx.x == 0) {
+        if (e.set) *own = e.ctl;
+        else verify_begin(e.st, e.draft, own, e.expect_k);
+        if (blockIdx.x == 0) *ctl = *own;
+    }
+    __syncthreads();
+    return own;
+}
+// The pass's last step, by one thread (res is not looked at if the pass did not run). seen: what pass_begin returned, where this
+// is the same kernel (in memory the first workgroup may have left it a moment ago).
+__device__ __forceinline__ void pass_end(const PassEnds &e, PassCtl *ctl, const PassCtl *seen, const HeadResult *res) {
+    if (e.kind == ENDS_DRAFT) draft_end(e.st, ctl, res, e.flags);
+    else if (e.kind == ENDS_VERIFY) accept(e.st, seen, res, e.out_tokens, e.flags + 1);
+    else if (e.kind == ENDS_CHECK) verify_accept(seen, res, e.out3);
 }
 
 }  // namespace ks

@@ -43,17 +43,6 @@ struct SmallBlock {              // addresses as numbers: see as_global
     uint64_t attn_norm, mlp_norm, wqkv, wo, wgu, wdown;
 };
 
-// What surrounds a pass of a generation: a draft step ends with draft_end, a verification starts with verify_begin and
-// ends with accept.
-enum { ENDS_NONE = 0, ENDS_DRAFT, ENDS_VERIFY };
-struct PassEnds {
-    int kind = ENDS_NONE;
-    GenState *st = nullptr;
-    PassCtl *draft = nullptr;
-    int expect_k = -1;               // verify_begin
-    int32_t *out_tokens = nullptr, *flags = nullptr;     // flags: host words, [0] and [2] of draft_end, [1] of accept
-};
-
 struct SmallArgs {
     PassCtl *ctl;
     PassEnds ends;
@@ -204,21 +193,10 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wg = blockIdx.x;
     if (wg == 0 && tid == 0) a.meets[(a.launch + SM_MEETS / 2) % SM_MEETS] = SmallMeet{MEET_OPEN, 0};     // for a later launch
     SmallMeet *const meet = a.meets + a.launch;
-    const PassCtl *ctl = a.ctl;
-    if (a.ends.kind == ENDS_VERIFY) {
-        // everybody works out the pass for itself; the state it is taken from changes when the whole pass is over
-        if (tid == 0) {
-            verify_begin(a.ends.st, a.ends.draft, &sl.ctl, a.ends.expect_k);
-            if (wg == 0) *a.ctl = sl.ctl;
-        }
-        __syncthreads();
-        ctl = &sl.ctl;
-    }
+    // (the state that a verification is taken from changes when the whole pass is over)
+    const PassCtl *ctl = pass_begin(a.ends, a.ctl, &sl.ctl);
     if (!ctl->active) {
-        if (wg == 0 && tid == 0) {
-            if (a.ends.kind == ENDS_DRAFT) draft_end(a.ends.st, a.ctl, a.head, a.ends.flags);
-            if (a.ends.kind == ENDS_VERIFY) accept(a.ends.st, &sl.ctl, a.head, a.ends.out_tokens, a.ends.flags + 1);
-        }
+        if (wg == 0 && tid == 0) pass_end(a.ends, a.ctl, ctl, a.head);
         return;
     }
     const int n_rows = min(ctl->n_rows, MR), start = ctl->start, head_from = ctl->head_from;
@@ -446,8 +424,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         }
         __syncthreads();
         if (tid == 0) {
-            if (a.ends.kind == ENDS_DRAFT) draft_end(a.ends.st, a.ctl, &sl.head, a.ends.flags);
-            if (a.ends.kind == ENDS_VERIFY) accept(a.ends.st, &sl.ctl, &sl.head, a.ends.out_tokens, a.ends.flags + 1);
+            pass_end(a.ends, a.ctl, ctl, &sl.head);
             if (n_wg > 1) __hip_atomic_fetch_add(&meet->left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return;

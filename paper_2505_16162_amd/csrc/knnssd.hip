@@ -627,7 +627,7 @@ static const float *next_gain(const knnssd_ctx *c, const uint8_t *mask, int afte
 // activations); false: verification / prefill (up to 16 rows on the matrix cores, activations as
 // three bf16 planes). want_head = false skips the LM head (prefill chunks before the last).
 // start: the position of the pass's first row as the host knows it (the control block will hold the same number).
-static int32_t run_pass_bf16(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, bool rows1, bool want_head, int n_rows, int start) {
+static int32_t run_pass_bf16(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, bool rows1, bool want_head, int n_rows, int start, const PassEnds &ends) {
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn;
     const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd;
@@ -694,8 +694,8 @@ static int32_t run_pass_bf16(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, b
     e.type = OP_EMBED; e.N = d; e.embed = (const bf16_t *)c->embed; e.x = x; e.gain_next = next_gain(c, mask, -1);
     e.act_out = act_d; e.ss_out = ss; e.n_rows = n_rows; e.out_kc = kc_next(-1);
     if (!others) {
-    } else if (rows1) hipLaunchKernelGGL((embed_producer_kernel<false>), dim3(KS_NWG), dim3(NT), 0, s, e, ctl);
-    else hipLaunchKernelGGL((embed_producer_kernel<true>), dim3(KS_NWG), dim3(NT), 0, s, e, ctl);
+    } else if (rows1) hipLaunchKernelGGL((embed_producer_kernel<false>), dim3(KS_NWG), dim3(NT), 0, s, e, ctl, ends);
+    else hipLaunchKernelGGL((embed_producer_kernel<true>), dim3(KS_NWG), dim3(NT), 0, s, e, ctl, ends);
 
     AttnArgs aa{};
     aa.q = qrot; aa.partial = c->wsp<float>(c->L.attn_part); aa.H = H; aa.Hkv = Hkv; aa.hd = hd; aa.max_seq = g.max_seq; aa.group = H / Hkv;
@@ -767,8 +767,7 @@ static int32_t run_pass_bf16(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, b
         h.ss_in = ss; h.logits = c->wsp<float>(c->L.logits); h.head_part = c->wsp<HeadPartial>(c->L.head_part);
         h.split = c->split_head;
         launch(h);
-        if (others) hipLaunchKernelGGL(head_final_kernel, dim3(KS_MAX_ROWS), dim3(NT), 0, s, c->wsp<HeadPartial>(c->L.head_part), KS_NWG,
-                           ctl, c->wsp<HeadResult>(c->L.head));
+        if (others) hipLaunchKernelGGL(head_final_kernel, dim3(1), dim3(NT), 0, s, c->wsp<HeadPartial>(c->L.head_part), ctl, c->wsp<HeadResult>(c->L.head), ends);
     }
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
@@ -784,23 +783,31 @@ static int32_t run_pass(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int mr
         KS_TRY(run_pass_small(c, ctl, mask, n_rows, start, ends, &done));
         if (done) return KNNSSD_OK;
     }
+    if (mr == 1 && c->tuned) return run_pass_bf16(c, ctl, mask, true, true, 1, start, ends);
+    if (mr != 1 && c->tuned_verify) return run_pass_bf16(c, ctl, mask, false, want_head, n_rows, start, ends);
     HeadResult *head = c->wsp<HeadResult>(c->L.head);
+    if (ends.set) hipLaunchKernelGGL(set_pass_kernel, dim3(1), dim3(64), 0, c->stream, ctl, ends.ctl);
     if (ends.kind == ENDS_VERIFY) hipLaunchKernelGGL(verify_begin_kernel, dim3(1), dim3(1), 0, c->stream, ends.st, ends.draft, ctl, ends.expect_k);
-    if (mr == 1 && c->tuned) KS_TRY(run_pass_bf16(c, ctl, mask, true, true, 1, start));
-    else if (mr != 1 && c->tuned_verify) KS_TRY(run_pass_bf16(c, ctl, mask, false, want_head, n_rows, start));
-    else if (wb && kb) KS_TRY((run_pass_t<bf16_t, bf16_t>(c, ctl, mask, n_rows)));
+    if (wb && kb) KS_TRY((run_pass_t<bf16_t, bf16_t>(c, ctl, mask, n_rows)));
     else if (wb) KS_TRY((run_pass_t<bf16_t, float>(c, ctl, mask, n_rows)));
     else if (kb) KS_TRY((run_pass_t<float, bf16_t>(c, ctl, mask, n_rows)));
     else KS_TRY((run_pass_t<float, float>(c, ctl, mask, n_rows)));
     if (ends.kind == ENDS_DRAFT) hipLaunchKernelGGL(draft_end_kernel, dim3(1), dim3(1), 0, c->stream, ends.st, ctl, head, ends.flags);
     if (ends.kind == ENDS_VERIFY) hipLaunchKernelGGL(accept_kernel, dim3(1), dim3(1), 0, c->stream, ends.st, ctl, head, ends.out_tokens, ends.flags + 1);
+    if (ends.kind == ENDS_CHECK) hipLaunchKernelGGL(verify_accept_kernel, dim3(1), dim3(1), 0, c->stream, ctl, head, ends.out3);
+    HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }
 
+static PassCtl pass_ctl(int active, int n_rows, int start, int head_from, const int32_t *toks) {
+    PassCtl p{};
+    p.active = active; p.n_rows = n_rows; p.start = start; p.head_from = head_from;
+    for (int i = 0; i < KS_MAX_ROWS; ++i) p.tok[i] = (i < n_rows) ? toks[i] : 0;
+    return p;
+}
+
 static int32_t set_pass(knnssd_ctx *c, PassCtl *ctl, int active, int n_rows, int start, int head_from, const int32_t *toks) {
-    TokArgs ta;
-    for (int i = 0; i < KS_MAX_ROWS; ++i) ta.t[i] = (i < n_rows) ? toks[i] : 0;
-    hipLaunchKernelGGL(set_pass_kernel, dim3(1), dim3(64), 0, c->stream, ctl, active, n_rows, start, head_from, ta);
+    hipLaunchKernelGGL(set_pass_kernel, dim3(1), dim3(64), 0, c->stream, ctl, pass_ctl(active, n_rows, start, head_from, toks));
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }
@@ -916,8 +923,7 @@ static int32_t prefill_head(knnssd_ctx *c, int n_tok, int row, float *last_hidde
     h.ss_in = c->wsp<float>(c->L.ss); h.logits = c->wsp<float>(c->L.logits) + (size_t)row * g.vocab;
     h.head_part = c->wsp<HeadPartial>(c->L.head_part); h.split = c->split_head; h.n_rows = 1;
     hipLaunchKernelGGL(gemv_kernel, dim3(KS_NWG), dim3(NT), gemv_lds_bytes(d), c->stream, h, ver);
-    hipLaunchKernelGGL(head_final_kernel, dim3(KS_MAX_ROWS), dim3(NT), 0, c->stream, c->wsp<HeadPartial>(c->L.head_part), KS_NWG, ver,
-                       c->wsp<HeadResult>(c->L.head));
+    hipLaunchKernelGGL(head_final_kernel, dim3(1), dim3(NT), 0, c->stream, c->wsp<HeadPartial>(c->L.head_part), ver, c->wsp<HeadResult>(c->L.head), PassEnds());
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }
@@ -1148,8 +1154,9 @@ extern "C" int32_t knnssd_draft_step(knnssd_ctx *ctx, int32_t token_in, int32_t 
     if (pos > ctx->draft_len) return KNNSSD_ERANGE;       // positions in between were never written
     if (token_in < 0 || token_in >= ctx->cfg.vocab) return KNNSSD_ERANGE;
     PassCtl *dr = ctx->wsp<PassCtl>(ctx->L.draft_ctl);
-    KS_TRY(set_pass(ctx, dr, 1, 1, pos, 0, &token_in));
-    KS_TRY(run_pass(ctx, dr, ctx->draft_mask.data(), 1, 1, pos));
+    PassEnds ends;
+    ends.set = 1; ends.ctl = pass_ctl(1, 1, pos, 0, &token_in);
+    KS_TRY(run_pass(ctx, dr, ctx->draft_mask.data(), 1, 1, pos, true, ends));
     KS_TRY(read_back(ctx, ctx->wsp<HeadResult>(ctx->L.head), sizeof(HeadResult)));
     HeadResult hr;
     memcpy(&hr, ctx->h_stage, sizeof(hr));
@@ -1168,11 +1175,10 @@ extern "C" int32_t knnssd_verify(knnssd_ctx *ctx, const int32_t *tokens_host, in
     if (start_pos > ctx->cache_len) return KNNSSD_ERANGE;  // the full model's K/V in between were never written (drafts fill only retained blocks)
     KS_TRY(check_tokens(ctx, tokens_host, n));
     PassCtl *ver = ctx->wsp<PassCtl>(ctx->L.ver_ctl);
-    KS_TRY(set_pass(ctx, ver, 1, n, start_pos, 0, tokens_host));
-    KS_TRY(run_pass(ctx, ver, nullptr, KS_MAX_ROWS, n, start_pos));
     int32_t *out3 = ctx->wsp<int32_t>(ctx->L.out3);
-    hipLaunchKernelGGL(verify_accept_kernel, dim3(1), dim3(1), 0, ctx->stream, ver, ctx->wsp<HeadResult>(ctx->L.head), out3);
-    HIP_TRY(hipGetLastError());
+    PassEnds ends;
+    ends.kind = ENDS_CHECK; ends.out3 = out3; ends.set = 1; ends.ctl = pass_ctl(1, n, start_pos, 0, tokens_host);
+    KS_TRY(run_pass(ctx, ver, nullptr, KS_MAX_ROWS, n, start_pos, true, ends));
     KS_TRY(read_back(ctx, out3, 12));
     *n_accepted_out = ctx->h_stage[0];
     *next_token_out = ctx->h_stage[1];
