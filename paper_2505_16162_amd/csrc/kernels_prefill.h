@@ -188,7 +188,7 @@ __device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v,
     pf_store_bf16x4(op.kv_block + (((size_t)op.Hkv + head) * op.max_seq + tok) * op.hd + d, val);
 }
 
-// TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS.
+// TA x TB tiles of 16 rows x 16 tokens per workgroup, 8 wavefronts in a WA x 8/WA grid, NS staged steps in LDS (PfShape).
 // What bounds it. 256 x 256 and 256 x 128: the matrix cores, at 1.53-1.6 PFLOP/s issued (three instructions per product), where a
 // large library product in bf16 reaches 1.59 on this card; one meeting per step for all wavefronts together kept the matrix
 // pipe 55 % busy, two groups one phase apart 80 %. 13B-shaped, 4096 rows: QKV 1.52-1.55 ms (with its own sums, below),
@@ -200,8 +200,9 @@ __device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v,
 // two 1348; the steps in the order in which the units lie in memory: no faster.) Which tile a matrix and a length take: pf_plan.
 // PP: the wavefronts form two groups (one wavefront of each on every SIMD) that run one phase apart: while one group
 // issues its matrix instructions the other reads its operands from LDS.
-template <int TA, int TB, int WA, int NSA, int NSB, bool PP>
+template <int TA, int TB, int WA, int NS, bool PP>
 struct PfShape {
+    static constexpr int NSA = NS, NSB = PP ? NS : NS - 2;          // buffers for weights, for activations
     static constexpr int WB = 8 / WA, TAW = TA / WA, TBW = TB / WB;
     static constexpr int TM = TA * 16;
     static constexpr int A_BYTES = TA * 1024, B_BYTES = PF_NP * TB * 1024;      // a step's weights and activations in LDS
@@ -214,11 +215,10 @@ struct PfShape {
     static constexpr size_t LDS = (size_t)NSA * A_BYTES + NSB * B_BYTES;
 };
 
-template <int TA, int TB, int WA, int NSA, int NSB, bool PP, int EPI, bool OWN>
+template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN>
 __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(PfArgs a) {
-    typedef PfShape<TA, TB, WA, NSA, NSB, PP> Sh;
-    static_assert(!PP || NSA == NSB, "one count of buffers");
-    constexpr int NS = NSA;
+    typedef PfShape<TA, TB, WA, NS, PP> Sh;
+    constexpr int NSA = Sh::NSA, NSB = Sh::NSB;
     constexpr int TAW = Sh::TAW, TBW = Sh::TBW, TM = Sh::TM;
     extern __shared__ __align__(16) char lds[];
     const GemmOp &op = a.op;

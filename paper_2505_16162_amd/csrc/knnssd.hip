@@ -206,17 +206,17 @@ struct knnssd_ctx {
 };
 
 // The prefill GEMM's builds: f(token tiles, epilogue, own sums, kernel, dynamic LDS) for each
-template <int TA, int TB, int WA, int NSA, int NSB, bool PP, int EPI, bool OWN, typename F> static void pf_build(F f) {
-    f(TB, EPI, OWN, prefill_gemm_kernel<TA, TB, WA, NSA, NSB, PP, EPI, OWN>, PfShape<TA, TB, WA, NSA, NSB, PP>::LDS);
+template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN, typename F> static void pf_build(F f) {
+    f(TB, EPI, OWN, prefill_gemm_kernel<TA, TB, WA, NS, PP, EPI, OWN>, PfShape<TA, TB, WA, NS, PP>::LDS);
 }
 template <typename F> static void pf_each_build(F f) {
-    pf_build<16, 16, 2, 2, 2, true, PF_PARTS, false>(f);
-    pf_build<16, 16, 2, 2, 2, true, PF_PARTS, true>(f);
-    pf_build<16, 16, 2, 2, 2, true, PF_SWIGLU, false>(f);
-    pf_build<16, 16, 2, 2, 2, true, PF_ROPE, true>(f);
-    pf_build<16, 8, 2, 3, 3, true, PF_PARTS, false>(f);
-    pf_build<16, 8, 2, 3, 3, true, PF_PARTS, true>(f);
-    pf_build<8, 4, 4, 5, 3, false, PF_PARTS, true>(f);
+    pf_build<16, 16, 2, 2, true, PF_PARTS, false>(f);
+    pf_build<16, 16, 2, 2, true, PF_PARTS, true>(f);
+    pf_build<16, 16, 2, 2, true, PF_SWIGLU, false>(f);
+    pf_build<16, 16, 2, 2, true, PF_ROPE, true>(f);
+    pf_build<16, 8, 2, 3, true, PF_PARTS, false>(f);
+    pf_build<16, 8, 2, 3, true, PF_PARTS, true>(f);
+    pf_build<8, 4, 4, 5, false, PF_PARTS, true>(f);
 }
 static hipError_t pf_set_lds_limits() {
     hipError_t e = hipSuccess;
