@@ -252,6 +252,21 @@ int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, int32_t n_p
 int32_t knnssd_profile_pass(knnssd_ctx *ctx, int32_t kind, const int32_t *tokens_host, int32_t n, int32_t start_pos,
                             int64_t *n_launches, int64_t *gemm_ns, int64_t *gemm_bytes, int64_t *pass_ns);
 
+/* How the passes of small any-shape models (matrices of at most 8 MB a block and in the head) are put on the stream:
+ * KNNSSD_PASS_AUTO (the default) chooses between one launch for the whole pass and a launch per step, KNNSSD_PASS_LAUNCHES
+ * takes the latter always, KNNSSD_PASS_ONE the former wherever the pass fits it. Other models always run as a launch per step.
+ * The workgroups of a one-launch pass wait for each other for a bounded time; if that runs out (they are not on the GPU
+ * together) the last one runs the pass by itself. Test aid: workgroup quit_workgroup (KNNSSD_QUIT_ALL: every one, -1: none)
+ * gives up at its first wait from block quit_block on (n_blocks: the LM head's). */
+#define KNNSSD_PASS_AUTO 0
+#define KNNSSD_PASS_LAUNCHES 1
+#define KNNSSD_PASS_ONE 2
+#define KNNSSD_QUIT_ALL 64
+int32_t knnssd_set_pass_mode(knnssd_ctx *ctx, int32_t mode, int32_t quit_workgroup, int32_t quit_block);
+
+/* One-launch passes of this context so far, and those of them that were broken up. */
+int32_t knnssd_pass_counts(knnssd_ctx *ctx, int64_t *one_launch_out, int64_t *broken_up_out);
+
 /* Parity/debug: fp32 logits of row `row` of the most recent pass (draft: row 0). */
 int32_t knnssd_get_logits(knnssd_ctx *ctx, int32_t row, float *logits_host);
 

@@ -25,7 +25,7 @@ EXPORTS = [
     "knnssd_pack_supported", "knnssd_pack_matrix",
     "knnssd_set_anchors", "knnssd_prefill", "knnssd_select_skipset", "knnssd_set_skipset", "knnssd_last_selection", "knnssd_knn_topk", "knnssd_route_static",
     "knnssd_draft_step", "knnssd_verify", "knnssd_generate", "knnssd_profile_pass", "knnssd_get_logits", "knnssd_read_kv",
-    "knnssd_strerror", "knnssd_stream_next_domain",
+    "knnssd_set_pass_mode", "knnssd_pass_counts", "knnssd_strerror", "knnssd_stream_next_domain",
 ]
 
 
@@ -113,6 +113,10 @@ def load_library() -> ctypes.CDLL:
     lib.knnssd_generate.argtypes = [vp, vp, i32, vp, ctypes.POINTER(GenCfg), vp, ctypes.POINTER(i32), ctypes.POINTER(Stats)]
     lib.knnssd_profile_pass.restype = i32
     lib.knnssd_profile_pass.argtypes = [vp, i32, vp, i32, i32] + [ctypes.POINTER(ctypes.c_int64)] * 4
+    lib.knnssd_set_pass_mode.restype = i32
+    lib.knnssd_set_pass_mode.argtypes = [vp, i32, i32, i32]
+    lib.knnssd_pass_counts.restype = i32
+    lib.knnssd_pass_counts.argtypes = [vp, ctypes.POINTER(ctypes.c_int64), ctypes.POINTER(ctypes.c_int64)]
     lib.knnssd_get_logits.restype = i32
     lib.knnssd_get_logits.argtypes = [vp, i32, vp]
     lib.knnssd_read_kv.restype = i32
@@ -340,6 +344,16 @@ class KnnSsd:
         _check(self.lib.knnssd_profile_pass(self.h, int(kind), toks, len(tokens), int(start_pos),
                                             *[ctypes.byref(o) for o in out]))
         return dict(n_launches=out[0].value, gemm_ns=out[1].value, gemm_bytes=out[2].value, pass_ns=out[3].value)
+
+    def knnssd_set_pass_mode(self, mode: str = "auto", quit_workgroup: int = -1, quit_block: int = 0):
+        """mode: "auto" | "launches" | "one" (passes of small any-shape models)."""
+        _check(self.lib.knnssd_set_pass_mode(self.h, {"auto": 0, "launches": 1, "one": 2}[mode], int(quit_workgroup), int(quit_block)))
+
+    def knnssd_pass_counts(self):
+        """(one-launch passes, those of them that were broken up)"""
+        n, broken = ctypes.c_int64(), ctypes.c_int64()
+        _check(self.lib.knnssd_pass_counts(self.h, ctypes.byref(n), ctypes.byref(broken)))
+        return int(n.value), int(broken.value)
 
     def knnssd_get_logits(self, row: int = 0) -> torch.Tensor:
         out = torch.empty(self.shape.vocab, dtype=torch.float32)

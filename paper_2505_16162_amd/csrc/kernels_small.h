@@ -19,7 +19,11 @@
 // Workgroups that wait for each other have to be resident together. Nothing guarantees that where many launches share the
 // GPU, so nothing relies on it: a workgroup that has looked at a word SM_SPIN times declares the launch broken up
 // (SmallMeet::state) and leaves; the last one to leave then runs the whole pass by itself, as a launch of one workgroup, which waits
-// for nobody and comes to the same values. Once the first workgroup has declared the pass done, nobody can break it up.
+// for nobody. Once the first workgroup has declared the pass done, nobody can break it up.
+// What a broken launch leaves behind is what the workgroup that stayed has stored: its own die's L2 holds those lines, and the L2 of
+// another die may hold lines of the same cache entries, logits or hidden state that a departed workgroup wrote earlier;
+// which of the two reaches memory last is not defined. So a workgroup that has given up stores nothing but handed-over words, and
+// those marked (SM_BAD_TAG). Whatever was stored before has been worked out from sound inputs and is the same bytes.
 //
 // The arithmetic is that of gemm_rows_kernel, attention_kernel and rmsnorm_kernel, operation for operation (the same
 // device code), so a row's logits do not depend on which of the two ways a pass takes.
@@ -64,6 +68,8 @@ struct SmallArgs {
     unsigned int tag;            // first tag of the launch
     int one_head;                // the LM head sees one row at most
     int score_len;               // attention scores: floats per item
+    int *flags;                  // host words, [3]: launches that were broken up
+    int quit_wg, quit_block;     // for tests: this workgroup (SM_G: every one) gives up at its first wait from this block on
 };
 
 // weight pieces of an output product requested ahead, 1 KB of a row each
@@ -89,7 +95,8 @@ __device__ __forceinline__ void word_put(u64 *p, float v, unsigned int tag, int 
 __device__ __forceinline__ u64 word_get(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Words 0..n-1 by threads tid of nt: at(i) is a word's address, put(i, value) receives its value. U words per thread are
-// looked at together. A wait that is given up leaves a mark (gave_up, in LDS), after which the workgroup waits no more.
+// looked at together. A wait that is given up leaves a mark (gave_up, in LDS), after which the workgroup waits no more. spin = 0:
+// it is given up whatever is there.
 template <int U, typename FA, typename FP>
 __device__ __forceinline__ void words_read(int n, int tid, int nt, unsigned int tag, int &gave_up, int spin, FA at, FP put) {
     const int most = gave_up ? 1 : spin;      // (after that it goes through the motions)
@@ -104,7 +111,7 @@ __device__ __forceinline__ void words_read(int n, int tid, int nt, unsigned int 
 #pragma unroll
             for (int u = 0; u < U; ++u) all = all && (unsigned int)(v[u] >> 32) == tag;
         } while (!all && ++look < most);
-        if (!all) gave_up = 1;
+        if (!all || spin == 0) gave_up = 1;
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (u == 0 || i0 + u * nt < n) put(i0 + u * nt, __uint_as_float((unsigned int)v[u]));
@@ -203,7 +210,9 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     int n_wg = SM_G;                                   // 1: the pass of a launch that was broken up
     for (;;) {
     int gw = wave * n_wg + wg;                         // workgroups first: see above
-    const int NW = n_wg * SM_NW, spin = n_wg == 1 ? 1 << 20 : SM_SPIN;      // (alone, only its own words can be on their way)
+    const int NW = n_wg * SM_NW;
+    int spin = n_wg == 1 ? 1 << 20 : SM_SPIN;          // (alone, only its own words can be on their way)
+    const bool quitter = n_wg > 1 && (a.quit_wg == wg || a.quit_wg == SM_G);
     const int d = a.d, hd = a.hd, half = hd >> 1, qd = a.H * hd, qkvd = (a.H + 2 * a.Hkv) * hd;
     float *xs = lds, *st = lds + (size_t)MR * d;       // residual stream; the input of a step
     if (tid == 0) sl.gave_up = 0;
@@ -246,6 +255,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     for (int b = 0; b < a.n_blocks; ++b) {
         const SmallBlock blk = a.blocks[b];
         asm volatile("" : "+v"(tid), "+v"(lane), "+v"(gw));       // addresses are worked out where they are used, not kept over the blocks
+        if (quitter && b >= a.quit_block) spin = 0;
         const float *attn_norm = as_global<float>(blk.attn_norm), *mlp_norm = as_global<float>(blk.mlp_norm);
         const unsigned int tag = a.tag + 5u * b;
         if (!((a.skip_attn >> b) & 1)) {
@@ -258,6 +268,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
             const int o0 = min(gw, items - 1);
             next.load(W + (size_t)row0(o0) * d, W + (size_t)row1(o0) * d, attn_norm, d);
             if (x_tag) gather(x_words, d, xs, x_tag);
+            const bool sound = !sl.gave_up;            // what a workgroup that has given up works out is stored nowhere
             const int pos = start + min(lane, n_rows - 1);
             float rope_c = a.cos_t[(size_t)pos * half + (gw & (half - 1))], rope_s = a.sin_t[(size_t)pos * half + (gw & (half - 1))];
             for (int o = gw; o < items; o += NW) {
@@ -275,16 +286,20 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
                         rotate_pair(v0, v1, c, s, ra, rb);
                         if (head >= a.H) {
                             const size_t base = ((size_t)(head - a.H) * a.max_seq + pos) * hd;
-                            store_rounded(kc, base + i, ra);
-                            store_rounded(kc, base + i + half, rb);
+                            if (sound) {
+                                store_rounded(kc, base + i, ra);
+                                store_rounded(kc, base + i + half, rb);
+                            }
                             ra = as_stored(ra, T()); rb = as_stored(rb, T());
                         }
                         v0 = ra; v1 = rb;
                     } else {
                         const int v = (o - P) * 2;
                         const size_t base = ((size_t)(v >> head_shift) * a.max_seq + pos) * hd + (v & (hd - 1));
-                        store_rounded(vc, base, v0);
-                        store_rounded(vc, base + 1, v1);
+                        if (sound) {
+                            store_rounded(vc, base, v0);
+                            store_rounded(vc, base + 1, v1);
+                        }
                         v0 = as_stored(v0, T()); v1 = as_stored(v1, T());
                     }
                     word_put(a.w_qkv + (size_t)lane * qkvd + r0, v0, tag, sl.gave_up);
@@ -322,12 +337,14 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     }
     asm volatile("" : "+v"(tid), "+v"(lane), "+v"(gw), "+v"(wave));
     const int n_head = n_rows - head_from;
+    if (quitter && a.n_blocks >= a.quit_block) spin = 0;
     if (n_head > 0) {
     const T *W = reinterpret_cast<const T *>(a.lm_head);
     RowsPieces<T, false, 1> p[IT];
 #pragma unroll
     for (int j = 0; j < IT; ++j) p[j].load(W + (size_t)min(gw + j * NW, a.V - 1) * d, nullptr, nullptr, d);
     if (x_tag) gather(x_words, d, xs, x_tag);
+    const bool sound = !sl.gave_up;
     // final norm, a row per 256 threads
     {
         const int hf = tid >> 8, t = tid & 255;
@@ -344,7 +361,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
             for (int i = t; i < d; i += 256) {
                 const float v = xr[i] * rs * a.final_norm[i];
                 st[(size_t)rr * d + i] = v;
-                if (wg == 0) a.xn[(size_t)(head_from + rr) * d + i] = v;
+                if (wg == 0 && sound) a.xn[(size_t)(head_from + rr) * d + i] = v;
             }
             __syncthreads();
         }
@@ -365,7 +382,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         for (int j = 0; j < IT; ++j) {
             const int o = o0 + j * NW;
             if (lane < n_head && o < a.V) {
-                a.logits[(size_t)(head_from + lane) * a.V + o] = v[j];
+                if (sound) a.logits[(size_t)(head_from + lane) * a.V + o] = v[j];
                 if (v[j] > m) { s = s * expf(m - v[j]) + 1.0f; m = v[j]; mi = o; }
                 else {
                     if (better(v[j], o, m, mi)) mi = o;
@@ -425,15 +442,19 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         __syncthreads();
         if (tid == 0) {
             pass_end(a.ends, a.ctl, ctl, &sl.head);
-            if (n_wg > 1) __hip_atomic_fetch_add(&meet->left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (n_wg == 1) ++a.flags[3];
+            else __hip_atomic_fetch_add(&meet->left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return;
     }
     }
     }
-    if (n_wg == 1) return;
+    if (n_wg == 1) {                                   // (a pass without a head)
+        if (tid == 0) ++a.flags[3];
+        return;
+    }
     // leave; the last one of a launch that was broken up stays for the whole pass
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // whatever this workgroup has written has arrived
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // the words this workgroup has handed over are where everybody looks for them
     __syncthreads();
     if (tid == 0) {
         int open = MEET_OPEN;

@@ -193,9 +193,10 @@ struct knnssd_ctx {
     int32_t last_anchor = -1, last_domain = -1;   // most recent routing
     // pinned host staging for small read-backs
     int32_t *h_stage;
-    int32_t *d_flags;   // device view of h_stage + 512: words the round-control kernels write for the host
+    int32_t *d_flags;   // device view of h_stage + 512: words the round-control kernels write for the host, [3] also the one-launch passes
     unsigned int small_tag = 0;    // last tag a small pass has used; 0: its words hold no tag
     unsigned int small_launch = 0; // small passes launched
+    int32_t pass_mode = KNNSSD_PASS_AUTO, quit_wg = -1, quit_block = 0;     // knnssd_set_pass_mode
     std::vector<hipEvent_t> events;
     // knnssd_profile_pass: enqueue only the weight-streaming launches of a pass and count them
     bool gemm_only = false;
@@ -238,6 +239,7 @@ template <typename F> static void small_each_build(F f) {
     both(std::integral_constant<int, 1>{}); both(std::integral_constant<int, 2>{}); both(std::integral_constant<int, 3>{});
     both(std::integral_constant<int, 5>{}); both(std::integral_constant<int, 9>{}); both(std::integral_constant<int, 16>{});
 }
+static_assert(KNNSSD_QUIT_ALL == SM_G, "the workgroup behind the last one: every one");
 static const size_t SMALL_MAX_LDS = 80 * 1024 - sizeof(SmallLds);     // two workgroups per unit
 static hipError_t small_set_lds_limits() {
     hipError_t e = hipSuccess;
@@ -389,6 +391,7 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         delete c;
         return KNNSSD_EHIP;
     }
+    memset(c->h_stage, 0, 4096);
     c->d_flags = nullptr;
     e = hipHostGetDevicePointer((void **)&c->d_flags, c->h_stage + 512, 0);
     if (e != hipSuccess) {
@@ -553,7 +556,7 @@ static int32_t run_pass_t(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int 
 // The same pass in one launch. *done stays false if it does not fit.
 static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int n_rows, int start, const PassEnds &ends, bool *done) {
     const knnssd_model_cfg &g = c->cfg;
-    if (!small_ok(g)) return KNNSSD_OK;
+    if (!small_ok(g) || c->pass_mode == KNNSSD_PASS_LAUNCHES) return KNNSSD_OK;
     const int d = g.d_model, qd = g.n_heads * g.head_dim, F = g.d_ffn, len = start + n_rows;
     int mr = 0;
     void (*kernel)(SmallArgs) = nullptr;
@@ -584,6 +587,7 @@ static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, 
     a.cos_t = c->wsp<float>(c->L.rope_cos); a.sin_t = c->wsp<float>(c->L.rope_sin);
     a.d = d; a.H = g.n_heads; a.Hkv = g.n_kv_heads; a.hd = g.head_dim; a.F = F; a.V = g.vocab; a.max_seq = g.max_seq; a.eps = g.rms_eps;
     a.tag = c->small_tag + 1; a.one_head = c->in_prefill; a.score_len = (len + 3) & ~3;
+    a.flags = c->d_flags; a.quit_wg = c->quit_wg; a.quit_block = c->quit_block;
     c->small_tag += tags;
     hipLaunchKernelGGL(kernel, dim3(SM_G), dim3(SM_NT), lds, c->stream, a);
     HIP_TRY(hipGetLastError());
@@ -1370,6 +1374,21 @@ extern "C" int32_t knnssd_stream_next_domain(int32_t current, int32_t n_domains,
     int32_t slot = (int32_t)(u_pick * (double)(n_domains - 1));       // one of the other N-1 domains, equally likely
     if (slot > n_domains - 2) slot = n_domains - 2;
     return slot < current ? slot : slot + 1;
+}
+
+extern "C" int32_t knnssd_set_pass_mode(knnssd_ctx *ctx, int32_t mode, int32_t quit_workgroup, int32_t quit_block) {
+    if (!ctx || mode < KNNSSD_PASS_AUTO || mode > KNNSSD_PASS_ONE) return KNNSSD_EINVAL;
+    if (quit_workgroup < -1 || quit_workgroup > SM_G || quit_block < 0 || quit_block > ctx->cfg.n_blocks) return KNNSSD_ERANGE;
+    ctx->pass_mode = mode; ctx->quit_wg = quit_workgroup; ctx->quit_block = quit_block;
+    return KNNSSD_OK;
+}
+
+extern "C" int32_t knnssd_pass_counts(knnssd_ctx *ctx, int64_t *one_launch_out, int64_t *broken_up_out) {
+    if (!ctx || !one_launch_out || !broken_up_out) return KNNSSD_EINVAL;
+    HIP_TRY(hipStreamSynchronize(ctx->stream));
+    *one_launch_out = ctx->small_launch;
+    *broken_up_out = ((volatile int32_t *)ctx->h_stage)[512 + 3];
+    return KNNSSD_OK;
 }
 
 extern "C" int32_t knnssd_get_logits(knnssd_ctx *ctx, int32_t row, float *logits_host) {

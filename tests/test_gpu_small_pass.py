@@ -1,7 +1,8 @@
 """Passes of small models in one launch: the smallest widths (one value per workgroup in some steps), ragged ones, both head sizes,
 grouped-query heads, weights just under and over the size up to which a pass is one launch, skipped sublayers, contexts of
 several rounds of the attention, every row count the builds split at. Logits against the oracle (and a row's logits the same however
-many rows share its pass), and many contexts at once on streams of their own: more workgroups than the chip holds."""
+many rows share its pass), launches whose workgroups give up waiting (all that a pass leaves behind is that of a launch per step,
+bit for bit), and contexts in threads on streams of their own."""
 import threading
 
 import pytest
@@ -68,6 +69,65 @@ def test_skipped_sublayers(mask):
     gpu.close()
 
 
+BROKEN = dict(n_blocks=3, d_model=136, n_heads=3, n_kv_heads=1, head_dim=64, d_ffn=200, vocab=311, max_seq=96)
+
+
+def _everything(gpu, tokens, skip):
+    """What a prompt in three chunks (two of them without a head), draft steps with skipped sublayers, verifications of every build's row
+    count and a generation return and leave in memory."""
+    out = []
+    gpu.kv.zero_()
+    gpu.knnssd_set_skipset(skip)
+    first, hidden = gpu.knnssd_prefill(tokens[:37])
+    out += [first, hidden.cpu(), gpu.knnssd_get_logits(4), gpu.kv.cpu()]
+    for i in range(3):
+        out += [gpu.knnssd_draft_step(tokens[37 + i], 37 + i)[0], gpu.knnssd_get_logits(0)]
+    out.append(gpu.kv.cpu())
+    for n in (16, 1, 2, 3, 5, 9):
+        out.append(gpu.knnssd_verify(tokens[37:37 + n], 37))
+        out += [gpu.knnssd_get_logits(r) for r in range(n)]
+    out.append(gpu.kv.cpu())
+    out.append(gpu.knnssd_generate(tokens[:20], 12, 4, 0.0, route=False)[0])
+    out.append(gpu.kv.cpu())
+    return out
+
+
+def _same(a, b):
+    return len(a) == len(b) and all(torch.equal(x, y) if isinstance(x, torch.Tensor) else x == y for x, y in zip(a, b))
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_broken_up_launches_leave_what_whole_ones_leave(dtype):
+    """A workgroup (the first, one in between, the last, every one) gives up its first wait in some block or in the head, the others theirs
+    when the bound on it runs out; the one that stays runs the pass alone."""
+    shape = synth.small_shape("small_broken_" + dtype, weight_dtype=dtype, kv_dtype=dtype, **BROKEN)
+    w, orc, gpu = make_pair(shape, seed=66, std=0.05)
+    tokens = synth.make_prompt(shape.vocab, 60, seed=67).tolist()
+    skip = [0, 0, 1, 1, 0, 0]
+    gpu.knnssd_set_pass_mode("launches")
+    want = _everything(gpu, tokens, skip)
+    assert gpu.knnssd_pass_counts() == (0, 0)
+    gpu.knnssd_set_pass_mode("one")
+    assert _same(_everything(gpu, tokens, skip), want)
+    whole, broken = gpu.knnssd_pass_counts()
+    assert whole > 12
+    for wg, block in [(0, 0), (0, 3), (17, 0), (17, 2), (63, 1), (63, 3), (64, 0), (64, 2)]:
+        print("case", dtype, wg, block, flush=True)
+        gpu.knnssd_set_pass_mode("one", wg, block)
+        before = gpu.knnssd_pass_counts()
+        assert _same(_everything(gpu, tokens, skip), want), (wg, block)
+        after = gpu.knnssd_pass_counts()
+        assert after[0] - before[0] >= whole - 4
+        # the head's wait is not met by the two chunks of a prompt that have no head; nor is a block by drafts that skip it
+        assert after[1] - before[1] >= (whole if block == 0 else 8), (wg, block, before, after)
+    gpu.knnssd_set_pass_mode("one")
+    before = gpu.knnssd_pass_counts()
+    assert _same(_everything(gpu, tokens, skip), want)
+    print("broken up without a quitter:", gpu.knnssd_pass_counts()[1] - before[1], "of", gpu.knnssd_pass_counts()[0] - before[0])
+    gpu.close()
+
+
 @pytest.mark.timeout(300)
 def test_many_contexts_at_once():
     shape = synth.small_shape("small_streams", weight_dtype="fp32", kv_dtype="fp32", n_blocks=4, vocab=1024, max_seq=96)
@@ -98,6 +158,7 @@ def test_many_contexts_at_once():
         t.start()
     for t in threads:
         t.join()
+    print("(one-launch passes, broken up):", [c.knnssd_pass_counts() for c in ctxs])
     for c in ctxs:
         c.close()
     assert got == want
