@@ -494,6 +494,57 @@ __global__ __launch_bounds__(1024) void argmax_kernel(const PassCtl *ctl, const 
     }
 }
 
+// The same for models whose passes may run in one launch (kernels_small.h): there HEAD_CLASSES wavefronts work out the logits, each
+// those of its own class (token modulo HEAD_CLASSES), and a row's sum of exponentials is formed class by class. Here a thread takes a
+// class, so that the probability has the same bits whichever way the pass ran, and a confidence rule never decides by it.
+constexpr int HEAD_GROUPS = 64, HEAD_WAVES = 8, HEAD_CLASSES = HEAD_GROUPS * HEAD_WAVES;     // class: wavefront * HEAD_GROUPS + workgroup
+// a class's largest logit so far (the lowest token on ties) and sum of exponentials: one more logit
+__device__ __forceinline__ void head_fold(float v, int o, float &m, float &s, int &mi) {
+    if (v > m) { s = fmaf(s, expf(m - v), 1.0f); m = v; mi = o; }
+    else {
+        if (better(v, o, m, mi)) mi = o;
+        s += v == -INFINITY ? 0.f : expf(v - m);
+    }
+}
+// a workgroup's classes, `stride` apart in hm, hs, hi
+__device__ __forceinline__ void head_join(const float *hm, const float *hs, const int *hi, int stride, float &bm, int &bi, float &sum) {
+    bm = hm[0]; bi = hi[0]; sum = 0.f;
+    for (int w = 1; w < HEAD_WAVES; ++w) if (better(hm[w * stride], hi[w * stride], bm, bi)) { bm = hm[w * stride]; bi = hi[w * stride]; }
+    for (int w = 0; w < HEAD_WAVES; ++w) if (hi[w * stride] != 0x7fffffff) sum = fmaf(hs[w * stride], expf(hm[w * stride] - bm), sum);
+}
+// all workgroups' shares, a lane each
+__device__ __forceinline__ void head_merge(float m, int mi, float s, int &token, float &prob) {
+    float bm = m;
+    token = mi;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+        const float ov = lane_xor(bm, off);
+        const int oi = lane_xor(token, off);
+        if (better(ov, oi, bm, token)) { bm = ov; token = oi; }
+    }
+    prob = 1.0f / wave_sum(mi != 0x7fffffff ? s * expf(m - bm) : 0.f);
+}
+
+__global__ __launch_bounds__(HEAD_CLASSES) void argmax_classes_kernel(const PassCtl *ctl, const float *logits, int V, HeadResult *res) {
+    if (!ctl->active) return;
+    const int r = blockIdx.x;
+    if (r >= ctl->n_rows || r < ctl->head_from) return;
+    __shared__ float hm[HEAD_CLASSES], hs[HEAD_CLASSES];
+    __shared__ int hi[HEAD_CLASSES];
+    const float *row = logits + (size_t)r * V;
+    float m = -INFINITY, s = 0.f;
+    int mi = 0x7fffffff;
+    for (int o = threadIdx.x; o < V; o += HEAD_CLASSES) head_fold(row[o], o, m, s, mi);
+    hm[threadIdx.x] = m; hs[threadIdx.x] = s; hi[threadIdx.x] = mi;
+    __syncthreads();
+    if (threadIdx.x >= HEAD_GROUPS) return;
+    float prob;
+    int token;
+    head_join(hm + threadIdx.x, hs + threadIdx.x, hi + threadIdx.x, HEAD_GROUPS, m, mi, s);
+    head_merge(m, mi, s, token, prob);
+    if (threadIdx.x == 0) { res->tok[r] = token; res->prob[r] = prob; }
+}
+
 // ------------------------------------------------------------------------------------------
 // KNN routing, Eq. 4: score_n = (v . a_n) / |a_n|  (|v| is a common positive factor), then arg-max
 // ------------------------------------------------------------------------------------------

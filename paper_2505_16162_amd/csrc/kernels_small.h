@@ -26,7 +26,8 @@
 // those marked (SM_BAD_TAG). Whatever was stored before has been worked out from sound inputs and is the same bytes.
 //
 // The arithmetic is that of gemm_rows_kernel, attention_kernel and rmsnorm_kernel, operation for operation (the same
-// device code), so a row's logits do not depend on which of the two ways a pass takes.
+// device code), and that of argmax_classes_kernel, so a row's logits and probability do not depend on which of the two ways a pass
+// takes, nor on whether a launch was broken up.
 #pragma once
 #include "kernels_generic.h"
 
@@ -233,6 +234,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         __syncthreads();
     };
     // A step's first weights are requested before its input is waited for, an item's while the item before is computed.
+    static_assert(SM_G == HEAD_GROUPS && SM_NW == HEAD_WAVES, "the head's classes");
     constexpr int NP = small_pieces(MR), IT = MR <= 6 ? 2 : 1;     // items a wavefront works on side by side
     // output product + residual
     auto residual = [&](const T *W, const u64 *in, int K, unsigned int tag_in, u64 *out) {
@@ -341,8 +343,9 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     if (n_head > 0) {
     const T *W = reinterpret_cast<const T *>(a.lm_head);
     RowsPieces<T, false, 1> p[IT];
+    const int c0 = wave * SM_G + wg;                   // the wavefront's (first) class of tokens
 #pragma unroll
-    for (int j = 0; j < IT; ++j) p[j].load(W + (size_t)min(gw + j * NW, a.V - 1) * d, nullptr, nullptr, d);
+    for (int j = 0; j < IT; ++j) p[j].load(W + (size_t)min(c0 + j * HEAD_CLASSES, a.V - 1) * d, nullptr, nullptr, d);
     if (x_tag) gather(x_words, d, xs, x_tag);
     const bool sound = !sl.gave_up;
     // final norm, a row per 256 threads
@@ -366,51 +369,48 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
             __syncthreads();
         }
     }
-    // LM head: lane r keeps row r's largest logit so far (the lowest token on ties) and its sum of exponentials
+    // LM head: lane r keeps row r's largest logit so far and its sum of exponentials. Alone, the workgroup takes the others' classes one
+    // after the other, so that the sums are formed as everybody together forms them.
+    const unsigned int tag = a.tag + 5u * a.n_blocks;
+    for (int g = wg; g < SM_G; g += n_wg) {
+    const int c = wave * SM_G + g;
     float m = -INFINITY, s = 0.f;
     int mi = 0x7fffffff;
-    for (int o0 = gw; o0 < a.V; o0 += IT * NW) {
+    for (int o0 = c; o0 < a.V; o0 += IT * HEAD_CLASSES) {
         float v[IT], unused;
 #pragma unroll
         for (int j = 0; j < IT; ++j) {
-            const T *w = W + (size_t)min(o0 + j * NW, a.V - 1) * d;
-            if (o0 != gw) p[j].load(w, nullptr, nullptr, d);
+            const T *w = W + (size_t)min(o0 + j * HEAD_CLASSES, a.V - 1) * d;
+            if (o0 != c0) p[j].load(w, nullptr, nullptr, d);
             if (a.one_head) rows_product<T, 1, false, false, 1>(p[j], w, nullptr, st, d, 1, d, nullptr, a.eps, v[j], unused);
             else rows_product<T, MR, false, false, 1>(p[j], w, nullptr, st, d, n_head, d, nullptr, a.eps, v[j], unused);
         }
 #pragma unroll
         for (int j = 0; j < IT; ++j) {
-            const int o = o0 + j * NW;
+            const int o = o0 + j * HEAD_CLASSES;
             if (lane < n_head && o < a.V) {
                 if (sound) a.logits[(size_t)(head_from + lane) * a.V + o] = v[j];
-                if (v[j] > m) { s = s * expf(m - v[j]) + 1.0f; m = v[j]; mi = o; }
-                else {
-                    if (better(v[j], o, m, mi)) mi = o;
-                    s += v[j] == -INFINITY ? 0.f : expf(v[j] - m);
-                }
+                head_fold(v[j], o, m, s, mi);
             }
         }
     }
-    const unsigned int tag = a.tag + 5u * a.n_blocks;
     if (lane < n_head) { sl.hm[wave][lane] = m; sl.hs[wave][lane] = s; sl.hi[wave][lane] = mi; }
     __syncthreads();
     if (tid < n_head) {
-        float bm = sl.hm[0][tid];
-        int bi = sl.hi[0][tid];
-        for (int w = 1; w < SM_NW; ++w) if (better(sl.hm[w][tid], sl.hi[w][tid], bm, bi)) { bm = sl.hm[w][tid]; bi = sl.hi[w][tid]; }
-        float sum = 0.f;
-        for (int w = 0; w < SM_NW; ++w) if (sl.hi[w][tid] != 0x7fffffff) sum += sl.hs[w][tid] * expf(sl.hm[w][tid] - bm);
-        u64 *o = a.w_head + ((size_t)tid * SM_G + wg) * 3;      // [row][workgroup]
+        float bm, sum;
+        int bi;
+        head_join(&sl.hm[0][tid], &sl.hs[0][tid], &sl.hi[0][tid], KS_MAX_ROWS, bm, bi, sum);
+        u64 *o = a.w_head + ((size_t)tid * SM_G + g) * 3;      // [row][workgroup]
         word_put(o, bm, tag, sl.gave_up);
         word_put(o + 1, __uint_as_float((unsigned int)bi), tag, sl.gave_up);
         word_put(o + 2, sum, tag, sl.gave_up);
     }
+    if (n_wg == 1) __syncthreads();                    // the next classes overwrite these
+    }
     if (wg == 0) {
     // the workgroups' shares, a lane each
-    static_assert(SM_G <= 64, "a lane per workgroup");
-    words_read<4>(3 * n_wg * n_head, tid, SM_NT, tag, sl.gave_up, spin,
-                  [&](unsigned int i) { const unsigned int r = i / (3 * n_wg); return a.w_head + r * 3 * SM_G + (i - r * 3 * n_wg); },
-                  [&](int i, float v) { st[i] = v; });
+    static_assert(SM_G == 64, "a lane per workgroup");
+    words_read<4>(3 * SM_G * n_head, tid, SM_NT, tag, sl.gave_up, spin, [&](unsigned int i) { return a.w_head + i; }, [&](int i, float v) { st[i] = v; });
     __syncthreads();
     if (tid == 0) {
         // from here on the launch cannot be broken up (alone it is not: nobody else is left)
@@ -420,22 +420,12 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     __syncthreads();
     if (sl.done) {
         for (int r = wave; r < n_head; r += SM_NW) {
-            const float *p = st + ((size_t)r * n_wg + min(lane, n_wg - 1)) * 3;
-            const bool live = lane < n_wg;
-            const float lm = live ? p[0] : -INFINITY, ls = live ? p[2] : 0.f;
-            const int li = live ? (int)__float_as_uint(p[1]) : 0x7fffffff;
-            float bm = lm;
-            int bi = li;
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) {
-                const float ov = lane_xor(bm, off);
-                const int oi = lane_xor(bi, off);
-                if (better(ov, oi, bm, bi)) { bm = ov; bi = oi; }
-            }
-            const float tot = wave_sum(li != 0x7fffffff ? ls * expf(lm - bm) : 0.f);
+            const float *p = st + ((size_t)r * SM_G + lane) * 3;
+            int token;
+            float prob;
+            head_merge(p[0], (int)__float_as_uint(p[1]), p[2], token, prob);
             if (lane == 0) {
-                const float prob = 1.0f / tot;
-                a.head->tok[head_from + r] = sl.head.tok[head_from + r] = bi;
+                a.head->tok[head_from + r] = sl.head.tok[head_from + r] = token;
                 a.head->prob[head_from + r] = sl.head.prob[head_from + r] = prob;
             }
         }

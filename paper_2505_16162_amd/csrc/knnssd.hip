@@ -548,7 +548,8 @@ static int32_t run_pass_t(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int 
     RowsOp h = product(xn, d, logits, g.vocab, g.vocab, d, nullptr);
     h.from_head = 1;
     launch_rows<WT, float, EPI_STORE>(c, ctl, c->in_prefill ? 1 : n_rows, c->lm_head, h);     // a prompt's pass: its last row, or none
-    hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
+    if (small_ok(g)) hipLaunchKernelGGL(argmax_classes_kernel, dim3(n_rows), dim3(HEAD_CLASSES), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
+    else hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }

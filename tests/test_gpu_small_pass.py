@@ -81,13 +81,13 @@ def _everything(gpu, tokens, skip):
     first, hidden = gpu.knnssd_prefill(tokens[:37])
     out += [first, hidden.cpu(), gpu.knnssd_get_logits(4), gpu.kv.cpu()]
     for i in range(3):
-        out += [gpu.knnssd_draft_step(tokens[37 + i], 37 + i)[0], gpu.knnssd_get_logits(0)]
+        out += [gpu.knnssd_draft_step(tokens[37 + i], 37 + i), gpu.knnssd_get_logits(0)]      # token and probability
     out.append(gpu.kv.cpu())
     for n in (16, 1, 2, 3, 5, 9):
         out.append(gpu.knnssd_verify(tokens[37:37 + n], 37))
         out += [gpu.knnssd_get_logits(r) for r in range(n)]
     out.append(gpu.kv.cpu())
-    out.append(gpu.knnssd_generate(tokens[:20], 12, 4, 0.0, route=False)[0])
+    out += [gpu.knnssd_generate(tokens[:20], 12, 4, conf, route=False)[0] for conf in (0.0, 0.5)]
     out.append(gpu.kv.cpu())
     return out
 
