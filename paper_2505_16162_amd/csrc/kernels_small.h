@@ -69,8 +69,8 @@ struct SmallArgs {
     unsigned int tag;            // first tag of the launch
     int one_head;                // the LM head sees one row at most
     int score_len;               // attention scores: floats per item
-    int *flags;                  // host words, [3]: launches that were broken up
-    int quit_wg, quit_block;     // for tests: this workgroup (SM_G: every one) gives up at its first wait from this block on
+    int *flags;                  // host words, [3]: launches that were broken up, [4]: a workgroup has waited in vain for its own words
+    int quit_wg, quit_block;     // for tests: this workgroup (SM_G: every one, SM_G + 1: also the one left alone) gives up at its first wait from this block on
 };
 
 // weight pieces of an output product requested ahead, 1 KB of a row each
@@ -192,6 +192,13 @@ __device__ __forceinline__ void small_attention(const SmallArgs &a, SmallLds &sl
     }
 }
 
+// The end of a pass that ran alone. One that has given up (it reads nothing but its own words, so this means that something is badly wrong)
+// has no result: the host finds the word and fails the call.
+__device__ __forceinline__ void small_alone(const SmallArgs &a, int gave_up) {
+    ++a.flags[3];
+    if (gave_up) a.flags[4] = 1;
+}
+
 // T: storage type of weights and cache; MR: rows the build holds (the pass has n_rows <= MR)
 template <typename T, int MR>
 __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
@@ -213,7 +220,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     int gw = wave * n_wg + wg;                         // workgroups first: see above
     const int NW = n_wg * SM_NW;
     int spin = n_wg == 1 ? 1 << 20 : SM_SPIN;          // (alone, only its own words can be on their way)
-    const bool quitter = n_wg > 1 && (a.quit_wg == wg || a.quit_wg == SM_G);
+    const bool quitter = n_wg == 1 ? a.quit_wg > SM_G : a.quit_wg >= SM_G || a.quit_wg == wg;
     const int d = a.d, hd = a.hd, half = hd >> 1, qd = a.H * hd, qkvd = (a.H + 2 * a.Hkv) * hd;
     float *xs = lds, *st = lds + (size_t)MR * d;       // residual stream; the input of a step
     if (tid == 0) sl.gave_up = 0;
@@ -431,8 +438,8 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         }
         __syncthreads();
         if (tid == 0) {
-            pass_end(a.ends, a.ctl, ctl, &sl.head);
-            if (n_wg == 1) ++a.flags[3];
+            if (!sl.gave_up) pass_end(a.ends, a.ctl, ctl, &sl.head);
+            if (n_wg == 1) small_alone(a, sl.gave_up);
             else __hip_atomic_fetch_add(&meet->left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return;
@@ -440,7 +447,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     }
     }
     if (n_wg == 1) {                                   // (a pass without a head)
-        if (tid == 0) ++a.flags[3];
+        if (tid == 0) small_alone(a, sl.gave_up);
         return;
     }
     // leave; the last one of a launch that was broken up stays for the whole pass

@@ -239,7 +239,7 @@ template <typename F> static void small_each_build(F f) {
     both(std::integral_constant<int, 1>{}); both(std::integral_constant<int, 2>{}); both(std::integral_constant<int, 3>{});
     both(std::integral_constant<int, 5>{}); both(std::integral_constant<int, 9>{}); both(std::integral_constant<int, 16>{});
 }
-static_assert(KNNSSD_QUIT_ALL == SM_G, "the workgroup behind the last one: every one");
+static_assert(KNNSSD_QUIT_ALL == SM_G && KNNSSD_QUIT_ALONE == SM_G + 1, "numbers behind the last workgroup's");
 static const size_t SMALL_MAX_LDS = 80 * 1024 - sizeof(SmallLds);     // two workgroups per unit
 static hipError_t small_set_lds_limits() {
     hipError_t e = hipSuccess;
@@ -818,10 +818,21 @@ static int32_t set_pass(knnssd_ctx *c, PassCtl *ctl, int active, int n_rows, int
 }
 
 // copy `bytes` from device to the pinned staging area and wait for it
+// everything enqueued is done; fails if a one-launch pass among it has no result
+static int32_t drain(knnssd_ctx *c) {
+    HIP_TRY(hipStreamSynchronize(c->stream));
+    volatile int32_t *const no_result = (volatile int32_t *)c->h_stage + 512 + 4;
+    if (*no_result) {
+        *no_result = 0;
+        snprintf(g_hip_err, sizeof(g_hip_err), "a pass ended without a result: a workgroup has waited in vain for its own words");
+        return KNNSSD_EHIP;
+    }
+    return KNNSSD_OK;
+}
+
 static int32_t read_back(knnssd_ctx *c, const void *dev, size_t bytes) {
     HIP_TRY(hipMemcpyAsync(c->h_stage, dev, bytes, hipMemcpyDeviceToHost, c->stream));
-    HIP_TRY(hipStreamSynchronize(c->stream));
-    return KNNSSD_OK;
+    return drain(c);
 }
 
 // The full model over the n_tok prompt rows with the matrix-core prefill kernels: fills the KV cache at positions
@@ -1284,7 +1295,7 @@ extern "C" int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, 
                 KS_TRY(mark(ctx, eb));
                 KS_TRY(enqueue_verify(expected, expected));
             }
-            HIP_TRY(hipStreamSynchronize(s));
+            KS_TRY(drain(ctx));
             if (!flags[0]) {                                   // the draft has stopped, after flags[2] steps
                 const int made = flags[2];
                 n_draft_passes -= k_host - made;               // steps enqueued beyond the stop did not run
@@ -1301,7 +1312,7 @@ extern "C" int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, 
         }
         ++n_verify_passes;
         round_ev.push_back(ea); round_ev.push_back(eb); round_ev.push_back(ec);
-        HIP_TRY(hipStreamSynchronize(s));
+        KS_TRY(drain(ctx));
         emitted_host = flags[1];
         done = emitted_host >= gen->max_new;
     }
@@ -1379,7 +1390,7 @@ extern "C" int32_t knnssd_stream_next_domain(int32_t current, int32_t n_domains,
 
 extern "C" int32_t knnssd_set_pass_mode(knnssd_ctx *ctx, int32_t mode, int32_t quit_workgroup, int32_t quit_block) {
     if (!ctx || mode < KNNSSD_PASS_AUTO || mode > KNNSSD_PASS_ONE) return KNNSSD_EINVAL;
-    if (quit_workgroup < -1 || quit_workgroup > SM_G || quit_block < 0 || quit_block > ctx->cfg.n_blocks) return KNNSSD_ERANGE;
+    if (quit_workgroup < -1 || quit_workgroup > KNNSSD_QUIT_ALONE || quit_block < 0 || quit_block > ctx->cfg.n_blocks) return KNNSSD_ERANGE;
     ctx->pass_mode = mode; ctx->quit_wg = quit_workgroup; ctx->quit_block = quit_block;
     return KNNSSD_OK;
 }

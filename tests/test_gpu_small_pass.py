@@ -129,6 +129,29 @@ def test_broken_up_launches_leave_what_whole_ones_leave(dtype):
 
 
 @pytest.mark.timeout(300)
+def test_a_pass_without_a_result_fails_the_call():
+    shape = synth.small_shape("small_no_result", weight_dtype="fp32", kv_dtype="fp32", **BROKEN)
+    w, orc, gpu = make_pair(shape, seed=68, std=0.05)
+    tokens = synth.make_prompt(shape.vocab, 60, seed=69).tolist()
+    skip = [0, 0, 1, 1, 0, 0]
+    gpu.knnssd_set_pass_mode("one")
+    want = _everything(gpu, tokens, skip)
+    calls = [lambda: gpu.knnssd_verify(tokens[37:40], 37), lambda: gpu.knnssd_draft_step(tokens[37], 37), lambda: gpu.knnssd_prefill(tokens[:40]),
+             lambda: gpu.knnssd_generate(tokens[:20], 12, 4, 0.0, route=False), lambda: gpu.knnssd_generate(tokens[:20], 12, 4, 0.5, route=False)]
+    for block in (0, shape.n_blocks):
+        for i, call in enumerate(calls):
+            print("case", block, i, flush=True)
+            gpu.knnssd_set_pass_mode("one")
+            gpu.knnssd_prefill(tokens[:37])
+            gpu.knnssd_set_pass_mode("one", 65, block)
+            with pytest.raises(binding.KnnSsdError, match="without a result"):
+                call()
+    gpu.knnssd_set_pass_mode("one")
+    assert _same(_everything(gpu, tokens, skip), want)
+    gpu.close()
+
+
+@pytest.mark.timeout(300)
 def test_many_contexts_at_once():
     shape = synth.small_shape("small_streams", weight_dtype="fp32", kv_dtype="fp32", n_blocks=4, vocab=1024, max_seq=96)
     w = {k: ([{n: t.cuda() for n, t in b.items()} for b in v] if k == "blocks" else v.cuda()) for k, v in synth.make_weights(shape, seed=65, gains="random", std=0.05).items()}
