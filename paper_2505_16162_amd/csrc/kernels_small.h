@@ -17,7 +17,7 @@
 // (knnssd_ctx::small_tag).
 //
 // Workgroups that wait for each other have to be resident together. Nothing guarantees that where many launches share the
-// GPU, so nothing relies on it: a workgroup that has looked at a word SM_SPIN times declares the launch broken up
+// GPU, so nothing relies on it: a workgroup that has waited for a word for SmallArgs::wait declares the launch broken up
 // (SmallMeet::state) and leaves; the last one to leave then runs the whole pass by itself, as a launch of one workgroup, which waits
 // for nobody. Once the first workgroup has declared the pass done, nobody can break it up.
 // What a broken launch leaves behind is what the workgroup that stayed has stored: its own die's L2 holds those lines, and the L2 of
@@ -30,15 +30,13 @@
 // takes, nor on whether a launch was broken up.
 #pragma once
 #include "kernels_generic.h"
+#include "small_plan.h"
 
 namespace ks {
 
 typedef unsigned long long u64;
 
-constexpr int SM_NT = 512, SM_NW = SM_NT / 64;   // threads, wavefronts of a workgroup
-constexpr int SM_G = 64;                         // workgroups
 constexpr int SM_MAX_BLOCKS = 64;                // skip masks travel as launch arguments
-constexpr int SM_SPIN = 512;                     // looks at a word before a workgroup gives up, most of a microsecond each
 constexpr unsigned int SM_BAD_TAG = 0x80000000u; // marks the words of a workgroup that has given up
 constexpr int SM_MEETS = 8;                      // launches whose SmallMeet are kept apart
 enum { MEET_OPEN = 0, MEET_BROKEN, MEET_DONE };
@@ -70,6 +68,7 @@ struct SmallArgs {
     int one_head;                // the LM head sees one row at most
     int score_len;               // attention scores: floats per item
     int *flags;                  // host words, [3]: launches that were broken up, [4]: a workgroup has waited in vain for its own words
+    int wait;                    // small_wait
     int quit_wg, quit_block;     // for tests: this workgroup (SM_G: every one, SM_G + 1: also the one left alone) gives up at its first wait from this block on
 };
 
@@ -77,17 +76,6 @@ struct SmallArgs {
 constexpr int small_pieces(int mr) { return mr <= 6 ? 3 : 1; }
 // tags a pass takes: five steps per block and the head
 inline unsigned int small_tags(int n_blocks) { return 5u * (unsigned int)n_blocks + 1u; }
-inline size_t small_stage_floats(int d, int qd, int F, int hd, int mr, int score_len) {
-    size_t n = (size_t)mr * (qd > F ? qd : F);
-    const size_t attn = SM_NT / 256 * ((size_t)hd + 2 * (size_t)mr * hd + score_len), head = (size_t)3 * SM_G * mr;
-    if ((size_t)mr * d > n) n = (size_t)mr * d;
-    if (attn > n) n = attn;
-    return head > n ? head : n;
-}
-inline size_t small_lds_bytes(int d, int qd, int F, int hd, int mr, int score_len) {
-    return ((size_t)mr * d + small_stage_floats(d, qd, F, hd, mr, score_len)) * 4;
-}
-
 // gave_up: the value is worth nothing
 __device__ __forceinline__ void word_put(u64 *p, float v, unsigned int tag, int gave_up) {
     if (gave_up) tag |= SM_BAD_TAG;
@@ -96,23 +84,28 @@ __device__ __forceinline__ void word_put(u64 *p, float v, unsigned int tag, int 
 __device__ __forceinline__ u64 word_get(const u64 *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
 
 // Words 0..n-1 by threads tid of nt: at(i) is a word's address, put(i, value) receives its value. U words per thread are
-// looked at together. A wait that is given up leaves a mark (gave_up, in LDS), after which the workgroup waits no more. spin = 0:
-// it is given up whatever is there.
+// looked at together. A wait that is given up, after `wait` ticks of the 100 MHz clock, leaves a mark (gave_up, in LDS), after which the
+// workgroup waits no more. wait = 0: it is given up whatever is there.
 template <int U, typename FA, typename FP>
-__device__ __forceinline__ void words_read(int n, int tid, int nt, unsigned int tag, int &gave_up, int spin, FA at, FP put) {
-    const int most = gave_up ? 1 : spin;      // (after that it goes through the motions)
+__device__ __forceinline__ void words_read(int n, int tid, int nt, unsigned int tag, int &gave_up, int wait, FA at, FP put) {
+    const int limit = gave_up ? 0 : wait;     // (after that it goes through the motions)
     for (int i0 = tid; i0 < n; i0 += nt * U) {
-        u64 v[U];
+        u64 v[U], until = 0;
         int look = 0;
-        bool all;
+        bool all, more = limit > 0;
         do {
             all = true;
 #pragma unroll
             for (int u = 0; u < U; ++u) v[u] = word_get(at((unsigned int)min(i0 + u * nt, n - 1)));
 #pragma unroll
             for (int u = 0; u < U; ++u) all = all && (unsigned int)(v[u] >> 32) == tag;
-        } while (!all && ++look < most);
-        if (!all || spin == 0) gave_up = 1;
+            if (!all && (++look & 15) == 0) {             // the clock, now and then
+                const u64 now = wall_clock64();
+                if (until == 0) until = now + limit;
+                more = more && now < until;
+            }
+        } while (!all && more);
+        if (!all || wait == 0) gave_up = 1;
 #pragma unroll
         for (int u = 0; u < U; ++u)
             if (u == 0 || i0 + u * nt < n) put(i0 + u * nt, __uint_as_float((unsigned int)v[u]));
@@ -141,7 +134,7 @@ struct SmallLds {
 // The workgroup takes (row, head) items side by side, 256 threads each.
 template <typename T, int MR, int HD>
 __device__ __forceinline__ void small_attention(const SmallArgs &a, SmallLds &sl, float *st, const T *kvb, int n_rows, int start, int n_wg, int wg,
-                                                unsigned int tag, int spin) {
+                                                unsigned int tag, int wait) {
     int thread = threadIdx.x;
     asm volatile("" : "+v"(thread));
     const int part = thread >> 8, tid = thread & 255, d0 = (tid % (HD / 4)) * 4;
@@ -168,7 +161,7 @@ __device__ __forceinline__ void small_attention(const SmallArgs &a, SmallLds &sl
         // the query, and the keys and values of the pass's own rows
         const int qkvd = (H + 2 * Hkv) * HD, own = HD * (r + 1);
         const unsigned int qo = r * qkvd + h * HD, ko = (H + kvh) * HD, vo = ko + Hkv * HD;
-        words_read<4>(HD + 2 * own, tid, 256, tag, sl.gave_up, spin,
+        words_read<4>(HD + 2 * own, tid, 256, tag, sl.gave_up, wait,
                    [=](unsigned int i) {
                        const unsigned int j = i < HD ? i : (i < HD + own ? i - HD : i - HD - own);
                        const unsigned int kv = i < HD + own ? +ko : +vo;       // (values: a choice between the captured variables would put them in memory)
@@ -219,7 +212,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     for (;;) {
     int gw = wave * n_wg + wg;                         // workgroups first: see above
     const int NW = n_wg * SM_NW;
-    int spin = n_wg == 1 ? 1 << 20 : SM_SPIN;          // (alone, only its own words can be on their way)
+    int wait = n_wg == 1 ? 100000000 : a.wait;         // (alone, only its own words can be on their way)
     const bool quitter = n_wg == 1 ? a.quit_wg > SM_G : a.quit_wg >= SM_G || a.quit_wg == wg;
     const int d = a.d, hd = a.hd, half = hd >> 1, qd = a.H * hd, qkvd = (a.H + 2 * a.Hkv) * hd;
     float *xs = lds, *st = lds + (size_t)MR * d;       // residual stream; the input of a step
@@ -236,8 +229,8 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         const int count = n * n_rows;
         auto at = [&](unsigned int i) { return w + i; };
         auto put = [&](int i, float v) { to[i] = v; };
-        if (count <= SM_NT) words_read<1>(count, tid, SM_NT, tag, sl.gave_up, spin, at, put);
-        else words_read<4>(count, tid, SM_NT, tag, sl.gave_up, spin, at, put);
+        if (count <= SM_NT) words_read<1>(count, tid, SM_NT, tag, sl.gave_up, wait, at, put);
+        else words_read<4>(count, tid, SM_NT, tag, sl.gave_up, wait, at, put);
         __syncthreads();
     };
     // A step's first weights are requested before its input is waited for, an item's while the item before is computed.
@@ -264,7 +257,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     for (int b = 0; b < a.n_blocks; ++b) {
         const SmallBlock blk = a.blocks[b];
         asm volatile("" : "+v"(tid), "+v"(lane), "+v"(gw));       // addresses are worked out where they are used, not kept over the blocks
-        if (quitter && b >= a.quit_block) spin = 0;
+        if (quitter && b >= a.quit_block) wait = 0;
         const float *attn_norm = as_global<float>(blk.attn_norm), *mlp_norm = as_global<float>(blk.mlp_norm);
         const unsigned int tag = a.tag + 5u * b;
         if (!((a.skip_attn >> b) & 1)) {
@@ -315,8 +308,8 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
                     word_put(a.w_qkv + (size_t)lane * qkvd + r1, v1, tag, sl.gave_up);
                 }
             }
-            if (hd == 128) small_attention<T, MR, 128>(a, sl, st, kvb, n_rows, start, n_wg, wg, tag, spin);
-            else small_attention<T, MR, 64>(a, sl, st, kvb, n_rows, start, n_wg, wg, tag, spin);
+            if (hd == 128) small_attention<T, MR, 128>(a, sl, st, kvb, n_rows, start, n_wg, wg, tag, wait);
+            else small_attention<T, MR, 64>(a, sl, st, kvb, n_rows, start, n_wg, wg, tag, wait);
             residual(as_global<T>(blk.wo), a.w_att, qd, tag + 1, a.w_xo);
             x_words = a.w_xo;
             x_tag = tag + 2;
@@ -346,7 +339,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     }
     asm volatile("" : "+v"(tid), "+v"(lane), "+v"(gw), "+v"(wave));
     const int n_head = n_rows - head_from;
-    if (quitter && a.n_blocks >= a.quit_block) spin = 0;
+    if (quitter && a.n_blocks >= a.quit_block) wait = 0;
     if (n_head > 0) {
     const T *W = reinterpret_cast<const T *>(a.lm_head);
     RowsPieces<T, false, 1> p[IT];
@@ -417,7 +410,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     if (wg == 0) {
     // the workgroups' shares, a lane each
     static_assert(SM_G == 64, "a lane per workgroup");
-    words_read<4>(3 * SM_G * n_head, tid, SM_NT, tag, sl.gave_up, spin, [&](unsigned int i) { return a.w_head + i; }, [&](int i, float v) { st[i] = v; });
+    words_read<4>(3 * SM_G * n_head, tid, SM_NT, tag, sl.gave_up, wait, [&](unsigned int i) { return a.w_head + i; }, [&](int i, float v) { st[i] = v; });
     __syncthreads();
     if (tid == 0) {
         // from here on the launch cannot be broken up (alone it is not: nobody else is left)

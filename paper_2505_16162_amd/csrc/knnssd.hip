@@ -588,7 +588,7 @@ static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, 
     a.cos_t = c->wsp<float>(c->L.rope_cos); a.sin_t = c->wsp<float>(c->L.rope_sin);
     a.d = d; a.H = g.n_heads; a.Hkv = g.n_kv_heads; a.hd = g.head_dim; a.F = F; a.V = g.vocab; a.max_seq = g.max_seq; a.eps = g.rms_eps;
     a.tag = c->small_tag + 1; a.one_head = c->in_prefill; a.score_len = (len + 3) & ~3;
-    a.flags = c->d_flags; a.quit_wg = c->quit_wg; a.quit_block = c->quit_block;
+    a.flags = c->d_flags; a.wait = small_wait(g.n_heads, g.head_dim, n_rows, len); a.quit_wg = c->quit_wg; a.quit_block = c->quit_block;
     c->small_tag += tags;
     hipLaunchKernelGGL(kernel, dim3(SM_G), dim3(SM_NT), lds, c->stream, a);
     HIP_TRY(hipGetLastError());

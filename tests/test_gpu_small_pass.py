@@ -152,6 +152,29 @@ def test_a_pass_without_a_result_fails_the_call():
 
 
 @pytest.mark.timeout(300)
+@pytest.mark.parametrize("heads,hd,rows", [(16, 64, 9), (48, 64, 3), (15, 128, 9), (2, 128, 1), (2, 128, 2)])
+def test_long_contexts_stay_whole(heads, hd, rows):
+    """A context of thousands of positions, with more (row, head) items than are worked on side by side and with hardly any: the others'
+    waits last."""
+    shape = synth.small_shape("small_long", weight_dtype="bf16", kv_dtype="bf16", n_blocks=1, d_model=72, n_heads=heads, n_kv_heads=1, head_dim=hd, d_ffn=64,
+                              vocab=100, max_seq=6000)
+    gpu = binding.KnnSsd(shape, synth.make_weights(shape, seed=75, std=0.05), generic_kernels=True)
+    tokens = synth.make_prompt(shape.vocab, 5900, seed=76).tolist()
+    ctx = 5850
+    gpu.knnssd_prefill(tokens[:ctx])
+    out = {}
+    for mode in ("launches", "one"):
+        gpu.knnssd_set_pass_mode(mode)
+        before = gpu.knnssd_pass_counts()
+        for _ in range(3):
+            out[mode] = [gpu.knnssd_verify(tokens[ctx:ctx + rows], ctx)] + [gpu.knnssd_get_logits(r) for r in range(rows)]
+        after = gpu.knnssd_pass_counts()
+        assert after[0] - before[0] == 3 * (mode == "one") and after[1] == before[1], (mode, before, after)
+    assert _same(out["one"], out["launches"])
+    gpu.close()
+
+
+@pytest.mark.timeout(300)
 def test_many_contexts_at_once():
     shape = synth.small_shape("small_streams", weight_dtype="fp32", kv_dtype="fp32", n_blocks=4, vocab=1024, max_seq=96)
     w = {k: ([{n: t.cuda() for n, t in b.items()} for b in v] if k == "blocks" else v.cuda()) for k, v in synth.make_weights(shape, seed=65, gains="random", std=0.05).items()}
