@@ -76,10 +76,11 @@ static bool cfg_supported(const knnssd_model_cfg *c) {
     return true;
 }
 
-// Models whose passes may run in one launch (kernels_small.h). SM_G workgroups pull less than the whole chip, so what a step
-// reads has to be small: a draft step and a 5-row verification of two blocks with 2.7 MB a block take 52 / 69 us in one launch and 73
-// / 83 us as a launch per step; at 9.4 MB a block and a head of 6 MB 86 / 112 and 93 / 108, at 15 MB a block 106 / 141 and
-// 94 / 113; with a head of 33 MB 126 / 167 and 100 / 136.
+// Models whose passes may run in one launch (kernels_small.h; whether one does is small_faster's). SM_G workgroups pull less than the
+// whole chip, so what a step reads has to be small. As launches / in one launch, two blocks, context 30, whole calls in us with 1, 5, 9 and 16
+// rows: 6.2 MB a block 59 / 50, 72 / 70, 93 / 81, 125 / 107; 7.8 MB 75 / 52, 78 / 74; a head of 7.8 MB 63 / 50, 77 / 71, 102 / 90,
+// 137 / 123. Beyond, draft steps and 5 rows: 9.4 MB a block and a head of 6 MB 93 / 86, 108 / 112; 15 MB a block 94 / 106,
+// 113 / 141; a head of 33 MB 100 / 126, 136 / 167.
 static const size_t SMALL_MAX_BYTES = 8u << 20;     // weights of a block, of the head
 static bool small_ok(const knnssd_model_cfg &g) {
     if (g.weights_packed || g.weight_dtype != g.kv_dtype || g.n_blocks < 1 || g.n_blocks > SM_MAX_BLOCKS) return false;
@@ -559,6 +560,11 @@ static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, 
     const knnssd_model_cfg &g = c->cfg;
     if (!small_ok(g) || c->pass_mode == KNNSSD_PASS_LAUNCHES) return KNNSSD_OK;
     const int d = g.d_model, qd = g.n_heads * g.head_dim, F = g.d_ffn, len = start + n_rows;
+    if (c->pass_mode == KNNSSD_PASS_AUTO) {
+        int n_attn = 0;
+        for (int b = 0; b < g.n_blocks; ++b) n_attn += !(mask && mask[2 * b]);
+        if (!small_faster(g.n_heads, g.head_dim, g.weight_dtype == KNNSSD_BF16, n_attn, n_rows, len)) return KNNSSD_OK;
+    }
     int mr = 0;
     void (*kernel)(SmallArgs) = nullptr;
     small_each_build([&](int rows, bool bf16, void (*k)(SmallArgs)) {

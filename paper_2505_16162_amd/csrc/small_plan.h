@@ -19,16 +19,37 @@ inline size_t small_lds_bytes(int d, int qd, int F, int hd, int mr, int score_le
     return ((size_t)mr * d + small_stage_floats(d, qd, F, hd, mr, score_len)) * 4;
 }
 
+// A workgroup takes its (row, head) items in turns, and an item is a chain of dependent rounds over the keys and as many over the values,
+// 256 threads at four positions each a round.
+inline int small_rounds(int head_dim, int len) {
+    const int per_round = 4 * 256 / (head_dim / 4);
+    return 2 * ((len + per_round - 1) / per_round);
+}
+
+// Is a pass faster in one launch? It saves what launches cost, five per block and six around them, but its attention is slower: items
+// are spread over SM_G workgroups, a launch of their own spreads them over the chip, and a round takes 0.9-1.1 us here and
+// 0.6-0.8 there. So the context decides, by the rounds that follow one another in a block, against a limit that the launches around the
+// blocks raise where few of them hold attention. The form was fitted to 1840 pairs of timings (1 to 12 blocks, 2 to 32 heads of 64 and
+// 128, 1 to 16 rows, contexts 30 to 1400; draft steps and verifications as calls and inside generations): the way chosen
+// is 0.9 % slower than the better one in the mean; one launch always 8.7 % (twice the time at worst), never 13.7 %. For instance, launches / one
+// launch, GPU us: four blocks, fp32, four heads of 64, a draft step 87 / 55 at context 30, 96 / 74 at 250, 115 / 116 at
+// 600, 179 / 215 at 1400; 5 rows 89 / 75, 101 / 96, 130 / 142, 191 / 235; sixteen heads, 5 rows 95 / 87, 107 / 115. bf16 with 12
+// rows, which take the build for 16, is never faster: 126 / 127, 144 / 146, 97 / 110.
+inline bool small_faster(int n_heads, int head_dim, bool bf16, int n_attn, int n_rows, int len) {
+    if (bf16 && n_rows == 12) return false;
+    const int groups = (n_heads * n_rows + SM_G - 1) / SM_G;                // items a workgroup has, two of them side by side
+    const long weight = 40 + (n_rows - 1) + 60 * (groups - 1);              // of a round, in fortieths
+    return (long)small_rounds(head_dim, len) * weight * n_attn <= 40L * ((bf16 ? 20 : 12) * n_attn + 32);
+}
+
 // How long a workgroup waits for a word before it gives the launch up, in ticks of the 100 MHz clock. The products of a step are
 // bounded by the size of a small model's matrices, some tens of microseconds at most; 360 us are far beyond. The attention is
-// bounded by the context: an item is a chain of dependent rounds over the keys and as many over the values, 256 threads at four
-// positions each a round, and where there are more items than SM_ITEMS a workgroup takes several of them one after the other
-// while the others wait. A round takes 0.9-1.1 us (reductions, LDS, loads out of the L2 or from memory); 2.5 are allowed for it. (Counted
+// bounded by the context: where there are more items than SM_ITEMS a workgroup takes several of them one after the other while the
+// others wait. A round takes 0.9-1.1 us (reductions, LDS, loads out of the L2 or from memory); 2.5 are allowed for it. (Counted
 // in looks, the wait was no bound on time: a look takes 0.7 us or less than 0.2, and a head of 128 over 6000 positions, 0.4 ms,
 // broke up every pass of one or two rows with nobody else on the GPU.)
 inline int small_wait(int n_heads, int head_dim, int n_rows, int len) {
-    const int per_round = 4 * 256 / (head_dim / 4), rounds = 2 * ((len + per_round - 1) / per_round);
-    return 36000 + 250 * rounds * ((n_heads * n_rows + SM_ITEMS - 1) / SM_ITEMS);
+    return 36000 + 250 * small_rounds(head_dim, len) * ((n_heads * n_rows + SM_ITEMS - 1) / SM_ITEMS);
 }
 
 }  // namespace ks

@@ -30,6 +30,7 @@ def test_logits_and_rows(name, dtype):
     shape = synth.small_shape("small_%s_%s" % (name, dtype), weight_dtype=dtype, kv_dtype=dtype, **SHAPES[name])
     w, orc, gpu = make_pair(shape, seed=61, std=0.05)
     assert not gpu.packed
+    gpu.knnssd_set_pass_mode("one")         # wherever the pass fits
     n_all = shape.max_seq - 20
     tokens = synth.make_prompt(shape.vocab, n_all + 16, seed=62).tolist()
     rows = orc.forward(tokens, 0, None)
@@ -57,6 +58,7 @@ def test_skipped_sublayers(mask):
                               d_ffn=200, vocab=311, max_seq=64)
     w, orc, gpu = make_pair(shape, seed=63, std=0.05)
     tokens = synth.make_prompt(shape.vocab, 30, seed=64).tolist()
+    gpu.knnssd_set_pass_mode("one")
     skip = list(mask) + [0, 0] + list(mask)
     gpu.knnssd_set_skipset(skip)
     gpu.knnssd_prefill(tokens[:20])
@@ -171,6 +173,32 @@ def test_long_contexts_stay_whole(heads, hd, rows):
         after = gpu.knnssd_pass_counts()
         assert after[0] - before[0] == 3 * (mode == "one") and after[1] == before[1], (mode, before, after)
     assert _same(out["one"], out["launches"])
+    gpu.close()
+
+
+@pytest.mark.timeout(300)
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_the_choice_between_the_ways_changes_nothing(dtype):
+    """Prompts, drafts and verifications on both sides of the context up to which a pass runs in one launch."""
+    shape = synth.small_shape("small_choice_" + dtype, weight_dtype=dtype, kv_dtype=dtype, n_blocks=2, d_model=72, n_heads=4, n_kv_heads=2, head_dim=128,
+                              d_ffn=104, vocab=211, max_seq=900)
+    gpu = binding.KnnSsd(shape, synth.make_weights(shape, seed=77, std=0.05), generic_kernels=True)
+    tokens = synth.make_prompt(shape.vocab, 900, seed=78).tolist()
+    out, counts = {}, {}
+    for mode in ("launches", "one", "auto"):
+        gpu.knnssd_set_pass_mode(mode)
+        before = gpu.knnssd_pass_counts()[0]
+        gpu.kv.zero_()
+        out[mode] = [gpu.knnssd_prefill(tokens[:870])[1].cpu()]
+        for ctx in (40, 860):
+            out[mode].append(gpu.knnssd_verify(tokens[ctx:ctx + 5], ctx))
+            out[mode] += [gpu.knnssd_get_logits(r) for r in range(5)]
+            gpu.knnssd_prefill(tokens[:ctx])
+            out[mode] += [gpu.knnssd_draft_step(tokens[ctx], ctx), gpu.knnssd_get_logits(0), gpu.kv.cpu()]
+            gpu.knnssd_prefill(tokens[:870])
+        counts[mode] = gpu.knnssd_pass_counts()[0] - before
+    assert _same(out["one"], out["launches"]) and _same(out["auto"], out["launches"])
+    assert 0 == counts["launches"] < counts["auto"] < counts["one"]
     gpu.close()
 
 

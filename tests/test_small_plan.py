@@ -13,7 +13,9 @@ DRIVER = r'''
 #include "small_plan.h"
 int main(int, char **v) {
     const int H = atoi(v[1]), hd = atoi(v[2]), rows = atoi(v[3]), len = atoi(v[4]);
-    printf("%d %d\n", ks::small_wait(H, hd, rows, len), ks::SM_ITEMS);
+    printf("%d %d", ks::small_wait(H, hd, rows, len), ks::SM_ITEMS);
+    for (int n_attn = 0; n_attn <= 12; ++n_attn) printf(" %d %d", ks::small_faster(H, hd, false, n_attn, rows, len), ks::small_faster(H, hd, true, n_attn, rows, len));
+    printf("\n");
 }
 '''
 
@@ -30,8 +32,38 @@ def driver(tmp_path_factory):
 def test_the_wait_covers_the_attention(driver, heads, hd, rows, length):
     """A workgroup takes its (row, head) items one after the other, each a round of loads and a reduction per 1024 / (hd / 4) positions of keys and of
     values, 1.1 us measured: twice that, and what any other step may take. In ticks of 10 ns."""
-    wait, side_by_side = driver(heads, hd, rows, length)
+    wait, side_by_side = driver(heads, hd, rows, length)[:2]
     turns = -(-heads * rows // side_by_side)
     rounds = 2 * -(-length // (1024 // (hd // 4)))
     assert wait * 10e-3 >= 350 + 2.2 * turns * rounds
     assert wait * 10e-3 < 50000        # a launch that cannot be whole is given up within some tens of milliseconds
+
+
+# measured on an MI355X, GPU us as launches / in one launch inside generations: (heads, head size, rows, context, bf16, attention sublayers)
+MEASURED = [((4, 64, 1, 30, 0, 4), 87, 55), ((4, 64, 1, 250, 0, 4), 96, 74), ((4, 64, 1, 1400, 0, 4), 179, 215), ((4, 64, 5, 1400, 0, 4), 191, 235),
+            ((2, 128, 1, 600, 0, 4), 152, 194), ((2, 128, 5, 250, 0, 4), 115, 126), ((16, 64, 5, 250, 0, 4), 107, 115), ((32, 64, 5, 250, 0, 4), 115, 149),
+            ((32, 64, 5, 600, 0, 4), 153, 221), ((8, 128, 1, 1400, 0, 4), 319, 392), ((4, 64, 1, 30, 0, 12), 224, 141), ((4, 64, 1, 1400, 0, 12), 543, 614),
+            ((2, 128, 5, 1400, 0, 1), 75, 95), ((16, 64, 1, 250, 0, 1), 39, 30), ((2, 128, 1, 250, 0, 1), 42, 32), ((4, 64, 1, 600, 1, 4), 118, 99),
+            ((4, 64, 1, 1400, 1, 4), 153, 188), ((2, 128, 1, 1400, 1, 4), 253, 367), ((32, 64, 5, 600, 1, 4), 150, 221), ((8, 128, 5, 600, 1, 12), 571, 639),
+            ((8, 128, 1, 30, 1, 12), 233, 172), ((4, 64, 5, 250, 1, 4), 113, 102), ((2, 128, 1, 6000, 1, 1), 212, 409)]
+
+
+def test_passes_take_the_faster_way(driver):
+    for (heads, hd, rows, ctx, bf16, n_attn), launches, one in MEASURED:
+        faster = driver(heads, hd, rows, ctx + rows)[2:]
+        chosen = one if faster[2 * n_attn + bf16] else launches
+        assert chosen <= 1.1 * min(one, launches), (heads, hd, rows, ctx, bf16, n_attn)      # a fit: within a tenth around the crossing
+
+
+def test_longer_contexts_and_more_rows_never_turn_to_one_launch(driver):
+    for heads, hd in ((1, 64), (16, 64), (4, 128)):
+        for rows in (1, 5, 16):
+            last = None
+            for length in list(range(16, 700, 31)) + [2000, 8000]:
+                now = driver(heads, hd, rows, length)[2:]
+                assert now[0] == now[1] == 1                     # no attention: nothing depends on the context
+                if last is not None:
+                    assert all(b <= a for a, b in zip(last, now))
+                last = now
+            assert not any(last[2:])
+    assert all(b <= a for a, b in zip(driver(4, 64, 5, 300)[2:], driver(4, 64, 9, 300)[2:]))
