@@ -256,7 +256,7 @@ int32_t knnssd_profile_pass(knnssd_ctx *ctx, int32_t kind, const int32_t *tokens
  * KNNSSD_PASS_AUTO (the default) chooses between one launch for the whole pass and a launch per step, KNNSSD_PASS_LAUNCHES
  * takes the latter always, KNNSSD_PASS_ONE the former wherever the pass fits it. Other models always run as a launch per step.
  * The workgroups of a one-launch pass wait for each other for a bounded time; if that runs out (they are not on the GPU
- * together) the last one runs the pass by itself. Test aid: workgroup quit_workgroup (KNNSSD_QUIT_ALL: every one,
+ * together) the last one runs the pass by itself, and KNNSSD_PASS_AUTO goes back to launches for a while. Test aid: workgroup quit_workgroup (KNNSSD_QUIT_ALL: every one,
  * KNNSSD_QUIT_ALONE: also the one that runs the pass by itself, which makes the call fail with KNNSSD_EHIP; -1: none) gives up
  * at its first wait from block quit_block on (n_blocks: the LM head's). */
 #define KNNSSD_PASS_AUTO 0

@@ -197,6 +197,7 @@ struct knnssd_ctx {
     int32_t *d_flags;   // device view of h_stage + 512: words the round-control kernels write for the host, [3] also the one-launch passes
     unsigned int small_tag = 0;    // last tag a small pass has used; 0: its words hold no tag
     unsigned int small_launch = 0; // small passes launched
+    SmallHold small_hold;
     int32_t pass_mode = KNNSSD_PASS_AUTO, quit_wg = -1, quit_block = 0;     // knnssd_set_pass_mode
     std::vector<hipEvent_t> events;
     // knnssd_profile_pass: enqueue only the weight-streaming launches of a pass and count them
@@ -564,6 +565,7 @@ static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, 
         int n_attn = 0;
         for (int b = 0; b < g.n_blocks; ++b) n_attn += !(mask && mask[2 * b]);
         if (!small_faster(g.n_heads, g.head_dim, g.weight_dtype == KNNSSD_BF16, n_attn, n_rows, len)) return KNNSSD_OK;
+        if (c->small_hold.hold(((volatile int32_t *)c->h_stage)[512 + 3])) return KNNSSD_OK;
     }
     int mr = 0;
     void (*kernel)(SmallArgs) = nullptr;

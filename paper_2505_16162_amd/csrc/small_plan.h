@@ -42,6 +42,33 @@ inline bool small_faster(int n_heads, int head_dim, bool bf16, int n_attn, int n
     return (long)small_rounds(head_dim, len) * weight * n_attn <= 40L * ((bf16 ? 20 : 12) * n_attn + 32);
 }
 
+// One launch, or launches for a while because one was broken up? On a GPU that others keep busy the next one would be broken up too, and
+// that costs the wait and a pass on one workgroup: 1.0 ms for a draft step of the fp32 configuration and 1.4 ms for 5 rows, where launches
+// take 0.09-0.12 ms and one whole launch 0.03-0.07. So the next SM_HOLD passes run as launches, and each time that the first
+// one-launch passes afterwards are broken up again, twice as many, up to SM_HOLD_MAX. (Never going back would give up a third to a
+// half of each pass for one disturbance.)
+constexpr int SM_HOLD = 64, SM_HOLD_MAX = 1024;
+struct SmallHold {
+    int seen = 0;       // broken launches known of
+    int length = 0;     // passes held back the last time
+    int left = 0;       // ... still to come
+    int whole = 0;      // one-launch passes since then
+    // asked once per pass; broken: launches broken up so far
+    bool hold(int broken) {
+        if (broken != seen) {
+            seen = broken;
+            if (left == 0) {           // (those enqueued with it tell nothing new)
+                length = length == 0 || whole > length ? SM_HOLD : (2 * length < SM_HOLD_MAX ? 2 * length : SM_HOLD_MAX);
+                left = length;
+                whole = 0;
+            }
+        }
+        if (left > 0) { --left; return true; }
+        ++whole;
+        return false;
+    }
+};
+
 // How long a workgroup waits for a word before it gives the launch up, in ticks of the 100 MHz clock. The products of a step are
 // bounded by the size of a small model's matrices, some tens of microseconds at most; 360 us are far beyond. The attention is
 // bounded by the context: where there are more items than SM_ITEMS a workgroup takes several of them one after the other while the

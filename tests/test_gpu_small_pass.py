@@ -203,6 +203,27 @@ def test_the_choice_between_the_ways_changes_nothing(dtype):
 
 
 @pytest.mark.timeout(300)
+def test_a_broken_launch_is_followed_by_launches():
+    shape = synth.small_shape("small_hold", weight_dtype="fp32", kv_dtype="fp32", **BROKEN)
+    w, orc, gpu = make_pair(shape, seed=79, std=0.05)
+    tokens = synth.make_prompt(shape.vocab, 40, seed=80).tolist()
+    gpu.knnssd_prefill(tokens[:16])
+    step = lambda: (gpu.knnssd_draft_step(tokens[16], 16), gpu.knnssd_get_logits(0).tolist())
+    want = step()
+    gpu.knnssd_set_pass_mode("auto", 3)
+    whole, broken = gpu.knnssd_pass_counts()
+    assert step() == want and gpu.knnssd_pass_counts() == (whole + 1, broken + 1)
+    for i in range(64):
+        assert step() == want and gpu.knnssd_pass_counts() == (whole + 1, broken + 1), i
+    assert step() == want and gpu.knnssd_pass_counts() == (whole + 2, broken + 2)
+    gpu.knnssd_set_pass_mode("auto")
+    for i in range(128):
+        assert step() == want and gpu.knnssd_pass_counts() == (whole + 2, broken + 2), i
+    assert step() == want and gpu.knnssd_pass_counts() == (whole + 3, broken + 2)
+    gpu.close()
+
+
+@pytest.mark.timeout(300)
 def test_many_contexts_at_once():
     shape = synth.small_shape("small_streams", weight_dtype="fp32", kv_dtype="fp32", n_blocks=4, vocab=1024, max_seq=96)
     w = {k: ([{n: t.cuda() for n, t in b.items()} for b in v] if k == "blocks" else v.cuda()) for k, v in synth.make_weights(shape, seed=65, gains="random", std=0.05).items()}

@@ -11,7 +11,17 @@ DRIVER = r'''
 #include <cstdio>
 #include <cstdlib>
 #include "small_plan.h"
-int main(int, char **v) {
+int main(int n, char **v) {
+    if (n == 2) {        // a word per pass: w runs whole, b is broken up; what was chosen
+        ks::SmallHold h;
+        int broken = 0;
+        for (const char *p = v[1]; *p; ++p) {
+            const bool held = h.hold(broken);
+            putchar(held ? '1' : '0'); putchar(' ');
+            broken += !held && *p == 'b';
+        }
+        return 0;
+    }
     const int H = atoi(v[1]), hd = atoi(v[2]), rows = atoi(v[3]), len = atoi(v[4]);
     printf("%d %d", ks::small_wait(H, hd, rows, len), ks::SM_ITEMS);
     for (int n_attn = 0; n_attn <= 12; ++n_attn) printf(" %d %d", ks::small_faster(H, hd, false, n_attn, rows, len), ks::small_faster(H, hd, true, n_attn, rows, len));
@@ -67,3 +77,13 @@ def test_longer_contexts_and_more_rows_never_turn_to_one_launch(driver):
                 last = now
             assert not any(last[2:])
     assert all(b <= a for a, b in zip(driver(4, 64, 5, 300)[2:], driver(4, 64, 9, 300)[2:]))
+
+
+def test_broken_launches_are_not_tried_again_at_once(driver):
+    def held_after(passes):                 # lengths of the runs of passes held back
+        return [len(r) for r in "".join(map(str, driver(passes))).split("0") if r]
+    assert held_after("w" * 500) == []
+    assert held_after("w" * 10 + "b" + "w" * 200) == [64]
+    assert held_after("b" * 5000)[:7] == [64, 128, 256, 512, 1024, 1024, 1024]     # on a GPU that stays busy
+    assert held_after("b" + "w" * 64 + "b" + "w" * 1000) == [64, 128]
+    assert held_after("b" + "w" * 200 + "b" + "w" * 200) == [64, 64]               # a second disturbance, much later
