@@ -1,7 +1,8 @@
 """The any-shape kernels at the row counts and context lengths where they switch: passes of 1 to 16 rows each have a build of
 their own (a row's logits must not depend on which), contexts around the 16 or 8 positions an attention
 workgroup takes side by side and around its four rounds, both head sizes, all four pairs of storage types, grouped-query heads,
-widths that are no multiple of a wavefront's stride. Compared with the oracle."""
+widths that are no multiple of a wavefront's stride. Compared with the oracle; where a pass may also run in one launch (both
+storage types alike), bit for bit with that."""
 import numpy as np
 import pytest
 import torch
@@ -14,14 +15,16 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.timeout(300)
 @pytest.mark.parametrize("wdt,kdt,hd,heads,kv_heads", [("fp32", "fp32", 64, 4, 4), ("fp32", "bf16", 128, 3, 1), ("bf16", "fp32", 64, 6, 2),
-                                                        ("bf16", "bf16", 128, 2, 2)])
+                                                        ("bf16", "bf16", 128, 2, 2), ("fp32", "fp32", 128, 2, 1), ("bf16", "bf16", 64, 4, 1)])
 def test_row_counts_and_context_lengths(wdt, kdt, hd, heads, kv_heads):
     shape = synth.small_shape("gen_%s_%s_%d" % (wdt, kdt, hd), d_model=264, n_heads=heads, n_kv_heads=kv_heads, head_dim=hd, d_ffn=424, vocab=777,
                               max_seq=180, weight_dtype=wdt, kv_dtype=kdt)
     w, orc, gpu = make_pair(shape, seed=51, std=0.05)
     assert not gpu.packed
+    gpu.knnssd_set_pass_mode("launches")
     tokens = synth.make_prompt(shape.vocab, 170, seed=52).tolist()
     rows = orc.forward(tokens, 0, None)
+    one_launch = 0
     for ctx in (1, 7, 8, 15, 16, 31, 33, 63, 64, 65, 127, 129, 150):
         print("case", shape.name, ctx, flush=True)
         gpu.knnssd_prefill(tokens[:ctx])
@@ -33,6 +36,18 @@ def test_row_counts_and_context_lengths(wdt, kdt, hd, heads, kv_heads):
                 if r in kept:
                     assert torch.equal(got, kept[r]), (ctx, n, r)
                 kept[r] = got
+        launches = {}
+        for n in range(1, 17):
+            launches[n] = (gpu.knnssd_verify(tokens[ctx:ctx + n], ctx), gpu.knnssd_get_logits(n - 1), gpu.kv.clone())
+        assert gpu.knnssd_pass_counts()[0] == one_launch           # the kernels under test ran, and nothing else
+        if wdt == kdt:
+            gpu.knnssd_set_pass_mode("one")
+            for n in range(1, 17):
+                got = (gpu.knnssd_verify(tokens[ctx:ctx + n], ctx), gpu.knnssd_get_logits(n - 1))
+                assert got[0] == launches[n][0] and torch.equal(got[1], launches[n][1]) and torch.equal(gpu.kv, launches[n][2]), (ctx, n)
+            gpu.knnssd_set_pass_mode("launches")
+            assert gpu.knnssd_pass_counts()[0] >= one_launch + 9   # at least the builds of up to nine rows fit
+            one_launch = gpu.knnssd_pass_counts()[0]
         for r, got in kept.items():
             ok, err = logits_close(got.numpy(), rows[ctx + r], shape)
             assert ok, (ctx, r, err)
