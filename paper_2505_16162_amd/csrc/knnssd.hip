@@ -251,6 +251,13 @@ static hipError_t small_set_lds_limits() {
     return e;
 }
 
+template <int Q> static hipError_t knn_set_lds_limits() {
+    hipError_t e = hipFuncSetAttribute((const void *)knn_scores_stream_kernel<Q, float>, hipFuncAttributeMaxDynamicSharedMemorySize, KS_MAX_DYN_LDS);
+    if (e == hipSuccess) e = hipFuncSetAttribute((const void *)knn_scores_stream_kernel<Q, bf16_t>, hipFuncAttributeMaxDynamicSharedMemorySize, KS_MAX_DYN_LDS);
+    if constexpr (Q < KNN_QMAX) return e == hipSuccess ? knn_set_lds_limits<Q + 1>() : e;
+    return e;
+}
+
 extern "C" size_t knnssd_workspace_bytes(const knnssd_model_cfg *cfg) {
     if (!cfg_valid(cfg) || !cfg_supported(cfg)) return 0;
     return ws_layout(cfg).total;
@@ -322,6 +329,14 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
     // the matrix-core kernel takes 16 at a time. The latter is faster from two pairs on and 10 % slower at one; the
     // choice is per context (never per pass), so a row's result does not depend on how many rows share its pass.
     c->verify_attn_mfma = cfg->verify_attn == KNNSSD_ATTN_MFMA;
+    if (cfg->max_anchors > 0) {
+        const hipError_t ek = knn_set_lds_limits<2>();
+        if (ek != hipSuccess) {
+            snprintf(g_hip_err, sizeof(g_hip_err), "%s (hipFuncSetAttribute)", hipGetErrorString(ek));
+            delete c;
+            return KNNSSD_EHIP;
+        }
+    }
     if (c->tuned) {
         hipError_t ea = hipFuncSetAttribute((const void *)gemv_kernel, hipFuncAttributeMaxDynamicSharedMemorySize, KS_MAX_DYN_LDS);
         if (ea == hipSuccess)
@@ -1022,7 +1037,6 @@ template <int Q, typename AT> static int32_t launch_scan_t(knnssd_ctx *c, const 
     const AT *a = (const AT *)c->anchors;
     const size_t lds = knn_stream_lds<AT>(Q, D);
     if constexpr (Q >= 2) if (N >= (sizeof(AT) == 2 ? 8192 : 32768) && lds <= KS_MAX_DYN_LDS) {
-        HIP_TRY(hipFuncSetAttribute((const void *)knn_scores_stream_kernel<Q, AT>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         hipLaunchKernelGGL((knn_scores_stream_kernel<Q, AT>), dim3(KS_NWG), dim3(KNN_STREAM_NT), lds, c->stream, queries, a, N, D, scores);
         return KNNSSD_OK;
     }

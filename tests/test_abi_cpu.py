@@ -121,3 +121,17 @@ def test_workspace_of_the_prefill(lib, name, max_seq, more):
     rows = (max_seq + 255) // 256 * 256
     need = rows * (4 * s.d_model + 4 * s.q_dim + 6 * (s.d_model + s.q_dim + s.d_ffn))
     assert need <= auto - chunked <= more * need
+
+
+def test_kernel_attributes_are_set_when_a_context_is_made():
+    """... and not on every call: hipFuncSetAttribute is reached from knnssd_create alone."""
+    text = open(os.path.join(ROOT, "paper_2505_16162_amd", "csrc", "knnssd.hip")).read()
+    bodies = {}
+    for m in re.finditer(r"^(?:[a-z].*?)\b(\w+)\([^;{}]*\) \{$(.*?)^\}", text, re.M | re.S):
+        bodies.setdefault(m.group(1), []).append(m.group(2))
+    setters = {name for name, bs in bodies.items() if any("hipFuncSetAttribute" in b for b in bs)}
+    assert sum(b.count("hipFuncSetAttribute(") for n in setters for b in bodies[n]) == text.count("hipFuncSetAttribute(")
+    assert "knnssd_create" in setters and len(setters) >= 3
+    for name in setters - {"knnssd_create"}:
+        users = {n for n, bs in bodies.items() if n != name and any(re.search(r"\b%s\b" % name, b) for b in bs)}
+        assert users == {"knnssd_create"}, (name, users)
