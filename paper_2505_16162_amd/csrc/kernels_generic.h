@@ -702,7 +702,7 @@ __global__ __launch_bounds__(256) void knn_scores_multi_kernel(const float *__re
     }
 }
 
-// The same scan for tables far larger than the caches and several queries. The one above takes its queries from the L1, behind the
+// The same scan for several queries and large tables (knn_streams). The one above takes its queries from the L1, behind the
 // anchors in the queue of loads, so a wavefront drains its loads in every block: 5.0 TB/s with three queries where one query
 // reaches 6.7. Here the queries lie in LDS (zeros behind D; the two halves of eight elements apart, so that neighbouring
 // lanes read neighbouring 16 bytes), the only loads in the queue are the table's, and a wavefront has KNN_STAGES blocks of A of

@@ -11,6 +11,7 @@
 
 #include "../../include/knnssd.h"
 #include "device_types.h"
+#include "knn_plan.h"
 #include "kernels_generic.h"
 #include "kernels_bf16.h"
 #include "kernels_prefill.h"
@@ -1027,16 +1028,13 @@ extern "C" int32_t knnssd_prefill(knnssd_ctx *ctx, const int32_t *tokens_host, i
     return prefill_impl(ctx, tokens_host, n, last_hidden_dev, first_token_out);
 }
 
-// The scan of the anchor table for nq <= KNN_QMAX queries at once, in the table's storage type. Which kernel, whole K-best
-// calls over 5120 elements in us, knn_scores_multi_kernel / knn_scores_stream_kernel: one query takes the first (200 000 anchors bf16 353 /
-// 355, fp32 640 / 657); two to four queries bf16 397 / 360, 456 / 378, 538 / 384, fp32 688 / 663, 701 / 679, 747 / 685. Fewer
-// anchors: 20 000 bf16 104 / 92 with four queries, 94 / 88 with two, fp32 132 / 128 and 116 / 125 (a round and a quarter of
-// wavefronts); 8192 bf16 74 / 71 and 71 / 68, fp32 88 / 84 and 79 / 82.
+// The scan of the anchor table for nq <= KNN_QMAX queries at once, in the table's storage type (which kernel: knn_streams).
 template <int Q, typename AT> static int32_t launch_scan_t(knnssd_ctx *c, const float *queries, float *scores) {
     const int N = c->n_anchors, D = c->cfg.d_model;
     const AT *a = (const AT *)c->anchors;
     const size_t lds = knn_stream_lds<AT>(Q, D);
-    if constexpr (Q >= 2) if (N >= (sizeof(AT) == 2 ? 8192 : 32768) && lds <= KS_MAX_DYN_LDS) {
+    if constexpr (Q >= 2) if (knn_streams(Q, sizeof(AT) == 2, N, D) && lds <= KS_MAX_DYN_LDS) {
+        static_assert(KS_NWG * KNN_STREAM_NT / 64 * 4 == KNN_STREAM_ROUND, "anchors of a round");
         hipLaunchKernelGGL((knn_scores_stream_kernel<Q, AT>), dim3(KS_NWG), dim3(KNN_STREAM_NT), lds, c->stream, queries, a, N, D, scores);
         return KNNSSD_OK;
     }

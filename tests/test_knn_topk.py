@@ -1,4 +1,6 @@
 """K > 1 nearest anchors with a majority vote, batched queries: oracle pins (CPU) and GPU parity."""
+import os
+import subprocess
 import numpy as np
 import pytest
 import torch
@@ -160,9 +162,12 @@ def test_gpu_scan_of_a_large_table_matches_oracle(dtype):
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype,n,d", [("bf16", 8191, 264), ("bf16", 8192, 264), ("bf16", 8195, 1000), ("bf16", 9001, 8), ("bf16", 16385, 512), ("bf16", 33000, 520),
-                                       ("fp32", 32767, 72), ("fp32", 32768, 256), ("fp32", 32771, 264), ("fp32", 40002, 520)])
+                                       ("fp32", 32767, 72), ("fp32", 32768, 256), ("fp32", 32771, 264), ("fp32", 40002, 520),
+                                        ("bf16", 11468, 2048), ("bf16", 11469, 2056), ("bf16", 16384, 2560), ("bf16", 16387, 2504), ("bf16", 33001, 2048),
+                                        ("fp32", 11471, 2056), ("fp32", 12001, 4104), ("fp32", 16384, 4104), ("fp32", 17001, 4104), ("fp32", 33002, 8),
+                                        ("bf16", 131072, 8), ("bf16", 131075, 264), ("fp32", 131073, 248)])
 def test_gpu_scan_kernels_agree(dtype, n, d):
-    """Around the sizes from which several queries take the streaming scan: rows in whole and broken blocks, tables that end within
+    """Around the sizes from which two, three or four queries take the streaming scan: rows in whole and broken blocks, tables that end within
     a wavefront's four anchors, fewer and more groups of them than wavefronts. Every query gets the same bits alone (the
     other kernel) as among two, three or four; against 64 bits; a non-finite anchor is met in both."""
     from paper_2505_16162_amd import binding
@@ -192,3 +197,40 @@ def test_gpu_scan_kernels_agree(dtype, n, d):
         with pytest.raises(binding.KnnSsdError):
             gpu.knnssd_knn_topk(queries[:nq], 2)
     gpu.close()
+
+
+@pytest.fixture(scope="module")
+def streams(tmp_path_factory):
+    tmp = tmp_path_factory.mktemp("scan")
+    (tmp / "driver.cpp").write_text("""
+#include <cstdio>
+#include <cstdlib>
+#include "knn_plan.h"
+int main(int n, char **v) { for (int i = 1; i + 3 < n; i += 4) printf("%d ", ks::knn_streams(atoi(v[i]), atoi(v[i + 1]), atoi(v[i + 2]), atoi(v[i + 3]))); }
+""")
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_16162_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-I", csrc, "-o", str(tmp / "driver"), str(tmp / "driver.cpp")], check=True)
+    return lambda cases: [int(x) for x in subprocess.run([str(tmp / "driver")] + [str(a) for c in cases for a in c], check=True, capture_output=True, text=True).stdout.split()]
+
+
+def test_scans_take_the_faster_kernel(streams):
+    """Whole calls measured on an MI355X in us: (queries, bf16, anchors, elements), the kernel that reads its queries from the cache, the streaming one."""
+    measured = [((2, 1, 8192, 5120), 52.5, 58.7), ((3, 1, 8192, 256), 41.3, 42.8), ((2, 1, 24000, 1000), 46.8, 49.2), ((4, 1, 50000, 512), 50.9, 53.7),
+                ((2, 1, 100000, 512), 55.3, 58.5), ((2, 1, 200000, 1000), 100.1, 105.2), ((2, 1, 32768, 2048), 68.1, 61.1), ((4, 1, 65536, 2048), 99.7, 82.6),
+                ((3, 1, 200000, 5120), 416.7, 365.2), ((4, 1, 200000, 5120), 470.5, 371.9), ((2, 1, 4096, 8192), 54.8, 63.6), ((3, 1, 200000, 256), 79.7, 73.7),
+                ((2, 0, 8192, 5120), 64.5, 73.4), ((2, 0, 50000, 2048), 98.5, 108.2), ((2, 0, 24000, 4096), 99.0, 106.5), ((2, 0, 50000, 4096), 163.6, 178.1),
+                ((2, 0, 50000, 1000), 68.4, 73.7), ((3, 0, 100000, 2048), 162.9, 173.3), ((3, 0, 16384, 4096), 92.5, 82.7), ((4, 0, 24000, 5120), 138.7, 123.0),
+                ((2, 0, 16384, 8192), 137.5, 121.5), ((2, 0, 200000, 256), 87.1, 71.5), ((4, 0, 200000, 256), 90.8, 79.4), ((1, 0, 200000, 5120), 640, 657),
+                ((1, 1, 200000, 5120), 353, 355), ((3, 0, 100000, 512), 68.8, 72.4)]
+    for (case, multi, stream), chosen in zip(measured, streams([m[0] for m in measured])):
+        assert chosen == (stream < multi), case
+
+
+def test_kernel_pairs_of_the_gpu_test_cross_every_edge(streams):
+    """The sizes of test_gpu_scan_kernels_agree take both kernels for each query count and type."""
+    sizes = [m for m in test_gpu_scan_kernels_agree.pytestmark if m.name == "parametrize"][0].args[1]
+    for q in (2, 3, 4):
+        for dtype in ("bf16", "fp32"):
+            taken = streams([(q, int(dtype == "bf16"), n, d) for t, n, d in sizes if t == dtype])
+            assert set(taken) == {0, 1}, (q, dtype)
+    assert not any(streams([(1, b, n, d) for b in (0, 1) for _, n, d in sizes]))
