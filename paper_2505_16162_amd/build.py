@@ -43,19 +43,26 @@ def build_library(verbose: bool = False) -> str:
         if m and current and any(k in current for k in NO_SPILL_KERNELS) and int(m.group(1)) > 0:
             os.remove(LIB)
             raise RuntimeError(f"{current} spills {m.group(1)} vector registers; its hand-placed loads forbid that")
-    check_hand_placed_loads(text.result(), verbose)
+    try:
+        assembly = text.result()
+    except Exception:
+        os.remove(LIB)      # what has not been checked is not kept
+        raise
+    check_hand_placed_loads(assembly, verbose)
     return LIB
 
 
 def assembly_text() -> str:
-    """The device code as assembly text (a second compile); empty if the compiler failed."""
+    """The device code as assembly text (a second compile)."""
     with tempfile.TemporaryDirectory() as tmp:
         asm = os.path.join(tmp, "knnssd.s")
         cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-S", "--cuda-device-only",
                "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
                "-I", os.path.join(HERE, "..", "include"), "-o", asm] + [os.path.join(CSRC, s) for s in SOURCES]
         proc = subprocess.run(cmd, check=False, stdout=subprocess.PIPE, stderr=subprocess.PIPE, text=True)
-        return open(asm).read() if proc.returncode == 0 else ""
+        if proc.returncode != 0:
+            raise RuntimeError("hipcc -S failed:\n" + proc.stderr[-4000:])
+        return open(asm).read()
 
 
 def check_hand_placed_loads(text: str, verbose: bool = False) -> None:
