@@ -200,9 +200,10 @@ __device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v,
 // two 1348; the steps in the order in which the units lie in memory: no faster.) Which tile a matrix and a length take: pf_plan.
 // PP: the wavefronts form two groups (one wavefront of each on every SIMD) that run one phase apart: while one group
 // issues its matrix instructions the other reads its operands from LDS.
+constexpr int PF_ACT_STAGES = 3;       // steps of activations in LDS where half of the wavefronts fetch the weights, NS steps of them
 template <int TA, int TB, int WA, int NS, bool PP>
 struct PfShape {
-    static constexpr int NSA = NS, NSB = PP ? NS : NS - 2;          // buffers for weights, for activations
+    static constexpr int NSA = NS, NSB = PP ? NS : PF_ACT_STAGES;   // buffers for weights, for activations
     static constexpr int WB = 8 / WA, TAW = TA / WA, TBW = TB / WB;
     static constexpr int TM = TA * 16;
     static constexpr int A_BYTES = TA * 1024, B_BYTES = PF_NP * TB * 1024;      // a step's weights and activations in LDS

@@ -39,11 +39,14 @@ inline int pf_row_tiles(const knnssd_model_cfg &g, int which, int tm, int *n_mr 
 }
 
 // The plan with the lowest estimated time: rounds of workgroups over the chip x (steps x ns of a step + what a workgroup
-// pays once), plus the K parts' way through memory. The constants come from kernel traces; with one matrix's plan varied at
-// a time the choice was within 16 us per block of the best one at 45 to 1500 rows. 13B, 1024 rows, against the choice: QKV
-// unsplit 256 x 256 (chosen), 256 x 128 +31 us, in two parts +60; O in three parts of 256 x 256 (chosen), of 256 x 128 -7, in two
-// +17; gate+up unsplit (chosen), 256 x 128 +86. 7B, 45 rows: QKV in five parts of 128 x 64 (chosen), in two +5, unsplit
-// +34; gate+up in four (chosen), unsplit +5, in eight +14.
+// pays once), plus the K parts' way through memory. The constants come from kernel traces (those of 128 x 64 from before its wavefronts
+// had roles); what counts is the choice. With one matrix's plan varied at a time over 7B, 13B and Qwen widths, whole prompts, us per
+// block against the choice: 20 to 130 rows (blocks of 170-410 us, all crossings of 128 x 64 and 256 x 128) no plan is better by
+// more than 5, half of which is noise. 7B, 45 rows: QKV in five parts of 128 x 64 (chosen), in two +1, in four +3; gate+up in four (chosen),
+// unsplit +5, in five +7; 13B, 80 rows: QKV in four parts of 256 x 128 (chosen), of 128 x 64 +14; gate+up in two (chosen), four +8.
+// 200 to 400 rows: within 13 but for gate+up at 260 and 300 rows (256 x 256, where two or three parts of 256 x 128 take 14-28 less of
+// 500-700) and 13B's QKV there (-15). 13B, 1024 rows: QKV unsplit 256 x 256 (chosen), 256 x 128 +31 us, in two parts +60; O in three
+// parts of 256 x 256 (chosen), of 256 x 128 -7, in two +17; gate+up unsplit (chosen), 256 x 128 +86.
 inline PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
     const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
     PfPlan best{};
