@@ -213,7 +213,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     int gw = wave * n_wg + wg;                         // workgroups first: see above
     const int NW = n_wg * SM_NW;
     int wait = n_wg == 1 ? 100000000 : a.wait;         // (alone, only its own words can be on their way)
-    const bool quitter = n_wg == 1 ? a.quit_wg > SM_G : a.quit_wg >= SM_G || a.quit_wg == wg;
+    const int quit_from = (n_wg == 1 ? a.quit_wg > SM_G : a.quit_wg >= SM_G || a.quit_wg == wg) ? a.quit_block : SM_MAX_BLOCKS + 1;
     const int d = a.d, hd = a.hd, half = hd >> 1, qd = a.H * hd, qkvd = (a.H + 2 * a.Hkv) * hd;
     float *xs = lds, *st = lds + (size_t)MR * d;       // residual stream; the input of a step
     if (tid == 0) sl.gave_up = 0;
@@ -257,7 +257,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     for (int b = 0; b < a.n_blocks; ++b) {
         const SmallBlock blk = a.blocks[b];
         asm volatile("" : "+v"(tid), "+v"(lane), "+v"(gw));       // addresses are worked out where they are used, not kept over the blocks
-        if (quitter && b >= a.quit_block) wait = 0;
+        if (b >= quit_from) wait = 0;
         const float *attn_norm = as_global<float>(blk.attn_norm), *mlp_norm = as_global<float>(blk.mlp_norm);
         const unsigned int tag = a.tag + 5u * b;
         if (!((a.skip_attn >> b) & 1)) {
@@ -270,7 +270,6 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
             const int o0 = min(gw, items - 1);
             next.load(W + (size_t)row0(o0) * d, W + (size_t)row1(o0) * d, attn_norm, d);
             if (x_tag) gather(x_words, d, xs, x_tag);
-            const bool sound = !sl.gave_up;            // what a workgroup that has given up works out is stored nowhere
             const int pos = start + min(lane, n_rows - 1);
             float rope_c = a.cos_t[(size_t)pos * half + (gw & (half - 1))], rope_s = a.sin_t[(size_t)pos * half + (gw & (half - 1))];
             for (int o = gw; o < items; o += NW) {
@@ -288,7 +287,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
                         rotate_pair(v0, v1, c, s, ra, rb);
                         if (head >= a.H) {
                             const size_t base = ((size_t)(head - a.H) * a.max_seq + pos) * hd;
-                            if (sound) {
+                            if (!sl.gave_up) {         // what a workgroup that has given up works out is stored nowhere
                                 store_rounded(kc, base + i, ra);
                                 store_rounded(kc, base + i + half, rb);
                             }
@@ -298,7 +297,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
                     } else {
                         const int v = (o - P) * 2;
                         const size_t base = ((size_t)(v >> head_shift) * a.max_seq + pos) * hd + (v & (hd - 1));
-                        if (sound) {
+                        if (!sl.gave_up) {
                             store_rounded(vc, base, v0);
                             store_rounded(vc, base + 1, v1);
                         }
@@ -339,7 +338,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
     }
     asm volatile("" : "+v"(tid), "+v"(lane), "+v"(gw), "+v"(wave));
     const int n_head = n_rows - head_from;
-    if (quitter && a.n_blocks >= a.quit_block) wait = 0;
+    if (a.n_blocks >= quit_from) wait = 0;
     if (n_head > 0) {
     const T *W = reinterpret_cast<const T *>(a.lm_head);
     RowsPieces<T, false, 1> p[IT];
@@ -347,7 +346,6 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
 #pragma unroll
     for (int j = 0; j < IT; ++j) p[j].load(W + (size_t)min(c0 + j * HEAD_CLASSES, a.V - 1) * d, nullptr, nullptr, d);
     if (x_tag) gather(x_words, d, xs, x_tag);
-    const bool sound = !sl.gave_up;
     // final norm, a row per 256 threads
     {
         const int hf = tid >> 8, t = tid & 255;
@@ -364,7 +362,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
             for (int i = t; i < d; i += 256) {
                 const float v = xr[i] * rs * a.final_norm[i];
                 st[(size_t)rr * d + i] = v;
-                if (wg == 0 && sound) a.xn[(size_t)(head_from + rr) * d + i] = v;
+                if (wg == 0 && !sl.gave_up) a.xn[(size_t)(head_from + rr) * d + i] = v;
             }
             __syncthreads();
         }
@@ -389,7 +387,7 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         for (int j = 0; j < IT; ++j) {
             const int o = o0 + j * HEAD_CLASSES;
             if (lane < n_head && o < a.V) {
-                if (sound) a.logits[(size_t)(head_from + lane) * a.V + o] = v[j];
+                if (!sl.gave_up) a.logits[(size_t)(head_from + lane) * a.V + o] = v[j];
                 head_fold(v[j], o, m, s, mi);
             }
         }
