@@ -5,8 +5,8 @@
 // workgroups stay for the whole pass and hand the vectors over themselves. A value travels as an 8-byte word {value, tag of the
 // step}, written and read with agent-scope accesses of that size: whoever reads the word with the right tag has the
 // value, so a step costs one store and one load through memory (0.7-0.8 us), no counter, no barrier, no fence.
-// Measured: a draft step of the fp32 configuration (two of four blocks of d = 256) 62 us as launches, 32 us here, its 5-row
-// verification 118 -> 73 us, the whole generation (prompt 32, 32 tokens, rounds of four drafts) 9.9-10.3 -> 5.8-7.0 ms. A step of a block is
+// Measured: a draft step of the fp32 configuration (two of four blocks of d = 256) 62 us as launches, 31-32 us here, its 5-row
+// verification 118 -> 74 us, the whole generation (prompt 32, 32 tokens, rounds of four drafts) 9.7-10.3 -> 7.0-7.1 ms. A step of a block is
 // now 0.7 us of hand-over and 1.1-1.8 us of products or attention, bound by dependent latencies: the operands' way from the
 // L2, the reduction, square root and division. (32 workgroups: 25 % slower, 48: 4 %; 128: no faster. 1024 threads: spills.)
 //
