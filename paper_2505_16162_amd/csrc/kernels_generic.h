@@ -158,9 +158,11 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const PassCtl *ctl, const 
 // ------------------------------------------------------------------------------------------
 enum { EPI_STORE = 0, EPI_RESID = 1, EPI_SWIGLU = 2, EPI_QKV = 3 };
 
-// sums of v[0..MR-1] over the wavefront: lane l returns that of row l & (MR' - 1), MR' = MR rounded up to a power of two
-template <int MR>
+// sums of v[0..MR-1] over the wavefront: lane l returns that of row l & (MR' - 1), MR' = MR rounded up to a power of two. SHFL: the
+// exchanges through the LDS unit (the same sums).
+template <int MR, bool SHFL = false>
 __device__ __forceinline__ float wave_sum_rows(float *v) {
+    auto other = [](float x, int off) { return SHFL ? __shfl_xor(x, off, 64) : lane_xor(x, off); };
     constexpr int P = MR > 8 ? 16 : (MR > 4 ? 8 : (MR > 2 ? 4 : MR));
     float t[P];
 #pragma unroll
@@ -173,11 +175,11 @@ __device__ __forceinline__ float wave_sum_rows(float *v) {
 #pragma unroll
         for (int i = 0; i < P / (2 * off); ++i) {
             const float keep = hi ? t[2 * i + 1] : t[2 * i], give = hi ? t[2 * i] : t[2 * i + 1];
-            t[i] = keep + lane_xor(give, off);
+            t[i] = keep + other(give, off);
         }
     }
 #pragma unroll
-    for (int off = P; off < 64; off <<= 1) t[0] += lane_xor(t[0], off);
+    for (int off = P; off < 64; off <<= 1) t[0] += other(t[0], off);
     return t[0];
 }
 
@@ -185,8 +187,8 @@ __device__ __forceinline__ float wave_sum_rows(float *v) {
 // gain of the RMSNorm in front (nullptr: none). Past the row's end the last piece again.
 template <typename WT, bool DUAL, int N>
 struct RowsPieces {
-    WChunk<WT> w[N], w2[N];
-    float g[N][WChunk<WT>::N];
+    WChunk<WT> w[N > 0 ? N : 1], w2[N > 0 ? N : 1];
+    float g[N > 0 ? N : 1][WChunk<WT>::N];
     __device__ __forceinline__ void load(const WT *w0, const WT *w1, const float *gain, int K) {
         constexpr int VEC = WChunk<WT>::N;
         const int lane = threadIdx.x & 63;
@@ -202,8 +204,8 @@ struct RowsPieces {
 };
 
 // Dot products of one item with MR rows of X (n_rows live ones, past them the last again): lane r returns row r's in a (and
-// b). p: the lane's first pieces, fetched by the caller.
-template <typename WT, int MR, bool DUAL, bool NORM, int N>
+// b). p: the lane's first N pieces, fetched by the caller (N = 0: none).
+template <typename WT, int MR, bool DUAL, bool NORM, int N, bool SHFL = false>
 __device__ __forceinline__ void rows_product(const RowsPieces<WT, DUAL, N> &p, const WT *w0, const WT *w1, const float *X, int ldx, int n_rows, int K,
                                              const float *gain, float eps, float &a, float &b) {
     constexpr int VEC = WChunk<WT>::N;
@@ -240,17 +242,14 @@ __device__ __forceinline__ void rows_product(const RowsPieces<WT, DUAL, N> &p, c
         if ((i * 64 + lane) * VEC < K) add(p.w[i], p.w2[i], p.g[i], (i * 64 + lane) * VEC);
     for (int k = (N * 64 + lane) * VEC; k < K; k += 64 * VEC) {
         WChunk<WT> w, w2;
-        float g[VEC];
         w.load(w0 + k);
         if (DUAL) w2.load(w1 + k);
-#pragma unroll
-        for (int j = 0; j < VEC; ++j) g[j] = gain ? gain[k + j] : 1.0f;
-        add(w, w2, g, k);
+        add(w, w2, gain + k, k);
     }
-    a = wave_sum_rows<MR>(acc);
-    b = DUAL ? wave_sum_rows<MR>(acc2) : 0.f;
+    a = wave_sum_rows<MR, SHFL>(acc);
+    b = DUAL ? wave_sum_rows<MR, SHFL>(acc2) : 0.f;
     if (NORM) {
-        const float sum = wave_sum_rows<MR>(ss);
+        const float sum = wave_sum_rows<MR, SHFL>(ss);
         if (gain) {
             const float rs = 1.0f / sqrtf(sum / (float)K + eps);
             a *= rs;
@@ -302,9 +301,13 @@ __global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, cons
         }
         float a, b;
         const WT *w0 = W + (size_t)r0 * K, *w1 = W + (size_t)r1 * K;
-        RowsPieces<WT, DUAL, 1> p;
-        p.load(w0, w1, op.gain, K);
-        rows_product<WT, MR, DUAL, EPI == EPI_QKV || EPI == EPI_SWIGLU, 1>(p, w0, w1, X, op.ldx, n_rows, K, op.gain, op.eps, a, b);
+        // No piece is requested ahead here, as the one-launch pass does: that takes more registers and other waits (1000 to 1500 columns, fp32: O and
+        // down with six and seven rows 8-9 us -> 20-30, QKV with eleven to sixteen 9-12 -> 15-29; bf16: SwiGLU 17.3 -> 22.2 with sixteen).
+        // Exchanges: the compiler places the loads better around those without the LDS unit in most builds (fp32, O and down with eight
+        // and nine rows 27-39 -> 9 us; bf16, QKV with fourteen and fifteen 14-19 -> 8-11) and worse in these (fp32 QKV 12.0 -> 14.6, a head
+        // of 20 000 rows 54 -> 62).
+        constexpr bool SHFL = EPI == EPI_STORE ? MR == 10 || MR == 14 : EPI == EPI_QKV && sizeof(WT) == 4 && (MR == 12 || MR == 14 || MR == 15);
+        rows_product<WT, MR, DUAL, EPI == EPI_QKV || EPI == EPI_SWIGLU, 0, SHFL>(RowsPieces<WT, DUAL, 0>(), w0, w1, X, op.ldx, n_rows, K, op.gain, op.eps, a, b);
         if (lane < n_rows) {           // lane r holds row r
             const int row = row_lo + lane;
             float *yp = op.Y + (size_t)row * op.ldy;
