@@ -3,11 +3,13 @@ their own (a row's logits must not depend on which), contexts around the 16 or 8
 workgroup takes side by side and around its four rounds, both head sizes, all four pairs of storage types, grouped-query heads,
 widths that are no multiple of a wavefront's stride. Compared with the oracle; where a pass may also run in one launch (both
 storage types alike), bit for bit with that."""
+import time
+
 import numpy as np
 import pytest
 import torch
 
-from paper_2505_16162_amd import synth
+from paper_2505_16162_amd import binding, synth
 from gpu_common import logits_close, make_pair
 
 pytestmark = pytest.mark.gpu
@@ -51,4 +53,28 @@ def test_row_counts_and_context_lengths(wdt, kdt, hd, heads, kv_heads):
         for r, got in kept.items():
             ok, err = logits_close(got.numpy(), rows[ctx + r], shape)
             assert ok, (ctx, r, err)
+    gpu.close()
+
+
+@pytest.mark.timeout(120)
+def test_two_more_rows_cost_little():
+    """Every row count has a build of its own, and a compiler may place the loads of one badly: O and down with six and seven fp32 rows once took
+    three times what they take with five, the pass 1.4-1.5 times (1.08 otherwise, medians of eight)."""
+    shape = synth.small_shape("gen_cost", n_blocks=6, d_model=1000, n_heads=8, n_kv_heads=4, head_dim=64, d_ffn=4000, vocab=2000, max_seq=200,
+                              weight_dtype="fp32", kv_dtype="fp32")
+    gpu = binding.KnnSsd(shape, synth.make_weights(shape, seed=53))
+    tokens = synth.make_prompt(shape.vocab, 140, seed=54).tolist()
+    gpu.knnssd_prefill(tokens[:100])
+
+    def cost(n):
+        def one():
+            t0 = time.perf_counter()
+            for _ in range(10):
+                gpu.knnssd_verify(tokens[100:100 + n], 100)
+            return time.perf_counter() - t0
+        one()
+        return sorted(one() for _ in range(8))[3]
+    five, seven = cost(5), cost(7)
+    print("5 rows %.0f us, 7 rows %.0f us" % (five * 1e5, seven * 1e5))
+    assert seven < 1.25 * five
     gpu.close()
