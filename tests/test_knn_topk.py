@@ -221,7 +221,7 @@ def test_scans_take_the_faster_kernel(streams):
                 ((2, 0, 8192, 5120), 64.5, 73.4), ((2, 0, 50000, 2048), 98.5, 108.2), ((2, 0, 24000, 4096), 99.0, 106.5), ((2, 0, 50000, 4096), 163.6, 178.1),
                 ((2, 0, 50000, 1000), 68.4, 73.7), ((3, 0, 100000, 2048), 162.9, 173.3), ((3, 0, 16384, 4096), 92.5, 82.7), ((4, 0, 24000, 5120), 138.7, 123.0),
                 ((2, 0, 16384, 8192), 137.5, 121.5), ((2, 0, 200000, 256), 87.1, 71.5), ((4, 0, 200000, 256), 90.8, 79.4), ((1, 0, 200000, 5120), 640, 657),
-                ((1, 1, 200000, 5120), 353, 355), ((3, 0, 100000, 512), 68.8, 72.4)]
+                ((1, 1, 200000, 5120), 353, 355), ((3, 0, 20000, 5120), 109.6, 117.3), ((4, 0, 20000, 4096), 99.2, 102.5), ((4, 1, 20000, 5120), 104, 92), ((3, 0, 100000, 512), 68.8, 72.4)]
     for (case, multi, stream), chosen in zip(measured, streams([m[0] for m in measured])):
         assert chosen == (stream < multi), case
 
