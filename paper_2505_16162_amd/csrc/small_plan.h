@@ -31,7 +31,7 @@ inline int small_rounds(int head_dim, int len) {
 // 0.6-0.8 there. So the context decides, by the rounds that follow one another in a block, against a limit that the launches around the
 // blocks raise where few of them hold attention. The form was fitted to 1840 pairs of timings (1 to 12 blocks, 2 to 32 heads of 64 and
 // 128, 1 to 16 rows, contexts 30 to 1400; draft steps and verifications as calls and inside generations): the way chosen
-// is 0.9 % slower than the better one in the mean; one launch always 8.7 % (twice the time at worst), never 13.7 %. For instance, launches / one
+// is 0.9 % slower than the better one in the mean; one launch always 8.7 % (twice the time at worst), never 15 %. For instance, launches / one
 // launch, GPU us: four blocks, fp32, four heads of 64, a draft step 87 / 55 at context 30, 96 / 74 at 250, 115 / 116 at
 // 600, 179 / 215 at 1400; 5 rows 89 / 75, 101 / 96, 130 / 142, 191 / 235; sixteen heads, 5 rows 95 / 87, 107 / 115. bf16 with 12
 // rows, which take the build for 16, is never faster: 126 / 127, 144 / 146, 97 / 110.
