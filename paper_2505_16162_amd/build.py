@@ -9,7 +9,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libknnssd.so")
 SOURCES = ["knnssd.hip"]
-NO_SPILL_KERNELS = ["gemv_kernel", "gemm_mfma_kernel", "prefill_gemm_kernel", "prefill_attn_kernel"]     # mangled-name fragments of the kernels that must not spill
+NO_SPILL_KERNELS = ["gemv_kernel", "gemm_mfma_kernel", "prefill_gemm_kernel", "prefill_thin_kernel", "prefill_attn_kernel"]     # mangled-name fragments of the kernels that must not spill
 
 
 def build_library(verbose: bool = False) -> str:
@@ -82,7 +82,7 @@ def check_hand_placed_loads(text: str, verbose: bool = False) -> None:
     for name, body in gemv + gemm:
         for n, t in isa_check.weight_register_copies(body)[:5]:
             problems.append(f"{name}: line {n}: {t}: reads a register of the weight stream")
-    prefill = isa_check.kernel_bodies(text, "prefill_gemm_kernel") + isa_check.kernel_bodies(text, "prefill_attn_kernel")
+    prefill = [b for k in ("prefill_gemm_kernel", "prefill_thin_kernel", "prefill_attn_kernel") for b in isa_check.kernel_bodies(text, k)]
     if not prefill:
         problems.append("prefill kernels not found in the assembly text")
     for name, body in prefill:

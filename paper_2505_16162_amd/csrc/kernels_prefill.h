@@ -459,6 +459,178 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
 }
 
 // ------------------------------------------------------------------------------------------
+// Prompts of up to PF_THIN token tiles over large matrices: the weight stream is what counts, as in a decode pass.
+// A workgroup owns 256 weight rows x all of the prompt's rows. Eight wavefronts take two row tiles each and load their weights from
+// memory straight into registers (a weight is an operand of one wavefront only, so LDS would be a detour); TB more do
+// nothing but fetch a token tile of the activations each, which all eight read, into LDS, so that the workgroup meets once per
+// pair of steps and neither kind of load waits behind the other. K is not cut into equal parts: the tiles' pairs of steps stand in one
+// row and each of the G workgroups takes an equal run of them (pf_share), so that no workgroup is left over
+// whatever the number of row tiles, and the stream runs on where a run crosses from one tile into the next.
+// Measured against the 128 x 64 tiles of prefill_gemm_kernel (7B widths, 17 / 45 rows, us a launch): QKV 29 / 32 -> 21 / 26, gate+up 58 / 62 ->
+// 40 / 48, down 26 / 28 -> 19 / 24; whole prompts of 17 rows, two blocks, 7B 372 -> 321 and 13B 511 -> 426, of 40 to 45 rows 410 -> 372 and
+// 538 -> 479, Qwen 33 rows 675 -> 617. What is left above the stream (17 / 30 / 15 us): 3 us to start, 4-7 us for the parts' way
+// out (22 MB), and the activations, each of which crosses from the L2 once per row tile: 0.3 us per token tile and step more than
+// the weights take. Four token tiles: as fast as prefill_gemm_kernel (7B, 64 rows 423 against 426). Four wavefronts with four row tiles each
+// (half the LDS reads): no change. Six steps ahead instead of four, three of activations per meeting: no change.
+// ------------------------------------------------------------------------------------------
+constexpr int PF_THIN_WAVES = 8, PF_THIN_BUFS = 5;     // pairs of steps whose activations are in LDS
+constexpr int pf_thin_nt(int tb) { return (PF_THIN_WAVES + tb) * 64; }
+constexpr size_t pf_thin_lds_bytes(int tb) { return (size_t)PF_THIN_BUFS * 2 * PF_NP * tb * 1024 + PF_THIN_TILES * 256 * sizeof(PfRow); }
+
+template <int TB>
+__global__ __launch_bounds__(pf_thin_nt(TB)) void prefill_thin_kernel(PfArgs a) {
+    constexpr int NB = PF_THIN_BUFS, TM = 256, RT = 16 / PF_THIN_WAVES;
+    constexpr int STEP = PF_NP * TB * 1024, PAIR = 2 * STEP, PER = 2 * PF_NP;
+    extern __shared__ __align__(16) char lds[];
+    const GemmOp &op = a.op;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kg = lane >> 4, r16 = lane & 15;
+    const int KS = op.K >> 5, KP = (KS + 1) >> 1, units = a.n_mt * KP, G = gridDim.x;
+    const int q0 = __builtin_amdgcn_readfirstlane(pf_share(units, G, blockIdx.x));        // (quotients come out of the vector unit)
+    const int n = __builtin_amdgcn_readfirstlane(pf_share(units, G, blockIdx.x + 1)) - q0;
+    int mt = __builtin_amdgcn_readfirstlane(q0 / KP), kp = q0 - mt * KP;
+    if (wave >= PF_THIN_WAVES) {
+        const int fw = wave - PF_THIN_WAVES;       // its token tile
+        const unsigned int l0 = (unsigned int)(uintptr_t)(__attribute__((address_space(3))) char *)lds + fw * 1024, voff = lane * 16;
+        const char *src = reinterpret_cast<const char *>(a.frag_in + frag_off(KS, a.TT, 0, 0, fw));
+        const size_t plane = (size_t)KS * a.TT * 1024, step = (size_t)a.TT * 1024;
+        int buf = 0;
+        auto fetch = [&]() {                       // the next pair (a step past the end of K repeats the last one)
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int pl = 0; pl < PF_NP; ++pl)
+                    dma_linear(src + min(2 * kp + s, KS - 1) * step + pl * plane, voff, l0 + buf * PAIR + s * STEP + pl * TB * 1024);
+            kp = kp == KP - 1 ? 0 : kp + 1;
+            buf = buf == NB - 1 ? 0 : buf + 1;
+        };
+        for (int c = 0; c < min(n, NB - 1); ++c) fetch();
+        for (int c = 0; c < n; ++c) {
+            const int younger = min(n - 1 - c, NB - 2);
+            static_assert(NB == 5, "the waits below");
+            if (younger == 3) dma_wait<3 * PER>();
+            else if (younger == 2) dma_wait<2 * PER>();
+            else if (younger == 1) dma_wait<PER>();
+            else dma_wait<0>();
+            pf_meet();                             // pair c is here, and everybody is done with pair c - 1
+            if (c + NB - 1 < n) fetch();
+        }
+        return;
+    }
+    float scale[TB];
+#pragma unroll
+    for (int j = 0; j < TB; ++j) scale[j] = a.rstd ? a.rstd[min(j * 16 + r16, a.n_tok - 1)] : 1.0f;
+    // where the wavefront's rows of the run's tiles lie, kept in LDS: fetched again where the run crosses into the next tile, a load would wait
+    // behind the weights
+    PfRow *const rows = reinterpret_cast<PfRow *>(lds + NB * PAIR) + wave * PF_THIN_TILES * RT * 16 + r16;
+    static_assert(PF_THIN_TILES == 4, "a group of 16 lanes per tile");
+#pragma unroll
+    for (int i = 0; i < RT; ++i) rows[(kg * RT + i) * 16] = a.rows[min(mt + kg, a.n_mt - 1) * TM + wave * RT * 16 + i * 16 + r16];
+    PfRow row[RT];
+    const unsigned int nfull = KS >> 4, rem = KS & 15;
+    u32x4 av[2][2][RT];                            // weights of two pairs
+    int lt = 0, lk = kp, lc = 0;                   // the next pair to be requested: tile of the run, place in it, number in the run
+    auto load_a = [&](int u, int s) {              // its step s; past the end one piece that all lanes share
+        unsigned int live = lc < n && 2 * lk + s < KS ? 0xffffffffu : 0u;
+        asm volatile("" : "+v"(live));             // (no branch around the loads: they stay countable)
+        const unsigned int st = 2 * lk + s, w16 = st & 15, blk = st >> 4;
+#pragma unroll
+        for (int i = 0; i < RT; ++i) {             // pf_unit_index, a lane's own deal of the columns
+            const unsigned int gs = row[i].y >> 16, rt = row[i].y & 0xffffu, first = (w16 >> gs) << gs;
+            const unsigned int unit = __umul24(nfull, first) + min(rem, first) + (blk << gs) + (w16 - first);
+            const unsigned int piece = (row[i].x + kg * rt + unit * rt * 4) & live;
+            av[u][s][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(op.W) + piece);
+        }
+    };
+    auto rows_of = [&]() {
+#pragma unroll
+        for (int i = 0; i < RT; ++i) row[i] = rows[(min(lt, PF_THIN_TILES - 1) * RT + i) * 16];
+    };
+    auto advance = [&]() {
+        ++lc;
+        lt += lk == KP - 1;
+        lk = lk == KP - 1 ? 0 : lk + 1;
+        rows_of();
+    };
+    rows_of();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        load_a(u, 0);
+        load_a(u, 1);
+        advance();
+    }
+    f32x4 acc[RT][TB];
+#pragma unroll
+    for (int i = 0; i < RT; ++i)
+#pragma unroll
+        for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+    const char *lb = lds + lane * 16;
+    int buf = 0;
+    auto pair = [&](int c, int u) {                // (one past the end requests its weights like the others, so that the loads in flight stay countable)
+        const bool on = c < n;
+        if (on) pf_meet();
+        const char *b = lb + buf * PAIR;
+        bf16x8 x[2][PF_NP];
+        f32x4 own[2][RT];                          // a step's three planes are summed on their own, see prefill_gemm_kernel; added under the next tile's matrix instructions
+        auto read = [&](int s, int j) {
+#pragma unroll
+            for (int p = 0; p < PF_NP; ++p) x[j & 1][p] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4 *>(b + s * STEP + (p * TB + j) * 1024));
+        };
+        auto step = [&](int s) {
+            read(s, 0);
+#pragma unroll
+            for (int j = 0; j <= TB; ++j) {
+                if (j + 1 < TB) read(s, j + 1);
+                if (j < TB) {
+#pragma unroll
+                    for (int p = PF_NP - 1; p >= 0; --p)
+#pragma unroll
+                        for (int i = 0; i < RT; ++i)
+                            own[j & 1][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, av[u][s][i]), x[j & 1][p],
+                                                                                    p == PF_NP - 1 ? f32x4{0.f, 0.f, 0.f, 0.f} : own[j & 1][i], 0, 0, 0);
+                }
+                if (j > 0)
+#pragma unroll
+                    for (int i = 0; i < RT; ++i) {
+                        acc[i][j - 1] += own[(j - 1) & 1][i];
+                        asm volatile("" : "+v"(acc[i][j - 1]));    // here, not behind all steps, where every step's sums would have to be kept
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        };
+        if (on) step(0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(u, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (on && 2 * kp + 1 < KS) step(1);
+        __builtin_amdgcn_sched_barrier(0);
+        load_a(u, 1);
+        advance();
+        __builtin_amdgcn_sched_barrier(0);
+        const bool last = kp == KP - 1;            // of its tile
+        if (on && (last || c == n - 1)) {
+            const int part = (int)blockIdx.x - pf_share_owner(units, G, mt * KP);
+#pragma unroll
+            for (int j = 0; j < TB; ++j) {
+                const int tok = j * 16 + r16;
+                float *o = a.out + ((size_t)part * a.out_rows + tok) * ((size_t)a.n_mt * TM) + mt * TM + wave * RT * 16 + 4 * kg;
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    if (tok < a.n_tok) *reinterpret_cast<f32x4 *>(o + i * 16) = acc[i][j] * scale[j];
+                    acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+            }
+            ++mt;
+        }
+        kp = last ? 0 : kp + 1;
+        buf = buf == NB - 1 ? 0 : buf + 1;
+    };
+    for (int c = 0; c < n; c += 2) {
+        pair(c, 0);
+        pair(c + 1, 1);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
 // Row kernels, between the products: they add up the K parts, finish a row and write the next product's operands. Bound by
 // memory. Four neighbouring features per thread, so that the loads of neighbouring lanes adjoin (with eight, 1024 rows of
 // 5120 in three parts take 32 us instead of 30, SwiGLU of 45 x 11008 in four parts 17.6 instead of 11.2). A row's share of a
@@ -470,6 +642,7 @@ struct PfRowArgs {
     const int32_t *toks;        // embedding: token ids
     const float *in;            // [S][out_rows][ld] K parts
     int n_tok, S, out_rows, ld, TM;     // TM: rows per tile of the product's column order
+    int KP, units, G;           // G > 0: the tiles' KP pairs of steps were dealt to G workgroups in one row of `units` (pf_share), a tile's number of parts follows
     int d;                      // features of the row
     float inv_dim, eps;
     float *x;                   // [n_tok][d] residual stream
@@ -490,10 +663,17 @@ __device__ __forceinline__ int pf_row_token(int n_tok) {
     return ((i >> 4) * 8 + die) * 16 + (i & 15);
 }
 
+// parts that the tile of column c was summed in
+__device__ __forceinline__ int pf_n_parts(const PfRowArgs &a, int c) {
+    if (a.G == 0) return a.S;
+    const int u = c / a.TM * a.KP;
+    return pf_share_owner(a.units, a.G, u + a.KP - 1) - pf_share_owner(a.units, a.G, u) + 1;
+}
 // columns c..c+3 of the K parts, added up in order
 __device__ __forceinline__ f32x4 pf_sum_parts(const PfRowArgs &a, int tok, int c) {
     const float *p = a.in + (size_t)tok * a.ld + c;
     const size_t st = (size_t)a.out_rows * a.ld;
+    const int S = pf_n_parts(a, c);
     f32x4 v = *reinterpret_cast<const f32x4 *>(p);
     int s = 1;
     auto take = [&](auto n) {              // that many loads in flight
@@ -504,10 +684,10 @@ __device__ __forceinline__ f32x4 pf_sum_parts(const PfRowArgs &a, int tok, int c
         for (int i = 0; i < decltype(n)::value; ++i) v += t[i];
         s += decltype(n)::value;
     };
-    while (s + 8 <= a.S) take(std::integral_constant<int, 8>{});
-    if (s + 4 <= a.S) take(std::integral_constant<int, 4>{});
-    if (s + 2 <= a.S) take(std::integral_constant<int, 2>{});
-    if (s < a.S) take(std::integral_constant<int, 1>{});
+    while (s + 8 <= S) take(std::integral_constant<int, 8>{});
+    if (s + 4 <= S) take(std::integral_constant<int, 4>{});
+    if (s + 2 <= S) take(std::integral_constant<int, 2>{});
+    if (s < S) take(std::integral_constant<int, 1>{});
     return v;
 }
 // column of the first member of pair p (the second sits 16 columns on): the row order of the product's tiles

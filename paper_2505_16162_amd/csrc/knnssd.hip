@@ -140,7 +140,7 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
             size_t part[PF_OPS] = {};
             for (int w = 0; w < PF_OPS; ++w)
                 for (int t = 1; t <= (int)tt; ++t) {
-                    const PfPlan p = pf_plan(*c, w, t);
+                    const PfPlan p = pf_choose(*c, w, t);
                     if (p.parts(w) && p.part_bytes() > part[w]) part[w] = p.part_bytes();
                 }
             auto most = [](size_t a, size_t b, size_t d) { return a > b ? (a > d ? a : d) : (b > d ? b : d); };
@@ -228,6 +228,8 @@ static hipError_t pf_set_lds_limits() {
         if (e == hipSuccess) e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     };
     pf_each_build([&](int, int, bool, void (*k)(PfArgs), size_t lds) { set((const void *)k, lds); });
+    set((const void *)prefill_thin_kernel<2>, pf_thin_lds_bytes(2));
+    set((const void *)prefill_thin_kernel<3>, pf_thin_lds_bytes(3));
     set((const void *)prefill_attn_kernel<128>, pf_attn_lds_bytes<128>());
     set((const void *)prefill_attn_kernel<64>, pf_attn_lds_bytes<64>());
     return e;
@@ -872,7 +874,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *rstd = c->wsp<float>(c->L.pf_rstd);
     bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att), *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
     PfPlan plan[PF_OPS];
-    for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_plan(g, w, TTL);
+    for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_choose(g, w, TTL);
 
     GemmOp base{};
     base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq;
@@ -885,6 +887,11 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         a.rows = c->wsp<PfRow>(c->L.pf_rows[which][p.tm() == 256]); a.out_rows = p.out_rows();
         a.n_mt = p.n_mt; a.n_mr = p.n_mr; a.n_tt = p.n_tt; a.S = p.S; a.inv_tiles = 1.0f / (float)p.tiles();
         a.steps = op.K / 32 / p.S; a.longer = op.K / 32 % p.S;
+        if (p.G > 0) {
+            const int tb = TTL <= 2 ? 2 : 3;
+            hipLaunchKernelGGL(tb == 2 ? prefill_thin_kernel<2> : prefill_thin_kernel<3>, dim3(p.G), dim3(pf_thin_nt(tb)), pf_thin_lds_bytes(tb), s, a);
+            return;
+        }
         const bool own = p.own_sums(which);
         pf_each_build([&](int tb, int e, bool ow, void (*k)(PfArgs), size_t lds) {
             if (tb == p.tb && e == epi && ow == own) hipLaunchKernelGGL(k, dim3((p.tiles() * p.S + 7) / 8 * 8), dim3(PF_NT), lds, s, a);
@@ -894,6 +901,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         const PfPlan &p = plan[which];
         PfRowArgs r{};
         r.op = base; r.n_tok = n_tok; r.in = c->wsp<float>(c->L.pf_part[which]); r.S = p.S; r.out_rows = p.out_rows(); r.ld = p.n_mt * p.tm(); r.TM = p.tm(); r.d = width; r.TT = TT;
+        if (p.G > 0) { r.G = p.G; r.KP = ((which == PF_O ? qd : (which == PF_DOWN ? F : d)) / 32 + 1) / 2; r.units = p.n_mt * r.KP; }
         r.inv_dim = 1.0f / (float)d; r.eps = g.rms_eps;
         return r;
     };

@@ -1,9 +1,15 @@
-// How the prompt prefill cuts its products into workgroups: host code only, no HIP.
+// How the prompt prefill cuts its products into workgroups: plain code, no HIP.
 #pragma once
 #include <stddef.h>
 
 #include "../../include/knnssd.h"
 #include "device_types.h"
+
+#ifdef __HIPCC__
+#define KS_HD __host__ __device__
+#else
+#define KS_HD
+#endif
 
 namespace ks {
 
@@ -14,17 +20,22 @@ enum { PF_QKV = 0, PF_O, PF_GU, PF_DOWN, PF_OPS };     // the four matrices of a
 // behind the loop, 4-5 us with everything in one build.)
 enum { PF_PARTS = 0, PF_SWIGLU, PF_ROPE };
 
+// Equal runs of n units for G workgroups: the first unit of run w (w = G: n), and the run that unit u belongs to
+KS_HD inline int pf_share(int n, int G, int w) { return (int)((unsigned int)n * (unsigned int)w / (unsigned int)G); }
+KS_HD inline int pf_share_owner(int n, int G, int u) { return (int)((((unsigned int)u + 1u) * (unsigned int)G - 1u) / (unsigned int)n); }
+
 // How the prefill GEMM covers one matrix for a prompt of tt token tiles (16 rows each)
 struct PfPlan {
     int tb;                  // token tiles per workgroup: 16, 8 (256 weight rows) or 4 (128 weight rows)
     int n_mt, n_mr, n_tt;    // row tiles, those of them with rotary pairs (OP_QKV), workgroup tiles along the tokens
-    int S;                   // parts K is split into
+    int S;                   // parts K is split into (G > 0: the most parts of a tile)
+    int G = 0;               // > 0: a thin launch of so many workgroups (prefill_thin_kernel), tiles of 256 weight rows x all tokens
     int tiles() const { return n_mt * n_tt; }
     // sums through memory to a row kernel? (residual rows always; the others unless one large workgroup finishes them)
-    bool parts(int which) const { return S > 1 || tb != 16 || which == PF_O || which == PF_DOWN; }
+    bool parts(int which) const { return G > 0 || S > 1 || tb != 16 || which == PF_O || which == PF_DOWN; }
     int epilogue(int which) const { return parts(which) ? PF_PARTS : (which == PF_GU ? PF_SWIGLU : PF_ROPE); }
     bool own_sums(int which) const { return which == PF_QKV || tb == 4; }       // sums of their own per step: see the kernel
-    int tm() const { return tb == 4 ? 128 : 256; }
+    int tm() const { return tb == 4 && G == 0 ? 128 : 256; }
     int out_rows() const { return n_tt * tb * 16; }
     size_t part_bytes() const { return (size_t)S * out_rows() * n_mt * tm() * 4; }       // K parts of the product
 };
@@ -71,6 +82,27 @@ inline PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
         }
     }
     return best;
+}
+
+// Prompts of up to PF_THIN token tiles take prefill_thin_kernel for matrices of at least PF_THIN_PAIRS pairs of steps a workgroup: with fewer
+// its fixed cost shows (7B's O projection, four pairs: 14.9 us against 14.5; models of 256 to 2000 columns with all products
+// this way 12-20 % slower), 13B's O projection with six and a quarter takes 18 against 20.
+constexpr int PF_THIN = 3, PF_THIN_PAIRS = 6, PF_THIN_TILES = 4;        // PF_THIN_TILES: row tiles a workgroup's run may touch
+inline PfPlan pf_choose(const knnssd_model_cfg &g, int which, int tt) {
+    const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KP = (K / 32 + 1) / 2;
+    PfPlan p{};
+    p.tb = 4;
+    p.G = KS_NWG;
+    p.n_mt = pf_row_tiles(g, which, p.tm(), &p.n_mr);
+    p.n_tt = 1;
+    const int units = p.n_mt * KP;
+    if (tt > PF_THIN || units < PF_THIN_PAIRS * KS_NWG || units > (PF_THIN_TILES - 2) * KP * KS_NWG) return pf_plan(g, which, tt);
+    for (int t = 0; t < p.n_mt; ++t) {
+        const int n = pf_share_owner(units, p.G, (t + 1) * KP - 1) - pf_share_owner(units, p.G, t * KP) + 1;
+        if (n > p.S) p.S = n;
+    }
+    if (p.S > 32) return pf_plan(g, which, tt);        // few rows, many columns: a row kernel would read them all
+    return p;
 }
 
 }  // namespace ks
