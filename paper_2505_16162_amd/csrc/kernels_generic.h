@@ -794,18 +794,8 @@ __global__ __launch_bounds__(KNN_STREAM_NT) void knn_scores_stream_kernel(const 
     }
 }
 
-// The K best (largest value, lowest anchor index on ties) of n entries, in rank order, by one workgroup of 1024
-// threads. Entry i has value val[i] and anchor index (map ? map[i] : first + i); entries with a negative index are
-// dead. Two levels of K rounds of arg-max, both inside single wavefronts (registers and cross-lane moves, no
-// meeting per round): every wavefront ranks the K best of its sixteenth of the entries (a lane looks at entries 64
-// apart and marks the ones it has given away in a 64-bit mask, hence n <= KNN_ROUNDS_MAX_N), the workgroup meets once,
-// and the first wavefront ranks the K best of the 16 x K survivors. taken_idx / taken_val receive the winners
-// (0x7fffffff / -inf once the entries run out); returns nonzero in the threads that met a non-finite value.
-#define KNN_ROUNDS_MAX_N (16 * 64 * 64)
-#define KNN_SLICES_MAX 256       // stage-1 slices per query: 256 x KNN_ROUNDS_MAX_N anchors at most
-struct KnnRoundsLds {
-    unsigned long long key[16][KNN_KMAX];
-};
+#define KNN_ROUNDS_MAX_N (16 * 64 * 64)      // scores a workgroup ranks at most: a lane keeps one mask bit per entry it looks at
+#define KNN_SLICES_MAX 256       // slices per query: 256 x KNN_ROUNDS_MAX_N anchors at most
 
 // An entry as one number: its value in an order-preserving form, above the complement of its index, so that the larger key is
 // the better entry (finite values; 0: a dead entry).
@@ -819,57 +809,79 @@ __device__ __forceinline__ float knn_key_value(KnnKey k) {
     return __uint_as_float(u ^ (u & 0x80000000u ? 0x80000000u : 0xffffffffu));
 }
 __device__ __forceinline__ int knn_key_index(KnnKey k) { return (int)(0xffffffffu - (unsigned int)k); }
-// the wavefront's largest key, in every lane
+// the wavefront's largest number, in every lane: rotations within the rows of 16, then the rows
+__device__ __forceinline__ unsigned int wave_max_u32(unsigned int x) {
+    x = max(x, (unsigned int)lane_dpp<0x121>((int)x, (int)x));
+    x = max(x, (unsigned int)lane_dpp<0x122>((int)x, (int)x));
+    x = max(x, (unsigned int)lane_dpp<0x124>((int)x, (int)x));
+    x = max(x, (unsigned int)lane_dpp<0x128>((int)x, (int)x));
+    const auto r = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = max((unsigned int)r[0], (unsigned int)r[1]);
+    const auto h = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return max((unsigned int)h[0], (unsigned int)h[1]);
+}
+// the wavefront's largest key, in every lane: its value first, then the index among those that have it
 __device__ __forceinline__ KnnKey knn_wave_best(KnnKey k) {
+    const unsigned int hi = wave_max_u32((unsigned int)(k >> 32));
+    return ((KnnKey)hi << 32) | wave_max_u32((unsigned int)(k >> 32) == hi ? (unsigned int)k : 0u);
+}
+// four keys of a lane, the largest first
+__device__ __forceinline__ void knn_sort4(KnnKey *k) {
+    auto order = [&](int i, int j) {
+        const KnnKey a = k[i], b = k[j];
+        k[i] = a > b ? a : b;
+        k[j] = a > b ? b : a;
+    };
+    order(0, 1); order(2, 3); order(0, 2); order(1, 3); order(1, 2);
+}
+// the largest of four is given away if `won`
+__device__ __forceinline__ void knn_take(KnnKey *k, bool won) {
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const KnnKey o = ((KnnKey)(unsigned int)lane_xor((int)(k >> 32), off) << 32) | (unsigned int)lane_xor((int)k, off);
-        k = o > k ? o : k;
-    }
-    return k;
+    for (int i = 0; i < 3; ++i) k[i] = won ? k[i + 1] : k[i];
+    k[3] = won ? 0 : k[3];
 }
 
-__device__ __forceinline__ int knn_rounds(const float *val, const int32_t *map, int first, int n, int K, int *taken_idx,
-                                          float *taken_val, KnnRoundsLds *wl) {
+struct KnnRankLds {
+    KnnKey key[16][KNN_KMAX];
+    KnnKey best[KNN_KMAX];       // the K best in rank order (0 once the entries run out)
+    float qn[16];
+    int last;
+};
+
+// The K best (largest value, lowest anchor index on ties) of n entries, in rank order, by one workgroup of 1024
+// threads; entry(i) is an entry's key. Two levels of K rounds of arg-max, both inside single wavefronts (registers and cross-lane
+// moves, no meeting per round): every wavefront ranks the K best of its sixteenth of the entries (a lane looks at entries 64
+// apart and marks the ones it has given away in a 64-bit mask, hence n <= KNN_ROUNDS_MAX_N), the workgroup meets once,
+// and the first wavefront ranks the K best of the 16 x K survivors into l.best, which it alone may read without a meeting.
+template <typename F> __device__ __forceinline__ void knn_rounds(int n, int K, KnnRankLds &l, F entry) {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int anybad = 0;
     {
         const int w0 = (int)((long long)n * wave / 16), w1 = (int)((long long)n * (wave + 1) / 16);
         const int M = (w1 - w0 + 63) >> 6;                 // <= 64
-        unsigned long long given = 0;                       // bit m: this lane's entry w0 + 64 m + lane is among the winners (m >= MR)
-        // the lane's first MR entries stay in registers over the rounds (slices of a few thousand scores and the
+        unsigned long long given = 0;                       // bit m: this lane's entry w0 + 64 m + lane is among the winners (m >= 4)
+        // the lane's first four entries stay in registers over the rounds, in order (slices of a few thousand scores and the
         // candidate lists have no more); entries beyond are read again in every round
-        constexpr int MR = 4;
-        KnnKey rk[MR];
-        auto entry = [&](int i) -> KnnKey {
-            const float v = val[i];
-            if (!isfinite(v)) { anybad = 1; return 0; }
-            const int gi = map ? map[i] : first + i;
-            return gi >= 0 ? knn_key(v, gi) : 0;
-        };
+        KnnKey rk[4];
 #pragma unroll
-        for (int m = 0; m < MR; ++m) {
+        for (int m = 0; m < 4; ++m) {
             const int i = w0 + (m << 6) + lane;
             rk[m] = i < w1 ? entry(i) : 0;
         }
+        knn_sort4(rk);
         for (int r = 0; r < K; ++r) {
             KnnKey mine = rk[0];
             int far = -1;                                   // where mine comes from, past the registers
-#pragma unroll
-            for (int m = 1; m < MR; ++m) mine = rk[m] > mine ? rk[m] : mine;
-            for (int m = MR; m < M; ++m) {
+            for (int m = 4; m < M; ++m) {
                 const int i = w0 + (m << 6) + lane;
                 if (i >= w1 || ((given >> m) & 1ull)) continue;
                 const KnnKey k = entry(i);
                 if (k > mine) { mine = k; far = m; }
             }
             const KnnKey best = knn_wave_best(mine);
-            if (best == mine && best != 0) {                // indices are all different: one lane
-                if (far >= 0) given |= 1ull << far;
-#pragma unroll
-                for (int m = 0; m < MR; ++m) rk[m] = rk[m] == best ? 0 : rk[m];
-            }
-            if (lane == 0) wl->key[wave][r] = best;
+            const bool won = best == mine && best != 0;     // indices are all different: one lane
+            if (won && far >= 0) given |= 1ull << far;
+            knn_take(rk, won && far < 0);
+            if (lane == 0) l.key[wave][r] = best;
         }
     }
     __syncthreads();
@@ -879,101 +891,92 @@ __device__ __forceinline__ int knn_rounds(const float *val, const int32_t *map, 
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             const int c = (m << 6) + lane;
-            ck[m] = c % KNN_KMAX < K ? wl->key[c / KNN_KMAX][c % KNN_KMAX] : 0;
+            ck[m] = c % KNN_KMAX < K ? l.key[c / KNN_KMAX][c % KNN_KMAX] : 0;
         }
+        knn_sort4(ck);
         for (int r = 0; r < K; ++r) {
-            KnnKey mine = ck[0];
-#pragma unroll
-            for (int m = 1; m < 4; ++m) mine = ck[m] > mine ? ck[m] : mine;
-            const KnnKey best = knn_wave_best(mine);
-#pragma unroll
-            for (int m = 0; m < 4; ++m) ck[m] = ck[m] == best ? 0 : ck[m];
+            const KnnKey best = knn_wave_best(ck[0]);
+            knn_take(ck, best == ck[0]);
+            if (lane == 0) l.best[r] = best;
+        }
+    }
+}
+
+// The ranking behind a scan, in one launch: workgroup (query q, slice b) ranks the K best of its slice of the scores; with several
+// slices it leaves them as candidates, and the one that arrives last ranks all slices' candidates and takes the vote. Nobody waits for anybody:
+// candidates are written through (agent scope), acknowledged, and counted in; `arrivals` is zero between launches.
+// Bound by dependent latencies: the rounds, and the hand-over between slices. As two launches (each with its own rounds of 64-bit
+// exchanges, the second with one thread for the vote) 31-33 us behind the scan of three queries over 200 000 anchors, 22 over 3000;
+// now 24 and 10. Whole calls with results in host memory: three queries over up to 3000 anchors 47-48 -> 32-34 us.
+// `res` may lie in host memory: a thread writes an entry.
+__global__ __launch_bounds__(1024) void knn_rank_kernel(const float *scores /*[Q][N]*/, int N, int K, int n_slices, KnnKey *cand /*[Q][n_slices][K]*/,
+                                                        int *bad_flag /*[Q][n_slices]*/, int *arrivals /*[Q]*/, const float *queries,
+                                                        const int32_t *labels, int D, KnnTopk *res) {
+    __shared__ KnnRankLds l;
+    const int q = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i0 = (int)((long long)N * b / n_slices), n = (int)((long long)N * (b + 1) / n_slices) - i0;
+    const float *val = scores + (size_t)q * N + i0;
+    int bad = 0;
+    knn_rounds(n, min(K, n), l, [&](int i) -> KnnKey {
+        const float v = val[i];
+        if (!isfinite(v)) { bad = 1; return 0; }
+        return knn_key(v, i0 + i);
+    });
+    bad = __syncthreads_or(bad);
+    if (n_slices > 1) {
+        KnnKey *const mine = cand + ((size_t)q * n_slices + b) * K;
+        if (tid < K) __hip_atomic_store(mine + tid, tid < n ? l.best[tid] : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (tid == 0) __hip_atomic_store(bad_flag + q * n_slices + b, bad ? 1 : 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        static_assert(KNN_KMAX <= 64, "the first wavefront's stores");
+        if (wave == 0) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");       // they are where everybody looks for them
             if (lane == 0) {
-                taken_idx[r] = best ? knn_key_index(best) : 0x7fffffff;
-                taken_val[r] = best ? knn_key_value(best) : -INFINITY;
+                l.last = __hip_atomic_fetch_add(arrivals + q, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == n_slices - 1;
+                if (l.last) __hip_atomic_store(arrivals + q, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
+        __syncthreads();
+        if (!l.last) return;
     }
-    __syncthreads();
-    return anybad;
-}
-
-// Stage 1 of the top-K: workgroup (query q, slice b) leaves the K best of its slice of the scores as candidates.
-__global__ __launch_bounds__(1024) void knn_topk_part_kernel(const float *scores /*[Q][N]*/, int N, int K, int n_slices,
-                                                             int32_t *cand_idx /*[Q][n_slices][KNN_KMAX]*/, float *cand_val,
-                                                             int *bad_flag /*[Q][n_slices]*/) {
-    __shared__ KnnRoundsLds wl;
-    __shared__ int tidx[KNN_KMAX];
-    __shared__ float tval[KNN_KMAX];
-    const int q = blockIdx.x, b = blockIdx.y;
-    const int i0 = (int)((long long)N * b / n_slices), i1 = (int)((long long)N * (b + 1) / n_slices);
-    const int kk = min(K, i1 - i0);
-    const int anybad = knn_rounds(scores + (size_t)q * N + i0, nullptr, i0, i1 - i0, kk, tidx, tval, &wl);
-    const int slice_bad = __syncthreads_or(anybad);           // every slice writes its own flag: nothing to clear beforehand
-    if (threadIdx.x == 0) bad_flag[q * n_slices + b] = slice_bad ? 1 : 0;
-    if (threadIdx.x < KNN_KMAX) {
-        const size_t o = ((size_t)q * n_slices + b) * KNN_KMAX + threadIdx.x;
-        const bool live = (int)threadIdx.x < kk && tidx[threadIdx.x] != 0x7fffffff;
-        cand_idx[o] = live ? tidx[threadIdx.x] : -1;
-        cand_val[o] = live ? tval[threadIdx.x] : -INFINITY;
-    }
-}
-
-// Stage 2: one workgroup per query merges the slices' candidates (K rounds again), then the vote.
-__global__ __launch_bounds__(1024) void knn_topk_kernel(const int32_t *cand_idx, const float *cand_val, int n_slices, const int *bad_flag,
-                                                        const float *queries, const int32_t *labels, int D, int K, KnnTopk *res) {
-    __shared__ KnnRoundsLds wl;
-    __shared__ int taken[KNN_KMAX];
-    __shared__ float tval[KNN_KMAX];
-    __shared__ float qn[16];
-    const int q = blockIdx.x, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const float *qv = queries + (size_t)q * D;
     float q2 = 0.f;
-    for (int i = threadIdx.x; i < D; i += 1024) { const float v = qv[i]; q2 = fmaf(v, v, q2); }
-    q2 = wave_sum(q2);
-    if (lane == 0) qn[wave] = q2;
-    __syncthreads();
-    const size_t o = (size_t)q * n_slices * KNN_KMAX;
-    knn_rounds(cand_val + o, cand_idx + o, 0, n_slices * KNN_KMAX, K, taken, tval, &wl);
-    int mybad = 0;
-    for (int b = threadIdx.x; b < n_slices; b += 1024) mybad |= bad_flag[q * n_slices + b];
-    const int bad = __syncthreads_or(mybad);
-    // the winners' labels, fetched side by side (the vote below walks them many times)
-    __shared__ int lab_of[KNN_KMAX];
-    if (threadIdx.x < KNN_KMAX) {
-        const int t = taken[threadIdx.x];
-        lab_of[threadIdx.x] = ((int)threadIdx.x < K && t != 0x7fffffff && t >= 0) ? labels[t] : -1;
+    for (int i = tid; i < D; i += 1024) { const float v = qv[i]; q2 = fmaf(v, v, q2); }
+    if (n_slices > 1) {
+        for (int i = tid; i < n_slices; i += 1024) bad |= __hip_atomic_load(bad_flag + q * n_slices + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const KnnKey *const all = cand + (size_t)q * n_slices * K;
+        knn_rounds(n_slices * K, K, l, [&](int i) -> KnnKey { return __hip_atomic_load(all + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); });
     }
-    __syncthreads();
-    // (no per-thread arrays below: they would live in scratch memory, one memory round trip per access)
+    q2 = wave_sum(q2);
+    if (lane == 0) l.qn[wave] = q2;
+    bad = __syncthreads_or(bad);
+    if (wave != 0) return;
     float qtot = 0.f;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) qtot += qn[w];
-    const bool degenerate = bad || !(qtot > 0.f) || !isfinite(qtot) || taken[0] == 0x7fffffff;
+    for (int w = 0; w < 16; ++w) qtot += l.qn[w];
+    const KnnKey first = l.best[0];
+    const bool degenerate = bad || !(qtot > 0.f) || !isfinite(qtot) || first == 0;
     const float invq = degenerate ? 0.f : 1.0f / sqrtf(qtot);
-    if (threadIdx.x < KNN_KMAX) {
-        const int r = threadIdx.x;
-        const bool live = r < K && !degenerate && taken[r] != 0x7fffffff;
-        res[q].idx[r] = live ? taken[r] : -1;
-        res[q].cosine[r] = live ? tval[r] * invq : 0.f;
-        if (!live) lab_of[r] = -1;                    // only this thread touches entry r here
+    // lane r: the anchor of rank r and its label
+    const KnnKey key = lane < K && !degenerate ? l.best[lane] : 0;
+    const int idx = key ? knn_key_index(key) : -1;
+    const int lab = key ? labels[idx] : -1;
+    // The vote: every label is counted, the best-ranked one among those with the highest count wins. A label below zero ends the list.
+    const unsigned long long over = __ballot(lab < 0);
+    const int live = min(__ffsll((long long)over) - 1, K);         // (lanes from K on have none)
+    int count = 0;
+    for (int r = 0; r < K; ++r) count += __shfl(lab, r) == lab;
+    int best_rank = 0, best_count = 0;
+    for (int r = 0; r < live; ++r) {
+        const int c = __shfl(count, r);
+        if (c > best_count) { best_count = c; best_rank = r; }
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        // ranked order: the first label to reach the highest count wins a tie only if its best anchor ranks first,
-        // i.e. count every label, then take the best-ranked label among those with the highest count
-        int best_label = -1, best_count = 0;
-        for (int r = 0; r < K && !degenerate; ++r) {
-            const int lab = lab_of[r];
-            if (lab < 0) break;                       // the winners ran out
-            bool seen = false;
-            for (int t = 0; t < r; ++t) seen = seen || (lab_of[t] == lab);
-            if (seen) continue;                       // counted when first met
-            int cnt = 0;
-            for (int t = r; t < K; ++t) if (lab_of[t] == lab) ++cnt;
-            if (cnt > best_count) { best_count = cnt; best_label = lab; }
-        }
-        res[q].domain = degenerate ? -1 : best_label;
+    const int domain = __shfl(lab, best_rank);
+    if (lane < KNN_KMAX) {
+        res[q].idx[lane] = idx;
+        res[q].cosine[lane] = key ? knn_key_value(key) * invq : 0.f;
+    }
+    if (lane == 0) {
+        res[q].domain = live > 0 ? domain : -1;
         res[q].degenerate = degenerate ? 1 : 0;
     }
 }

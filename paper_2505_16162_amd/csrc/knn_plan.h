@@ -4,6 +4,12 @@
 
 namespace ks {
 
+// Scores of a workgroup of knn_rank_kernel: as many as its lanes hold in registers; one workgroup takes up to twice that, since a second
+// one costs the hand-over (three queries, K = 8, 5000 anchors: 43 us a call in two slices, 37 in one; 8000: 43.5 / 42.8).
+constexpr int KNN_SLICE = 4096;
+// Routing over at least so many anchors ranks with knn_rank_kernel instead of knn_argmax_kernel's one workgroup: 5000 anchors of
+// 256 22.3 / 21.9 us, 8000 23.7 / 23.6, 16 000 28.1 / 26.1, 200 000 134 / 67; below, knn_argmax_kernel is the shorter one.
+constexpr int KNN_RANK_ONE = 8192;
 constexpr int KNN_STREAM_ROUND = 16384;      // anchors that knn_scores_stream_kernel's wavefronts take at a time: 256 x 16 wavefronts, four each
 
 // knn_scores_stream_kernel, or knn_scores_multi_kernel? The first has its queries in LDS and keeps the table's loads rolling across

@@ -43,8 +43,8 @@ static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Workspace layout (byte offsets, all 256-byte aligned).
 struct WsLayout {
-    size_t draft_ctl, ver_ctl, gen, head, knn, out3;
-    size_t x, xn, qkv, att, u, logits, hidden_last, rope_cos, rope_sin, knn_scores, knn_topk, knn_cand_idx, knn_cand_val, knn_bad, out_tokens;
+    size_t draft_ctl, ver_ctl, gen, head, out3;
+    size_t x, xn, qkv, att, u, logits, hidden_last, rope_cos, rope_sin, knn_scores, knn_cand, knn_bad, knn_arrivals, out_tokens;
     // tuned bf16 path
     size_t act_d, qrot, ss, head_part, attn_part, attn_arrivals, split_tab;
     // tuned prompt prefill (stream-order weights only): all prompt rows at once
@@ -101,7 +101,6 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
     L.ver_ctl = take(sizeof(PassCtl));
     L.gen = take(sizeof(GenState));
     L.head = take(sizeof(HeadResult));
-    L.knn = take(sizeof(KnnResult));
     L.out3 = take(4 * sizeof(int32_t));
     L.x = take(R * c->d_model * 4);
     L.xn = take(R * c->d_model * 4);
@@ -113,10 +112,9 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
     L.rope_cos = take((size_t)c->max_seq * (c->head_dim / 2) * 4);
     L.rope_sin = take((size_t)c->max_seq * (c->head_dim / 2) * 4);
     L.knn_scores = take((size_t)(c->max_anchors > 0 ? c->max_anchors : 1) * 4 * KNN_QMAX);
-    L.knn_topk = take(sizeof(KnnTopk) * KNN_QMAX);
-    L.knn_cand_idx = take((size_t)KNN_QMAX * KNN_SLICES_MAX * KNN_KMAX * 4);
-    L.knn_cand_val = take((size_t)KNN_QMAX * KNN_SLICES_MAX * KNN_KMAX * 4);
+    L.knn_cand = take((size_t)KNN_QMAX * KNN_SLICES_MAX * KNN_KMAX * sizeof(KnnKey));
     L.knn_bad = take((size_t)KNN_QMAX * KNN_SLICES_MAX * 4);
+    L.knn_arrivals = take(KNN_QMAX * sizeof(int));
     L.out_tokens = take((size_t)c->max_seq * 4);
     {
         const size_t qd = (size_t)c->n_heads * c->head_dim;
@@ -207,6 +205,7 @@ struct knnssd_ctx {
     bool in_prefill = false;   // the pass being enqueued belongs to a prompt prefill
 
     template <typename T> T *wsp(size_t off) { return reinterpret_cast<T *>(ws + off); }
+    template <typename T> T *staged() { return reinterpret_cast<T *>(d_flags - 512); }     // the pinned staging area as kernels see it
 };
 
 // The prefill GEMM's builds: f(token tiles, epilogue, own sums, kernel, dynamic LDS) for each
@@ -420,6 +419,7 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         delete c;
         return KNNSSD_EHIP;
     }
+    hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, c->stream, c->wsp<int>(c->L.knn_arrivals), KNN_QMAX);     // zero between launches
     const int half = cfg->head_dim / 2;
     const int n = cfg->max_seq * half;
     hipLaunchKernelGGL(rope_table_kernel, dim3((n + 255) / 256), dim3(256), 0, c->stream, c->wsp<float>(c->L.rope_cos),
@@ -1063,16 +1063,37 @@ static int32_t launch_scan(knnssd_ctx *c, const float *queries, int nq, float *s
     return c->anchor_dtype == KNNSSD_BF16 ? launch_scan_q<bf16_t>(c, queries, nq, scores) : launch_scan_q<float>(c, queries, nq, scores);
 }
 
+// The ranking behind a scan of nq queries: the K best of each and their vote, in the pinned staging area behind drain()
+static int32_t launch_rank(knnssd_ctx *c, const float *queries, int nq, int k, const float *scores, KnnTopk *res) {
+    const int N = c->n_anchors;
+    int n_slices = N < 2 * KNN_SLICE ? 1 : (N + KNN_SLICE - 1) / KNN_SLICE;      // workgroups per query
+    if (n_slices > KNN_SLICES_MAX) n_slices = KNN_SLICES_MAX;
+    // a slice is ranked by one workgroup, whose lanes keep one mask bit per entry they look at
+    if ((N + n_slices - 1) / n_slices > KNN_ROUNDS_MAX_N) n_slices = (N + KNN_ROUNDS_MAX_N - 1) / KNN_ROUNDS_MAX_N;
+    if (n_slices > KNN_SLICES_MAX) return KNNSSD_ERANGE;       // more than 16.7 million anchors
+    hipLaunchKernelGGL(knn_rank_kernel, dim3(nq, n_slices), dim3(1024), 0, c->stream, scores, N, k, n_slices, c->wsp<KnnKey>(c->L.knn_cand),
+                       c->wsp<int>(c->L.knn_bad), c->wsp<int>(c->L.knn_arrivals), queries, c->labels, c->cfg.d_model, res);
+    HIP_TRY(hipGetLastError());
+    return KNNSSD_OK;
+}
+
 static int32_t select_impl(knnssd_ctx *c, const float *query_dev, int32_t *idx_out, int32_t *dom_out) {
     const int N = c->n_anchors, D = c->cfg.d_model;
     float *scores = c->wsp<float>(c->L.knn_scores);
-    KnnResult *res = c->wsp<KnnResult>(c->L.knn);
     KS_TRY(launch_scan(c, query_dev, 1, scores));
-    hipLaunchKernelGGL(knn_argmax_kernel, dim3(1), dim3(1024), 0, c->stream, scores, query_dev, c->labels, N, D, res);
-    HIP_TRY(hipGetLastError());
-    KS_TRY(read_back(c, res, sizeof(KnnResult)));
     KnnResult r;
-    memcpy(&r, c->h_stage, sizeof(r));
+    if (N >= KNN_RANK_ONE && N <= KNN_SLICES_MAX * KNN_ROUNDS_MAX_N) {
+        KnnTopk t;
+        KS_TRY(launch_rank(c, query_dev, 1, 1, scores, c->staged<KnnTopk>()));
+        KS_TRY(drain(c));
+        memcpy(&t, c->h_stage, sizeof(t));
+        r.degenerate = t.degenerate; r.idx = t.idx[0]; r.label = t.domain;
+    } else {
+        hipLaunchKernelGGL(knn_argmax_kernel, dim3(1), dim3(1024), 0, c->stream, scores, query_dev, c->labels, N, D, c->staged<KnnResult>());
+        HIP_TRY(hipGetLastError());
+        KS_TRY(drain(c));
+        memcpy(&r, c->h_stage, sizeof(r));
+    }
     if (r.degenerate) return KNNSSD_EDEGENERATE;
     if (r.label < 0 || r.label >= c->n_domains) return KNNSSD_ERANGE;
     const size_t ml = (size_t)2 * c->cfg.n_blocks;
@@ -1089,26 +1110,15 @@ extern "C" int32_t knnssd_knn_topk(knnssd_ctx *ctx, const float *queries_dev, in
     if (!ctx->anchors) return KNNSSD_ESTATE;
     if ((uintptr_t)queries_dev & 15) return KNNSSD_EINVAL;
     if (n_queries <= 0 || k < 1 || k > KNN_KMAX || k > ctx->n_anchors) return KNNSSD_ERANGE;
-    const int N = ctx->n_anchors, D = ctx->cfg.d_model;
+    const int D = ctx->cfg.d_model;
     float *scores = ctx->wsp<float>(ctx->L.knn_scores);
-    KnnTopk *res = ctx->wsp<KnnTopk>(ctx->L.knn_topk);
+    static_assert(sizeof(KnnTopk) * KNN_QMAX <= 512 * sizeof(int32_t), "the flags lie behind the results");
     for (int q0 = 0; q0 < n_queries; q0 += KNN_QMAX) {
         const int nq = n_queries - q0 < KNN_QMAX ? n_queries - q0 : KNN_QMAX;
         const float *qp = queries_dev + (size_t)q0 * D;
         KS_TRY(launch_scan(ctx, qp, nq, scores));
-        int n_slices = N / 2048;                      // stage 1 slices per query: a few thousand scores each
-        if (n_slices < 1) n_slices = 1;
-        if (n_slices > KNN_SLICES_MAX) n_slices = KNN_SLICES_MAX;
-        // a slice is ranked by one workgroup, whose lanes keep one mask bit per entry they look at
-        if ((N + n_slices - 1) / n_slices > KNN_ROUNDS_MAX_N) n_slices = (N + KNN_ROUNDS_MAX_N - 1) / KNN_ROUNDS_MAX_N;
-        if (n_slices > KNN_SLICES_MAX) return KNNSSD_ERANGE;       // more than 16.7 million anchors
-        int32_t *cand_idx = ctx->wsp<int32_t>(ctx->L.knn_cand_idx);
-        float *cand_val = ctx->wsp<float>(ctx->L.knn_cand_val);
-        int *bad = ctx->wsp<int>(ctx->L.knn_bad);
-        hipLaunchKernelGGL(knn_topk_part_kernel, dim3(nq, n_slices), dim3(1024), 0, ctx->stream, scores, N, k, n_slices, cand_idx, cand_val, bad);
-        hipLaunchKernelGGL(knn_topk_kernel, dim3(nq), dim3(1024), 0, ctx->stream, cand_idx, cand_val, n_slices, bad, qp, ctx->labels, D, k, res);
-        HIP_TRY(hipGetLastError());
-        KS_TRY(read_back(ctx, res, sizeof(KnnTopk) * nq));
+        KS_TRY(launch_rank(ctx, qp, nq, k, scores, ctx->staged<KnnTopk>()));
+        KS_TRY(drain(ctx));
         const KnnTopk *h = reinterpret_cast<const KnnTopk *>(ctx->h_stage);
         for (int q = 0; q < nq; ++q) {
             if (h[q].degenerate) return KNNSSD_EDEGENERATE;
