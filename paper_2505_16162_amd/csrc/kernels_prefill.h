@@ -192,7 +192,8 @@ __device__ __forceinline__ void pf_value_store(const GemmOp &op, int tok, int v,
 // What bounds it. 256 x 256 and 256 x 128: the matrix cores, at 1.53-1.6 PFLOP/s issued (three instructions per product), where a
 // large library product in bf16 reaches 1.59 on this card; one meeting per step for all wavefronts together kept the matrix
 // pipe 55 % busy, two groups one phase apart 80 %. 13B-shaped, 4096 rows: QKV 1.52-1.55 ms (with its own sums, below),
-// gate+up 2.26-2.33, O 0.44, down 1.12. 128 x 64 (few rows): operand reads out of LDS about as much as the weight stream: a 4 x 2 grid
+// gate+up 2.26-2.33, O 0.44, down 1.12. 256 x 192 (three staged steps, a step's matrix instructions in one cluster): 1.36 us a step, 0.113 a token tile
+// where 256 x 256 takes 1.93 and 0.121, 256 x 128 1.04 and 0.13; with its own sums 1.65. 128 x 64 (few rows): operand reads out of LDS about as much as the weight stream: a 4 x 2 grid
 // of wavefronts reads 8 KB a wavefront and step, 8 x 1 reads 13 (7B, 45 rows, gate+up unsplit 79 -> 75 us); 5-6 us of a
 // launch are its fixed cost. Half of the wavefronts request the weights and half the activations, so that the weights run five steps
 // ahead and the activations three, and the operands of the next step are read under the matrix instructions of this one: whole prompts
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
 #pragma unroll
         for (int j = 0; j < TBW; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const char *la = lds + wa * TAW * 1024 + voff, *lb = lds + Sh::B0 + wb * TBW * 1024 + voff;
-    constexpr int JC = TBW < 2 ? TBW : 2, CL = TBW / JC;       // token tiles per cluster of matrix instructions, clusters per step
+    constexpr int JC = TBW <= 3 ? TBW : 2, CL = TBW / JC;      // token tiles per cluster of matrix instructions, clusters per step
     constexpr int SETS = PP ? 1 : 2;                           // operands of two steps in registers: the next one's are read under this one's matrix instructions
     u32x4 avs[SETS][TAW], bvs[SETS][JC][PF_NP];
     auto read_a = [&](int buf, int set = 0) {
@@ -663,17 +664,17 @@ __device__ __forceinline__ int pf_row_token(int n_tok) {
     return ((i >> 4) * 8 + die) * 16 + (i & 15);
 }
 
-// parts that the tile of column c was summed in
-__device__ __forceinline__ int pf_n_parts(const PfRowArgs &a, int c) {
-    if (a.G == 0) return a.S;
+// parts that the tile of column c was summed in. (CUT, a build of its own: a number that differs between lanes keeps the sum's loops in the
+// vector unit; 1300 rows of 256 in 6.5 us without, 8.8 with.)
+template <bool CUT> __device__ __forceinline__ int pf_n_parts(const PfRowArgs &a, int c) {
+    if (!CUT) return a.S;
     const int u = c / a.TM * a.KP;
     return pf_share_owner(a.units, a.G, u + a.KP - 1) - pf_share_owner(a.units, a.G, u) + 1;
 }
-// columns c..c+3 of the K parts, added up in order
-__device__ __forceinline__ f32x4 pf_sum_parts(const PfRowArgs &a, int tok, int c) {
+// columns c..c+3 of the S parts, added up in order
+__device__ __forceinline__ f32x4 pf_sum_parts(const PfRowArgs &a, int tok, int c, int S) {
     const float *p = a.in + (size_t)tok * a.ld + c;
     const size_t st = (size_t)a.out_rows * a.ld;
-    const int S = pf_n_parts(a, c);
     f32x4 v = *reinterpret_cast<const f32x4 *>(p);
     int s = 1;
     auto take = [&](auto n) {              // that many loads in flight
@@ -697,7 +698,7 @@ __device__ __forceinline__ int pf_pair_col(int p, int TM) {
 }
 
 // x = E[tok] or x += the product's row; the next norm's operands gain (.) x and the row's factor. One workgroup per token.
-template <bool EMBED>
+template <bool EMBED, bool CUT>
 __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
     __shared__ float shares[PF_RT / 64];
     const int tok = pf_row_token(a.n_tok);
@@ -711,7 +712,7 @@ __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
             v = f32x4{bf_lo(w.x), bf_hi(w.x), bf_lo(w.y), bf_hi(w.y)};
         } else {
             const f32x4 x0 = *xp;
-            v = x0 + pf_sum_parts(a, tok, n);
+            v = x0 + pf_sum_parts(a, tok, n, CUT ? __builtin_amdgcn_readfirstlane(pf_n_parts<CUT>(a, n)) : a.S);     // (a wavefront's columns lie in one tile)
         }
         *xp = v;
 #pragma unroll
@@ -733,27 +734,30 @@ __global__ __launch_bounds__(PF_RT) void prefill_x_row_kernel(PfRowArgs a) {
 }
 
 // SwiGLU of a gate+up product's K parts; gridDim.y workgroups per row
+template <bool CUT>
 __global__ __launch_bounds__(PF_RT) void prefill_u_row_kernel(PfRowArgs a) {
     const int tok = pf_row_token(a.n_tok);
     if (tok >= a.n_tok) return;
     for (int n = (blockIdx.y * blockDim.x + threadIdx.x) * 4; n < a.d; n += gridDim.y * blockDim.x * 4) {
-        const int c = pf_pair_col(n, a.TM);
-        store_frag4(a.frag, a.d >> 5, a.TT, tok >> 4, tok & 15, n, pf_swiglu(pf_sum_parts(a, tok, c), pf_sum_parts(a, tok, c + 16)));
+        const int c = pf_pair_col(n, a.TM), S = pf_n_parts<CUT>(a, c);
+        store_frag4(a.frag, a.d >> 5, a.TT, tok >> 4, tok & 15, n, pf_swiglu(pf_sum_parts(a, tok, c, S), pf_sum_parts(a, tok, c + 16, S)));
     }
 }
 
 // rotary embedding, queries and cache entries from the K parts of a split QKV product (n_mr: its row tiles of rotary pairs)
+template <bool CUT>
 __global__ __launch_bounds__(PF_RT) void prefill_qkv_row_kernel(PfRowArgs a, int n_mr) {
     const int tok = pf_row_token(a.n_tok);
     if (tok >= a.n_tok) return;
     const int P = (a.op.H + a.op.Hkv) * (a.op.hd >> 1), VR = a.op.Hkv * a.op.hd;
     for (int i = (blockIdx.y * blockDim.x + threadIdx.x) * 4; i < P + VR; i += gridDim.y * blockDim.x * 4) {     // gridDim.y workgroups per row
         if (i < P) {
-            const int c = pf_pair_col(i, a.TM);
-            const f32x4 x0 = pf_sum_parts(a, tok, c), x1 = pf_sum_parts(a, tok, c + 16);
+            const int c = pf_pair_col(i, a.TM), S = pf_n_parts<CUT>(a, c);
+            const f32x4 x0 = pf_sum_parts(a, tok, c, S), x1 = pf_sum_parts(a, tok, c + 16, S);
             pf_rope_store(a.op, tok, i, x0, x1);
         } else {
-            pf_value_store(a.op, tok, i - P, pf_sum_parts(a, tok, n_mr * a.TM + i - P));
+            const int c = n_mr * a.TM + i - P;
+            pf_value_store(a.op, tok, i - P, pf_sum_parts(a, tok, c, pf_n_parts<CUT>(a, c)));
         }
     }
 }

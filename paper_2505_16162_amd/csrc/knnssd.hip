@@ -212,6 +212,7 @@ struct knnssd_ctx {
 template <int TA, int TB, int WA, int NS, bool PP, int EPI, bool OWN, typename F> static void pf_build(F f) {
     f(TB, EPI, OWN, prefill_gemm_kernel<TA, TB, WA, NS, PP, EPI, OWN>, PfShape<TA, TB, WA, NS, PP>::LDS);
 }
+template <int TB, int EPI, bool OWN, typename F> static void pf_build_wide(F f) { pf_build<16, TB, 2, 3, true, EPI, OWN>(f); }
 template <typename F> static void pf_each_build(F f) {
     pf_build<16, 16, 2, 2, true, PF_PARTS, false>(f);
     pf_build<16, 16, 2, 2, true, PF_PARTS, true>(f);
@@ -220,6 +221,13 @@ template <typename F> static void pf_each_build(F f) {
     pf_build<16, 8, 2, 3, true, PF_PARTS, false>(f);
     pf_build<16, 8, 2, 3, true, PF_PARTS, true>(f);
     pf_build<8, 4, 4, 5, false, PF_PARTS, true>(f);
+    // those that only pf_choose takes
+    pf_build_wide<8, PF_SWIGLU, false>(f);
+    pf_build_wide<8, PF_ROPE, true>(f);
+    pf_build_wide<12, PF_PARTS, false>(f);
+    pf_build_wide<12, PF_PARTS, true>(f);
+    pf_build_wide<12, PF_SWIGLU, false>(f);
+    pf_build_wide<12, PF_ROPE, true>(f);
 }
 static hipError_t pf_set_lds_limits() {
     hipError_t e = hipSuccess;
@@ -908,7 +916,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     auto x_row = [&](int which, int after) {
         PfRowArgs r = row_args(which, d);
         r.x = x; r.gain = next_gain(c, nullptr, after); r.frag = frag_d; r.rstd = rstd;
-        hipLaunchKernelGGL((prefill_x_row_kernel<false>), rows, dim3(PF_RT), 0, s, r);
+        hipLaunchKernelGGL((r.G > 0 ? prefill_x_row_kernel<false, true> : prefill_x_row_kernel<false, false>), rows, dim3(PF_RT), 0, s, r);
     };
     {
         int32_t *toks = c->wsp<int32_t>(c->L.pf_tokens);
@@ -916,7 +924,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         PfRowArgs r = row_args(PF_O, d);
         r.op.embed = (const bf16_t *)c->embed; r.toks = toks;
         r.x = x; r.gain = next_gain(c, nullptr, -1); r.frag = frag_d; r.rstd = rstd;
-        hipLaunchKernelGGL((prefill_x_row_kernel<true>), rows, dim3(PF_RT), 0, s, r);
+        hipLaunchKernelGGL((prefill_x_row_kernel<true, false>), rows, dim3(PF_RT), 0, s, r);
     }
     for (int b = 0; b < g.n_blocks; ++b) {
         bf16_t *kvb = (bf16_t *)(c->kv + (size_t)b * c->kv_block_bytes);
@@ -926,7 +934,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         if (plan[PF_QKV].parts(PF_QKV)) {
             PfRowArgs r = row_args(PF_QKV, 0);
             r.op = o;
-            hipLaunchKernelGGL(prefill_qkv_row_kernel, dim3(rows.x, ((H + Hkv) * hd / 2 + Hkv * hd + 1023) / 1024), dim3(256), 0, s, r, plan[PF_QKV].n_mr);
+            hipLaunchKernelGGL((r.G > 0 ? prefill_qkv_row_kernel<true> : prefill_qkv_row_kernel<false>), dim3(rows.x, ((H + Hkv) * hd / 2 + Hkv * hd + 1023) / 1024), dim3(256), 0, s, r, plan[PF_QKV].n_mr);
         }
         PfAttn at{};
         at.q = q; at.kv_block = kvb; at.frag_out = frag_att; at.H = H; at.Hkv = Hkv; at.max_seq = g.max_seq; at.n_tok = n_tok; at.TT = TT;
@@ -942,7 +950,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
         if (plan[PF_GU].parts(PF_GU)) {
             PfRowArgs ru = row_args(PF_GU, F);
             ru.frag = frag_u;
-            hipLaunchKernelGGL(prefill_u_row_kernel, dim3(rows.x, (F + 4 * u_nt - 1) / (4 * u_nt)), dim3(u_nt), 0, s, ru);
+            hipLaunchKernelGGL((ru.G > 0 ? prefill_u_row_kernel<true> : prefill_u_row_kernel<false>), dim3(rows.x, (F + 4 * u_nt - 1) / (4 * u_nt)), dim3(u_nt), 0, s, ru);
         }
         GemmOp dn = base;
         dn.type = OP_RESID; dn.W = (const bf16_t *)c->wdown[b]; dn.N = d; dn.K = F; dn.split = c->split_down;

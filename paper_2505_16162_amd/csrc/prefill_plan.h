@@ -26,17 +26,19 @@ KS_HD inline int pf_share_owner(int n, int G, int u) { return (int)((((unsigned 
 
 // How the prefill GEMM covers one matrix for a prompt of tt token tiles (16 rows each)
 struct PfPlan {
-    int tb;                  // token tiles per workgroup: 16, 8 (256 weight rows) or 4 (128 weight rows)
+    int tb;                  // token tiles per workgroup: 16, 12, 8 (256 weight rows) or 4 (128 weight rows)
     int n_mt, n_mr, n_tt;    // row tiles, those of them with rotary pairs (OP_QKV), workgroup tiles along the tokens
+    int rows;                // rows of the prompt's token tiles
     int S;                   // parts K is split into (G > 0: the most parts of a tile)
+    bool fused = false;      // workgroups of 256 rows that walk all of K finish their rows themselves, whatever tb is
     int G = 0;               // > 0: a thin launch of so many workgroups (prefill_thin_kernel), tiles of 256 weight rows x all tokens
     int tiles() const { return n_mt * n_tt; }
     // sums through memory to a row kernel? (residual rows always; the others unless one large workgroup finishes them)
-    bool parts(int which) const { return G > 0 || S > 1 || tb != 16 || which == PF_O || which == PF_DOWN; }
+    bool parts(int which) const { return G > 0 || S > 1 || (tb != 16 && !fused) || which == PF_O || which == PF_DOWN; }
     int epilogue(int which) const { return parts(which) ? PF_PARTS : (which == PF_GU ? PF_SWIGLU : PF_ROPE); }
     bool own_sums(int which) const { return which == PF_QKV || tb == 4; }       // sums of their own per step: see the kernel
     int tm() const { return tb == 4 && G == 0 ? 128 : 256; }
-    int out_rows() const { return n_tt * tb * 16; }
+    int out_rows() const { return rows; }
     size_t part_bytes() const { return (size_t)S * out_rows() * n_mt * tm() * 4; }       // K parts of the product
 };
 
@@ -58,30 +60,53 @@ inline int pf_row_tiles(const knnssd_model_cfg &g, int which, int tm, int *n_mr 
 // 200 to 400 rows: within 13 but for gate+up at 260 and 300 rows (256 x 256, where two or three parts of 256 x 128 take 14-28 less of
 // 500-700) and 13B's QKV there (-15). 13B, 1024 rows: QKV unsplit 256 x 256 (chosen), 256 x 128 +31 us, in two parts +60; O in three
 // parts of 256 x 256 (chosen), of 256 x 128 -7, in two +17; gate+up unsplit (chosen), 256 x 128 +86.
-inline PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt) {
+// least > 0 (pf_choose): also tiles of 256 x 192, and 256 x 128 ones that finish their rows themselves where K is whole; at least so many parts,
+// of at most `room` bytes together.
+inline PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt, int least = 0, size_t room = 0) {
     const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KS = K / 32;
     PfPlan best{};
     double best_cost = 0;
-    for (int tb = 4; tb <= 16; tb *= 2) {
+    for (int tb = 4; tb <= 16; tb += 4) {
+        if (tb == 12 && least == 0) continue;
         PfPlan p{};
         p.tb = tb;
+        p.fused = least > 0 && tb >= 8;
         const int tm = p.tm();
         p.n_mt = pf_row_tiles(g, which, tm, &p.n_mr);
         p.n_tt = (tt + tb - 1) / tb;
-        // 256 x 256 and 256 x 128: one workgroup per unit, bound by the matrix cores. 128 x 64: the two workgroups a unit holds
+        p.rows = tt * 16;
+        // 256 x 256 to 256 x 128: one workgroup per unit, bound by the matrix cores. 128 x 64: the two workgroups a unit holds
         // take turns at its LDS, but pay their fixed cost together
-        const double step = tb == 16 ? (which == PF_QKV ? 2340 : 1930) : (tb == 8 ? (which == PF_QKV ? 1290 : 1040) : 540), fixed = tb == 16 ? 14000 : (tb == 8 ? 10000 : 6000);
-        for (int S = 1; S <= 16; ++S) {
+        const double step = tb == 16 ? (which == PF_QKV ? 2340 : 1930) : tb == 12 ? (which == PF_QKV ? 1660 : 1380) : tb == 8 ? (which == PF_QKV ? 1290 : 1040) : 540;
+        const double fixed = tb == 16 ? 14000 : tb == 12 ? 12000 : tb == 8 ? 10000 : 6000;
+        for (int S = least > 0 ? least : 1; S <= 16; ++S) {
             if (S > 1 && S * 4 > KS) break;
             p.S = S;
             const int rounds = (p.tiles() * S + KS_NWG - 1) / KS_NWG;
             if (S > 1 && rounds > 8) break;
+            if (least > 0 && p.parts(which) && p.part_bytes() > room) break;
             const double moved = p.parts(which) ? 2.0 * S * tt * 16 * p.n_mt * tm * 4 : 0;
+            if (best_cost > 0 && moved / 3000 >= best_cost) break;     // (only grows with S)
             const double cost = rounds * ((KS + S - 1) / S * step) + (tb == 4 ? (rounds + 1) / 2 : rounds) * fixed + moved / 3000;
             if (best_cost == 0 || cost < best_cost) { best = p; best_cost = cost; }
         }
     }
     return best;
+}
+
+// The tiles a product takes: the best of pf_plan's and of the wide ones with no fewer parts, so that no sum has more roundings in a row than
+// it would have without them (256 x 192 tiles of two parts instead of 256 x 256 ones of three for the O projection, and QKV rows of one part
+// instead of two: 0.72 % of a Qwen-shaped prompt's cache entries on another bf16 value than in 64 bits, 777 rows, instead of 0.62). Gate+up rows
+// may: they reach the cache through the down product alone (13B 257 rows 0.686 / 0.686 %, 7B 777 0.424 / 0.425 %, hidden states within 2 %).
+// 128 x 64 tiles add up each step's planes on their own (own_sums), which the residual and SwiGLU rows do nowhere else: those stay.
+// Measured against pf_plan alone, whole prompts, two blocks, us: 7B 180 rows 738 -> 660, 257 1110 -> 983, 777 2201 -> 2005, 13B 257 1474 -> 1255, 600
+// 2575 -> 2313, 2200 7776 -> 7066, Qwen 513 2280 -> 2003, 777 2919 -> 2845; where the plan stays (100, 400, 1024 rows) 0.997-1.003.
+constexpr size_t PF_PART_ROOM = (size_t)128 << 20;     // what pf_plan's parts take at some length anyway, in the shipped widths: the workspace does not grow
+inline PfPlan pf_tiles(const knnssd_model_cfg &g, int which, int tt) {
+    const PfPlan p = pf_plan(g, which, tt);
+    if (p.tb == 4 && which != PF_QKV) return p;
+    const size_t room = p.parts(which) ? p.part_bytes() : 0;
+    return pf_plan(g, which, tt, which == PF_GU ? 1 : p.S, room > PF_PART_ROOM ? room : PF_PART_ROOM);
 }
 
 // Prompts of up to PF_THIN token tiles take prefill_thin_kernel for matrices of at least PF_THIN_PAIRS pairs of steps a workgroup: with fewer
@@ -95,13 +120,14 @@ inline PfPlan pf_choose(const knnssd_model_cfg &g, int which, int tt) {
     p.G = KS_NWG;
     p.n_mt = pf_row_tiles(g, which, p.tm(), &p.n_mr);
     p.n_tt = 1;
+    p.rows = tt * 16;
     const int units = p.n_mt * KP;
-    if (tt > PF_THIN || units < PF_THIN_PAIRS * KS_NWG || units > (PF_THIN_TILES - 2) * KP * KS_NWG) return pf_plan(g, which, tt);
+    if (tt > PF_THIN || units < PF_THIN_PAIRS * KS_NWG || units > (PF_THIN_TILES - 2) * KP * KS_NWG) return pf_tiles(g, which, tt);
     for (int t = 0; t < p.n_mt; ++t) {
         const int n = pf_share_owner(units, p.G, (t + 1) * KP - 1) - pf_share_owner(units, p.G, t * KP) + 1;
         if (n > p.S) p.S = n;
     }
-    if (p.S > 32) return pf_plan(g, which, tt);        // few rows, many columns: a row kernel would read them all
+    if (p.S > 32) return pf_tiles(g, which, tt);        // few rows, many columns: a row kernel would read them all
     return p;
 }
 

@@ -16,7 +16,7 @@ int main(int n, char **v) {
     g.d_model = atoi(v[1]); g.n_heads = atoi(v[2]); g.n_kv_heads = atoi(v[3]); g.head_dim = atoi(v[4]); g.d_ffn = atoi(v[5]);
     for (int w = 0; w < ks::PF_OPS; ++w)
         for (int tt = 2; tt <= 5; ++tt) {
-            const ks::PfPlan p = ks::pf_choose(g, w, tt), r = ks::pf_plan(g, w, tt);
+            const ks::PfPlan p = ks::pf_choose(g, w, tt), r = ks::pf_tiles(g, w, tt);
             const int K = w == ks::PF_O ? g.n_heads * g.head_dim : (w == ks::PF_DOWN ? g.d_ffn : g.d_model), KP = (K / 32 + 1) / 2, units = p.n_mt * KP;
             printf("%d %d %d %d %d %d %d %d\n", w, tt, p.G, p.S, p.n_mt * p.tm(), p.out_rows(), (int)(p.parts(w)), (int)(p.tb == r.tb && p.S == r.S));
             if (!p.G) continue;
