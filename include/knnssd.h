@@ -69,7 +69,8 @@ typedef struct knnssd_model_cfg {
                                tuned bf16 kernels run; 0: row-major, generic kernels. embed is always row-major. */
     int32_t prefill_mode;   /* KNNSSD_PREFILL_AUTO: prompts go through the many-row prefill kernels where the shape
                                fits them; KNNSSD_PREFILL_CHUNKED: through 16-row passes of the verification kernels.
-                               Only read with weights_packed = 1. */
+                               Row-major weights: AUTO takes a prompt's rows side by side, with the bits of 16-row
+                               passes, if the workspace has room for them (knnssd_workspace_bytes of that cfg). */
     int32_t verify_attn;    /* which split-KV attention kernel verification passes (and the draft steps of
                                grouped-query models, and of any model once the context brings more (kv head,
                                256-position chunk) items than 512) use: KNNSSD_ATTN_MFMA (matrix cores, the default) or

@@ -114,8 +114,28 @@ __global__ void rope_table_kernel(float *cos_t, float *sin_t, int max_seq, int h
 // ------------------------------------------------------------------------------------------
 // embedding gather: x[r][:] = E[tok[r]][:]
 // ------------------------------------------------------------------------------------------
+// A prompt's rows as chunks of so many side by side (PromptRows): chunk c's control block is ctl[c], its rows lie behind those of the chunks
+// before it. The row kernels take a chunk where a pass takes its rows, with the same device code, so a row has the bits that
+// it has in a pass. A pass of 16 rows leaves most of the chip idle and pays five launches a block (or a one-launch pass's chain of
+// hand-overs) for them: 250 rows, two blocks, fp32 / bf16: 192 columns 938 / 922 us in passes, 132 / 140 here, 520 columns 1885 / 1748 and 241 / 263, 1000
+// columns 3185 / 2410 and 575 / 594, 1912 columns 5813 / 4288 and 2064 / 2116 (bound by the rows' way through the L1); 33 rows 162-932 and
+// 97-491; 17 rows of 192 columns 106 / 105 and 98-108. Chunks of eight rows: the products' builds of up to nine rows are the ones whose loads the compiler places well.
+constexpr int PR_CHUNK = 8, PR_ROWS = 256;
+struct PromptRows {
+    int32_t start, n;           // position of the first row, rows
+    int32_t tok[PR_ROWS];
+};
+__global__ void set_prompt_kernel(PassCtl *ctl, PromptRows p) {
+    const int c = blockIdx.x, first = c * PR_CHUNK, n = min(PR_CHUNK, p.n - first);
+    if (threadIdx.x < KS_MAX_ROWS) ctl[c].tok[threadIdx.x] = (int)threadIdx.x < n ? p.tok[first + threadIdx.x] : 0;
+    if (threadIdx.x == 0) { ctl[c].active = 1; ctl[c].n_rows = n; ctl[c].start = p.start + first; ctl[c].head_from = n; }
+}
+
+// (gridDim.y chunks)
 template <typename WT>
 __global__ void embed_kernel(const PassCtl *ctl, const WT *E, float *x, int d) {
+    ctl += blockIdx.y;
+    x += (size_t)blockIdx.y * PR_CHUNK * d;
     if (!ctl->active) return;
     int r = blockIdx.x;
     if (r >= ctl->n_rows) return;
@@ -276,17 +296,29 @@ struct RowsOp {
     void *kv_block;
     const float *cos_t, *sin_t;
     int H, Hkv, hd, max_seq;
+    int chunks;                 // of a prompt's rows
 };
 
-template <typename WT, typename KT, int MR, int EPI>
+// CHUNKS: a prompt's rows, op.chunks chunks of MR; the workgroups that share weights (one group of items, all chunks) are consecutive ones
+// of a die, so that its L2 fetches a weight once.
+template <typename WT, typename KT, int MR, int EPI, bool CHUNKS = false>
 __global__ __launch_bounds__(256) void gemm_rows_kernel(const PassCtl *ctl, const WT *__restrict__ W, RowsOp op) {
+    int group = blockIdx.x, n_groups = gridDim.x;
+    if constexpr (CHUNKS) {
+        const int i = blockIdx.x >> 3, g = i / op.chunks, c = i - g * op.chunks;
+        group = g * 8 + (blockIdx.x & 7);
+        n_groups = gridDim.x / op.chunks;
+        ctl += c;
+        op.X += (size_t)c * MR * op.ldx;
+        op.Y += (size_t)c * MR * op.ldy;
+    }
     if (!ctl->active) return;
     const int row_lo = op.from_head ? ctl->head_from : 0;
     const int n_rows = min(ctl->n_rows - row_lo, MR);
     if (n_rows <= 0) return;
     const int lane = threadIdx.x & 63;
-    const int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const int n_waves = (gridDim.x * blockDim.x) >> 6;
+    const int wave = (group * blockDim.x + threadIdx.x) >> 6;
+    const int n_waves = (n_groups * blockDim.x) >> 6;
     constexpr bool DUAL = EPI == EPI_SWIGLU || EPI == EPI_QKV;      // two weight rows per item
     const int K = op.K, half = op.hd >> 1;
     const int P = EPI == EPI_QKV ? (op.H + op.Hkv) * half : 0;      // rotary pairs; behind them pairs of value rows
@@ -436,8 +468,11 @@ __device__ __forceinline__ void attention_item(float4 q, int len, int tid, float
 template <typename KT, int HD>
 __global__ __launch_bounds__(256) void attention_kernel(const PassCtl *ctl, const float *qkv, const KT *kv_block,
                                                         float *att, int H, int Hkv, int max_seq) {
+    const int h = blockIdx.x, r = blockIdx.y, c = blockIdx.z;      // (gridDim.z chunks of a prompt's rows)
+    ctl += c;
+    qkv += (size_t)c * PR_CHUNK * (H + 2 * Hkv) * HD;
+    att += (size_t)c * PR_CHUNK * H * HD;
     if (!ctl->active) return;
-    const int h = blockIdx.x, r = blockIdx.y;
     if (r >= ctl->n_rows) return;
     extern __shared__ float scores[];                        // [len]
     __shared__ AttnItemLds lds;

@@ -49,6 +49,7 @@ struct WsLayout {
     size_t act_d, qrot, ss, head_part, attn_part, attn_arrivals, split_tab;
     // tuned prompt prefill (stream-order weights only): all prompt rows at once
     size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_rstd, pf_part[PF_OPS], pf_rows[PF_OPS][2];
+    size_t pr_ctl, pr_x, pr_qkv, pr_att, pr_u;      // a prompt's rows on the any-shape kernels
     int pf_tt;          // token tiles the fragment buffers are laid out for
     // small models' one-launch passes: block table, handed-over vectors
     size_t small_tab, small_meets, small_words, small_words_bytes;
@@ -83,6 +84,8 @@ static bool cfg_supported(const knnssd_model_cfg *c) {
 // 137 / 123. Beyond, draft steps and 5 rows: 9.4 MB a block and a head of 6 MB 93 / 86, 108 / 112; 15 MB a block 94 / 106,
 // 113 / 141; a head of 33 MB 100 / 126, 136 / 167.
 static const size_t SMALL_MAX_BYTES = 8u << 20;     // weights of a block, of the head
+// prompts on the any-shape kernels take their rows side by side instead of 16 at a time
+static bool prompt_rows_ok(const knnssd_model_cfg &g) { return !g.weights_packed && g.prefill_mode == KNNSSD_PREFILL_AUTO; }
 static bool small_ok(const knnssd_model_cfg &g) {
     if (g.weights_packed || g.weight_dtype != g.kv_dtype || g.n_blocks < 1 || g.n_blocks > SM_MAX_BLOCKS) return false;
     const size_t elt = g.weight_dtype == KNNSSD_BF16 ? 2 : 4, d = (size_t)g.d_model, hd = (size_t)g.head_dim;
@@ -149,6 +152,14 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
             for (int w = 0; w < PF_OPS; ++w)
                 for (int i = 0; i < 2; ++i) L.pf_rows[w][i] = take((size_t)pf_row_tiles(*c, w, i ? 256 : 128) * (i ? 256 : 128) * sizeof(PfRow));
         }
+    }
+    if (prompt_rows_ok(*c)) {
+        const size_t rows = (size_t)PR_ROWS, qd = (size_t)c->n_heads * c->head_dim;
+        L.pr_ctl = take(PR_ROWS / PR_CHUNK * sizeof(PassCtl));
+        L.pr_x = take(rows * c->d_model * 4);
+        L.pr_qkv = take(rows * qkv_dim * 4);
+        L.pr_att = take(rows * qd * 4);
+        L.pr_u = take(rows * (size_t)c->d_ffn * 4);
     }
     if (small_ok(*c)) {
         const size_t qd = (size_t)c->n_heads * c->head_dim;
@@ -300,7 +311,10 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
     if (!cfg_valid(cfg) || !w || !kv_dev || !ws_dev) return KNNSSD_EINVAL;
     if (!cfg_supported(cfg)) return KNNSSD_ESHAPE;
     // the kernels index these buffers by the layout of THIS cfg: a buffer sized for another one must not get through
-    if (ws_bytes < ws_layout(cfg).total || kv_bytes < knnssd_kvcache_bytes(cfg)) return KNNSSD_EINVAL;
+    // (with row-major weights one without room for a prompt's rows will do: prompts take 16-row passes then)
+    knnssd_model_cfg own = *cfg;
+    if (prompt_rows_ok(own) && ws_bytes < ws_layout(&own).total) own.prefill_mode = KNNSSD_PREFILL_CHUNKED;
+    if (ws_bytes < ws_layout(&own).total || kv_bytes < knnssd_kvcache_bytes(cfg)) return KNNSSD_EINVAL;
     if (cfg->weights_packed && !tuned_ok(*cfg)) return KNNSSD_ESHAPE;
     if (((uintptr_t)kv_dev & 255) || ((uintptr_t)ws_dev & 255)) return KNNSSD_EINVAL;
     if (!w->embed || !w->lm_head || !w->final_norm) return KNNSSD_EINVAL;
@@ -317,8 +331,8 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
 
     knnssd_ctx *c = new (std::nothrow) knnssd_ctx();
     if (!c) return KNNSSD_EINVAL;
-    c->cfg = *cfg;
-    c->L = ws_layout(cfg);
+    c->cfg = own;
+    c->L = ws_layout(&own);
     c->stream = (hipStream_t)hip_stream;
     c->ws = (char *)ws_dev;
     c->kv = (char *)kv_dev;
@@ -526,6 +540,15 @@ extern "C" int32_t knnssd_set_skipset(knnssd_ctx *ctx, const uint8_t *mask_host)
 // ------------------------------------------------------------------------------------------
 // one forward pass: every retained sublayer in order, then the head
 // ------------------------------------------------------------------------------------------
+// gemm_rows_kernel over the chunks of a prompt's rows
+template <typename WT, typename KT, int EPI> static void launch_prompt_rows(knnssd_ctx *c, const PassCtl *ctl, int chunks, const void *W, RowsOp op) {
+    const int items = EPI == EPI_QKV ? (op.H + 2 * op.Hkv) * op.hd / 2 : op.N;
+    int groups = (items + 31) / 32 * 8;
+    if (groups > 2048) groups = 2048;
+    op.chunks = chunks;
+    hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, PR_CHUNK, EPI, true>), dim3(groups * chunks), dim3(256), 0, c->stream, ctl, (const WT *)W, op);
+}
+
 // gemm_rows_kernel in the build for n_rows rows: one per count, so that no pass carries dead rows
 template <typename WT, typename KT, int EPI, int MR = KS_MAX_ROWS>
 static void launch_rows(knnssd_ctx *c, const PassCtl *ctl, int n_rows, const void *W, const RowsOp &op) {
@@ -538,13 +561,68 @@ static void launch_rows(knnssd_ctx *c, const PassCtl *ctl, int n_rows, const voi
     hipLaunchKernelGGL((gemm_rows_kernel<WT, KT, MR, EPI>), dim3(wgs), dim3(256), 0, c->stream, ctl, (const WT *)W, op);
 }
 
+// The final norm and the LM head over a pass's rows, whose residual stream is x
+template <typename WT>
+static int32_t run_head_t(knnssd_ctx *c, const PassCtl *ctl, const float *x, int n_rows) {
+    const knnssd_model_cfg &g = c->cfg;
+    const int d = g.d_model;
+    float *xn = c->wsp<float>(c->L.xn), *logits = c->wsp<float>(c->L.logits);
+    hipStream_t s = c->stream;
+    hipLaunchKernelGGL(rmsnorm_kernel, dim3(n_rows), dim3(256), 0, s, ctl, x, c->final_norm, xn, d, g.rms_eps);
+    RowsOp h{};
+    h.eps = g.rms_eps;
+    h.X = xn; h.ldx = d; h.Y = logits; h.ldy = g.vocab; h.N = g.vocab; h.K = d;
+    h.from_head = 1;
+    launch_rows<WT, float, EPI_STORE>(c, ctl, c->in_prefill ? 1 : n_rows, c->lm_head, h);     // a prompt's pass: its last row, or none
+    if (small_ok(g)) hipLaunchKernelGGL(argmax_classes_kernel, dim3(n_rows), dim3(HEAD_CLASSES), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
+    else hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
+    HIP_TRY(hipGetLastError());
+    return KNNSSD_OK;
+}
+
+// The full model's blocks over n rows of a prompt from position `start` on, at most PR_ROWS: residual stream in pr_x, cache filled.
+template <typename WT, typename KT>
+static int32_t run_prompt_t(knnssd_ctx *c, const int32_t *tokens, int start, int n) {
+    const knnssd_model_cfg &g = c->cfg;
+    const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn, qd = H * hd, qkvd = (H + 2 * Hkv) * hd;
+    const int chunks = (n + PR_CHUNK - 1) / PR_CHUNK;
+    PassCtl *ctl = c->wsp<PassCtl>(c->L.pr_ctl);
+    float *x = c->wsp<float>(c->L.pr_x), *qkv = c->wsp<float>(c->L.pr_qkv), *att = c->wsp<float>(c->L.pr_att), *u = c->wsp<float>(c->L.pr_u);
+    hipStream_t s = c->stream;
+    PromptRows p{};
+    p.start = start; p.n = n;
+    memcpy(p.tok, tokens, (size_t)n * 4);
+    hipLaunchKernelGGL(set_prompt_kernel, dim3(chunks), dim3(64), 0, s, ctl, p);
+    hipLaunchKernelGGL((embed_kernel<WT>), dim3(PR_CHUNK, chunks), dim3(256), 0, s, ctl, (const WT *)c->embed, x, d);
+    auto product = [&](const float *X, int ldx, float *Y, int ldy, int N, int K, const float *gain) {
+        RowsOp o{};
+        o.eps = g.rms_eps; o.cos_t = c->wsp<float>(c->L.rope_cos); o.sin_t = c->wsp<float>(c->L.rope_sin);
+        o.H = H; o.Hkv = Hkv; o.hd = hd; o.max_seq = g.max_seq;
+        o.X = X; o.ldx = ldx; o.Y = Y; o.ldy = ldy; o.N = N; o.K = K; o.gain = gain;
+        return o;
+    };
+    for (int b = 0; b < g.n_blocks; ++b) {
+        KT *kvb = (KT *)(c->kv + (size_t)b * c->kv_block_bytes);
+        RowsOp o = product(x, d, qkv, qkvd, qkvd, d, c->attn_norm[b]);
+        o.kv_block = kvb;
+        launch_prompt_rows<WT, KT, EPI_QKV>(c, ctl, chunks, c->wqkv[b], o);
+        const size_t lds = (size_t)(start + n) * 4;
+        if (hd == 128) hipLaunchKernelGGL((attention_kernel<KT, 128>), dim3(H, PR_CHUNK, chunks), dim3(256), lds, s, ctl, qkv, kvb, att, H, Hkv, g.max_seq);
+        else hipLaunchKernelGGL((attention_kernel<KT, 64>), dim3(H, PR_CHUNK, chunks), dim3(256), lds, s, ctl, qkv, kvb, att, H, Hkv, g.max_seq);
+        launch_prompt_rows<WT, float, EPI_RESID>(c, ctl, chunks, c->wo[b], product(att, qd, x, d, d, qd, nullptr));
+        launch_prompt_rows<WT, float, EPI_SWIGLU>(c, ctl, chunks, c->wgu[b], product(x, d, u, F, F, d, c->mlp_norm[b]));
+        launch_prompt_rows<WT, float, EPI_RESID>(c, ctl, chunks, c->wdown[b], product(u, F, x, d, d, F, nullptr));
+    }
+    HIP_TRY(hipGetLastError());
+    return KNNSSD_OK;
+}
+
 template <typename WT, typename KT>
 static int32_t run_pass_t(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int n_rows) {
     const knnssd_model_cfg &g = c->cfg;
     const int d = g.d_model, H = g.n_heads, Hkv = g.n_kv_heads, hd = g.head_dim, F = g.d_ffn;
     const int qd = H * hd, qkvd = (H + 2 * Hkv) * hd;
-    float *x = c->wsp<float>(c->L.x), *xn = c->wsp<float>(c->L.xn), *qkv = c->wsp<float>(c->L.qkv);
-    float *att = c->wsp<float>(c->L.att), *u = c->wsp<float>(c->L.u), *logits = c->wsp<float>(c->L.logits);
+    float *x = c->wsp<float>(c->L.x), *qkv = c->wsp<float>(c->L.qkv), *att = c->wsp<float>(c->L.att), *u = c->wsp<float>(c->L.u);
     hipStream_t s = c->stream;
     RowsOp base{};
     base.eps = g.rms_eps; base.cos_t = c->wsp<float>(c->L.rope_cos); base.sin_t = c->wsp<float>(c->L.rope_sin);
@@ -572,16 +650,8 @@ static int32_t run_pass_t(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int 
             launch_rows<WT, float, EPI_RESID>(c, ctl, n_rows, c->wdown[b], product(u, F, x, d, d, F, nullptr));
         }
     }
-    hipLaunchKernelGGL(rmsnorm_kernel, dim3(n_rows), dim3(256), 0, s, ctl, x, c->final_norm, xn, d, g.rms_eps);
-    RowsOp h = product(xn, d, logits, g.vocab, g.vocab, d, nullptr);
-    h.from_head = 1;
-    launch_rows<WT, float, EPI_STORE>(c, ctl, c->in_prefill ? 1 : n_rows, c->lm_head, h);     // a prompt's pass: its last row, or none
-    if (small_ok(g)) hipLaunchKernelGGL(argmax_classes_kernel, dim3(n_rows), dim3(HEAD_CLASSES), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
-    else hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
-    HIP_TRY(hipGetLastError());
-    return KNNSSD_OK;
+    return run_head_t<WT>(c, ctl, x, n_rows);
 }
-
 // The same pass in one launch. *done stays false if it does not fit.
 static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int n_rows, int start, const PassEnds &ends, bool *done) {
     const knnssd_model_cfg &g = c->cfg;
@@ -990,6 +1060,36 @@ static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, flo
         KS_TRY(prefill_tuned(c, tokens, n));
         KS_TRY(prefill_head(c, n, (n - 1) % KS_MAX_ROWS, last_hidden_dev));
         KS_TRY(read_back(c, c->wsp<HeadResult>(c->L.head)->tok, 4));
+        *first_token = c->h_stage[0];
+        c->prefilled = true;
+        c->cache_len = n;
+        c->draft_len = n;
+        return KNNSSD_OK;
+    }
+    const knnssd_model_cfg &g = c->cfg;
+    if (prompt_rows_ok(g) && n > KS_MAX_ROWS && c->pass_mode != KNNSSD_PASS_ONE) {
+        const bool wb = g.weight_dtype == KNNSSD_BF16, kb = g.kv_dtype == KNNSSD_BF16;
+        int at = 0;
+        for (int s = 0; s < n; s += PR_ROWS) {
+            at = s;
+            const int rows = n - s < PR_ROWS ? n - s : PR_ROWS;
+            if (wb && kb) KS_TRY((run_prompt_t<bf16_t, bf16_t>(c, tokens + s, s, rows)));
+            else if (wb) KS_TRY((run_prompt_t<bf16_t, float>(c, tokens + s, s, rows)));
+            else if (kb) KS_TRY((run_prompt_t<float, bf16_t>(c, tokens + s, s, rows)));
+            else KS_TRY((run_prompt_t<float, float>(c, tokens + s, s, rows)));
+        }
+        // the last row's head, as in a pass of the prompt's last rows
+        const int rows = (n - 1) % KS_MAX_ROWS + 1;
+        const float *x = c->wsp<float>(c->L.pr_x) + (size_t)(n - rows - at) * g.d_model;
+        KS_TRY(set_pass(c, ver, 1, rows, n - rows, rows - 1, tokens + n - rows));
+        c->in_prefill = true;
+        const int32_t rc_head = wb ? run_head_t<bf16_t>(c, ver, x, rows) : run_head_t<float>(c, ver, x, rows);
+        c->in_prefill = false;
+        KS_TRY(rc_head);
+        const float *xn_last = c->wsp<float>(c->L.xn) + (size_t)(rows - 1) * g.d_model;
+        HIP_TRY(hipMemcpyAsync(c->wsp<float>(c->L.hidden_last), xn_last, (size_t)g.d_model * 4, hipMemcpyDeviceToDevice, c->stream));
+        if (last_hidden_dev) HIP_TRY(hipMemcpyAsync(last_hidden_dev, xn_last, (size_t)g.d_model * 4, hipMemcpyDeviceToDevice, c->stream));
+        KS_TRY(read_back(c, &c->wsp<HeadResult>(c->L.head)->tok[rows - 1], 4));
         *first_token = c->h_stage[0];
         c->prefilled = true;
         c->cache_len = n;
