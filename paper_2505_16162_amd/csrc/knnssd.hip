@@ -43,7 +43,7 @@ static size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
 // Workspace layout (byte offsets, all 256-byte aligned).
 struct WsLayout {
-    size_t draft_ctl, ver_ctl, gen, head, out3;
+    size_t draft_ctl, ver_ctl, gen, head;
     size_t x, xn, qkv, att, u, logits, hidden_last, rope_cos, rope_sin, knn_scores, knn_cand, knn_bad, knn_arrivals, out_tokens;
     // tuned bf16 path
     size_t act_d, qrot, ss, head_part, attn_part, attn_arrivals, split_tab;
@@ -104,7 +104,6 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
     L.ver_ctl = take(sizeof(PassCtl));
     L.gen = take(sizeof(GenState));
     L.head = take(sizeof(HeadResult));
-    L.out3 = take(4 * sizeof(int32_t));
     L.x = take(R * c->d_model * 4);
     L.xn = take(R * c->d_model * 4);
     L.qkv = take(R * qkv_dim * 4);
@@ -216,7 +215,16 @@ struct knnssd_ctx {
     bool in_prefill = false;   // the pass being enqueued belongs to a prompt prefill
 
     template <typename T> T *wsp(size_t off) { return reinterpret_cast<T *>(ws + off); }
+    // where a pass leaves its tokens: where only the host asks for them, in host memory, without a copy (2 us of a call)
+    bool head_staged = false;
+    HeadResult *head() { return head_staged ? staged<HeadResult>() : wsp<HeadResult>(L.head); }
     template <typename T> T *staged() { return reinterpret_cast<T *>(d_flags - 512); }     // the pinned staging area as kernels see it
+};
+
+struct HeadStaged {          // for the length of a call
+    knnssd_ctx *c;
+    explicit HeadStaged(knnssd_ctx *ctx) : c(ctx) { c->head_staged = true; }
+    ~HeadStaged() { c->head_staged = false; }
 };
 
 // The prefill GEMM's builds: f(token tiles, epilogue, own sums, kernel, dynamic LDS) for each
@@ -574,8 +582,8 @@ static int32_t run_head_t(knnssd_ctx *c, const PassCtl *ctl, const float *x, int
     h.X = xn; h.ldx = d; h.Y = logits; h.ldy = g.vocab; h.N = g.vocab; h.K = d;
     h.from_head = 1;
     launch_rows<WT, float, EPI_STORE>(c, ctl, c->in_prefill ? 1 : n_rows, c->lm_head, h);     // a prompt's pass: its last row, or none
-    if (small_ok(g)) hipLaunchKernelGGL(argmax_classes_kernel, dim3(n_rows), dim3(HEAD_CLASSES), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
-    else hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->wsp<HeadResult>(c->L.head));
+    if (small_ok(g)) hipLaunchKernelGGL(argmax_classes_kernel, dim3(n_rows), dim3(HEAD_CLASSES), 0, s, ctl, logits, g.vocab, c->head());
+    else hipLaunchKernelGGL(argmax_kernel, dim3(n_rows), dim3(1024), 0, s, ctl, logits, g.vocab, c->head());
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }
@@ -687,7 +695,7 @@ static int32_t run_pass_small(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, 
     const size_t R = KS_MAX_ROWS;
     a.w_qkv = w; a.w_att = a.w_qkv + R * (g.n_heads + 2 * g.n_kv_heads) * g.head_dim; a.w_xo = a.w_att + R * qd; a.w_xd = a.w_xo + R * d;
     a.w_u = a.w_xd + R * d; a.w_head = a.w_u + R * F;
-    a.xn = c->wsp<float>(c->L.xn); a.logits = c->wsp<float>(c->L.logits); a.head = c->wsp<HeadResult>(c->L.head);
+    a.xn = c->wsp<float>(c->L.xn); a.logits = c->wsp<float>(c->L.logits); a.head = c->head();
     a.meets = c->wsp<SmallMeet>(c->L.small_meets); a.launch = c->small_launch++ % SM_MEETS;
     a.cos_t = c->wsp<float>(c->L.rope_cos); a.sin_t = c->wsp<float>(c->L.rope_sin);
     a.d = d; a.H = g.n_heads; a.Hkv = g.n_kv_heads; a.hd = g.head_dim; a.F = F; a.V = g.vocab; a.max_seq = g.max_seq; a.eps = g.rms_eps;
@@ -876,7 +884,7 @@ static int32_t run_pass_bf16(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, b
         h.ss_in = ss; h.logits = c->wsp<float>(c->L.logits); h.head_part = c->wsp<HeadPartial>(c->L.head_part);
         h.split = c->split_head;
         launch(h);
-        if (others) hipLaunchKernelGGL(head_final_kernel, dim3(1), dim3(NT), 0, s, c->wsp<HeadPartial>(c->L.head_part), ctl, c->wsp<HeadResult>(c->L.head), ends);
+        if (others) hipLaunchKernelGGL(head_final_kernel, dim3(1), dim3(NT), 0, s, c->wsp<HeadPartial>(c->L.head_part), ctl, c->head(), ends);
     }
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
@@ -894,7 +902,7 @@ static int32_t run_pass(knnssd_ctx *c, PassCtl *ctl, const uint8_t *mask, int mr
     }
     if (mr == 1 && c->tuned) return run_pass_bf16(c, ctl, mask, true, true, 1, start, ends);
     if (mr != 1 && c->tuned_verify) return run_pass_bf16(c, ctl, mask, false, want_head, n_rows, start, ends);
-    HeadResult *head = c->wsp<HeadResult>(c->L.head);
+    HeadResult *head = c->head();
     if (ends.set) hipLaunchKernelGGL(set_pass_kernel, dim3(1), dim3(64), 0, c->stream, ctl, ends.ctl);
     if (ends.kind == ENDS_VERIFY) hipLaunchKernelGGL(verify_begin_kernel, dim3(1), dim3(1), 0, c->stream, ends.st, ends.draft, ctl, ends.expect_k);
     if (wb && kb) KS_TRY((run_pass_t<bf16_t, bf16_t>(c, ctl, mask, n_rows)));
@@ -1049,18 +1057,20 @@ static int32_t prefill_head(knnssd_ctx *c, int n_tok, int row, float *last_hidde
     h.ss_in = c->wsp<float>(c->L.ss); h.logits = c->wsp<float>(c->L.logits) + (size_t)row * g.vocab;
     h.head_part = c->wsp<HeadPartial>(c->L.head_part); h.split = c->split_head; h.n_rows = 1;
     hipLaunchKernelGGL(gemv_kernel, dim3(KS_NWG), dim3(NT), gemv_lds_bytes(d), c->stream, h, ver);
-    hipLaunchKernelGGL(head_final_kernel, dim3(1), dim3(NT), 0, c->stream, c->wsp<HeadPartial>(c->L.head_part), ver, c->wsp<HeadResult>(c->L.head), PassEnds());
+    hipLaunchKernelGGL(head_final_kernel, dim3(1), dim3(NT), 0, c->stream, c->wsp<HeadPartial>(c->L.head_part), ver, c->head(), PassEnds());
     HIP_TRY(hipGetLastError());
     return KNNSSD_OK;
 }
 
 static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, float *last_hidden_dev, int32_t *first_token) {
     PassCtl *ver = c->wsp<PassCtl>(c->L.ver_ctl);
+    const HeadStaged staged(c);
+    const HeadResult *host_head = reinterpret_cast<const HeadResult *>(c->h_stage);
     if (c->tuned_prefill && n >= PF_MIN_ROWS) {
         KS_TRY(prefill_tuned(c, tokens, n));
         KS_TRY(prefill_head(c, n, (n - 1) % KS_MAX_ROWS, last_hidden_dev));
-        KS_TRY(read_back(c, c->wsp<HeadResult>(c->L.head)->tok, 4));
-        *first_token = c->h_stage[0];
+        KS_TRY(drain(c));
+        *first_token = host_head->tok[0];
         c->prefilled = true;
         c->cache_len = n;
         c->draft_len = n;
@@ -1089,8 +1099,8 @@ static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, flo
         const float *xn_last = c->wsp<float>(c->L.xn) + (size_t)(rows - 1) * g.d_model;
         HIP_TRY(hipMemcpyAsync(c->wsp<float>(c->L.hidden_last), xn_last, (size_t)g.d_model * 4, hipMemcpyDeviceToDevice, c->stream));
         if (last_hidden_dev) HIP_TRY(hipMemcpyAsync(last_hidden_dev, xn_last, (size_t)g.d_model * 4, hipMemcpyDeviceToDevice, c->stream));
-        KS_TRY(read_back(c, &c->wsp<HeadResult>(c->L.head)->tok[rows - 1], 4));
-        *first_token = c->h_stage[0];
+        KS_TRY(drain(c));
+        *first_token = host_head->tok[rows - 1];
         c->prefilled = true;
         c->cache_len = n;
         c->draft_len = n;
@@ -1120,8 +1130,8 @@ static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, flo
                 if (last_hidden_dev)
                     HIP_TRY(hipMemcpyAsync(last_hidden_dev, xn_last, (size_t)c->cfg.d_model * 4, hipMemcpyDeviceToDevice, c->stream));
             }
-            KS_TRY(read_back(c, &c->wsp<HeadResult>(c->L.head)->tok[rows - 1], 4));
-            *first_token = c->h_stage[0];
+            KS_TRY(drain(c));
+            *first_token = host_head->tok[rows - 1];
         }
     }
     c->prefilled = true;
@@ -1318,8 +1328,9 @@ extern "C" int32_t knnssd_draft_step(knnssd_ctx *ctx, int32_t token_in, int32_t 
     PassCtl *dr = ctx->wsp<PassCtl>(ctx->L.draft_ctl);
     PassEnds ends;
     ends.set = 1; ends.ctl = pass_ctl(1, 1, pos, 0, &token_in);
+    const HeadStaged staged(ctx);
     KS_TRY(run_pass(ctx, dr, ctx->draft_mask.data(), 1, 1, pos, true, ends));
-    KS_TRY(read_back(ctx, ctx->wsp<HeadResult>(ctx->L.head), sizeof(HeadResult)));
+    KS_TRY(drain(ctx));
     HeadResult hr;
     memcpy(&hr, ctx->h_stage, sizeof(hr));
     *token_out = hr.tok[0];
@@ -1337,11 +1348,11 @@ extern "C" int32_t knnssd_verify(knnssd_ctx *ctx, const int32_t *tokens_host, in
     if (start_pos > ctx->cache_len) return KNNSSD_ERANGE;  // the full model's K/V in between were never written (drafts fill only retained blocks)
     KS_TRY(check_tokens(ctx, tokens_host, n));
     PassCtl *ver = ctx->wsp<PassCtl>(ctx->L.ver_ctl);
-    int32_t *out3 = ctx->wsp<int32_t>(ctx->L.out3);
+    int32_t *out3 = ctx->staged<int32_t>();
     PassEnds ends;
     ends.kind = ENDS_CHECK; ends.out3 = out3; ends.set = 1; ends.ctl = pass_ctl(1, n, start_pos, 0, tokens_host);
     KS_TRY(run_pass(ctx, ver, nullptr, KS_MAX_ROWS, n, start_pos, true, ends));
-    KS_TRY(read_back(ctx, out3, 12));
+    KS_TRY(drain(ctx));
     *n_accepted_out = ctx->h_stage[0];
     *next_token_out = ctx->h_stage[1];
     if (new_cache_len_out) *new_cache_len_out = ctx->h_stage[2];
