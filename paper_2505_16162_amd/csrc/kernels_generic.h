@@ -1019,38 +1019,48 @@ __global__ __launch_bounds__(1024) void knn_rank_kernel(const float *scores /*[Q
 // ------------------------------------------------------------------------------------------
 // draft / verify round control (Sec. 4.2), advanced on the device
 // ------------------------------------------------------------------------------------------
-__global__ void gen_init_kernel(GenState *st, int cache_len, int x_last, int max_new, int max_draft, float thr,
-                                int32_t *out_tokens) {
-    st->cache_len = cache_len; st->x_last = x_last; st->emitted = 1; st->max_new = max_new;
-    st->max_draft = max_draft; st->conf_thr = thr; st->kmax = 0; st->k = 0; st->done = (max_new <= 1);
-    st->n_accepted = 0; st->rounds = 0; st->drafted = 0; st->accepted = 0; st->draft_passes = 0;
-    out_tokens[0] = x_last;
-}
-
-__global__ void round_begin_kernel(GenState *st, PassCtl *draft) {
+// A round begins: the draft's first control block
+__device__ inline void round_begin(GenState *st, PassCtl *draft) {
     int remaining = st->max_new - st->emitted;
     int kmax = st->done ? 0 : min(st->max_draft, remaining - 1);
     if (kmax < 0) kmax = 0;
     st->kmax = kmax; st->k = 0;
     draft->active = kmax > 0; draft->n_rows = 1; draft->start = st->cache_len; draft->head_from = 0;
     draft->tok[0] = st->x_last;
+    st->t_draft = wall_clock64();
 }
 
-// host_flag (may be null): two pinned host words: [0] receives the pass's new `active` value, so the host can decide on
-// the next draft step after a plain stream synchronisation, without a copy; [2] the drafts made so far in the round
-__device__ inline void draft_end(GenState *st, PassCtl *draft, const HeadResult *res, int32_t *host_flag) {
-    if (!draft->active) { if (host_flag) { host_flag[0] = 0; host_flag[2] = st->k; } return; }
+__global__ void gen_init_kernel(GenState *st, PassCtl *draft, int cache_len, int x_last, int max_new, int max_draft, float thr,
+                                int32_t *out_tokens) {
+    st->cache_len = cache_len; st->x_last = x_last; st->emitted = 1; st->max_new = max_new;
+    st->max_draft = max_draft; st->conf_thr = thr; st->done = (max_new <= 1);
+    st->n_accepted = 0; st->rounds = 0; st->drafted = 0; st->accepted = 0; st->draft_passes = 0;
+    st->ticks_draft = 0; st->ticks_verify = 0;
+    out_tokens[0] = x_last;
+    round_begin(st, draft);
+}
+
+// What a pass of a generation tells the host: one 8-byte word in host memory, its number and what came of it, so that the host sees both
+// or neither. [0]: the last draft step, [1]: the last verification (a step that did not run says how things stand).
+__device__ __forceinline__ void tell_host(unsigned long long *word, unsigned int number, unsigned int value) {
+    __hip_atomic_store(word, ((unsigned long long)number << 32) | value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+constexpr unsigned int DRAFT_GOES_ON = 256;       // beside the drafts made so far in the round
+
+__device__ inline void draft_end(GenState *st, PassCtl *draft, const HeadResult *res, unsigned long long *host, unsigned int number) {
+    if (!draft->active) { tell_host(host, number, st->k); return; }
     int k = st->k;
     int d = res->tok[0]; float p = res->prob[0];
     st->drafts[k] = d; st->draft_p[k] = p;
     k += 1; st->k = k; st->draft_passes += 1;
     bool stop = (k >= st->kmax) || (st->conf_thr > 0.f && p < st->conf_thr);
     draft->active = stop ? 0 : 1;
-    if (host_flag) { host_flag[0] = stop ? 0 : 1; host_flag[2] = k; }
+    tell_host(host, number, k + (stop ? 0 : DRAFT_GOES_ON));
     draft->tok[0] = d;
     draft->start = st->cache_len + k;
+    st->t_draft_end = wall_clock64();
 }
-__global__ void draft_end_kernel(GenState *st, PassCtl *draft, const HeadResult *res, int32_t *host_flag) { draft_end(st, draft, res, host_flag); }
+__global__ void draft_end_kernel(GenState *st, PassCtl *draft, const HeadResult *res, unsigned long long *host, unsigned int number) { draft_end(st, draft, res, host, number); }
 
 // expect_k >= 0: the pass was enqueued ahead of the host's knowledge, for a round of exactly expect_k drafts (its
 // launch arguments and activation layout are those of expect_k + 1 rows); it runs only if the draft did stop there
@@ -1061,30 +1071,36 @@ __device__ inline void verify_begin(const GenState *st, const PassCtl *draft, Pa
     ver->tok[0] = st->x_last;
     for (int i = 0; i < st->k; ++i) ver->tok[i + 1] = st->drafts[i];
 }
-__global__ void verify_begin_kernel(const GenState *st, const PassCtl *draft, PassCtl *ver, int expect_k) { verify_begin(st, draft, ver, expect_k); }
+__global__ void verify_begin_kernel(GenState *st, const PassCtl *draft, PassCtl *ver, int expect_k) {
+    verify_begin(st, draft, ver, expect_k);
+    st->t_verify = wall_clock64();
+}
 
 // Greedy acceptance and rollback: keep the leading drafts that equal the full model's own
-// token, emit the model's next token after them, move the cache length behind the last kept row.
-// host_emitted (may be null): pinned host word that receives the new count of emitted tokens
+// token, emit the model's next token after them, move the cache length behind the last kept row. The next round begins at once.
+// The host learns the new count of emitted tokens.
 // ver: the pass whose result this is; a pass that did not run (enqueued ahead for a draft count that did not come
 // true) leaves the state alone
-__device__ inline void accept(GenState *st, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, int32_t *host_emitted) {
-    if (st->done || !ver->active) { if (host_emitted) *host_emitted = st->emitted; return; }
+__device__ inline void accept(GenState *st, PassCtl *draft, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, unsigned long long *host, unsigned int number) {
+    if (st->done || !ver->active) { tell_host(host + 1, number, st->emitted); return; }
     int k = st->k, j = 0;
     while (j < k && st->drafts[j] == res->tok[j]) ++j;
     int e = st->emitted;
     for (int i = 0; i < j; ++i) out_tokens[e + i] = st->drafts[i];
     out_tokens[e + j] = res->tok[j];
     st->emitted = e + j + 1;
+    tell_host(host + 1, number, e + j + 1);
     st->cache_len += j + 1;
     st->x_last = res->tok[j];
     st->n_accepted = j;
     st->rounds += 1; st->drafted += k; st->accepted += j;
     if (st->emitted >= st->max_new) st->done = 1;
-    if (host_emitted) *host_emitted = st->emitted;
+    st->ticks_verify += wall_clock64() - st->t_verify;
+    if (k > 0) st->ticks_draft += st->t_draft_end - st->t_draft;
+    round_begin(st, draft);
 }
-__global__ void accept_kernel(GenState *st, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, int32_t *host_emitted) {
-    accept(st, ver, res, out_tokens, host_emitted);
+__global__ void accept_kernel(GenState *st, PassCtl *draft, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, unsigned long long *host, unsigned int number) {
+    accept(st, draft, ver, res, out_tokens, host, number);
 }
 
 // Acceptance for a stand-alone verification call: rows tok[0..n-1] = [x_last, d_1..d_k].
@@ -1103,13 +1119,19 @@ struct PassEnds {
     GenState *st = nullptr;
     PassCtl *draft = nullptr;
     int expect_k = -1;               // verify_begin
-    int32_t *out_tokens = nullptr, *flags = nullptr;     // flags: host words, [0] and [2] of draft_end, [1] of accept
+    int32_t *out_tokens = nullptr;   // accept
+    unsigned long long *host = nullptr;      // tell_host
+    unsigned int number = 0;         // of the pass
     int32_t *out3 = nullptr;         // verify_accept
     int set = 0;                     // the control block is `ctl`
     PassCtl ctl = {};
 };
 // The pass's control block for every workgroup of its first kernel (own: LDS); the first one leaves it for the other kernels.
 __device__ __forceinline__ const PassCtl *pass_begin(const PassEnds &e, PassCtl *ctl, PassCtl *own) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        if (e.kind == ENDS_VERIFY) e.st->t_verify = wall_clock64();
+        else if (e.kind == ENDS_DRAFT && e.st->k == 0) e.st->t_draft = wall_clock64();
+    }
     if (e.kind != ENDS_VERIFY && !e.set) return ctl;
     if (threadIdx.x == 0) {
         if (e.set) *own = e.ctl;
@@ -1122,8 +1144,8 @@ __device__ __forceinline__ const PassCtl *pass_begin(const PassEnds &e, PassCtl 
 // The pass's last step, by one thread (res is not looked at if the pass did not run). seen: what pass_begin returned, where this
 // is the same kernel (in memory the first workgroup may have left it a moment ago).
 __device__ __forceinline__ void pass_end(const PassEnds &e, PassCtl *ctl, const PassCtl *seen, const HeadResult *res) {
-    if (e.kind == ENDS_DRAFT) draft_end(e.st, ctl, res, e.flags);
-    else if (e.kind == ENDS_VERIFY) accept(e.st, seen, res, e.out_tokens, e.flags + 1);
+    if (e.kind == ENDS_DRAFT) draft_end(e.st, ctl, res, e.host, e.number);
+    else if (e.kind == ENDS_VERIFY) accept(e.st, e.draft, seen, res, e.out_tokens, e.host, e.number);
     else if (e.kind == ENDS_CHECK) verify_accept(seen, res, e.out3);
 }
 
