@@ -380,7 +380,7 @@ def knn_probe(n_anchors, dev):
             dt = (time.time() - t0) / reps
             out[f"{tag}_q{nq}"] = {"ms": round(dt * 1e3, 3), "scan_GBps": round(n_anchors * d * eb / dt / 1e9, 1),
                                    "frac_of_peak": round(n_anchors * d * eb / dt / 1e9 / HBM_PEAK_GBS, 4)}
-    out["note"] = "K = 8 nearest anchors per query, whole call (scan, two-stage selection, read-back), host-timed"
+    out["note"] = "K = 8 nearest anchors per query, whole call (scan, ranking), host-timed"
     gpu.close()
     return out
 

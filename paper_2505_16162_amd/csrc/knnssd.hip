@@ -1068,7 +1068,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
 }
 
 // Prompts of at least this many rows take the prefill kernels in one go, shorter ones one pass of the verification kernels
-// (7B widths, 4 blocks: a 16-row pass 0.67 ms, 45 rows 0.76 ms here, two 16-row passes 1.2 ms)
+// (7B widths, 4 blocks: a 16-row pass 0.67 ms, 45 rows 0.66 ms here, two 16-row passes 1.2 ms)
 static const int PF_MIN_ROWS = 17;
 
 // The LM head over the prompt's last row (a one-row pass of the decode kernel) behind prefill_tuned. `row`: the logits row
