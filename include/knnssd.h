@@ -114,7 +114,8 @@ typedef struct knnssd_gen_cfg {
 
 /* Counters of one knnssd_generate call. Mean generated length M = (emitted-1)/rounds and
  * acceptance rate alpha = accepted/drafted are the paper's App. C.2 metrics. Times are GPU
- * time from HIP events on the context's stream. */
+ * time from HIP events on the context's stream; ns_draft, ns_verify: from the device's clock, a round's
+ * draft steps from the end of the round before, its verification from there on (the two are the whole decode). */
 typedef struct knnssd_stats {
     int64_t rounds, drafted, accepted, emitted;
     int64_t ns_prefill, ns_knn, ns_draft, ns_verify, ns_total;

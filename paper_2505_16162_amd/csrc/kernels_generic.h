@@ -1027,7 +1027,7 @@ __device__ inline void round_begin(GenState *st, PassCtl *draft) {
     st->kmax = kmax; st->k = 0;
     draft->active = kmax > 0; draft->n_rows = 1; draft->start = st->cache_len; draft->head_from = 0;
     draft->tok[0] = st->x_last;
-    st->t_draft = wall_clock64();
+    st->t_begin = wall_clock64();
 }
 
 __global__ void gen_init_kernel(GenState *st, PassCtl *draft, int cache_len, int x_last, int max_new, int max_draft, float thr,
@@ -1071,10 +1071,7 @@ __device__ inline void verify_begin(const GenState *st, const PassCtl *draft, Pa
     ver->tok[0] = st->x_last;
     for (int i = 0; i < st->k; ++i) ver->tok[i + 1] = st->drafts[i];
 }
-__global__ void verify_begin_kernel(GenState *st, const PassCtl *draft, PassCtl *ver, int expect_k) {
-    verify_begin(st, draft, ver, expect_k);
-    st->t_verify = wall_clock64();
-}
+__global__ void verify_begin_kernel(const GenState *st, const PassCtl *draft, PassCtl *ver, int expect_k) { verify_begin(st, draft, ver, expect_k); }
 
 // Greedy acceptance and rollback: keep the leading drafts that equal the full model's own
 // token, emit the model's next token after them, move the cache length behind the last kept row. The next round begins at once.
@@ -1095,8 +1092,9 @@ __device__ inline void accept(GenState *st, PassCtl *draft, const PassCtl *ver, 
     st->n_accepted = j;
     st->rounds += 1; st->drafted += k; st->accepted += j;
     if (st->emitted >= st->max_new) st->done = 1;
-    st->ticks_verify += wall_clock64() - st->t_verify;
-    if (k > 0) st->ticks_draft += st->t_draft_end - st->t_draft;
+    // between a round's beginning and its end nothing is left out: what lies in front of a pass counts with it
+    if (k > 0) st->ticks_draft += st->t_draft_end - st->t_begin;
+    st->ticks_verify += wall_clock64() - (k > 0 ? st->t_draft_end : st->t_begin);
     round_begin(st, draft);
 }
 __global__ void accept_kernel(GenState *st, PassCtl *draft, const PassCtl *ver, const HeadResult *res, int32_t *out_tokens, unsigned long long *host, unsigned int number) {
@@ -1128,10 +1126,6 @@ struct PassEnds {
 };
 // The pass's control block for every workgroup of its first kernel (own: LDS); the first one leaves it for the other kernels.
 __device__ __forceinline__ const PassCtl *pass_begin(const PassEnds &e, PassCtl *ctl, PassCtl *own) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        if (e.kind == ENDS_VERIFY) e.st->t_verify = wall_clock64();
-        else if (e.kind == ENDS_DRAFT && e.st->k == 0) e.st->t_draft = wall_clock64();
-    }
     if (e.kind != ENDS_VERIFY && !e.set) return ctl;
     if (threadIdx.x == 0) {
         if (e.set) *own = e.ctl;
