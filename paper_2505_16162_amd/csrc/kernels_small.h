@@ -187,9 +187,11 @@ __device__ __forceinline__ void small_attention(const SmallArgs &a, SmallLds &sl
 
 // The end of a pass that ran alone. One that has given up (it reads nothing but its own words, so this means that something is badly wrong)
 // has no result: the host finds the word and fails the call.
+// It is counted before the pass tells the host that it is over (pass_end): a host that sees a pass's number holds the next ones back.
 __device__ __forceinline__ void small_alone(const SmallArgs &a, int gave_up) {
     ++a.flags[3];
     if (gave_up) a.flags[4] = 1;
+    __threadfence_system();
 }
 
 // T: storage type of weights and cache; MR: rows the build holds (the pass has n_rows <= MR)
@@ -429,9 +431,9 @@ __global__ __launch_bounds__(SM_NT) void small_pass_kernel(SmallArgs a) {
         }
         __syncthreads();
         if (tid == 0) {
-            if (!sl.gave_up) pass_end(a.ends, a.ctl, ctl, &sl.head);
             if (n_wg == 1) small_alone(a, sl.gave_up);
-            else __hip_atomic_fetch_add(&meet->left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (!sl.gave_up) pass_end(a.ends, a.ctl, ctl, &sl.head);
+            if (n_wg != 1) __hip_atomic_fetch_add(&meet->left, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
         return;
     }

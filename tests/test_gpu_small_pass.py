@@ -224,6 +224,24 @@ def test_a_broken_launch_is_followed_by_launches():
 
 
 @pytest.mark.timeout(300)
+def test_a_round_knows_that_the_pass_before_was_broken_up():
+    """A generation waits for a pass's number, not for the stream: the broken-up launch is counted before the number is there, so the very
+    next pass is held back."""
+    shape = synth.small_shape("small_hold_rounds", weight_dtype="fp32", kv_dtype="fp32", **BROKEN)
+    w = synth.make_weights(shape, seed=81, std=0.05)
+    prompt = synth.make_prompt(shape.vocab, 40, seed=82).tolist()
+    for wg in (0, 3, 63, 64):
+        gpu = binding.KnnSsd(shape, w, generic_kernels=True)
+        want = gpu.knnssd_generate(prompt, 30, 0)[0]
+        gpu.knnssd_set_pass_mode("auto", wg)
+        whole, broken = gpu.knnssd_pass_counts()
+        assert whole > 0 and broken == 0
+        assert gpu.knnssd_generate(prompt, 30, 0)[0] == want          # 29 passes of one row, each waited for
+        assert gpu.knnssd_pass_counts() == (whole + 1, 1), wg
+        gpu.close()
+
+
+@pytest.mark.timeout(300)
 def test_many_contexts_at_once():
     shape = synth.small_shape("small_streams", weight_dtype="fp32", kv_dtype="fp32", n_blocks=4, vocab=1024, max_seq=96)
     w = {k: ([{n: t.cuda() for n, t in b.items()} for b in v] if k == "blocks" else v.cuda()) for k, v in synth.make_weights(shape, seed=65, gains="random", std=0.05).items()}
