@@ -2,7 +2,6 @@
 // kernels of a draft step, a verification pass and a generation are put on the stream.
 #include <hip/hip_runtime.h>
 
-#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
@@ -13,6 +12,7 @@
 #include "../../include/knnssd.h"
 #include "device_types.h"
 #include "knn_plan.h"
+#include "told_wait.h"
 #include "kernels_generic.h"
 #include "kernels_bf16.h"
 #include "kernels_prefill.h"
@@ -947,22 +947,18 @@ static int32_t drain(knnssd_ctx *c) {
     return KNNSSD_OK;
 }
 
-// The value that pass `number` has told the host (word 0: draft steps, 1: verifications), as soon as it is there. The host looks at the word
-// for a while and then waits for the stream; a stream that has ended without it has failed (or its last pass has no result).
+// The value that pass `number` has told the host (word 0: draft steps, 1: verifications), as soon as it is there, however long the pass takes
+// (told_wait); a stream that has ended without it has failed (or its last pass has no result).
 static int32_t wait_told(knnssd_ctx *c, int word, uint32_t number, uint32_t *value) {
     const volatile uint64_t *const told = reinterpret_cast<const volatile uint64_t *>(c->h_stage + 512 + TOLD) + word;
-    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(5);
-    for (int look = 0;; ++look) {
-        const uint64_t v = *told;
-        if ((uint32_t)(v >> 32) == number) { *value = (uint32_t)v; return KNNSSD_OK; }
-        if ((look & 63) == 63 && std::chrono::steady_clock::now() >= until) break;
-#if defined(__x86_64__)
-        __builtin_ia32_pause();
-#endif
-    }
-    KS_TRY(drain(c));
-    const uint64_t v = *told;
-    if ((uint32_t)(v >> 32) != number) {
+    uint64_t v = 0;
+    const bool came = told_wait([&] { v = *told; return (uint32_t)(v >> 32) == number; }, [&] {
+        if (hipStreamQuery(c->stream) != hipErrorNotReady) return true;
+        (void)hipGetLastError();       // "not ready" is no error of a call
+        return false;
+    });
+    if (!came) {
+        KS_TRY(drain(c));
         snprintf(g_hip_err, sizeof(g_hip_err), "a pass has ended without telling its number");
         return KNNSSD_EHIP;
     }
