@@ -145,7 +145,9 @@ size_t knnssd_kvcache_bytes(const knnssd_model_cfg *cfg);
 /* Create a context over caller-owned device memory. kv_dev and ws_dev must be 256-byte
  * aligned; kv_bytes and ws_bytes are the sizes of the two buffers, and the call fails with
  * KNNSSD_EINVAL when either is smaller than the size queries above say for THIS cfg (the queries
- * depend on every field, weights_packed included). hip_stream is a hipStream_t (NULL = the null
+ * depend on every field, weights_packed included). With KNNSSD_PREFILL_AUTO a workspace that lacks only the room
+ * that makes prompts faster is accepted and prompts go without it: row-major weights take 16-row passes
+ * (the size that KNNSSD_PREFILL_CHUNKED asks for is enough), stream-order ones the plain tiles of the prefill kernels. hip_stream is a hipStream_t (NULL = the null
  * stream). Launches a few set-up kernels (RoPE table, the workgroups' shares of each matrix) on the stream.
  * The library reads no environment variable: every switch is a cfg field. */
 int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weights *w, void *kv_dev, size_t kv_bytes,

@@ -52,6 +52,7 @@ struct WsLayout {
     size_t pf_tokens, pf_x, pf_q, pf_frag_d, pf_frag_att, pf_frag_u, pf_rstd, pf_part[PF_OPS], pf_rows[PF_OPS][2];
     size_t pr_ctl, pr_x, pr_qkv, pr_att, pr_u;      // a prompt's rows on the any-shape kernels
     int pf_tt;          // token tiles the fragment buffers are laid out for
+    bool pf_plain;      // products take pf_plan's tiles
     // small models' one-launch passes: block table, handed-over vectors
     size_t small_tab, small_meets, small_words, small_words_bytes;
     size_t total;
@@ -95,8 +96,9 @@ static bool small_ok(const knnssd_model_cfg &g) {
     return g.d_ffn >= SM_G && (g.n_heads + 2 * g.n_kv_heads) * g.head_dim / 2 >= SM_G;      // every workgroup contributes to these steps
 }
 
-static WsLayout ws_layout(const knnssd_model_cfg *c) {
+static WsLayout ws_layout(const knnssd_model_cfg *c, bool pf_plain = false) {
     WsLayout L{};
+    L.pf_plain = pf_plain;
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, 256); return o; };
     const size_t R = KS_MAX_ROWS;
@@ -141,7 +143,7 @@ static WsLayout ws_layout(const knnssd_model_cfg *c) {
             size_t part[PF_OPS] = {};
             for (int w = 0; w < PF_OPS; ++w)
                 for (int t = 1; t <= (int)tt; ++t) {
-                    const PfPlan p = pf_choose(*c, w, t);
+                    const PfPlan p = pf_tiles_of(*c, w, t, pf_plain);
                     if (p.parts(w) && p.part_bytes() > part[w]) part[w] = p.part_bytes();
                 }
             auto most = [](size_t a, size_t b, size_t d) { return a > b ? (a > d ? a : d) : (b > d ? b : d); };
@@ -324,10 +326,17 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
     if (!cfg_valid(cfg) || !w || !kv_dev || !ws_dev) return KNNSSD_EINVAL;
     if (!cfg_supported(cfg)) return KNNSSD_ESHAPE;
     // the kernels index these buffers by the layout of THIS cfg: a buffer sized for another one must not get through
-    // (with row-major weights one without room for a prompt's rows will do: prompts take 16-row passes then)
+    // (with row-major weights one without room for a prompt's rows will do: prompts take 16-row passes then; with stream-order weights one
+    // without room for the wide tiles' and short prompts' partial sums: products take pf_plan's tiles then)
     knnssd_model_cfg own = *cfg;
-    if (prompt_rows_ok(own) && ws_bytes < ws_layout(&own).total) own.prefill_mode = KNNSSD_PREFILL_CHUNKED;
-    if (ws_bytes < ws_layout(&own).total || kv_bytes < knnssd_kvcache_bytes(cfg)) return KNNSSD_EINVAL;
+    WsLayout L = ws_layout(&own);
+    if (ws_bytes < L.total && prompt_rows_ok(own)) {
+        own.prefill_mode = KNNSSD_PREFILL_CHUNKED;
+        L = ws_layout(&own);
+    } else if (ws_bytes < L.total && own.weights_packed && own.prefill_mode == KNNSSD_PREFILL_AUTO) {
+        L = ws_layout(&own, true);
+    }
+    if (ws_bytes < L.total || kv_bytes < knnssd_kvcache_bytes(cfg)) return KNNSSD_EINVAL;
     if (cfg->weights_packed && !tuned_ok(*cfg)) return KNNSSD_ESHAPE;
     if (((uintptr_t)kv_dev & 255) || ((uintptr_t)ws_dev & 255)) return KNNSSD_EINVAL;
     if (!w->embed || !w->lm_head || !w->final_norm) return KNNSSD_EINVAL;
@@ -345,7 +354,7 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
     knnssd_ctx *c = new (std::nothrow) knnssd_ctx();
     if (!c) return KNNSSD_EINVAL;
     c->cfg = own;
-    c->L = ws_layout(&own);
+    c->L = L;
     c->stream = (hipStream_t)hip_stream;
     c->ws = (char *)ws_dev;
     c->kv = (char *)kv_dev;
@@ -984,7 +993,7 @@ static int32_t prefill_tuned(knnssd_ctx *c, const int32_t *tokens_host, int n_to
     float *x = c->wsp<float>(c->L.pf_x), *q = c->wsp<float>(c->L.pf_q), *rstd = c->wsp<float>(c->L.pf_rstd);
     bf16_t *frag_d = c->wsp<bf16_t>(c->L.pf_frag_d), *frag_att = c->wsp<bf16_t>(c->L.pf_frag_att), *frag_u = c->wsp<bf16_t>(c->L.pf_frag_u);
     PfPlan plan[PF_OPS];
-    for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_choose(g, w, TTL);
+    for (int w = 0; w < PF_OPS; ++w) plan[w] = pf_tiles_of(g, w, TTL, c->L.pf_plain);
 
     GemmOp base{};
     base.H = H; base.Hkv = Hkv; base.hd = hd; base.max_seq = g.max_seq;

@@ -101,7 +101,11 @@ inline PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt, int least = 
 // 128 x 64 tiles add up each step's planes on their own (own_sums), which the residual and SwiGLU rows do nowhere else: those stay.
 // Measured against pf_plan alone, whole prompts, two blocks, us: 7B 180 rows 738 -> 660, 257 1110 -> 983, 777 2201 -> 2005, 13B 257 1474 -> 1255, 600
 // 2575 -> 2313, 2200 7776 -> 7066, Qwen 513 2280 -> 2003, 777 2919 -> 2845; where the plan stays (100, 400, 1024 rows) 0.997-1.003.
-constexpr size_t PF_PART_ROOM = (size_t)128 << 20;     // what pf_plan's parts take at some length anyway, in the shipped widths: the workspace does not grow
+// Room for the parts of a product: what pf_plan's take in the shipped widths at the lengths where they take most. The workspace grows where a context's
+// max_seq does not reach those lengths (four blocks, pf_plan alone -> with these: 13B up to 256 positions 83 -> 115 MB, 1024 288 -> 322,
+// Qwen 256 92 -> 119) and shrinks where other tiles need fewer parts (7B 576 287 -> 233, 1024 320 -> 244, 13B 512 182 -> 128); from 4608 positions
+// on it is the same. A context over a buffer that is too small for it takes pf_plan's tiles.
+constexpr size_t PF_PART_ROOM = (size_t)128 << 20;
 inline PfPlan pf_tiles(const knnssd_model_cfg &g, int which, int tt) {
     const PfPlan p = pf_plan(g, which, tt);
     if (p.tb == 4 && which != PF_QKV) return p;
@@ -130,5 +134,8 @@ inline PfPlan pf_choose(const knnssd_model_cfg &g, int which, int tt) {
     if (p.S > 32) return pf_tiles(g, which, tt);        // few rows, many columns: a row kernel would read them all
     return p;
 }
+
+// plain: the workspace has room for pf_plan's parts only
+inline PfPlan pf_tiles_of(const knnssd_model_cfg &g, int which, int tt, bool plain) { return plain ? pf_plan(g, which, tt) : pf_choose(g, which, tt); }
 
 }  // namespace ks

@@ -123,6 +123,30 @@ def test_workspace_of_the_prefill(lib, name, max_seq, more):
     assert need <= auto - chunked <= more * need
 
 
+# what the size query said (4 blocks) before prompts took wide tiles and streamed large matrices, where it has grown since or shrunk
+PLAIN_BYTES = [("llama13b", 256, 83224576), ("llama13b", 576, 267570432), ("llama13b", 1024, 287540224), ("qwen14b", 64, 91727104),
+               ("qwen14b", 256, 91826176), ("llama7b", 256, 113208832), ("llama7b", 576, 286933760), ("llama7b", 4608, 697850368)]
+
+
+@pytest.mark.parametrize("name,max_seq,plain", PLAIN_BYTES)
+def test_a_workspace_without_room_for_the_wide_tiles_will_do(lib, name, max_seq, plain):
+    """A context with stream-order weights over a buffer of the earlier size. Nothing here touches a device: with fp32 matrices, which no
+    stream-order context takes, knnssd_create ends with KNNSSD_ESHAPE right behind the size check (the layout does not depend on the type)."""
+    cfg = binding.make_cfg(synth.workload(name).shape, 0)
+    cfg.n_blocks, cfg.max_seq, cfg.weights_packed = 4, max_seq, 1
+    full, kv = lib.knnssd_workspace_bytes(ctypes.byref(cfg)), lib.knnssd_kvcache_bytes(ctypes.byref(cfg))
+    cfg.weight_dtype = 0
+    assert lib.knnssd_workspace_bytes(ctypes.byref(cfg)) == full
+    cfg.prefill_mode = 1
+    chunked = lib.knnssd_workspace_bytes(ctypes.byref(cfg))
+    cfg.prefill_mode = 0
+    h, w, fake = ctypes.c_void_p(), binding.Weights(), ctypes.c_void_p(0x100000)
+    create = lambda size: lib.knnssd_create(ctypes.byref(cfg), ctypes.byref(w), fake, kv, fake, size, None, ctypes.byref(h))
+    assert create(plain) == -2 and create(full) == -2
+    assert create(chunked) == -1          # a prompt's rows it must hold
+    assert not h.value
+
+
 def test_kernel_attributes_are_set_when_a_context_is_made():
     """... and not on every call: hipFuncSetAttribute is reached from knnssd_create alone."""
     text = open(os.path.join(ROOT, "paper_2505_16162_amd", "csrc", "knnssd.hip")).read()
