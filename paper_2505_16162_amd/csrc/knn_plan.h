@@ -7,9 +7,11 @@ namespace ks {
 // Scores of a workgroup of knn_rank_kernel: as many as its lanes hold in registers; one workgroup takes up to twice that, since a second
 // one costs the hand-over (three queries, K = 8, 5000 anchors: 43 us a call in two slices, 37 in one; 8000: 43.5 / 42.8).
 constexpr int KNN_SLICE = 4096;
-// Routing over at least so many anchors ranks with knn_rank_kernel instead of knn_argmax_kernel's one workgroup: 5000 anchors of
-// 256 22.3 / 21.9 us, 8000 23.7 / 23.6, 16 000 28.1 / 26.1, 200 000 134 / 67; below, knn_argmax_kernel is the shorter one.
-constexpr int KNN_RANK_ONE = 8192;
+// Routing over at least so many anchors ranks with knn_rank_kernel's slices instead of knn_argmax_kernel's one workgroup, whose time grows with the
+// table; below, what the slices' hand-over costs is more. Whole calls in us, one workgroup / slices: rows of 256 elements, 1000 anchors 20.2 / 21.3,
+// 8192 22.6 / 24.3, 12 000 24.2 / 24.8, 13 000 24.8 / 24.9, 14 000 25.1 / 25.1, 16 000 26.5 / 25.9, 100 000 75 / 44; 2048 elements, 12 000 34.5 / 35.2,
+// 13 000 36.7 / 36.9, 14 000 37.4 / 37.0; 5120 elements, 8192 44.4 / 45.8, 13 000 60.7 / 60.9, 14 000 62.6 / 62.2, 100 000 344 / 313.
+constexpr int KNN_RANK_ONE = 13500;
 constexpr int KNN_STREAM_ROUND = 16384;      // anchors that knn_scores_stream_kernel's wavefronts take at a time: 256 x 16 wavefronts, four each
 
 // knn_scores_stream_kernel, or knn_scores_multi_kernel? The first has its queries in LDS and keeps the table's loads rolling across

@@ -226,6 +226,20 @@ def test_scans_take_the_faster_kernel(streams):
         assert chosen == (stream < multi), case
 
 
+def test_routing_takes_the_faster_ranking(tmp_path):
+    """Whole routing calls measured on an MI355X in us: (anchors, elements), one workgroup, slices; from KNN_RANK_ONE anchors on the slices rank. A
+    tenth of a microsecond or two is noise."""
+    measured = [((8, 256), 18.9, 20.1), ((1000, 256), 20.2, 21.3), ((4097, 256), 21.1, 22.4), ((8000, 1000), 25.0, 26.5), ((8192, 256), 22.6, 24.3), ((8192, 5120), 44.4, 45.8),
+                ((10000, 1000), 26.6, 27.9), ((12000, 64), 23.9, 24.2), ((12000, 2048), 34.5, 35.2), ((13000, 256), 24.8, 24.9), ((13000, 5120), 60.7, 60.9),
+                ((14000, 256), 25.1, 25.1), ((14000, 2048), 37.4, 37.0), ((14000, 5120), 62.6, 62.2), ((16000, 1000), 31.4, 30.3), ((20000, 5120), 81.7, 80.6), ((100000, 256), 74.9, 44.5)]
+    (tmp_path / "driver.cpp").write_text('#include <cstdio>\n#include "knn_plan.h"\nint main() { printf("%d", ks::KNN_RANK_ONE); }\n')
+    csrc = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))), "paper_2505_16162_amd", "csrc")
+    subprocess.run(["g++", "-std=c++17", "-I", csrc, "-o", str(tmp_path / "driver"), str(tmp_path / "driver.cpp")], check=True)
+    least = int(subprocess.run([str(tmp_path / "driver")], check=True, capture_output=True, text=True).stdout)
+    for (anchors, _), one, slices in measured:
+        assert (slices if anchors >= least else one) <= min(one, slices) + 0.2, anchors
+
+
 def test_kernel_pairs_of_the_gpu_test_cross_every_edge(streams):
     """The sizes of test_gpu_scan_kernels_agree take both kernels for each query count and type."""
     sizes = [m for m in test_gpu_scan_kernels_agree.pytestmark if m.name == "parametrize"][0].args[1]
