@@ -7,6 +7,7 @@
 #include <stdint.h>
 
 #include "device_types.h"
+#include "prompt_plan.h"
 
 namespace ks {
 
@@ -114,13 +115,12 @@ __global__ void rope_table_kernel(float *cos_t, float *sin_t, int max_seq, int h
 // ------------------------------------------------------------------------------------------
 // embedding gather: x[r][:] = E[tok[r]][:]
 // ------------------------------------------------------------------------------------------
-// A prompt's rows as chunks of so many side by side (PromptRows): chunk c's control block is ctl[c], its rows lie behind those of the chunks
+// A prompt's rows as chunks of PR_CHUNK side by side (PromptRows): chunk c's control block is ctl[c], its rows lie behind those of the chunks
 // before it. The row kernels take a chunk where a pass takes its rows, with the same device code, so a row has the bits that
 // it has in a pass. A pass of 16 rows leaves most of the chip idle and pays five launches a block (or a one-launch pass's chain of
-// hand-overs) for them: 250 rows, two blocks, fp32 / bf16: 192 columns 938 / 922 us in passes, 132 / 140 here, 520 columns 1885 / 1748 and 241 / 263, 1000
-// columns 3185 / 2410 and 575 / 594, 1912 columns 5813 / 4288 and 2064 / 2116 (bound by the rows' way through the L1); 33 rows 162-932 and
-// 97-491; 17 rows of 192 columns 106 / 105 and 98-108. Chunks of eight rows: the products' builds of up to nine rows are the ones whose loads the compiler places well.
-constexpr int PR_CHUNK = 8, PR_ROWS = 256;
+// hand-overs) for them: 250 rows, two blocks, fp32 / bf16: 200 columns 1049 / 1014 us in passes, 151 / 161 here, 520 columns 2362 / 1939 and 348 / 366, 1000
+// columns 3604 / 2734 and 732 / 743, 1912 columns 6610 / 4489 and 2418 / 2393 (bound by the rows' way through the L1); where passes are the
+// better way: prompt_rows. Chunks of eight rows: the products' builds of up to nine rows are the ones whose loads the compiler places well.
 struct PromptRows {
     int32_t start, n;           // position of the first row, rows
     int32_t tok[PR_ROWS];

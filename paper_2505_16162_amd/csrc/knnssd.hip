@@ -86,7 +86,7 @@ static bool cfg_supported(const knnssd_model_cfg *c) {
 // 137 / 123. Beyond, draft steps and 5 rows: 9.4 MB a block and a head of 6 MB 93 / 86, 108 / 112; 15 MB a block 94 / 106,
 // 113 / 141; a head of 33 MB 100 / 126, 136 / 167.
 static const size_t SMALL_MAX_BYTES = 8u << 20;     // weights of a block, of the head
-// prompts on the any-shape kernels take their rows side by side instead of 16 at a time
+// prompts on the any-shape kernels take their rows side by side instead of 16 at a time (which: prompt_rows)
 static bool prompt_rows_ok(const knnssd_model_cfg &g) { return !g.weights_packed && g.prefill_mode == KNNSSD_PREFILL_AUTO; }
 static bool small_ok(const knnssd_model_cfg &g) {
     if (g.weights_packed || g.weight_dtype != g.kv_dtype || g.n_blocks < 1 || g.n_blocks > SM_MAX_BLOCKS) return false;
@@ -1110,12 +1110,13 @@ static int32_t prefill_impl(knnssd_ctx *c, const int32_t *tokens, int32_t n, flo
         return KNNSSD_OK;
     }
     const knnssd_model_cfg &g = c->cfg;
-    if (prompt_rows_ok(g) && n > KS_MAX_ROWS && c->pass_mode != KNNSSD_PASS_ONE) {
+    const int side = prompt_rows_ok(g) && c->pass_mode != KNNSSD_PASS_ONE ? prompt_rows(g, n) : 0;
+    if (side > 0) {
         const bool wb = g.weight_dtype == KNNSSD_BF16, kb = g.kv_dtype == KNNSSD_BF16;
         int at = 0;
-        for (int s = 0; s < n; s += PR_ROWS) {
+        for (int s = 0; s < n; s += side) {
             at = s;
-            const int rows = n - s < PR_ROWS ? n - s : PR_ROWS;
+            const int rows = n - s < side ? n - s : side;
             if (wb && kb) KS_TRY((run_prompt_t<bf16_t, bf16_t>(c, tokens + s, s, rows)));
             else if (wb) KS_TRY((run_prompt_t<bf16_t, float>(c, tokens + s, s, rows)));
             else if (kb) KS_TRY((run_prompt_t<float, bf16_t>(c, tokens + s, s, rows)));

@@ -1,5 +1,5 @@
 """Prompts on the any-shape kernels take their rows side by side; a context that sends prompts through 16-row passes is the reference, bit
-for bit: hidden state, logits, cache. Lengths around a chunk (8), a pass (16) and a launch's rows (256), all pairs of storage types, ragged
+for bit: hidden state, logits, cache. Lengths around a chunk (8), a pass (16) and a launch's rows (256; 128 with wide bf16 rows), all pairs of storage types, ragged
 widths. And a passes-then-prompt mix: a prompt after a verification starts from the same state."""
 import ctypes
 
@@ -10,12 +10,12 @@ from paper_2505_16162_amd import binding, synth
 
 pytestmark = pytest.mark.gpu
 
-LENGTHS = (16, 17, 23, 24, 25, 32, 33, 64, 255, 256, 257, 272, 521)
+LENGTHS = (16, 17, 23, 24, 25, 32, 33, 64, 128, 129, 161, 255, 256, 257, 272, 521)
 
 
 @pytest.mark.timeout(120)
 @pytest.mark.parametrize("wt,kt,hd,h,kvh,d,f", [("fp32", "fp32", 64, 4, 2, 264, 504), ("bf16", "bf16", 128, 3, 1, 328, 1000), ("bf16", "fp32", 64, 5, 1, 72, 40),
-                                                ("fp32", "bf16", 128, 2, 2, 1016, 88)])
+                                                ("fp32", "bf16", 128, 2, 2, 1016, 88), ("bf16", "bf16", 64, 2, 1, 2808, 72), ("bf16", "fp32", 64, 1, 1, 3208, 64)])
 def test_prompt_rows_have_the_bits_of_passes(wt, kt, hd, h, kvh, d, f):
     shape = synth.ModelShape("rows", 2, d, h, kvh, hd, f, 613, 560, wt, kt)
     w = synth.make_weights(shape, seed=71, gains="random", std=0.05)
