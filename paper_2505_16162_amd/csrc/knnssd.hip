@@ -214,6 +214,7 @@ struct knnssd_ctx {
     SmallHold small_hold;
     int32_t pass_mode = KNNSSD_PASS_AUTO, quit_wg = -1, quit_block = 0;     // knnssd_set_pass_mode
     std::vector<hipEvent_t> events;
+    int clock_khz = 0;             // of the device's wall clock
     // knnssd_profile_pass: enqueue only the weight-streaming launches of a pass and count them
     bool gemm_only = false;
     int64_t prof_launches = 0, prof_bytes = 0;
@@ -462,6 +463,18 @@ extern "C" int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weigh
         (void)hipHostFree(c->h_stage);
         delete c;
         return KNNSSD_EHIP;
+    }
+    {
+        int dev = 0;
+        e = hipGetDevice(&dev);
+        if (e == hipSuccess) e = hipDeviceGetAttribute(&c->clock_khz, hipDeviceAttributeWallClockRate, dev);
+        if (e == hipSuccess && c->clock_khz <= 0) e = hipErrorInvalidValue;
+        if (e != hipSuccess) {
+            snprintf(g_hip_err, sizeof(g_hip_err), "%s (wall clock rate)", hipGetErrorString(e));
+            (void)hipHostFree(c->h_stage);
+            delete c;
+            return KNNSSD_EHIP;
+        }
     }
     hipLaunchKernelGGL(fill_zero_kernel, dim3(1), dim3(64), 0, c->stream, c->wsp<int>(c->L.knn_arrivals), KNN_QMAX);     // zero between launches
     const int half = cfg->head_dim / 2;
@@ -1418,6 +1431,8 @@ static int64_t elapsed_ns(knnssd_ctx *c, size_t a, size_t b) {
     return (int64_t)((double)ms * 1e6);
 }
 
+static int64_t ticks_ns(const knnssd_ctx *c, int64_t ticks) { return (int64_t)((double)ticks * 1e6 / (double)c->clock_khz); }
+
 extern "C" int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, int32_t n_prompt, const float *query_dev,
                                    const knnssd_gen_cfg *gen, int32_t *out_tokens_host, int32_t *n_out, knnssd_stats *stats) {
     if (!ctx || !prompt_host || !gen || !out_tokens_host || !n_out) return KNNSSD_EINVAL;
@@ -1515,7 +1530,7 @@ extern "C" int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, 
         stats->rounds = hs.rounds; stats->drafted = hs.drafted; stats->accepted = hs.accepted; stats->emitted = emitted;
         stats->ns_prefill = elapsed_ns(ctx, 0, 1);
         stats->ns_knn = elapsed_ns(ctx, 1, 2);
-        stats->ns_draft = hs.ticks_draft * 10; stats->ns_verify = hs.ticks_verify * 10;
+        stats->ns_draft = ticks_ns(ctx, hs.ticks_draft); stats->ns_verify = ticks_ns(ctx, hs.ticks_verify);
         stats->ns_total = elapsed_ns(ctx, 0, e_end);
         stats->draft_passes = n_draft_passes; stats->verify_passes = n_verify_passes;
     }
