@@ -472,7 +472,11 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
 // 538 -> 479, Qwen 33 rows 675 -> 617. What is left above the stream (17 / 30 / 15 us): 3 us to start, 4-7 us for the parts' way
 // out (22 MB), and the activations, each of which crosses from the L2 once per row tile: 0.3 us per token tile and step more than
 // the weights take. Four token tiles: as fast as prefill_gemm_kernel (7B, 64 rows 423 against 426). Four wavefronts with four row tiles each
-// (half the LDS reads): no change. Six steps ahead instead of four, three of activations per meeting: no change.
+// (half the LDS reads): no change. Six steps ahead instead of four, three of activations per meeting: no change. A run's sums are folded into a second
+// set every PF_THIN_FOLD pairs, so that a run longer than prefill_gemm_kernel's parts (7B's gate+up rows: 44 steps instead of 32) has no more
+// roundings in a row: no change in time (45 rows, 7B 348 -> 339, 13B 460 -> 455, Qwen 421 -> 417 us); cache entries of the next block on another bf16 value
+// than in 64 bits, over 192 prompts each of 17, 33 and 45 rows, against the 128 x 64 tiles: 7B -8, -3, -2 % without, -17, -11, -10 % with;
+// 13B -18 and -25 %, Qwen -26 to -42 % and -25 to -44 %.
 // ------------------------------------------------------------------------------------------
 constexpr int PF_THIN_WAVES = 8, PF_THIN_BUFS = 5;     // pairs of steps whose activations are in LDS
 constexpr int pf_thin_nt(int tb) { return (PF_THIN_WAVES + tb) * 64; }
@@ -559,13 +563,13 @@ __global__ __launch_bounds__(pf_thin_nt(TB)) void prefill_thin_kernel(PfArgs a) 
         load_a(u, 1);
         advance();
     }
-    f32x4 acc[RT][TB];
+    f32x4 acc[RT][TB], sum[RT][TB];                // of the last pairs, of those before
 #pragma unroll
     for (int i = 0; i < RT; ++i)
 #pragma unroll
-        for (int j = 0; j < TB; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int j = 0; j < TB; ++j) acc[i][j] = sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
     const char *lb = lds + lane * 16;
-    int buf = 0;
+    int buf = 0, young = 0;                        // pairs in acc
     auto pair = [&](int c, int u) {                // (one past the end requests its weights like the others, so that the loads in flight stay countable)
         const bool on = c < n;
         if (on) pf_meet();
@@ -608,6 +612,16 @@ __global__ __launch_bounds__(pf_thin_nt(TB)) void prefill_thin_kernel(PfArgs a) 
         advance();
         __builtin_amdgcn_sched_barrier(0);
         const bool last = kp == KP - 1;            // of its tile
+        if (on && (++young == PF_THIN_FOLD || last || c == n - 1)) {
+            young = 0;
+#pragma unroll
+            for (int j = 0; j < TB; ++j)
+#pragma unroll
+                for (int i = 0; i < RT; ++i) {
+                    sum[i][j] += acc[i][j];
+                    acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                }
+        }
         if (on && (last || c == n - 1)) {
             const int part = (int)blockIdx.x - pf_share_owner(units, G, mt * KP);
 #pragma unroll
@@ -616,8 +630,8 @@ __global__ __launch_bounds__(pf_thin_nt(TB)) void prefill_thin_kernel(PfArgs a) 
                 float *o = a.out + ((size_t)part * a.out_rows + tok) * ((size_t)a.n_mt * TM) + mt * TM + wave * RT * 16 + 4 * kg;
 #pragma unroll
                 for (int i = 0; i < RT; ++i) {
-                    if (tok < a.n_tok) *reinterpret_cast<f32x4 *>(o + i * 16) = acc[i][j] * scale[j];
-                    acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (tok < a.n_tok) *reinterpret_cast<f32x4 *>(o + i * 16) = sum[i][j] * scale[j];
+                    sum[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
                 }
             }
             ++mt;

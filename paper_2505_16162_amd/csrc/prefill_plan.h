@@ -96,8 +96,12 @@ inline PfPlan pf_plan(const knnssd_model_cfg &g, int which, int tt, int least = 
 
 // The tiles a product takes: the best of pf_plan's and of the wide ones with no fewer parts, so that no sum has more roundings in a row than
 // it would have without them (256 x 192 tiles of two parts instead of 256 x 256 ones of three for the O projection, and QKV rows of one part
-// instead of two: 0.72 % of a Qwen-shaped prompt's cache entries on another bf16 value than in 64 bits, 777 rows, instead of 0.62). Gate+up rows
-// may: they reach the cache through the down product alone (13B 257 rows 0.686 / 0.686 %, 7B 777 0.424 / 0.425 %, hidden states within 2 %).
+// instead of two: 0.72 % of a Qwen-shaped prompt's cache entries on another bf16 value than in 64 bits, 777 rows, instead of 0.62). Gate+up rows may have
+// fewer (in the shipped widths one part instead of two, 13B and Qwen with 257 to 288 and 577 to 640 rows, 7B with 641 to 784): they reach the cache through the down
+// product alone. Measured against pf_plan alone over 96 prompts each: the next block's cache entries lie on another bf16 value 0.1 to 0.3 % more often (13B 257
+// and 600 rows +0.13 and +0.12 % of 1.3-1.4 %, Qwen +0.34 and +0.23 %, 7B 777 +0.19 %), hidden states' error +0.5, -0.8, -0.1, -0.4, +0.7 % with a standard error
+// of 0.5 to 0.8. With no fewer parts these prompts take 4-6 % longer (13B 257 rows, two blocks, 1096 -> 1166 us, 608 2076 -> 2168, Qwen 257 983 -> 1045, 7B 777 1772 ->
+// 1859) and up to 31 % more workspace (7B, 576 positions); with sums of their own per step as long (1167, 2216, 1037, 1872).
 // 128 x 64 tiles add up each step's planes on their own (own_sums), which the residual and SwiGLU rows do nowhere else: those stay.
 // Measured against pf_plan alone, whole prompts, two blocks, us: 7B 180 rows 738 -> 660, 257 1110 -> 983, 777 2201 -> 2005, 13B 257 1474 -> 1255, 600
 // 2575 -> 2313, 2200 7776 -> 7066, Qwen 513 2280 -> 2003, 777 2919 -> 2845; where the plan stays (100, 400, 1024 rows) 0.997-1.003.
@@ -117,6 +121,7 @@ inline PfPlan pf_tiles(const knnssd_model_cfg &g, int which, int tt) {
 // its fixed cost shows (7B's O projection, four pairs: 14.9 us against 14.5; models of 256 to 2000 columns with all products
 // this way 12-20 % slower), 13B's O projection with six and a quarter takes 18 against 20.
 constexpr int PF_THIN = 3, PF_THIN_PAIRS = 6, PF_THIN_TILES = 4;        // PF_THIN_TILES: row tiles a workgroup's run may touch
+constexpr int PF_THIN_FOLD = 8;                        // pairs of steps that are summed on their own
 inline PfPlan pf_choose(const knnssd_model_cfg &g, int which, int tt) {
     const int K = which == PF_O ? g.n_heads * g.head_dim : (which == PF_DOWN ? g.d_ffn : g.d_model), KP = (K / 32 + 1) / 2;
     PfPlan p{};

@@ -49,6 +49,37 @@ def driver(tmp_path_factory):
     return str(tmp / "driver")
 
 
+CHAIN = r'''
+#include <cstdio>
+#include <cstdlib>
+#include "prefill_plan.h"
+int main(int n, char **v) {
+    knnssd_model_cfg g{};
+    g.d_model = atoi(v[1]); g.n_heads = atoi(v[2]); g.n_kv_heads = atoi(v[3]); g.head_dim = atoi(v[4]); g.d_ffn = atoi(v[5]);
+    for (int w = 0; w < ks::PF_OPS; ++w)
+        for (int tt = 2; tt <= 3; ++tt) {
+            const ks::PfPlan p = ks::pf_choose(g, w, tt), r = ks::pf_plan(g, w, tt);
+            if (!p.G || !r.own_sums(w)) continue;
+            const int K = w == ks::PF_O ? g.n_heads * g.head_dim : (w == ks::PF_DOWN ? g.d_ffn : g.d_model), KP = (K / 32 + 1) / 2, units = p.n_mt * KP;
+            const int run = (units + p.G - 1) / p.G < KP ? (units + p.G - 1) / p.G : KP;       // pairs of steps
+            printf("%d %d %d %d %d\n", run, ks::PF_THIN_FOLD, p.S, (K / 32 + r.S - 1) / r.S, r.S);
+        }
+}
+'''
+
+
+@pytest.mark.parametrize("shape", [(4096, 32, 32, 128, 11008), (5120, 40, 40, 128, 13824), (5120, 40, 8, 128, 13824), (3200, 25, 25, 128, 8640), (8192, 64, 8, 128, 28672)])
+def test_no_sum_has_more_roundings_in_a_row_than_with_tiles(tmp_path, shape):
+    """Steps within a fold, folds and parts, against steps within a part and parts of the 128 x 64 tiles (both add a step's planes on their own)."""
+    (tmp_path / "chain.cpp").write_text(CHAIN)
+    subprocess.run(["g++", "-std=c++17", "-I", CSRC, "-o", str(tmp_path / "chain"), str(tmp_path / "chain.cpp")], check=True)
+    lines = subprocess.run([str(tmp_path / "chain")] + [str(v) for v in shape], check=True, capture_output=True, text=True).stdout.splitlines()
+    assert lines
+    for line in lines:
+        run, fold, parts, steps, tile_parts = map(int, line.split())
+        assert min(2 * fold, 2 * run) + -(-run // fold) + parts <= steps + tile_parts, line
+
+
 @pytest.mark.parametrize("shape,thin", [((4096, 32, 32, 128, 11008), {0, 2, 3}), ((5120, 40, 40, 128, 13824), {0, 1, 2, 3}), ((2080, 4, 2, 128, 6048), {2}),
                                         ((320, 2, 1, 64, 352), set()), ((64, 2, 1, 64, 120000), set()), ((8192, 64, 8, 128, 28672), {0, 1, 2, 3})])
 def test_runs_cover_the_steps(driver, shape, thin):
