@@ -36,7 +36,7 @@ struct GenState {
     int32_t drafts[KS_MAX_ROWS];
     float draft_p[KS_MAX_ROWS];
     int64_t rounds, drafted, accepted, draft_passes;
-    int64_t t_begin, t_draft_end;                // the round began, its last draft step ended (the device's wall clock)
+    int64_t t_begin, t_draft_end;                // the round began, its last draft step ended (100 MHz clock)
     int64_t ticks_draft, ticks_verify;           // all rounds' draft steps, verifications
 };
 

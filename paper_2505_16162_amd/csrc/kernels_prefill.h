@@ -475,8 +475,8 @@ __global__ __launch_bounds__(PF_NT, TA == 16 ? 2 : 4) void prefill_gemm_kernel(P
 // (half the LDS reads): no change. Six steps ahead instead of four, three of activations per meeting: no change. A run's sums are folded into a second
 // set every PF_THIN_FOLD pairs, so that a run longer than prefill_gemm_kernel's parts (7B's gate+up rows: 44 steps instead of 32) has no more
 // roundings in a row: no change in time (45 rows, 7B 348 -> 339, 13B 460 -> 455, Qwen 421 -> 417 us); cache entries of the next block on another bf16 value
-// than in 64 bits, over 192 prompts each of 17, 33 and 45 rows, against the 128 x 64 tiles: 7B -8, -3, -2 % without, -17, -11, -10 % with;
-// 13B -18 and -25 %, Qwen -26 to -42 % and -25 to -44 %.
+// than in 64 bits, against the 128 x 64 tiles (geometric means over 192 prompts each of 17, 33 and 45 rows): 7B 0.92, 0.97, 0.98 without, 0.84, 0.89, 0.90 with;
+// 13B 0.84 and 0.78, Qwen 0.66 to 0.77 and 0.64 to 0.78.
 // ------------------------------------------------------------------------------------------
 constexpr int PF_THIN_WAVES = 8, PF_THIN_BUFS = 5;     // pairs of steps whose activations are in LDS
 constexpr int pf_thin_nt(int tb) { return (PF_THIN_WAVES + tb) * 64; }

@@ -1469,8 +1469,10 @@ extern "C" int32_t knnssd_generate(knnssd_ctx *ctx, const int32_t *prompt_host, 
     // once and the host carries on step by step. Without a threshold the count is known and nothing is waited for.
     // What the host waits for is a pass's own word (tell_host), not the stream: a round ends with its verification's acceptance, which also
     // begins the next one, and its times are taken on the device. With a stream synchronisation, a launch and three events per round
-    // the GPU waited 20 to 30 us between two rounds of 200 (fp32 configuration) to 700 us (7B-shaped, four blocks): whole generations 5.9 -> 5.5
-    // and 26.2 -> 25.3 ms.
+    // the GPU waited 20 to 30 us between two rounds of 200 (fp32 configuration) to 700 us (7B-shaped, four blocks), and still waits for the host
+    // to see the word and enqueue the next pass, about 10: whole generations 6.13 -> 5.50 ms (the prompt's rows side by side included) and 27.3 -> 26.4
+    // (1.02 to 1.035 from machine to machine). At full depth a round is long and the gain small: 13B shape, 40 blocks, 132.2 -> 132.5
+    // tokens/s, without drafts 196.5 -> 197.2.
     int pred_k = 1;
     uint32_t value = 0;
     while (!done) {
