@@ -69,8 +69,8 @@ typedef struct knnssd_model_cfg {
                                tuned bf16 kernels run; 0: row-major, generic kernels. embed is always row-major. */
     int32_t prefill_mode;   /* KNNSSD_PREFILL_AUTO: prompts go through the many-row prefill kernels where the shape
                                fits them; KNNSSD_PREFILL_CHUNKED: through 16-row passes of the verification kernels.
-                               Row-major weights: AUTO takes a prompt's rows side by side, with the bits of 16-row
-                               passes, if the workspace has room for them (knnssd_workspace_bytes of that cfg). */
+                               Row-major weights: AUTO takes a prompt's rows side by side where that is faster, with the
+                               bits of 16-row passes, if the workspace has room for them (knnssd_workspace_bytes of that cfg). */
     int32_t verify_attn;    /* which split-KV attention kernel verification passes (and the draft steps of
                                grouped-query models, and of any model once the context brings more (kv head,
                                256-position chunk) items than 512) use: KNNSSD_ATTN_MFMA (matrix cores, the default) or
@@ -147,7 +147,8 @@ size_t knnssd_kvcache_bytes(const knnssd_model_cfg *cfg);
  * KNNSSD_EINVAL when either is smaller than the size queries above say for THIS cfg (the queries
  * depend on every field, weights_packed included). With KNNSSD_PREFILL_AUTO a workspace that lacks only the room
  * that makes prompts faster is accepted and prompts go without it: row-major weights take 16-row passes
- * (the size that KNNSSD_PREFILL_CHUNKED asks for is enough), stream-order ones the plain tiles of the prefill kernels. hip_stream is a hipStream_t (NULL = the null
+ * (the size that KNNSSD_PREFILL_CHUNKED asks for is enough), stream-order ones the plain tiles of the prefill
+ * kernels (at some sizes a third less than the query says). hip_stream is a hipStream_t (NULL = the null
  * stream). Launches a few set-up kernels (RoPE table, the workgroups' shares of each matrix) on the stream.
  * The library reads no environment variable: every switch is a cfg field. */
 int32_t knnssd_create(const knnssd_model_cfg *cfg, const knnssd_weights *w, void *kv_dev, size_t kv_bytes,
